@@ -315,7 +315,7 @@ SolveWs plan_solve(Arena &a, int64_t n, int64_t k, int prec) {
     const size_t panel = (size_t)kp * ld;
     SolveWs w;
     // split-K partials for the largest candidate split counts
-    w.part = a.take<char>(panel * std::max<size_t>(8 * (size_t)residual_splits(ld, kp, n, 2),
+    w.part = a.take<char>(panel * std::max<size_t>(8 * (size_t)residual_splits_max(ld, kp, n),
                                                    4 * (size_t)apply_splits(prec, ld, kp, n, 2)));
     w.Yt = a.take<double>(panel);
     w.Xt = a.take<double>(panel);
@@ -1080,13 +1080,13 @@ static WProduct stored_product(cdl_ctx *ctx, const double *W, int64_t n, int64_t
             std::vector<double> ms(3);
             for (int q = 0; q < 3; ++q)
                 HIPCHK(time_launch(ctx, [&] {
-                    return launch_residual_gemm(Vt, W, ld, n, kp, residual_splits(ld, kp, n, q), P,
+                    return launch_residual_gemm(Vt, W, ld, n, k, kp, residual_splits(ld, kp, n, q), P,
                                                 ctx->stream);
                 }, &ms[q]));
             ch = cdl::tune_put(cdl::tune_arch(ctx->device), cdl::tune_key("residual", 0, ld, kp), ms);
         }
         S = residual_splits(ld, kp, n, ch);
-        { Timed t_(ctx, "residual"); HIPCHK(launch_residual_gemm(Vt, W, ld, n, kp, S, P, ctx->stream)); }
+        { Timed t_(ctx, "residual"); HIPCHK(launch_residual_gemm(Vt, W, ld, n, k, kp, S, P, ctx->stream)); }
         return CDL_OK;
     };
 }
@@ -1484,7 +1484,7 @@ cdl_status cdl_stream_embedding(cdl_ctx *ctx, const double *X, int64_t n, int64_
             for (int64_t r0 = 0; r0 < n; r0 += P) {
                 const int64_t rows = std::min(P, ld - r0);
                 { Timed t_(ctx, "stream_gram_exp"); HIPCHK(launch_gram_panel(w.Xp, Tp, w.sqn, n, ld, r0, rows, true, w.panel, stats, s)); }
-                { Timed t_(ctx, "stream_product"); HIPCHK(launch_panel_product(Vt, w.panel, ld, n, kp, r0, rows, Pp, s)); }
+                { Timed t_(ctx, "stream_product"); HIPCHK(launch_panel_product(Vt, w.panel, ld, n, k, kp, r0, rows, Pp, s)); }
             }
             return CDL_OK;
         };
@@ -1518,7 +1518,7 @@ cdl_status cdl_stream_embedding(cdl_ctx *ctx, const double *X, int64_t n, int64_
             } else {
                 { Timed t_(ctx, "stream_gram_exp"); HIPCHK(launch_gram_panel(w.Xp, Tp, w.sqn, n, ld, r0, rows, true, w.panel, stats, s)); }
             }
-            { Timed t_(ctx, "stream_product"); HIPCHK(launch_panel_product(Vt, w.panel, ld, n, kp, r0, rows, w.Prod, s)); }
+            { Timed t_(ctx, "stream_product"); HIPCHK(launch_panel_product(Vt, w.panel, ld, n, k, kp, r0, rows, w.Prod, s)); }
         }
         return CDL_OK;
     };
@@ -1531,7 +1531,7 @@ cdl_status cdl_stream_embedding(cdl_ctx *ctx, const double *X, int64_t n, int64_
         // X += P1 R, P1 = D^{-1} + D^{-1} W D^{-1}
         { Timed t_(ctx, "stream_scale"); HIPCHK(launch_stream_scale(w.Rt, w.rdeg, ld, kp, w.Ut, s)); }
         if ((st = product_sweep(w.Ut, it == 0)) != CDL_OK) return st;
-        { Timed t_(ctx, "stream_update"); HIPCHK(launch_stream_update(w.Ut, w.Prod, w.rdeg, ld, kp, w.Xt, s)); }
+        { Timed t_(ctx, "stream_update"); HIPCHK(launch_stream_update(w.Ut, w.Prod, w.rdeg, ld, k, w.Xt, s)); }
         if (it == 0) {
             // ||S~||_F^2 = ||S||_F^2 - 1 for the deflated S~ = S - u u^T
             std::vector<double> fro(n);
@@ -2037,8 +2037,8 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
     std::vector<BatchSnap> hs(P);
     std::vector<ChainBuf> chains(P);
     std::vector<SolveWs> solves(P);
-    // Split-K counts for the grouped launches: one count S for the whole group,
-    // the smallest power of two that gives the group at least two workgroups
+    // Split-K count of the grouped applications: one count S for the whole
+    // group, the smallest power of two that gives the group at least two workgroups
     // per CU (the per-snapshot counts fill the chip with one snapshot alone and
     // multiply the partial sums' traffic when many snapshots share a launch),
     // clamped per snapshot to what its length and its workspace allow.
@@ -2046,24 +2046,14 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
         const int64_t n = sn[t].n, ld = pad_n(n);
         return std::min(cdl::apply_splits_fixed(prec, n, S), apply_splits(prec, ld, kp, n, 2));
     };
-    auto res_split = [&](int t, int S) {
-        const int64_t n = sn[t].n, ld = pad_n(n);
-        return std::min(cdl::residual_splits_fixed(n, S), residual_splits(ld, kp, n, 2));
-    };
     constexpr int64_t kGroupWgs = 2 * 256;
-    int Sa = 1, Sr = 1;
+    int Sa = 1;
     auto ap_tiles = [&](int S) {
         int64_t c = 0;
         for (int t = 0; t < P; ++t) c += cdl::apply_gemm_tiles(pad_n(sn[t].n), kp, ap_split(t, S));
         return c;
     };
-    auto res_tiles = [&](int S) {
-        int64_t c = 0;
-        for (int t = 0; t < P; ++t) c += cdl::residual_gemm_tiles(pad_n(sn[t].n), kp, res_split(t, S));
-        return c;
-    };
     while (Sa < 256 && ap_tiles(Sa) < kGroupWgs && ap_tiles(2 * Sa) > ap_tiles(Sa)) Sa *= 2;
-    while (Sr < 256 && res_tiles(Sr) < kGroupWgs && res_tiles(2 * Sr) > res_tiles(Sr)) Sr *= 2;
     // a choice pinned on the context (cdl_ctx_force_choice) keeps the
     // per-snapshot split counts, so that the grouped launches compute exactly
     // the per-snapshot path's partial sums
@@ -2072,6 +2062,15 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
         return f != ctx->forced.end() && f->second >= 0 && f->second < 3 ? f->second : -1;
     };
     const int pin_ap = pinned("apply"), pin_res = pinned("residual");
+    std::vector<int64_t> ns(P), lds(P);
+    std::vector<int> rcap(P), rsplit(P);
+    for (int t = 0; t < P; ++t) {
+        ns[t] = sn[t].n;
+        lds[t] = pad_n(ns[t]);
+        rcap[t] = pin_res >= 0 ? residual_splits(lds[t], kp, ns[t], pin_res) : residual_splits_max(lds[t], kp, ns[t]);
+    }
+    const int res_shape = cdl::residual_group_plan(P, ns.data(), lds.data(), k, kp, rcap.data(),
+                                                   pin_res >= 0 ? rcap.data() : nullptr, rsplit.data());
     for (int t = 0; t < P; ++t) {
         const int64_t n = sn[t].n, ld = pad_n(n);
         Arena ac(base + L.chain[t]);
@@ -2102,7 +2101,7 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
         d.mpart = w.mpart;
         d.scal = w.scal;
         d.ap_splits = pin_ap >= 0 ? apply_splits(prec, ld, kp, n, pin_ap) : ap_split(t, Sa);
-        d.res_splits = pin_res >= 0 ? residual_splits(ld, kp, n, pin_res) : res_split(t, Sr);
+        d.res_splits = rsplit[t];
     }
     std::vector<BatchPair> hp(NP);
     std::vector<int32_t> hm, m0, m1;
@@ -2153,7 +2152,7 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
     // that the launches after every snapshot has converged stay cheap
     constexpr int kEltWgs = 256;
     const int tot_ar = fill(2, P, [&](int t) { return apply_reduce_blocks(hs[t].ld, kp, kEltWgs); });
-    const int tot_rg = fill(3, P, [&](int t) { return residual_gemm_tiles(hs[t].ld, kp, hs[t].res_splits); });
+    const int tot_rg = fill(3, P, [&](int t) { return residual_gemm_tiles(res_shape, hs[t].ld, k, kp, hs[t].res_splits); });
     const int tot_rr = fill(4, P, [&](int t) { return (int)std::min<int64_t>(hs[t].ld / 256 * kp, kEltWgs); });
     const int tot_pv = fill(5, P, [&](int t) { return apply_reduce_blocks(hs[t].ld, kp, kEltWgs); });
     const int tot_zh = fill(6, NP, [&](int t) { return (int)hp[t].mpad; });
@@ -2261,7 +2260,7 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
             { Timed t_(ctx, "square"); HIPCHK(cdl::launch_square_grouped(prec, dsnap, dtable(0), P, tot_sq, l, s0)); }
         // done and iteration flags (their region is rounded up to 256 bytes)
         { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(done, (2 * (size_t)P * sizeof(int) + 15) / 16 * 16, s0)); }
-        { Timed t_(ctx, "residual_init"); HIPCHK(cdl::launch_residual_grouped(prec, dsnap, dtable(3), tot_rg, dtable(4), tot_rr, P, kp, k, 1, done, s0)); }
+        { Timed t_(ctx, "residual_init"); HIPCHK(cdl::launch_residual_grouped(prec, dsnap, res_shape, dtable(3), tot_rg, dtable(4), tot_rr, P, kp, k, 1, done, s0)); }
         { Timed t_(ctx, "col_norms"); HIPCHK(cdl::launch_norms_grouped(dsnap, P, kp, k, scaled, q->tol, 1, ynorm, rel, done, iters, s0)); }
         for (int it = 0; it < q->max_iter; ++it) {
             if (scaled) { Timed t_(ctx, "prep_v"); HIPCHK(cdl::launch_prep_grouped(prec, dsnap, dtable(5), tot_pv, P, kp, done, s0)); }
@@ -2271,7 +2270,7 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
                                                                      l + 1 == depth, done, s0)); }
                 cur ^= 1;
             }
-            { Timed t_(ctx, "residual"); HIPCHK(cdl::launch_residual_grouped(prec, dsnap, dtable(3), tot_rg, dtable(4), tot_rr, P, kp, k, 0, done, s0)); }
+            { Timed t_(ctx, "residual"); HIPCHK(cdl::launch_residual_grouped(prec, dsnap, res_shape, dtable(3), tot_rg, dtable(4), tot_rr, P, kp, k, 0, done, s0)); }
             { Timed t_(ctx, "col_norms"); HIPCHK(cdl::launch_norms_grouped(dsnap, P, kp, k, scaled, q->tol, 0, ynorm, rel, done, iters, s0)); }
         }
         for (int t = 0; t < P; ++t)

@@ -1,19 +1,16 @@
-// Generic LDS-tiled MFMA core for C = A * B^T (A row-major along the
-// reduction index k; B row-major along k, or with BT = true row-major along
-// n, i.e. element (n, k) at B[k * ldb + n]), used by every dense contraction
-// of the path: kernel-distance Gram, chain squarings, chain application,
-// FP64 residual and the score Gram.  BT reads a k-tile of B as BK rows of BN
-// contiguous elements (1 KB segments for 128 doubles) instead of BN rows of
-// BK; for a symmetric B both forms multiply the same values in the same
-// order.  Callers supply padded operands (K a multiple of BK, tile rows
-// inside the allocation), so the core has no bounds checks.
+// LDS-tiled MFMA cores for C = A * B^T (both operands row-major along the
+// reduction index k), used by every dense contraction of the path.  Callers
+// supply padded operands (K a multiple of BK, tile rows inside the
+// allocation), so the cores have no bounds checks.  GemmCore stages through
+// registers (FP32 levels); DmaCore (16-bit levels) and Dma64Core (FP64) load
+// straight into LDS.
 #pragma once
 
 #include "common.h"
 
 namespace cdl {
 
-template <class Mf, int BM, int BN, int BK, int WM, int WN, bool BT = false>
+template <class Mf, int BM, int BN, int BK, int WM, int WN>
 struct GemmCore {
     using T = typename Mf::T;
     using Frag = typename Mf::Frag;
@@ -28,15 +25,9 @@ struct GemmCore {
     static constexpr int B_CH = BN * CPR / NT;
     static constexpr int WTM = BM / WM / Mf::M;
     static constexpr int WTN = BN / WN / Mf::M;
-    // BT: B's k-tile as BK rows of BN (+ pad: consecutive k rows start 32
-    // banks apart, so the two k rows that one half-wave of a fragment read
-    // takes, 16 consecutive doubles each, cover the 64 banks once)
-    static constexpr int LDSN = BN + 16;
-    static constexpr int CPN = BN / CE;                 // chunks per B^T tile row
-    static constexpr int STAGE = BM * LDSK + (BT ? BK * LDSN : BN * LDSK);   // elements per stage
+    static constexpr int STAGE = (BM + BN) * LDSK;     // elements per stage
     static constexpr size_t SMEM = 2 * (size_t)STAGE * sizeof(T);
     static_assert(BM * CPR % NT == 0 && BN * CPR % NT == 0, "tile/thread mismatch");
-    static_assert(!BT || (Mf::E == 1 && BN % CE == 0), "B^T tiles need one k per fragment");
     static_assert(WTM >= 1 && WTN >= 1, "wave tile too small");
     static_assert(BK % Mf::KI == 0 && BK % CE == 0, "bad BK");
 
@@ -62,13 +53,8 @@ struct GemmCore {
         }
 #pragma unroll
         for (int c = 0; c < B_CH; ++c) {
-            if (BT) {
-                int ch = tid + c * NT, row = ch / CPN, nc = ch % CPN;
-                rb[c] = *(const uint4 *)(B + (k0 + row) * ldb + n0 + nc * CE);
-            } else {
-                int ch = tid + c * NT, row = ch / CPR, kc = ch % CPR;
-                rb[c] = *(const uint4 *)(B + (n0 + row) * ldb + k0 + kc * CE);
-            }
+            int ch = tid + c * NT, row = ch / CPR, kc = ch % CPR;
+            rb[c] = *(const uint4 *)(B + (n0 + row) * ldb + k0 + kc * CE);
         }
     }
 
@@ -82,13 +68,8 @@ struct GemmCore {
         }
 #pragma unroll
         for (int c = 0; c < B_CH; ++c) {
-            if (BT) {
-                int ch = tid + c * NT, row = ch / CPN, nc = ch % CPN;
-                *(uint4 *)(sB + row * LDSN + nc * CE) = rb[c];
-            } else {
-                int ch = tid + c * NT, row = ch / CPR, kc = ch % CPR;
-                *(uint4 *)(sB + row * LDSK + kc * CE) = rb[c];
-            }
+            int ch = tid + c * NT, row = ch / CPR, kc = ch % CPR;
+            *(uint4 *)(sB + row * LDSK + kc * CE) = rb[c];
         }
     }
 
@@ -96,7 +77,7 @@ struct GemmCore {
         const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
         const int wm = wid % WM, wn = wid / WM;
         const T *sA = s + (wm * WTM * Mf::M) * LDSK;
-        const T *sB = s + BM * LDSK + (wn * WTN * Mf::M) * (BT ? 1 : LDSK);
+        const T *sB = s + BM * LDSK + (wn * WTN * Mf::M) * LDSK;
         const int fr = lane % Mf::M, fk = Mf::E * (lane / Mf::M);
 #pragma unroll
         for (int kk = 0; kk < BK; kk += Mf::KI) {
@@ -106,8 +87,7 @@ struct GemmCore {
                 a[i] = *(const Frag *)(sA + (i * Mf::M + fr) * LDSK + kk + fk);
 #pragma unroll
             for (int j = 0; j < WTN; ++j)
-                b[j] = BT ? *(const Frag *)(sB + (kk + fk) * LDSN + j * Mf::M + fr)
-                          : *(const Frag *)(sB + (j * Mf::M + fr) * LDSK + kk + fk);
+                b[j] = *(const Frag *)(sB + (j * Mf::M + fr) * LDSK + kk + fk);
 #pragma unroll
             for (int i = 0; i < WTM; ++i)
 #pragma unroll
@@ -250,6 +230,12 @@ typedef __attribute__((address_space(3))) void lds_void;
 template <int N> __device__ inline void wait_vmcnt() {
     static_assert(N >= 0 && N < 64, "vmcnt range");
     asm volatile("s_waitcnt vmcnt(%0)" ::"n"(N) : "memory");
+}
+
+// The same, and every LDS read of this wave has returned.
+template <int N> __device__ inline void wait_vmcnt_lds() {
+    static_assert(N >= 0 && N < 64, "vmcnt range");
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)" ::"n"(N) : "memory");
 }
 
 // Workgroup barrier without a memory fence (the loads into LDS are waited
@@ -419,6 +405,192 @@ struct DmaCore {
     __device__ static inline int col_of(int j) {
         const int lane = threadIdx.x & 63, wn = (threadIdx.x >> 6) / WM;
         return wn * WTN * Mf::M + j * Mf::M + Mf::ccol(lane);
+    }
+};
+
+// ---------------------------------------------------------------------------
+// FP64 core fed by direct global->LDS loads, for every FP64 contraction
+// (distance Gram, score Gram, residual and panel products, FP64 levels).
+// An FP64 MFMA holds its matrix pipe for 64 cycles, so neither LDS nor L2
+// bandwidth bounds a tile; what costs time is every cycle in which all waves
+// of a SIMD wait at once: the register-staged core stored the next k-tile and
+// met a barrier after its last MFMA (MFMA pipes 74-84 % busy).  Here the loads
+// go straight into LDS, the fragments of k-step q + 1 are read while the MFMAs
+// of k-step q run, and the barrier lies before the last k-step's MFMAs, whose
+// fragments are already in registers, so the next k-tile's first fragments
+// arrive under them.
+//
+// Rows of 16 doubles (128 bytes) with the 16-byte chunks XOR-swizzled by
+// (row >> 1) & 7: the 16 rows x 2 k that a half-wave reads cover the 64 banks
+// once.  NS: LDS stages (2 for the large tiles, whose k-tile takes
+// microseconds; 3 where a k-tile is nearer the load latency).  The k order of
+// every sum is that of GemmCore, so the results are the same bits for every
+// tile shape.
+//
+// Measured at 256 x 16384 x 16384 (the residual product's shape) on one card,
+// in bursts: 256 x 128 tiles of 8 waves 1.86 ms (74 TFLOP/s), 128 x 128 of 8
+// waves 1.89, 128 x 64 of 4 waves 1.95, 64 x 64 of 4 waves 2.02; the
+// register-staged core 2.08-2.30.  Reading a symmetric B as B^T (k-tiles of 1 KB
+// rows), which had paid there, gives nothing here (1.88).
+template <int BM, int BN, int WM, int WN, int NS = 2>
+struct Dma64Core {
+    using T = double;
+    using Frag = double;
+    using AccV = f64x4;
+    using MF = MfmaF64;
+    static constexpr int BK = 16;
+    static constexpr int TBM = BM, TBN = BN;
+    static constexpr int NW = WM * WN, NT = NW * 64;
+    static constexpr int ROWB = BK * 8;              // bytes per LDS row
+    static constexpr int STAGE = (BM + BN) * ROWB;
+    static constexpr size_t SMEM = (size_t)NS * STAGE;
+    static constexpr int WTM = BM / WM / 16, WTN = BN / WN / 16;
+    // 1 KB loads (8 rows) per wave and stage; where they do not divide evenly
+    // the last block is loaded more than once (the same bytes to the same
+    // place), so that every wave counts the same number
+    static constexpr int AB = BM / 8, BB = BN / 8;
+    static constexpr int AI = (AB + NW - 1) / NW, BI = (BB + NW - 1) / NW;
+    static constexpr int NKK = BK / 4;
+    static constexpr int NF = WTM + WTN, NM = WTM * WTN;
+    static_assert(WTM * WM * 16 == BM && WTN * WN * 16 == BN, "wave tiles of 16");
+    static_assert(WTM >= 1 && WTN >= 1 && NS >= 2, "tile shape");
+
+    AccV acc[WTM][WTN];
+
+    __device__ static inline int swz(int c, int row) { return c ^ ((row >> 1) & 7); }
+
+    // Loads of the k-tile starting at element k0 into the LDS stage at byte
+    // offset `stage`.
+    __device__ inline void issue(uint32_t stage, __amdgpu_buffer_rsrc_t ra, __amdgpu_buffer_rsrc_t rb,
+                                 int64_t lda, int64_t ldb, int64_t k0, int w, uint32_t va0,
+                                 uint32_t va1, uint32_t vb0, uint32_t vb1) {
+#pragma unroll
+        for (int q = 0; q < AI; ++q) {
+            int blk = w + q * NW;
+            if (AB % NW) blk = blk < AB ? blk : AB - 1;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                ra, (lds_void *)(uintptr_t)(stage + blk * 1024), 16, blk & 1 ? va1 : va0,
+                (uint32_t)(((int64_t)(blk * 8) * lda + k0) * 8), 0, 0);
+        }
+#pragma unroll
+        for (int q = 0; q < BI; ++q) {
+            int blk = w + q * NW;
+            if (BB % NW) blk = blk < BB ? blk : BB - 1;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                rb, (lds_void *)(uintptr_t)(stage + BM * ROWB + blk * 1024), 16, blk & 1 ? vb1 : vb0,
+                (uint32_t)(((int64_t)(blk * 8) * ldb + k0) * 8), 0, 0);
+        }
+    }
+
+    __device__ inline void load_frags(const char *s, int kk, Frag *f) {
+        const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+        const int wm = wid % WM, wn = wid / WM;
+        const int k = kk + (lane >> 4), r16 = lane & 15;
+        const char *sA = s, *sB = s + BM * ROWB;
+#pragma unroll
+        for (int i = 0; i < WTM; ++i) {
+            const int row = (wm * WTM + i) * 16 + r16;
+            f[i] = *(const double *)(sA + row * ROWB + 16 * swz(k >> 1, row) + 8 * (k & 1));
+        }
+#pragma unroll
+        for (int j = 0; j < WTN; ++j) {
+            const int row = (wn * WTN + j) * 16 + r16;
+            f[WTM + j] = *(const double *)(sB + row * ROWB + 16 * swz(k >> 1, row) + 8 * (k & 1));
+        }
+    }
+
+    __device__ inline void mmas(const Frag *f) {
+#pragma unroll
+        for (int i = 0; i < WTM; ++i)
+#pragma unroll
+            for (int j = 0; j < WTN; ++j) acc[i][j] = MF::mma(f[i], f[WTM + j], acc[i][j]);
+    }
+
+    template <int I = 0> __device__ static inline void interleave() {
+        constexpr int G = NF > NM ? NF : NM;
+        constexpr int nd = (I + 1) * NF / G - I * NF / G;
+        constexpr int nm = (I + 1) * NM / G - I * NM / G;
+        if constexpr (nd > 0) __builtin_amdgcn_sched_group_barrier(0x100, nd, 0);
+        if constexpr (nm > 0) __builtin_amdgcn_sched_group_barrier(0x008, nm, 0);
+        if constexpr (I + 1 < G) interleave<I + 1>();
+    }
+
+    // Full K loop (K a multiple of 16; rows m0.. and n0.. inside the
+    // allocations).  smem holds SMEM bytes and is free again on return.
+    __device__ inline void run(const T *A, int64_t lda, const T *B, int64_t ldb, int64_t m0,
+                               int64_t n0, int64_t K, T *smem_t) {
+        char *smem = (char *)smem_t;
+#pragma unroll
+        for (int i = 0; i < WTM; ++i)
+#pragma unroll
+            for (int j = 0; j < WTN; ++j)
+#pragma unroll
+                for (int r = 0; r < MF::R; ++r) acc[i][j][r] = 0;
+        const int nk = (int)(K / BK);
+        if (nk == 0) return;
+        const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+        const uint32_t s0 = (uint32_t)(uintptr_t)(lds_void *)smem;
+        __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)(A + m0 * lda), 0, (int)(BM * lda * 8), 0x00020000);
+        __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
+            (void *)(B + n0 * ldb), 0, (int)(BN * ldb * 8), 0x00020000);
+        // this lane's offset within a block of 8 rows: even and odd blocks
+        const int rl = (threadIdx.x & 63) >> 3, sl = threadIdx.x & 7;
+        const uint32_t c0 = 16 * (sl ^ (rl >> 1)), c1 = 16 * (sl ^ ((rl >> 1) + 4));
+        const uint32_t va0 = (uint32_t)(rl * lda * 8) + c0, va1 = (uint32_t)(rl * lda * 8) + c1;
+        const uint32_t vb0 = (uint32_t)(rl * ldb * 8) + c0, vb1 = (uint32_t)(rl * ldb * 8) + c1;
+        // the first NS stages, then wait for stage 0
+#pragma unroll
+        for (int p = 0; p < NS; ++p)
+            if (p < nk) issue(s0 + p * STAGE, ra, rb, lda, ldb, (int64_t)p * BK, w, va0, va1, vb0, vb1);
+        if (nk >= NS) wait_vmcnt<(NS - 1) * (AI + BI)>();
+        else wait_vmcnt<0>();
+        lds_barrier();
+        Frag f[2][NF];
+        load_frags(smem, 0, f[0]);
+        int cur = 0;
+        for (int kt = 0; kt < nk - 1; ++kt) {
+            const char *sc = smem + cur * STAGE;
+            const int nxt = cur + 1 == NS ? 0 : cur + 1;
+#pragma unroll
+            for (int q = 0; q < NKK - 1; ++q) {
+                load_frags(sc, (q + 1) * 4, f[(q + 1) & 1]);
+                mmas(f[q & 1]);
+                interleave();
+            }
+            // stage kt + 1 has landed (up to NS - 2 later stages may be in
+            // flight; near the end fewer are, so wait for all) and this wave's
+            // last reads of stage kt have returned; then the same for every wave
+            if (kt + NS - 1 < nk) wait_vmcnt_lds<(NS - 2) * (AI + BI)>();
+            else wait_vmcnt_lds<0>();
+            lds_barrier();
+            load_frags(smem + nxt * STAGE, 0, f[0]);
+            mmas(f[1]);
+            interleave();
+            // nobody reads stage kt any more
+            if (kt + NS < nk)
+                issue(s0 + cur * STAGE, ra, rb, lda, ldb, (int64_t)(kt + NS) * BK, w, va0, va1, vb0, vb1);
+            cur = nxt;
+        }
+        const char *sc = smem + cur * STAGE;
+#pragma unroll
+        for (int q = 0; q < NKK - 1; ++q) {
+            load_frags(sc, (q + 1) * 4, f[(q + 1) & 1]);
+            mmas(f[q & 1]);
+            interleave();
+        }
+        mmas(f[1]);
+        wait_vmcnt_lds<0>();
+        lds_barrier();
+    }
+
+    __device__ static inline int row_of(int i, int r) {
+        const int lane = threadIdx.x & 63, wm = (threadIdx.x >> 6) % WM;
+        return (wm * WTM + i) * 16 + MF::crow(lane, r);
+    }
+    __device__ static inline int col_of(int j) {
+        const int lane = threadIdx.x & 63, wn = (threadIdx.x >> 6) / WM;
+        return (wn * WTN + j) * 16 + MF::ccol(lane);
     }
 };
 

@@ -164,9 +164,10 @@ hipError_t launch_rhs_rows(const double *Wp, int64_t ld, int64_t n, int64_t row0
                            const int32_t *gid, int64_t k, int64_t kpad, uint64_t seed,
                            double *Yt, hipStream_t s);
 // Prod[r][row0 + q] = sum_j Vt[r][j] Wp[q][j] for the rows of a panel
-// (rows a multiple of 128; one FP64 MFMA pass, no split).
+// (rows a multiple of 128; one FP64 MFMA pass, no split).  Rows r >= k of
+// Prod may be left unwritten.
 hipError_t launch_panel_product(const double *Vt, const double *Wp, int64_t ld, int64_t n,
-                                int64_t kpad, int64_t row0, int64_t rows, double *Prod,
+                                int64_t k, int64_t kpad, int64_t row0, int64_t rows, double *Prod,
                                 hipStream_t s);
 // The residual reduction with S explicit split partials (S = 1: P is W X);
 // dm (ld entries) scales the maxima written to mpart.
@@ -175,13 +176,13 @@ hipError_t launch_residual_reduce(const double *P, int S, const double *Yt, cons
                                   int64_t kpad, int64_t k, double *Rt, double *npart,
                                   double *mpart, hipStream_t s);
 // Streamed solve steps: dinv = D^{-1/2}, rdeg = D^{-1}; Ut = rdeg * Rt;
-// Xt += Ut + rdeg * Prod (Xt += P1 r for the one-level chain).
+// Xt += Ut + rdeg * Prod on the k columns (Xt += P1 r for the one-level chain).
 hipError_t launch_stream_prep(const double *deg, int64_t n, int64_t ld, double *dinv,
                               double *rdeg, hipStream_t s);
 hipError_t launch_stream_scale(const double *Rt, const double *rdeg, int64_t ld, int64_t kpad,
                                double *Ut, hipStream_t s);
 hipError_t launch_stream_update(const double *Ut, const double *Prod, const double *rdeg,
-                                int64_t ld, int64_t kpad, double *Xt, hipStream_t s);
+                                int64_t ld, int64_t k, double *Xt, hipStream_t s);
 // R = Y - deg * X + W X (skip_gemm: R = Y - deg * X).  P: residual_splits()
 // x kpad x ld doubles of split-K partials.  For prec 0..2 the reduction also
 // writes V = dm * R (V64) and its rounded copy (Vlo); prec 3 leaves V alone.
@@ -191,13 +192,15 @@ hipError_t launch_residual_k(int prec, const double *Xt, const double *W, const 
                              double *V64, void *Vlo, double *npart, double *mpart,
                              hipStream_t s);
 // Split-K count of the residual product: choice 0 the default, 1 half of
-// it, 2 twice it (the candidates of the tuner; workspaces hold choice 2).
+// it, 2 twice it (the candidates of the tuner), none above what a solve
+// workspace holds.
+int residual_splits_max(int64_t ld, int64_t kpad, int64_t n);
 int residual_splits(int64_t ld, int64_t kpad, int64_t n, int choice);
 // The two halves of launch_residual_k: the split-K product W X into S
-// partials of P, and the reduction over S partials (S = 0: none,
+// partials of P (rows r >= k may be left unwritten), and the reduction over S partials (S = 0: none,
 // R = Y - deg X) that forms R, the operand V and the norm partials.
 hipError_t launch_residual_gemm(const double *Xt, const double *W, int64_t ld, int64_t n,
-                                int64_t kpad, int S, double *P, hipStream_t s);
+                                int64_t k, int64_t kpad, int S, double *P, hipStream_t s);
 hipError_t launch_residual_reduce_k(int prec, const double *P, int S, const double *Yt,
                                     const double *Xt, const double *deg, const double *dm,
                                     int64_t ld, int64_t n, int64_t kpad, int64_t k, double *Rt,

@@ -18,6 +18,9 @@
 //
 // Vectors of k columns are stored transposed: row r of a kpad x ld panel
 // holds column r over all (padded) nodes.
+#include <algorithm>
+#include <vector>
+
 #include "batch.h"
 #include "common.h"
 #include "gemm.h"
@@ -414,30 +417,75 @@ hipError_t launch_rhs(const double *W, int64_t ld, int64_t n, const int32_t *gid
 // P[s][r][i] = sum_{j in split s} Xt[r][j] W[i][j] followed by a reduction
 // that forms R, the next preconditioner operand and the column-norm partials.
 
-// BT: W is the whole symmetric matrix, read along its rows as W^T (k-tiles of
-// 16 rows x 128 contiguous columns); row panels are read as they are.
-template <int BM, bool BT = false> struct ResCfg {
-    static constexpr int WM = BM / 64, WN = 8 / (BM / 64);
-    using Core = GemmCore<MfmaF64, BM, 128, 16, WM, WN, BT>;
-};
+// Tile shapes of the product (the same bits from each; see residual_cost):
+// 0 and 1 for whole panels of 256 and 128 columns, 2..8 for c 16-column groups
+// (BM = 16 c rows of X, each wave all of them by 16 nodes).
+constexpr int kResShapes = 9;
+template <int SHAPE> struct ResCfg { using Core = Dma64Core<16 * SHAPE, 64, 1, 4, 3>; };
+template <> struct ResCfg<0> { using Core = Dma64Core<256, 128, 4, 2, 2>; };
+template <> struct ResCfg<1> { using Core = Dma64Core<128, 128, 2, 4, 2>; };
+
+static int64_t res_bm(int shape) { return shape == 0 ? 256 : shape == 1 ? 128 : 16 * shape; }
+static int64_t res_bn(int shape) { return shape < 2 ? 128 : 64; }
+static bool res_fits(int shape, int64_t kpad) { return shape >= 2 || kpad % res_bm(shape) == 0; }
+// Tile rows: every column of the panel (shapes 0, 1), or the 16-column groups
+// that hold one of the k columns.
+static int64_t res_mt(int shape, int64_t kpad, int64_t k) {
+    return shape < 2 ? kpad / res_bm(shape) : cdiv(cdiv(k, 16), shape);
+}
+// Whether the tiles stay inside the panel (shape 4 always does).
+static bool res_inside(int shape, int64_t kpad, int64_t k) {
+    return res_fits(shape, kpad) && res_mt(shape, kpad, k) * res_bm(shape) <= kpad;
+}
+
+// Share of the matrix pipes' rate that a shape reaches: a wave of c 16-column
+// groups runs c MFMAs per c + 1 fragment reads, and a CU that holds one small
+// tile alone has one wave per SIMD (measured at k = 128: n = 4096 in 128 x 128
+// tiles 69 us with S = 8 and 135 with S = 4, where 64 x 64 tiles take 72; n =
+// 2048, S = 8: 39 against 23 us).
+static double res_eff(int shape, bool alone) {
+    constexpr double e[kResShapes] = {1.0, 1.0, 0.75, 0.82, 0.90, 0.91, 0.92, 0.93, 0.94};
+    return shape >= 2 && alone ? 0.92 * e[shape] : e[shape];
+}
+
+// Modelled seconds of a product of `cols` nodes over K reduction steps in S
+// splits: the matrix pipes of a CU run one tile's work at about 0.29 TFLOP/s
+// however many tiles share it, so the time is that of the CU with the most
+// tiles.
+static double residual_cost(int shape, int64_t k, int64_t kpad, int64_t cols, int64_t K, int S) {
+    const int64_t wgs = res_mt(shape, kpad, k) * (cols / res_bn(shape)) * S, rounds = cdiv(wgs, 256);
+    const double eff = res_eff(shape, rounds == 1);
+    return 4e-6 + (double)rounds * 2.0 * (double)(res_bm(shape) * res_bn(shape)) * (double)cdiv(K, S) / (0.29e12 * eff);
+}
+
+static int residual_shape(int64_t k, int64_t kpad, int64_t cols, int64_t K, int S) {
+    int best = 4;   // 64 x 64: fits every panel
+    double tb = 1e300;
+    for (int q = 0; q < kResShapes; ++q) {
+        if (!res_inside(q, kpad, k)) continue;
+        const double t = residual_cost(q, k, kpad, cols, K, S);
+        if (t < tb) { tb = t; best = q; }
+    }
+    return best;
+}
 
 // W may be a row panel: its row q holds node row0 + q, whose products land in
 // column row0 + q of the partials (row0 = 0 for the whole matrix).
-template <int BM, bool BT>
+template <int SHAPE>
 __device__ __forceinline__ void residual_gemm_tile(const double *Xt, const double *W, int64_t ld,
                                           int64_t kend, int64_t ks, int mt, int nt, double *P,
                                           int64_t kpad, int64_t row0, int id, char *smem_raw) {
-    using Core = typename ResCfg<BM, BT>::Core;
+    using Core = typename ResCfg<SHAPE>::Core;
     double *smem = (double *)smem_raw;
     // split-major order: the WGs of one split stream the same K range
     const int split = id / (mt * nt);
     int I, J;
     rect_tile<4>(id % (mt * nt), mt, nt, I, J);
-    const int64_t m0 = (int64_t)I * BM, n0 = (int64_t)J * 128;
+    const int64_t m0 = (int64_t)I * Core::TBM, n0 = (int64_t)J * Core::TBN;
     const int64_t k0 = (int64_t)split * ks;
     const int64_t kk = k0 < kend ? (kend - k0 < ks ? kend - k0 : ks) : 0;
     Core g;
-    g.run(Xt + k0, ld, BT ? W + k0 * ld : W + k0, ld, m0, n0, kk, smem);
+    g.run(Xt + k0, ld, W + k0, ld, m0, n0, kk, smem);
     double *Ps = P + (int64_t)split * kpad * ld + row0;
 #pragma unroll
     for (int a = 0; a < Core::WTM; ++a)
@@ -448,17 +496,14 @@ __device__ __forceinline__ void residual_gemm_tile(const double *Xt, const doubl
                 Ps[(m0 + Core::row_of(a, rr)) * ld + n0 + Core::col_of(b)] = g.acc[a][b][rr];
 }
 
-template <int BM, bool BT>
-__global__ __launch_bounds__(512) void k_residual_gemm(const double *Xt, const double *W,
-                                                       int64_t ld, int64_t kend, int64_t ks,
-                                                       int mt, int nt, int S, double *P,
-                                                       int64_t kpad, int64_t row0) {
+template <int SHAPE>
+__global__ __launch_bounds__(ResCfg<SHAPE>::Core::NT) void k_residual_gemm(
+    const double *Xt, const double *W, int64_t ld, int64_t kend, int64_t ks, int mt, int nt, int S,
+    double *P, int64_t kpad, int64_t row0) {
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
     const int id = xcd_remap(blockIdx.x, mt * nt * S);
-    residual_gemm_tile<BM, BT>(Xt, W, ld, kend, ks, mt, nt, P, kpad, row0, id, smem_raw);
+    residual_gemm_tile<SHAPE>(Xt, W, ld, kend, ks, mt, nt, P, kpad, row0, id, smem_raw);
 }
-
-static int res_bm(int64_t kpad) { return kpad % 256 == 0 ? 256 : (kpad % 128 == 0 ? 128 : 64); }
 
 // k-range of one split of the residual product (16-element multiples).
 __host__ __device__ inline int64_t residual_split_len(int64_t n, int S) {
@@ -466,78 +511,73 @@ __host__ __device__ inline int64_t residual_split_len(int64_t n, int S) {
     return (cdiv(kend, S) + 15) / 16 * 16;
 }
 
-// Split-K count of the FP64 residual product: choice 0 aims at >= 256
-// workgroups, 1 halves that count, 2 doubles it (at least four 16-wide
-// k-tiles per split either way).
-int residual_splits_fixed(int64_t n, int S) {
-    const int64_t kend = (n + 63) / 64 * 64;
-    const int64_t smax = kend / 64 > 0 ? kend / 64 : 1;   // >= 4 k-tiles per split
-    return (int)(S < 1 ? 1 : S > smax ? smax : S);
+// The most splits that a solve workspace holds: two rounds of one 256 x 128
+// (or narrower) tile per CU, at least four 16-wide k-tiles per split.
+int residual_splits_max(int64_t ld, int64_t kpad, int64_t n) {
+    const int64_t bm = kpad % 256 == 0 ? 256 : kpad % 128 == 0 ? 128 : 64;
+    const int64_t base = (kpad / bm) * (ld / 128), smax = (n + 63) / 64;
+    return (int)std::max<int64_t>(1, std::min<int64_t>(2 * cdiv(256, base), smax));
 }
 
+// Split-K count of the FP64 residual product: choice 0 the count whose
+// modelled product plus the writing and reading of its partial panels (at 3.5
+// TB/s) is least, 1 half that count, 2 twice.
 int residual_splits(int64_t ld, int64_t kpad, int64_t n, int choice) {
-    const int64_t base = (kpad / res_bm(kpad)) * (ld / 128);
     const int64_t kend = (n + 63) / 64 * 64;
-    int64_t S = (256 + base - 1) / base;          // aim at >= 256 workgroups
+    const int cap = residual_splits_max(ld, kpad, n);
+    int S = 1;
+    double tb = 1e300;
+    for (int c = 1; c <= cap; c *= 2) {
+        const int q = residual_shape(kpad, kpad, ld, kend, c);
+        const double t = residual_cost(q, kpad, kpad, ld, kend, c) + 16.0 * (double)(c * kpad * ld) / 3.5e12;
+        if (t < tb) { tb = t; S = c; }
+    }
     if (choice == 1) S = S / 2;
     if (choice == 2) S = 2 * S;
-    const int64_t smax = kend / 64 > 0 ? kend / 64 : 1;   // >= 4 k-tiles per split
-    if (S > smax) S = smax;
-    if (S < 1) S = 1;
-    return (int)S;
+    return std::max(1, std::min(S, cap));
 }
 
-template <int BM>
-static hipError_t resg_launch(const double *Xt, const double *W, int64_t ld, int64_t n,
-                              int64_t kpad, int S, double *P, hipStream_t s) {
-    using Core = typename ResCfg<BM, true>::Core;
+template <int SHAPE>
+static hipError_t resg_launch(const double *Xt, const double *W, int64_t ld, int64_t n, int64_t cols,
+                              int64_t row0, int64_t k, int64_t kpad, int S, double *P,
+                              hipStream_t s) {
+    using Core = typename ResCfg<SHAPE>::Core;
     static bool attr = false;
     if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_residual_gemm<BM, true>,
+        hipError_t e = hipFuncSetAttribute((const void *)k_residual_gemm<SHAPE>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)Core::SMEM);
         if (e != hipSuccess) return e;
         attr = true;
     }
-    const int mt = (int)(kpad / BM), nt = (int)(ld / 128);
-    const int64_t kend = (n + 63) / 64 * 64;
-    const int64_t ks = (cdiv(kend, S) + 15) / 16 * 16;
-    hipLaunchKernelGGL((k_residual_gemm<BM, true>), dim3(mt * nt * S), dim3(512), Core::SMEM, s, Xt, W,
-                       ld, kend, ks, mt, nt, S, P, kpad, (int64_t)0);
+    const int mt = (int)res_mt(SHAPE, kpad, k), nt = (int)(cols / Core::TBN);
+    hipLaunchKernelGGL(k_residual_gemm<SHAPE>, dim3(mt * nt * S), dim3(Core::NT), Core::SMEM, s, Xt, W,
+                       ld, (n + 63) / 64 * 64, residual_split_len(n, S), mt, nt, S, P, kpad, row0);
     return hipGetLastError();
 }
 
-template <int BM>
-static hipError_t panel_launch(const double *Vt, const double *Wp, int64_t ld, int64_t n,
-                               int64_t kpad, int64_t row0, int64_t rows, double *Prod,
-                               hipStream_t s) {
-    using Core = typename ResCfg<BM, false>::Core;
-    static bool attr = false;
-    if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_residual_gemm<BM, false>,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)Core::SMEM);
-        if (e != hipSuccess) return e;
-        attr = true;
+static hipError_t residual_product(const double *Xt, const double *W, int64_t ld, int64_t n,
+                                   int64_t cols, int64_t row0, int64_t k, int64_t kpad, int S,
+                                   double *P, hipStream_t s) {
+    switch (residual_shape(k, kpad, cols, (n + 63) / 64 * 64, S)) {
+    case 0: return resg_launch<0>(Xt, W, ld, n, cols, row0, k, kpad, S, P, s);
+    case 1: return resg_launch<1>(Xt, W, ld, n, cols, row0, k, kpad, S, P, s);
+    case 2: return resg_launch<2>(Xt, W, ld, n, cols, row0, k, kpad, S, P, s);
+    case 3: return resg_launch<3>(Xt, W, ld, n, cols, row0, k, kpad, S, P, s);
+    case 4: return resg_launch<4>(Xt, W, ld, n, cols, row0, k, kpad, S, P, s);
+    case 5: return resg_launch<5>(Xt, W, ld, n, cols, row0, k, kpad, S, P, s);
+    case 6: return resg_launch<6>(Xt, W, ld, n, cols, row0, k, kpad, S, P, s);
+    case 7: return resg_launch<7>(Xt, W, ld, n, cols, row0, k, kpad, S, P, s);
+    default: return resg_launch<8>(Xt, W, ld, n, cols, row0, k, kpad, S, P, s);
     }
-    const int mt = (int)(kpad / BM), nt = (int)(rows / 128);
-    const int64_t kend = (n + 63) / 64 * 64;
-    const int64_t ks = (kend + 15) / 16 * 16;
-    hipLaunchKernelGGL((k_residual_gemm<BM, false>), dim3(mt * nt), dim3(512), Core::SMEM, s, Vt, Wp, ld,
-                       kend, ks, mt, nt, 1, Prod, kpad, row0);
-    return hipGetLastError();
 }
 
 hipError_t launch_panel_product(const double *Vt, const double *Wp, int64_t ld, int64_t n,
-                                int64_t kpad, int64_t row0, int64_t rows, double *Prod,
+                                int64_t k, int64_t kpad, int64_t row0, int64_t rows, double *Prod,
                                 hipStream_t s) {
-    if (rows <= 0 || rows % 128 || row0 < 0 || row0 + rows > ld || kpad % 64)
+    if (rows <= 0 || rows % 128 || row0 < 0 || row0 + rows > ld || kpad % 64 || k < 1 || k > kpad)
         return hipErrorInvalidValue;
-    switch (res_bm(kpad)) {
-    case 256: return panel_launch<256>(Vt, Wp, ld, n, kpad, row0, rows, Prod, s);
-    case 128: return panel_launch<128>(Vt, Wp, ld, n, kpad, row0, rows, Prod, s);
-    default: return panel_launch<64>(Vt, Wp, ld, n, kpad, row0, rows, Prod, s);
-    }
+    return residual_product(Vt, Wp, ld, n, rows, row0, k, kpad, 1, Prod, s);
 }
 
 // R[r][i] = Y - deg X + sum_s P[s] (zero outside r < k, i < n; Y = NULL
@@ -649,20 +689,16 @@ __global__ void k_stream_update(const double *Ut, const double *Prod, const doub
 }
 
 hipError_t launch_stream_update(const double *Ut, const double *Prod, const double *rdeg,
-                                int64_t ld, int64_t kpad, double *Xt, hipStream_t s) {
-    const int64_t total = ld * kpad;
+                                int64_t ld, int64_t k, double *Xt, hipStream_t s) {
+    const int64_t total = ld * k;
     hipLaunchKernelGGL(k_stream_update, dim3((unsigned)cdiv(total, 256)), dim3(256), 0, s, Ut,
                        Prod, rdeg, ld, total, Xt);
     return hipGetLastError();
 }
 
 hipError_t launch_residual_gemm(const double *Xt, const double *W, int64_t ld, int64_t n,
-                                int64_t kpad, int S, double *P, hipStream_t s) {
-    switch (res_bm(kpad)) {
-    case 256: return resg_launch<256>(Xt, W, ld, n, kpad, S, P, s);
-    case 128: return resg_launch<128>(Xt, W, ld, n, kpad, S, P, s);
-    default: return resg_launch<64>(Xt, W, ld, n, kpad, S, P, s);
-    }
+                                int64_t k, int64_t kpad, int S, double *P, hipStream_t s) {
+    return residual_product(Xt, W, ld, n, ld, 0, k, kpad, S, P, s);
 }
 
 hipError_t launch_residual_reduce_k(int prec, const double *P, int S, const double *Yt,
@@ -689,7 +725,7 @@ hipError_t launch_residual_k(int prec, const double *Xt, const double *W, const 
                              hipStream_t s) {
     const int S = residual_splits(ld, kpad, n, 0);
     if (!skip_gemm) {
-        hipError_t e = launch_residual_gemm(Xt, W, ld, n, kpad, S, P, s);
+        hipError_t e = launch_residual_gemm(Xt, W, ld, n, k, kpad, S, P, s);
         if (e != hipSuccess) return e;
     }
     return launch_residual_reduce_k(prec, P, skip_gemm ? 0 : S, Yt,
@@ -783,16 +819,16 @@ hipError_t launch_prep_v2(int prec, const double *Rt, const double *dm, int64_t 
 // Grouped over the snapshots of a sequence (one launch for all of them;
 // converged snapshots skip their workgroups).
 
-template <int BM>
-__global__ __launch_bounds__(512) void k_residual_gemm_grouped(const BatchSnap *snaps, const int *prefix,
-                                                               int P, int64_t kpad, const int *done) {
+template <int SHAPE>
+__global__ __launch_bounds__(ResCfg<SHAPE>::Core::NT) void k_residual_gemm_grouped(
+    const BatchSnap *snaps, const int *prefix, int P, int64_t kpad, int mt, const int *done) {
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
     const int p = group_find(prefix, P, blockIdx.x);
     if (done[p]) return;
     const BatchSnap &d = snaps[p];
-    const int mt = (int)(kpad / BM), nt = (int)(d.ld / 128);
+    const int nt = (int)(d.ld / ResCfg<SHAPE>::Core::TBN);
     const int id = xcd_remap(blockIdx.x - prefix[p], prefix[p + 1] - prefix[p]);
-    residual_gemm_tile<BM, true>(d.Xt, d.W, d.ld, (d.n + 63) / 64 * 64, residual_split_len(d.n, d.res_splits),
+    residual_gemm_tile<SHAPE>(d.Xt, d.W, d.ld, (d.n + 63) / 64 * 64, residual_split_len(d.n, d.res_splits),
                            mt, nt, d.Pres, kpad, 0, id, smem_raw);
 }
 
@@ -815,37 +851,83 @@ __global__ __launch_bounds__(256) void k_residual_reduce_grouped(const BatchSnap
     }
 }
 
-template <int BM>
+template <int SHAPE>
 static hipError_t resg_grouped_launch(const BatchSnap *snaps, const int *prefix, int total, int P,
-                                      int64_t kpad, const int *done, hipStream_t s) {
-    using Core = typename ResCfg<BM, true>::Core;
+                                      int64_t k, int64_t kpad, const int *done, hipStream_t s) {
+    using Core = typename ResCfg<SHAPE>::Core;
     static bool attr = false;
     if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_residual_gemm_grouped<BM>,
+        hipError_t e = hipFuncSetAttribute((const void *)k_residual_gemm_grouped<SHAPE>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)Core::SMEM);
         if (e != hipSuccess) return e;
         attr = true;
     }
-    hipLaunchKernelGGL(k_residual_gemm_grouped<BM>, dim3(total), dim3(512), Core::SMEM, s, snaps,
-                       prefix, P, kpad, done);
+    hipLaunchKernelGGL(k_residual_gemm_grouped<SHAPE>, dim3(total), dim3(Core::NT), Core::SMEM, s, snaps,
+                       prefix, P, kpad, (int)res_mt(SHAPE, kpad, k), done);
     return hipGetLastError();
 }
 
-int residual_gemm_tiles(int64_t ld, int64_t kpad, int S) {
-    return (int)(kpad / res_bm(kpad) * (ld / 128)) * S;
+int residual_gemm_tiles(int shape, int64_t ld, int64_t k, int64_t kpad, int S) {
+    return (int)(res_mt(shape, kpad, k) * (ld / res_bn(shape))) * S;
 }
 
-hipError_t launch_residual_grouped(int prec, const BatchSnap *snaps, const int *prefix_gemm,
+// Tile shape and splits of a grouped product.  Its workgroups start in
+// snapshot order, so unequal reduction lengths (1024 to 8192 nodes) left the
+// chip to the longest at the end (39 of 78.6 TFLOP/s over the 24 snapshots);
+// every split now has about the same length Kc, the one whose work, longest
+// workgroup and partial panels are least by the same model.
+int residual_group_plan(int P, const int64_t *n, const int64_t *ld, int64_t k, int64_t kpad,
+                        const int *cap, const int *fixed, int *splits) {
+    int best = 4, bs = 0;
+    double tb = 1e300;
+    std::vector<int> S(P);
+    for (int q = 0; q < kResShapes; ++q) {
+        if (!res_inside(q, kpad, k)) continue;
+        for (int64_t kc = 512; kc <= 16384; kc *= 2) {
+            double work = 0.0, longest = 0.0, bytes = 0.0;
+            int64_t wgs = 0;
+            for (int t = 0; t < P; ++t) {
+                const int64_t kend = (n[t] + 63) / 64 * 64;
+                S[t] = fixed ? fixed[t] : (int)std::max<int64_t>(1, std::min<int64_t>(cdiv(kend, kc), cap[t]));
+                const int64_t c = residual_gemm_tiles(q, ld[t], k, kpad, S[t]);
+                const double one = 2.0 * (double)(res_bm(q) * res_bn(q)) * (double)cdiv(kend, S[t]) / 0.29e12;
+                work += one * (double)c;
+                longest = std::max(longest, one);
+                bytes += 16.0 * (double)S[t] * (double)(kpad * ld[t]);
+                wgs += c;
+            }
+            const double eff = res_eff(q, wgs <= 256);
+            const double t = std::max(work / 256.0 + 0.5 * longest, longest) / eff + bytes / 3.5e12;
+            if (t < tb) {
+                tb = t;
+                best = q;
+                bs = (int)kc;
+            }
+        }
+    }
+    for (int t = 0; t < P; ++t)
+        splits[t] = fixed ? fixed[t]
+                          : (int)std::max<int64_t>(1, std::min<int64_t>(cdiv((n[t] + 63) / 64 * 64, bs), cap[t]));
+    return best;
+}
+
+hipError_t launch_residual_grouped(int prec, const BatchSnap *snaps, int shape, const int *prefix_gemm,
                                    int total_gemm, const int *prefix_red, int total_red, int P,
                                    int64_t kpad, int64_t k, int skip_gemm, const int *done,
                                    hipStream_t s) {
     if (!skip_gemm) {
         hipError_t e;
-        switch (res_bm(kpad)) {
-        case 256: e = resg_grouped_launch<256>(snaps, prefix_gemm, total_gemm, P, kpad, done, s); break;
-        case 128: e = resg_grouped_launch<128>(snaps, prefix_gemm, total_gemm, P, kpad, done, s); break;
-        default: e = resg_grouped_launch<64>(snaps, prefix_gemm, total_gemm, P, kpad, done, s); break;
+        switch (shape) {
+        case 0: e = resg_grouped_launch<0>(snaps, prefix_gemm, total_gemm, P, k, kpad, done, s); break;
+        case 1: e = resg_grouped_launch<1>(snaps, prefix_gemm, total_gemm, P, k, kpad, done, s); break;
+        case 2: e = resg_grouped_launch<2>(snaps, prefix_gemm, total_gemm, P, k, kpad, done, s); break;
+        case 3: e = resg_grouped_launch<3>(snaps, prefix_gemm, total_gemm, P, k, kpad, done, s); break;
+        case 4: e = resg_grouped_launch<4>(snaps, prefix_gemm, total_gemm, P, k, kpad, done, s); break;
+        case 5: e = resg_grouped_launch<5>(snaps, prefix_gemm, total_gemm, P, k, kpad, done, s); break;
+        case 6: e = resg_grouped_launch<6>(snaps, prefix_gemm, total_gemm, P, k, kpad, done, s); break;
+        case 7: e = resg_grouped_launch<7>(snaps, prefix_gemm, total_gemm, P, k, kpad, done, s); break;
+        default: e = resg_grouped_launch<8>(snaps, prefix_gemm, total_gemm, P, k, kpad, done, s); break;
         }
         if (e != hipSuccess) return e;
     }
