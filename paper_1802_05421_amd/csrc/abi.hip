@@ -336,16 +336,15 @@ SolveWs plan_solve(Arena &a, int64_t n, int64_t k, int prec) {
 }
 
 struct ScoreWs {
-    double *Zh, *Zhe, *sq, *part;
+    double *Zh, *sq, *part;
     void *topk;
 };
 ScoreWs plan_score(Arena &a, int64_t m, int64_t k) {
     const int64_t mp = pad_n(m), kp = pad_k(k);
     ScoreWs w;
     w.Zh = a.take<double>((size_t)mp * 2 * kp);
-    w.Zhe = a.take<double>((size_t)mp * 2 * kp);
     w.sq = a.take<double>(mp);
-    w.part = a.take<double>((size_t)score_tiles_1d(mp) * mp);
+    w.part = a.take<double>((size_t)score_part_doubles(mp, kp));
     const int64_t cap = topk_scratch_elems(m, CDL_MAX_TOPK);
     w.topk = a.take<char>((size_t)cap * (2 * sizeof(double) + 2 * sizeof(int32_t)));
     return w;
@@ -1581,13 +1580,16 @@ cdl_status cdl_stream_embedding(cdl_ctx *ctx, const double *X, int64_t n, int64_
 
 // ---- scores -----------------------------------------------------------------------
 
-static cdl_status check_map(cdl_ctx *ctx, const int32_t *map, int64_t m, int64_t n) {
-    if (!map) return m == n ? CDL_OK : fail(ctx, CDL_E_ARG, "identity map needs m == n");
-    std::vector<int32_t> h(m);
-    HIPCHK(read_to_host(ctx, ctx->stream, {{h.data(), map, m * sizeof(int32_t)}}));
-    for (int32_t v : h)
-        if (v < 0 || v >= n) return fail(ctx, CDL_E_ARG, "map entry out of range");
-    return CDL_OK;
+// The common-node maps (both or neither): identity maps need m == n0 == n1;
+// given ones are checked on the device before anything reads through them
+// (one kernel and one 4-byte read; `flag` is scratch in device memory).
+static cdl_status check_maps(cdl_ctx *ctx, const int32_t *map0, const int32_t *map1, int64_t m,
+                             int64_t n0, int64_t n1, int *flag) {
+    if (!map0) return m == n0 && m == n1 ? CDL_OK : fail(ctx, CDL_E_ARG, "identity map needs m == n");
+    int bad = 0;
+    HIPCHK(launch_check_maps(map0, map1, m, n0, n1, flag, ctx->stream));
+    HIPCHK(read_to_host(ctx, ctx->stream, {{&bad, flag, sizeof(int)}}));
+    return bad ? fail(ctx, CDL_E_ARG, "map entry out of range") : CDL_OK;
 }
 
 // Argument checks shared by both score entry points (everything but the
@@ -1628,10 +1630,11 @@ static cdl_status score_enqueue(cdl_ctx *ctx, bool timed, const double *Z0, cons
         Timed t_(ctx, nm);
         return fn();
     };
-    HIPCHK(scope("build_zhat", [&] { return launch_build_zhat(Z0, Z1, map0, map1, m, mp, k, kp, stats0, stats1, w.Zh, w.Zhe, w.sq, s); }));
-    HIPCHK(scope("score", [&] { return launch_score(w.Zh, w.Zhe, kp, w.sq, m, mp, W0, pad_n(n0), W1, pad_n(n1), map0, map1,
+    const int shape = score_shape(1, &mp, kp, mode == CDL_SCORE_DELTA_A);
+    HIPCHK(scope("build_zhat", [&] { return launch_build_zhat(Z0, Z1, map0, map1, m, mp, k, stats0, stats1, w.Zh, w.sq, nullptr, s); }));
+    HIPCHK(scope("score", [&] { return launch_score(shape, w.Zh, k, w.sq, m, mp, W0, pad_n(n0), W1, pad_n(n1), map0, map1,
                                                     mode == CDL_SCORE_DELTA_A, w.part, nullptr, s); }));
-    HIPCHK(scope("score_reduce", [&] { return launch_score_reduce(w.part, score_tiles_1d(mp), m, mp, F, s); }));
+    HIPCHK(scope("score_reduce", [&] { return launch_score_reduce(shape, w.part, m, mp, F, s); }));
     if (top_k > 0) HIPCHK(scope("topk", [&] { return launch_topk(F, m, top_k, w.topk, top_idx, s); }));
     return CDL_OK;
 }
@@ -1651,9 +1654,8 @@ cdl_status cdl_anomaly_scores(cdl_ctx *ctx, const double *Z0, const double *W0,
     plan_score(need, m, k);
     if (ws_bytes < need.off) return fail(ctx, CDL_E_WORKSPACE, "score workspace too small");
     HIPCHK(hipSetDevice(ctx->device));
-    cdl_status st = check_map(ctx, map0, m, n0);
-    if (st != CDL_OK) return st;
-    st = check_map(ctx, map1, m, n1);
+    Arena a(ws);
+    const cdl_status st = check_maps(ctx, map0, map1, m, n0, n1, (int *)plan_score(a, m, k).topk);
     if (st != CDL_OK) return st;
     return score_enqueue(ctx, true, Z0, W0, stats0, n0, Z1, W1, stats1, n1, k, map0, map1, m, mode,
                          F, top_k, top_idx, ws);
@@ -1726,32 +1728,33 @@ cdl_status cdl_anomaly_edges(cdl_ctx *ctx, const double *Z0, const double *W0,
     plan_edges(need, m, k, top_k);
     if (ws_bytes < need.off) return fail(ctx, CDL_E_WORKSPACE, "edge workspace too small");
     HIPCHK(hipSetDevice(ctx->device));
-    cdl_status st = check_map(ctx, map0, m, n0);
-    if (st != CDL_OK) return st;
-    st = check_map(ctx, map1, m, n1);
-    if (st != CDL_OK) return st;
     Arena a(ws);
     EdgeWs e = plan_edges(a, m, k, top_k);
+    const cdl_status st = check_maps(ctx, map0, map1, m, n0, n1, (int *)e.sw.topk);
+    if (st != CDL_OK) return st;
     ScoreWs &w = e.sw;
     const int64_t mp = pad_n(m), kp = pad_k(k);
     const int weighted = mode == CDL_SCORE_DELTA_A;
     hipStream_t s = ctx->stream;
-    { Timed t_(ctx, "build_zhat"); HIPCHK(launch_build_zhat(Z0, Z1, map0, map1, m, mp, k, kp, stats0, stats1, w.Zh, w.Zhe, w.sq, s)); }
-    { Timed t_(ctx, "score"); HIPCHK(launch_score(w.Zh, w.Zhe, kp, w.sq, m, mp, W0, pad_n(n0), W1, pad_n(n1), map0, map1,
+    const int shape = score_shape(1, &mp, kp, weighted);
+    { Timed t_(ctx, "build_zhat"); HIPCHK(launch_build_zhat(Z0, Z1, map0, map1, m, mp, k, stats0, stats1, w.Zh, w.sq, e.tmax, s)); }
+    { Timed t_(ctx, "score"); HIPCHK(launch_score(shape, w.Zh, k, w.sq, m, mp, W0, pad_n(n0), W1, pad_n(n1), map0, map1,
                         weighted, w.part, e.tmax, s)); }
-    { Timed t_(ctx, "score_reduce"); HIPCHK(launch_score_reduce(w.part, score_tiles_1d(mp), m, mp, F, s)); }
+    { Timed t_(ctx, "score_reduce"); HIPCHK(launch_score_reduce(shape, w.part, m, mp, F, s)); }
     const int nt2 = score_tiles_2d(mp);
-    { Timed t_(ctx, "topk"); HIPCHK(launch_topk(e.tmax, nt2, top_k, e.tscratch, e.order, s)); }
-    { Timed t_(ctx, "edge_collect"); HIPCHK(launch_edge_collect(w.Zh, w.Zhe, kp, w.sq, m, mp, W0, pad_n(n0), W1, pad_n(n1),
+    { Timed t_(ctx, "topk"); HIPCHK(launch_topk(e.tmax, nt2, std::min(top_k, nt2), e.tscratch, e.order, s)); }
+    { Timed t_(ctx, "edge_collect"); HIPCHK(launch_edge_collect(w.Zh, k, w.sq, m, mp, W0, pad_n(n0), W1, pad_n(n1),
                                map0, map1, weighted, e.tmax, e.order, top_k, e.tau, e.cap,
                                e.count, e.cval, e.cidx, s)); }
-    { Timed t_(ctx, "topk"); HIPCHK(launch_topk64(e.cval, e.cidx, e.cap, e.count, top_k, e.cscratch, edge_val, e.idx, s)); }
-    { Timed t_(ctx, "edge_split"); HIPCHK(launch_edge_split(e.idx, m, top_k, edge_a, edge_b, s)); }
+    // the number of candidates (a few times top_k out of e.cap) sets the
+    // rounds of the final selection
     unsigned int cnt = 0;
     HIPCHK(read_to_host(ctx, s, {{&cnt, e.count, sizeof(cnt)}}));
     if ((int64_t)cnt > e.cap)
         return fail(ctx, CDL_E_UNSUPPORTED, "more than " + std::to_string(e.cap) +
                                                 " edges reach the K-th edge score (massive ties)");
+    { Timed t_(ctx, "topk"); HIPCHK(launch_topk64(e.cval, e.cidx, cnt, top_k, e.cscratch, edge_val, e.idx, s)); }
+    { Timed t_(ctx, "edge_split"); HIPCHK(launch_edge_split(e.idx, m, top_k, edge_a, edge_b, s)); }
     return CDL_OK;
 }
 
@@ -2129,10 +2132,10 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
         Arena as(base + L.score[t - 1]);
         const ScoreWs sw = plan_score(as, m, k);
         r.Zh = sw.Zh;
-        r.Zhe = sw.Zhe;
         r.sq = sw.sq;
         r.part = sw.part;
         r.F = F[t - 1];
+        r.top = top_idx ? top_idx[t - 1] : nullptr;
         mcnt[t - 1] = m;
     }
     // prefix tables: 0 squaring, 1 apply product, 2 apply update, 3 residual
@@ -2156,7 +2159,10 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
     const int tot_rr = fill(4, P, [&](int t) { return (int)std::min<int64_t>(hs[t].ld / 256 * kp, kEltWgs); });
     const int tot_pv = fill(5, P, [&](int t) { return apply_reduce_blocks(hs[t].ld, kp, kEltWgs); });
     const int tot_zh = fill(6, NP, [&](int t) { return (int)hp[t].mpad; });
-    const int tot_sc = fill(7, NP, [&](int t) { return score_tiles_2d(hp[t].mpad); });
+    std::vector<int64_t> mpads(NP);
+    for (int t = 0; t < NP; ++t) mpads[t] = hp[t].mpad;
+    const int sc_shape = score_shape(NP, mpads.data(), kp, q->mode == CDL_SCORE_DELTA_A);
+    const int tot_sc = fill(7, NP, [&](int t) { return score_tile_count(sc_shape, mpads[t]); });
     const int tot_sr = fill(8, NP, [&](int t) { return (int)((hp[t].m + 63) / 64); });
     BatchSnap *dsnap = (BatchSnap *)(base + L.snaps);
     BatchPair *dpair = (BatchPair *)(base + L.pairs);
@@ -2276,16 +2282,10 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
         for (int t = 0; t < P; ++t)
             { Timed t_(ctx, "finalize_z"); HIPCHK(launch_finalize_z2(solves[t].Xt, hs[t].ld, sn[t].n, kp, k, solves[t].mean,
                                                              (double *)(base + L.Z[t]), s0)); }
-        { Timed t_(ctx, "score"); HIPCHK(cdl::launch_score_grouped(dpair, dtable(6), tot_zh, dtable(7), tot_sc, dtable(8), tot_sr, NP, k, kp,
+        { Timed t_(ctx, "score"); HIPCHK(cdl::launch_score_grouped(sc_shape, dpair, dtable(6), tot_zh, dtable(7), tot_sc, dtable(8), tot_sr, NP, k,
                                                              weighted, s0)); }
         if (top_idx && q->top_k > 0)
-            for (int t = 0; t < NP; ++t) {
-                Arena as(base + L.score[t]);
-                const ScoreWs sw = plan_score(as, mcnt[t], k);
-                const int32_t K = std::min<int32_t>(q->top_k, (int32_t)mcnt[t]);
-                Timed t_(ctx, "topk");
-                HIPCHK(launch_topk(F[t], mcnt[t], K, sw.topk, top_idx[t], s0));
-            }
+            { Timed t_(ctx, "topk"); HIPCHK(cdl::launch_topk_grouped(dpair, mcnt.data(), NP, q->top_k, s0)); }
         return CDL_OK;
     };
     // the key of a graph: buffers, shapes, parameters, global ids
@@ -2493,11 +2493,12 @@ cdl_status cdl_score_sequence(cdl_ctx *ctx, int32_t n_snap, const cdl_snapshot *
                     ScoreWs w = plan_score(as, m, q->k);
                     const int32_t K = top_idx ? std::min<int32_t>(q->top_k, (int32_t)m) : 0;
                     const int weighted = q->mode == CDL_SCORE_DELTA_A;
+                    const int shape = score_shape(1, &mp, kp, weighted);
                     hipError_t e = hipSuccess;
-                    { Timed t_(ctx, "build_zhat"); e = launch_build_zhat(Z3[pb], Z3[b], mp0, mp1, m, mp, q->k, kp, st3[pb], st3[b], w.Zh, w.Zhe, w.sq, es); }
-                    if (e == hipSuccess) { Timed t_(ctx, "score"); e = launch_score(w.Zh, w.Zhe, kp, w.sq, m, mp, W3[pb], pad_n(y.n), W3[b], pad_n(x.n),
+                    { Timed t_(ctx, "build_zhat"); e = launch_build_zhat(Z3[pb], Z3[b], mp0, mp1, m, mp, q->k, st3[pb], st3[b], w.Zh, w.sq, nullptr, es); }
+                    if (e == hipSuccess) { Timed t_(ctx, "score"); e = launch_score(shape, w.Zh, q->k, w.sq, m, mp, W3[pb], pad_n(y.n), W3[b], pad_n(x.n),
                                         mp0, mp1, weighted, w.part, nullptr, es); }
-                    if (e == hipSuccess) { Timed t_(ctx, "score_reduce"); e = launch_score_reduce(w.part, score_tiles_1d(mp), m, mp, F[t - 1], es); }
+                    if (e == hipSuccess) { Timed t_(ctx, "score_reduce"); e = launch_score_reduce(shape, w.part, m, mp, F[t - 1], es); }
                     if (e == hipSuccess && K > 0) { Timed t_(ctx, "topk"); e = launch_topk(F[t - 1], m, K, w.topk, top_idx[t - 1], es); }
                     if (e != hipSuccess) {
                         st = fail(ctx, CDL_E_HIP, std::string("score launch: ") + hipGetErrorString(e));

@@ -175,6 +175,16 @@ __host__ __device__ inline void upper_band_tile(int id, int I0, int nrows, int n
         r0 += h;
     }
 }
+// The id of tile (I, J) of the whole matrix's cover (J >= 2 I): the inverse of
+// upper_band_tile with I0 = 0, nrows = ncol / 2.
+template <int G> __host__ __device__ inline int upper_band_id(int I, int J, int ncol) {
+    const int nrows = ncol / 2;
+    int id = 0, r0 = 0;
+    for (; r0 + G <= I; r0 += G) id += G * (G + 1) + (ncol - 2 * r0 - 2 * G) * G;
+    const int h = nrows - r0 < G ? nrows - r0 : G, c = J - 2 * r0;
+    if (c < 2 * h) return id + (c / 2) * (c / 2 + 1) + (c & 1) * (c / 2 + 1) + I - r0;
+    return id + h * (h + 1) + (c - 2 * h) * h + I - r0;
+}
 __host__ __device__ inline int rect_upper_tiles(int64_t ld) {
     const int ncol = (int)(ld / 128), nrow = (int)(ld / 256);
     return nrow * ncol - nrow * (nrow - 1);

@@ -515,8 +515,20 @@ struct Dma64Core {
         if constexpr (I + 1 < G) interleave<I + 1>();
     }
 
+    __device__ inline void negate() {
+#pragma unroll
+        for (int i = 0; i < WTM; ++i)
+#pragma unroll
+            for (int j = 0; j < WTN; ++j)
+#pragma unroll
+                for (int r = 0; r < MF::R; ++r) acc[i][j][r] = -acc[i][j][r];
+    }
+
     // Full K loop (K a multiple of 16; rows m0.. and n0.. inside the
     // allocations).  smem holds SMEM bytes and is free again on return.
+    // DIFF: the second half of the k range minus the first (the sums are
+    // negated half way, which is exact; K a multiple of 32).
+    template <bool DIFF = false>
     __device__ inline void run(const T *A, int64_t lda, const T *B, int64_t ldb, int64_t m0,
                                int64_t n0, int64_t K, T *smem_t) {
         char *smem = (char *)smem_t;
@@ -552,6 +564,7 @@ struct Dma64Core {
         for (int kt = 0; kt < nk - 1; ++kt) {
             const char *sc = smem + cur * STAGE;
             const int nxt = cur + 1 == NS ? 0 : cur + 1;
+            if (DIFF && 2 * kt == nk) negate();
 #pragma unroll
             for (int q = 0; q < NKK - 1; ++q) {
                 load_frags(sc, (q + 1) * 4, f[(q + 1) & 1]);
@@ -573,6 +586,7 @@ struct Dma64Core {
             cur = nxt;
         }
         const char *sc = smem + cur * STAGE;
+        if (DIFF && nk == 2) negate();
 #pragma unroll
         for (int q = 0; q < NKK - 1; ++q) {
             load_frags(sc, (q + 1) * 4, f[(q + 1) & 1]);

@@ -219,19 +219,25 @@ hipError_t launch_finalize_z2(const double *Xt, int64_t ld, int64_t n, int64_t k
                               double *mean, double *Z, hipStream_t s);
 
 // ---- scores -------------------------------------------------------------------
+// Row pitch of the signature embeddings (two halves of k padded to 16).
+int64_t score_ldz(int64_t k);
+// tmax != nullptr: also sets the score_tiles_2d(mpad) tile maxima to -1.
 hipError_t launch_build_zhat(const double *Z0, const double *Z1, const int32_t *map0,
                              const int32_t *map1, int64_t m, int64_t mpad, int64_t k,
-                             int64_t kpad, const double *stats0, const double *stats1,
-                             double *Zh, double *Zhe, double *sq, hipStream_t s);
-// Partial-sum slots of mpad entries each (mpad / 128 + mpad / 256).
-int score_tiles_1d(int64_t mpad);
+                             const double *stats0, const double *stats1, double *Zh, double *sq,
+                             double *tmax, hipStream_t s);
+// Doubles that a score workspace holds for partial sums.
+int64_t score_part_doubles(int64_t mpad, int64_t kpad);
+// Tile shape of the score Gram of P pairs in one launch, and a shape's tiles.
+int score_shape(int P, const int64_t *mpad, int64_t kpad, int weighted);
+int score_tile_count(int shape, int64_t mpad);
 // *flag = 1 if an entry of map0 (map1) is outside [0, n0) ([0, n1)), else 0.
 hipError_t launch_check_maps(const int32_t *map0, const int32_t *map1, int64_t m, int64_t n0,
                              int64_t n1, int *flag, hipStream_t s);
-// Score tiles: 256 x 128 over the upper triangle (rect_upper_tiles).
-// tmax: per-tile maximum edge score (a < b), score_tiles_2d(mpad) entries,
-// or nullptr.
-hipError_t launch_score(const double *Zh, const double *Zhe, int64_t kpad, const double *sq,
+// tmax: the largest edge score of each 256 x 128 tile of the upper triangle
+// (score_tiles_2d(mpad) entries in the order of rect_upper_tiles, cleared by
+// launch_build_zhat), or nullptr.
+hipError_t launch_score(int shape, const double *Zh, int64_t k, const double *sq,
                         int64_t m, int64_t mpad, const double *W0, int64_t ld0,
                         const double *W1, int64_t ld1, const int32_t *map0,
                         const int32_t *map1, int weighted, double *part, double *tmax,
@@ -240,7 +246,7 @@ int score_tiles_2d(int64_t mpad);
 // tile_order: tile indices by descending maximum (first K used); sets tau
 // and clears *count, then appends the edges with score >= tau to
 // (cval, cidx) through *count (at most cap stored).
-hipError_t launch_edge_collect(const double *Zh, const double *Zhe, int64_t kpad,
+hipError_t launch_edge_collect(const double *Zh, int64_t k,
                                const double *sq, int64_t m, int64_t mpad, const double *W0,
                                int64_t ld0, const double *W1, int64_t ld1,
                                const int32_t *map0, const int32_t *map1, int weighted,
@@ -249,11 +255,12 @@ hipError_t launch_edge_collect(const double *Zh, const double *Zhe, int64_t kpad
                                int64_t *cidx, hipStream_t s);
 hipError_t launch_edge_split(const int64_t *idx, int64_t m, int K, int32_t *a, int32_t *b,
                              hipStream_t s);
-hipError_t launch_topk64(const double *val, const int64_t *idx, int64_t cap,
-                         const unsigned int *dcount, int K, void *scratch, double *val_out,
-                         int64_t *idx_out, hipStream_t s);
-hipError_t launch_score_reduce(const double *part, int nparts, int64_t m, int64_t mpad,
-                               double *F, hipStream_t s);
+// Best K of `count` candidates; scratch holds 2 * topk_scratch_elems(count, K)
+// doubles and as many int64.
+hipError_t launch_topk64(const double *val, const int64_t *idx, int64_t count, int K, void *scratch,
+                         double *val_out, int64_t *idx_out, hipStream_t s);
+hipError_t launch_score_reduce(int shape, const double *part, int64_t m, int64_t mpad, double *F,
+                               hipStream_t s);
 // Top-K by (descending value, ascending index); scratch holds 2 * cand_cap
 // doubles + 2 * cand_cap ints, cand_cap = topk_scratch_elems(m, K).
 int64_t topk_scratch_elems(int64_t m, int K);

@@ -54,3 +54,79 @@ def test_products_of_every_column_count(cdl, n, k):
         _, Zs, info = cdl.stream_embedding(dev(X), k, SEED, sigma=6.0, tol=1e-12, max_iter=60,
                                            panel_rows=256)
         assert info.converged and rel(host(Zs), want) <= 1e-10
+
+
+def score_inputs(cdl, n, k, weighted, rng):
+    """Embeddings and graphs of two snapshots straight from random numbers."""
+    Z = [rng.standard_normal((n, k)) for _ in range(2)]
+    Z[1] = 0.9 * Z[0] + 0.3 * Z[1]
+    vol = [float(n * n) / 3, float(n * n) / 4]
+    gs, W = [], []
+    for t in range(2):
+        A = np.zeros((cdl.ld(n), cdl.ld(n)))
+        if weighted:
+            B = rng.uniform(0.1, 1.0, (n, n))
+            A[:n, :n] = np.triu(B, 1) + np.triu(B, 1).T
+        W.append(A[:n, :n])
+        gs.append(cdl.Graph(W=dev(A), deg=dev(np.ones(n)), stats=dev(np.array([vol[t], 1.0, 1.0, 1.0])), n=n))
+    return Z, vol, W, gs
+
+
+def edge_matrix(Z, vol, W, weighted, m0, m1):
+    E = np.zeros((len(m0), len(m0)))
+    for z, v, m, s in ((Z[0], vol[0], m0, 1.0), (Z[1], vol[1], m1, -1.0)):
+        z = z[m] * np.sqrt(v)
+        sq = (z * z).sum(1)
+        E += s * (sq[:, None] + sq[None, :] - 2.0 * z @ z.T)
+    np.fill_diagonal(E, 0.0)
+    E = np.abs(E)
+    return E * np.abs(W[1][np.ix_(m1, m1)] - W[0][np.ix_(m0, m0)]) if weighted else E
+
+
+# The score Gram takes 64 x 64, 128 x 128 or 256 x 128 tiles by m; its k range
+# is two halves padded to 16 columns.  Each dc is a sum of 2k products rounded
+# in FP64 (numpy's the same, in another order): relative error of F below
+# (2k + 3) 2^-53 times the cancellation in sq_a + sq_b - 2 G, here under 1e3.
+@pytest.mark.parametrize("n,m,k,weighted", [(2, 2, 1, False), (65, 64, 16, True), (300, 257, 17, False),
+                                            (700, 641, 40, True), (2600, 2305, 33, True),
+                                            (3100, 3100, 130, False), (4700, 4353, 8, False)])
+def test_scores_of_every_tile_shape(cdl, n, m, k, weighted):
+    rng = np.random.default_rng(n + m)
+    print("score case n=%d m=%d k=%d" % (n, m, k), flush=True)
+    Z, vol, W, gs = score_inputs(cdl, n, k, weighted, rng)
+    maps = [np.arange(n) if m == n else np.sort(rng.choice(n, m, replace=False)) for _ in range(2)]
+    E = edge_matrix(Z, vol, W, weighted, *maps)
+    want = E.sum(1)
+    kw = {} if m == n else dict(map0=dev(maps[0].astype(np.int32)), map1=dev(maps[1].astype(np.int32)))
+    mode, K = ("delta_a" if weighted else "unweighted"), min(50, m)
+    Zd = [dev(z) for z in Z]
+    F, top = cdl.anomaly_scores(Zd[0], gs[0], Zd[1], gs[1], mode=mode, top_k=K, **kw)
+    tol = (2 * k + 3) * 2.0 ** -53 * 1e3
+    assert np.abs(host(F) - want).max() <= tol * np.abs(want).max()
+    Fh = host(F)
+    np.testing.assert_array_equal(host(top), np.lexsort((np.arange(m), -Fh))[:K])
+    if m > 2:
+        F2, a, b, v = cdl.anomaly_edges(Zd[0], gs[0], Zd[1], gs[1], top_k=K, mode=mode, **kw)
+        np.testing.assert_array_equal(host(F2), Fh)
+        iu = np.triu_indices(m, 1)
+        order = np.argsort(-E[iu], kind="stable")[:K]
+        assert np.abs(host(v) - E[iu][order]).max() <= tol * E.max()
+        got = E[host(a), host(b)]
+        assert np.all(host(a) < host(b)) and np.abs(got - host(v)).max() <= tol * E.max()
+
+
+# Top-K over one chunk of 512, several, and enough for two further rounds, with
+# exact ties (ordered by index).
+@pytest.mark.parametrize("m,K", [(2, 1), (511, 50), (513, 256), (5000, 256), (70000, 50)])
+def test_topk_rounds_and_ties(cdl, m, K):
+    K = min(K, m)
+    rng = np.random.default_rng(m)
+    # scores through the public call: one column, two clusters at distance 0 or
+    # d_c, so that many nodes tie exactly; the order must be (-F, index)
+    lev = rng.integers(0, 3, m).astype(np.float64)
+    Z0, Z1 = lev[:, None], np.zeros((m, 1))
+    st = dev(np.array([1.0, 1.0, 1.0, 1.0]))
+    g = cdl.Graph(W=None, deg=dev(np.ones(m)), stats=st, n=m)
+    F, top = cdl.anomaly_scores(dev(Z0), g, dev(Z1), g, top_k=K)
+    Fh = host(F)
+    np.testing.assert_array_equal(host(top), np.lexsort((np.arange(m), -Fh))[:K])
