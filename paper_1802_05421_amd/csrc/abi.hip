@@ -456,12 +456,11 @@ cdl_status graph_enqueue(cdl_ctx *ctx, const double *X, int64_t n, int64_t T, in
     GraphWs w = plan_graph(a, n, T);
     const int64_t ld = pad_n(n), Tp = pad_t(T);
     hipStream_t s = ctx->stream;
-    { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w.flags, 256, s)); }
-    { Timed t_(ctx, "pad_series"); HIPCHK(launch_pad_series(X, n, T, ldx, w.Xp, ld, Tp, w.sqn, w.flags, s)); }
+    { Timed t_(ctx, "pad_series"); HIPCHK(launch_pad_series(X, n, T, ldx, w.Xp, ld, Tp, w.sqn, nullptr, w.flags + kDegreeTicket, s)); }
     // the median's bracket comes from a sample taken from the series, so that
     // the Gram's epilogue can count and gather it (no pass over D2 for it)
     const bool br = sigma <= 0.0 && select_uses_bracket(n, ctx->select_mode == 0);
-    if (sigma <= 0.0) { Timed t_(ctx, "select_median"); HIPCHK(launch_select_reset(w.sel, s)); }
+    if (sigma <= 0.0 && !br) { Timed t_(ctx, "select_median"); HIPCHK(launch_select_reset(w.sel, s)); }
     if (br) { Timed t_(ctx, "select_median"); HIPCHK(launch_select_presample(w.Xp, Tp, w.sqn, n, w.sel, w.selbuf, s)); }
     { Timed t_(ctx, "gram_dist"); HIPCHK(launch_gram_dist(w.Xp, Tp, w.sqn, n, ld, W, sigma > 0.0 ? nullptr : w.sel,
                                                           br ? w.selbuf : nullptr, select_buffer_keys(n), s)); }
@@ -469,8 +468,7 @@ cdl_status graph_enqueue(cdl_ctx *ctx, const double *X, int64_t n, int64_t T, in
         { Timed t_(ctx, "set_sigma"); HIPCHK(launch_set_sigma(sigma, stats, s)); }
     else
         { Timed t_(ctx, "select_median"); HIPCHK(launch_select_median(W, ld, n, w.sel, w.selbuf, br, stats, s)); }
-    { Timed t_(ctx, "exp_degree"); HIPCHK(launch_exp_degree(W, ld, n, stats, deg, w.dpart, s)); }
-    { Timed t_(ctx, "graph_stats"); HIPCHK(launch_graph_stats(deg, n, stats, s)); }
+    { Timed t_(ctx, "exp_degree"); HIPCHK(launch_exp_degree(W, ld, n, stats, deg, w.dpart, w.flags + kDegreeTicket, s)); }
     return CDL_OK;
 }
 
@@ -1392,7 +1390,7 @@ cdl_status cdl_stream_embedding(cdl_ctx *ctx, const double *X, int64_t n, int64_
     hipStream_t s = ctx->stream;
 
     { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w.flags, 256, s)); }
-    { Timed t_(ctx, "pad_series"); HIPCHK(launch_pad_series(X, n, T, ldx, w.Xp, ld, Tp, w.sqn, w.flags, s)); }
+    { Timed t_(ctx, "pad_series"); HIPCHK(launch_pad_series(X, n, T, ldx, w.Xp, ld, Tp, w.sqn, w.flags, nullptr, s)); }
     int hflag = 0;
     HIPCHK(read_to_host(ctx, s, {{&hflag, w.flags, sizeof(int)}}));
     if (hflag) return fail(ctx, CDL_E_NONFINITE, "non-finite node series");
@@ -1406,10 +1404,11 @@ cdl_status cdl_stream_embedding(cdl_ctx *ctx, const double *X, int64_t n, int64_
         { Timed t_(ctx, "set_sigma"); HIPCHK(launch_set_sigma(sigma, stats, s)); }
     } else {
         const int64_t cap = select_stream_keys(n);
-        { Timed t_(ctx, "stream_select"); HIPCHK(launch_select_start_top(w.sel, n, s)); }
         int src = 0, mode = 0;
-        if (ctx->select_mode == 0) {   // 1: the digit sweeps only (cdl_ctx_set_select)
-            { Timed t_(ctx, "stream_select"); HIPCHK(launch_select_sample_x(w.Xp, Tp, w.sqn, n, w.sel, s)); }
+        // 1: the digit sweeps only (cdl_ctx_set_select)
+        if (ctx->select_mode == 0) { Timed t_(ctx, "stream_select"); HIPCHK(launch_select_sample_x(w.Xp, Tp, w.sqn, n, w.sel, w.selbuf, s)); }
+        { Timed t_(ctx, "stream_select"); HIPCHK(launch_select_start_top(w.sel, n, s)); }
+        if (ctx->select_mode == 0) {
             for (int64_t r0 = 0; r0 < n; r0 += P) {
                 const int64_t rows = std::min(P, ld - r0);
                 { Timed t_(ctx, "stream_gram_upper"); HIPCHK(launch_gram_panel(w.Xp, Tp, w.sqn, n, ld, r0, rows, false, w.panel, nullptr, s)); }
@@ -2174,6 +2173,7 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
     HIPCHK(hipMemcpyAsync(dpre, pre.data(), pre.size() * sizeof(int), hipMemcpyHostToDevice, s));
     // the graph build and level-0 chains of all snapshots: descriptors and
     // prefix tables of the grouped launches
+    const int gram_shape = cdl::graph_gram_shape(P, lds.data());
     std::vector<cdl::GraphSnap> hg(P);
     std::vector<int> gpre((size_t)cdl::kGraphTables * (P + 1), 0), gtot(cdl::kGraphTables, 0);
     for (int t = 0; t < P; ++t) {
@@ -2208,7 +2208,7 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
         g.bracket = br ? 1 : 0;
         for (int tb = 0; tb < cdl::kGraphTables; ++tb) {
             int *row = gpre.data() + (size_t)tb * (P + 1);
-            row[t + 1] = row[t] + cdl::graph_table_count(tb, n, ld, br);
+            row[t + 1] = row[t] + cdl::graph_table_count(tb, n, ld, br, gram_shape);
         }
     }
     for (int tb = 0; tb < cdl::kGraphTables; ++tb) gtot[tb] = gpre[(size_t)tb * (P + 1) + P];
@@ -2237,7 +2237,7 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
         hipStream_t ss[kSeqStreams] = {s0, s1, ctx->extra[0], ctx->extra[1]};
         cdl_status st = CDL_OK;
         // graphs and level-0 chains: grouped launches over all snapshots
-        { Timed t_(ctx, "graph_grouped"); HIPCHK(cdl::launch_graph_grouped(dgs, dgpre, gtot.data(), P, q->sigma, s0)); }
+        { Timed t_(ctx, "graph_grouped"); HIPCHK(cdl::launch_graph_grouped(dgs, dgpre, gtot.data(), P, *std::max_element(ns.begin(), ns.end()), q->sigma, gram_shape, s0)); }
         { Timed t_(ctx, "chain_level0"); HIPCHK(cdl::launch_chain_level0_grouped(prec, dgs, dgpre, gtot.data(), P, s0)); }
         // right-hand sides per snapshot over the streams
         HIPCHK(hipEventRecord(evs[0], s0));

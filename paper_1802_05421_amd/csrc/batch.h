@@ -51,12 +51,12 @@ struct GraphSnap {
 
 // Prefix tables of the grouped graph build (one per workgroup count):
 enum GraphTable {
-    kGtRows,      // padded rows: ld
+    kGtRows,      // padded rows, four per workgroup: ld / 4
     kGtOne,       // one workgroup per snapshot
-    kGtGram,      // upper-triangle 256 x 128 tiles
-    kGtSample,    // one per snapshot whose selection starts with a sampled bracket
-    kGtKeys,      // 16 per such snapshot (its sample's keys from the series)
-    kGtPass,      // min(n, 2048) per snapshot
+    kGtGram,      // upper-triangle tiles of the group's shape
+    kGtSample,    // 64 per snapshot whose selection starts with a sampled bracket (ranks)
+    kGtKeys,      // 64 per such snapshot (its sample's keys from the series)
+    kGtPass,      // n / 32, 1 to 256, per snapshot
     kGtSym,       // upper 64 x 64 tiles
     kGtNodes64,   // ceil(n / 64)
     kGtPrep,      // ceil(ld / 256)
@@ -64,7 +64,9 @@ enum GraphTable {
 };
 // Workgroup counts of table `tb` for a snapshot (bracket: its selection
 // starts with the sampled bracket).
-int graph_table_count(int tb, int64_t n, int64_t ld, bool bracket);
+int graph_table_count(int tb, int64_t n, int64_t ld, bool bracket, int gram_shape);
+// Tile shape of the group's distance Gram.
+int graph_gram_shape(int P, const int64_t *ld);
 // Whether the stored selection of n keys' matrix starts with a sampled
 // bracket (the bracket must fit the buffer).
 bool select_uses_bracket(int64_t n, bool allowed);
@@ -72,9 +74,10 @@ bool select_uses_bracket(int64_t n, bool allowed);
 // The graph of every snapshot: padding, Gram (with the key bounds when
 // selecting), the exact lower median (sigma <= 0) or the given sigma,
 // weights, degrees and statistics.  tables: kGraphTables x (P + 1) prefix
-// tables in device memory; totals: their last entries (host).
+// tables in device memory; totals: their last entries (host); nmax: the
+// largest snapshot's nodes.
 hipError_t launch_graph_grouped(const GraphSnap *snaps, const int *tables, const int *totals,
-                                int P, double sigma, hipStream_t s);
+                                int P, int64_t nmax, double sigma, int gram_shape, hipStream_t s);
 // Level 0 of every snapshot's chain: (cD)^{-1/2}, u and the normalised,
 // deflated, rounded level with its norm partials.
 hipError_t launch_chain_level0_grouped(int prec, const GraphSnap *snaps, const int *tables,

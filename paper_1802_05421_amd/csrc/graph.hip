@@ -52,6 +52,25 @@ __device__ inline double block_sum256(double v, double *red) {
     return (red[0] + red[1]) + (red[2] + red[3]);
 }
 
+// Whether this workgroup is the last of nb to come here (the ticket is 0
+// before the first and after the last); what the others wrote before is then
+// visible to it.  One thread's fences cover its workgroup (the barriers order
+// the rest): a fence per wave writes the L2 back as often (25 against 8 us for
+// 256 workgroups).  Every thread must call; `last` is a shared word.
+__device__ __forceinline__ bool last_workgroup(unsigned int *ticket, unsigned int nb, int *last) {
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+        *last = __hip_atomic_fetch_add(ticket, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == nb - 1u;
+        if (*last) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+            *ticket = 0u;
+        }
+    }
+    __syncthreads();
+    return *last != 0;
+}
+
 // ---------------------------------------------------------------------------
 
 __global__ void k_fill_zero(uint4 *p, size_t n16) {
@@ -91,12 +110,11 @@ hipError_t launch_copy16(const void *src, void *dst, size_t bytes, hipStream_t s
     return hipGetLastError();
 }
 
-// One wave per (padded) row.
 // Padded row i of the series and its squared norm (one wave).
 __device__ __forceinline__ void pad_row(const double *X, int64_t n, int64_t T, int64_t ldx,
                                         double *Xp, int64_t Tp, double *sqn, int *flags,
                                         int64_t i) {
-    const int lane = threadIdx.x;
+    const int lane = threadIdx.x & 63;
     double s = 0.0;
     int bad = 0;
     for (int64_t t = lane; t < Tp; t += 64) {
@@ -107,234 +125,318 @@ __device__ __forceinline__ void pad_row(const double *X, int64_t n, int64_t T, i
     }
     s = wave_sum(s);
     if (lane == 0) sqn[i] = s;
-    if (bad) atomicOr(flags, 1);
+    if (flags && bad) atomicOr(flags, 1);
 }
 
-__global__ void k_pad_series(const double *X, int64_t n, int64_t T, int64_t ldx,
-                             double *Xp, int64_t Tp, double *sqn, int *flags) {
-    pad_row(X, n, T, ldx, Xp, Tp, sqn, flags, blockIdx.x);
+// Four rows per workgroup; ticket != nullptr: cleared for the degrees' count.
+__global__ __launch_bounds__(256) void k_pad_series(const double *X, int64_t n, int64_t T, int64_t ldx,
+                                                    double *Xp, int64_t Tp, double *sqn, int *flags,
+                                                    int *ticket) {
+    if (ticket && blockIdx.x == 0 && threadIdx.x == 0) *ticket = 0;
+    pad_row(X, n, T, ldx, Xp, Tp, sqn, flags, (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6));
 }
 
 hipError_t launch_pad_series(const double *X, int64_t n, int64_t T, int64_t ldx,
                              double *Xp, int64_t rows, int64_t Tp, double *sqn,
-                             int *flags, hipStream_t s) {
-    hipLaunchKernelGGL(k_pad_series, dim3((unsigned)rows), dim3(64), 0, s, X, n, T, ldx, Xp,
-                       Tp, sqn, flags);
+                             int *flags, int *ticket, hipStream_t s) {
+    if (rows % 4) return hipErrorInvalidValue;
+    hipLaunchKernelGGL(k_pad_series, dim3((unsigned)(rows / 4)), dim3(256), 0, s, X, n, T, ldx, Xp,
+                       Tp, sqn, flags, ticket);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
 // Squared distances from the Gram matrix of the series (FP64 MFMA).
 
-// The cover is made of 256 x 128 tiles; each is computed as two 128 x 128
-// halves by two workgroups of four waves (each wave 64 x 64: 16 MFMAs per 8
-// fragment reads), BK 16.  A half takes 74 KB of LDS, so two workgroups fit
-// on a CU and one's epilogue (distances, median bracket, stores) runs beside
-// the other's MFMAs.
-using GramCore = GemmCore<MfmaF64, 128, 128, 16, 2, 2>;
-constexpr int kGramWgPerTile = 2;
-constexpr size_t kGramSmem = GramCore::SMEM;
+// Tile shapes (the same bits from each).  0: 128 x 128 by eight waves, two
+// workgroups on a CU; the cover's 256 x 128 tiles (whose order shares operand
+// panels in an XCD's L2) are each computed as two such halves.  1: 64 x 64 by
+// four waves, three on a CU, for sizes that 128 x 128 tiles cannot spread over
+// the CUs.  What a tile costs beside its MFMAs (2 n^2 T / 2 flop in all) is
+// the first loads and the epilogue: distances, median bracket, stores; other
+// workgroups' MFMAs run beside them.
+template <int SHAPE> struct GramCfg;
+template <> struct GramCfg<0> {
+    using Core = Dma64Core<128, 128, 2, 4, 2>;
+    static constexpr int WAVES = 4;   // waves per SIMD that the registers leave room for
+};
+template <> struct GramCfg<1> {
+    using Core = Dma64Core<64, 64, 2, 2, 3>;
+    static constexpr int WAVES = 3;
+};
+// The tiles' counts of keys below the bracket: words of the selection state's
+// candidate array (free until the last pass), one per 128 bytes.
+constexpr int kBelowParts = 64, kBelowPitch = 16;
+static_assert(kBelowParts * kBelowPitch <= kSelCap, "counts must fit the candidates");
+// What a launch covers: the upper triangle of the whole matrix, the upper
+// triangle's part of a row panel, or every tile of a row panel.
+enum GramCover { kGramUpper, kGramPanelUpper, kGramPanelFull };
 
+// Workgroups of shape `shape` on rows [row0, row0 + rows) (multiples of 256).
+static int64_t gram_wgs(int shape, GramCover cover, int64_t ld, int64_t row0, int64_t rows) {
+    if (shape == 0) return 2 * gram_panel_tiles(ld, row0, rows, cover == kGramPanelFull);
+    const int64_t nt = ld / 64;
+    if (cover == kGramUpper) return nt * (nt + 1) / 2;
+    return rows / 64 * (cover == kGramPanelFull ? nt : (ld - row0) / 64);
+}
 
+// The busiest CU's work in 64 x 64 tiles: the small tiles' rate is 0.8 of the
+// large ones' (twice the first loads and operand traffic per flop).
+static int gram_shape(GramCover cover, int64_t ld, int64_t row0, int64_t rows) {
+    const double t0 = 4.0 * (double)cdiv(gram_wgs(0, cover, ld, row0, rows), 256);
+    const double t1 = (double)cdiv(gram_wgs(1, cover, ld, row0, rows), 256) / 0.8;
+    return t1 < t0 ? 1 : 0;
+}
 
-// Tiles of row blocks [I0, I0 + pb): those of the upper-triangle cover
-// (full = 0; I0 = 0 and pb = ld / 256 give the whole cover) or all ncol of
-// each row block (full = 1).  Row i is stored at D2 + (i - 256 I0) ld, so a
-// row panel needs a buffer of 256 pb rows only.
+// First row and column of workgroup `id` (after the XCD remap); false: no tile.
+template <int SHAPE>
+__device__ inline bool gram_place(int cover, int id, int64_t ld, int64_t row0, int64_t rows,
+                                  int64_t &m0, int64_t &n0) {
+    int I, J;
+    if (SHAPE == 0) {
+        const int tile = id >> 1, half = id & 1, I0 = (int)(row0 / 256), pb = (int)(rows / 256);
+        const int ncol = (int)(ld / 128);
+        if (cover == kGramPanelFull) {
+            rect_tile<4>(tile, pb, ncol, I, J);
+            I += I0;
+        } else {
+            upper_band_tile<4>(tile, I0, pb, ncol, I, J);
+        }
+        m0 = (int64_t)I * 256 + 128 * half;
+        n0 = (int64_t)J * 128;
+        return true;
+    }
+    if (cover == kGramUpper) {
+        sym_tile<8>(id, (int)(ld / 64), I, J);
+    } else {
+        const int64_t first = cover == kGramPanelFull ? 0 : row0;
+        rect_tile<8>(id, (int)(rows / 64), (int)((ld - first) / 64), I, J);
+        I += (int)(row0 / 64);
+        J += (int)(first / 64);
+    }
+    m0 = (int64_t)I * 64;
+    n0 = (int64_t)J * 64;
+    return cover == kGramPanelFull || I <= J;
+}
+
+// One tile.  Row i is stored at D2 + (i - row0) ld, so a row panel needs a
+// buffer of its own rows only.
 // st != nullptr: also fold the smallest and largest upper-triangle key
 // (i < j) into st->kmin / st->kmax (the median selection starts below their
 // common bit prefix); with brbuf as well, the bracket pass of the selection
 // on the tile's upper-triangle keys: count those below st->lo into st->below
 // and append those in [lo, hi] to brbuf (capacity brcap) through an LDS
-// stage in the GEMM's staging memory, one segment per wave filled at ballot
-// positions (a wave with more of them than its segment holds marks the
-// buffer full, which sends the selection to its passes over the matrix:
-// exact either way).  kExp: store the
-// weights exp(-D2 / sigma^2) instead (zero on the diagonal and outside n;
-// sigma = wstats[1]), the expression of the separate exponential kernels, so
-// the values are the same bits.
-template <bool kExp>
+// stage in the GEMM's staging memory, one segment per wave (a wave with more
+// of them than its segment holds marks the buffer full, which sends the
+// selection to its passes over the matrix: exact either way).  Each lane counts
+// its own keys below and up to the bracket's end, one scan over the wave gives
+// its place, and a second walk over its registers appends them (a ballot and a
+// popcount per element before: the epilogue took half of a launch at T = 120).
+// NaN distances (non-finite series) are stored and left out of the selection.
+// kExp: store the weights exp(-D2 / sigma^2) instead (zero on the diagonal and
+// outside n; sigma = wstats[1]), the expression of the separate exponential
+// kernels, so the values are the same bits.
+template <int SHAPE, bool kExp>
 __device__ __forceinline__ void gram_tile(const double *Xp, int64_t Tp, const double *sqn,
-                                          int64_t n, int64_t ld, double *D2, int ncol, int I0,
-                                          int pb, int full, int id, SelectState *st,
+                                          int64_t n, int64_t ld, double *D2, int64_t row0,
+                                          int64_t rows, int cover, int id, SelectState *st,
                                           const double *wstats, double *smem,
                                           unsigned long long *brbuf = nullptr,
                                           int64_t brcap = 0) {
-    // workgroup id: half id & 1 (rows 128 (id & 1) ..) of tile id >> 1
-    const int tile = id >> 1, half = id & 1;
-    int I, J;
-    if (full) {
-        rect_tile<4>(tile, pb, ncol, I, J);
-        I += I0;
-    } else {
-        upper_band_tile<4>(tile, I0, pb, ncol, I, J);
+    using Core = typename GramCfg<SHAPE>::Core;
+    constexpr int R = MfmaF64::R;
+    int64_t m0, n0;
+    if (!gram_place<SHAPE>(cover, id, ld, row0, rows, m0, n0)) return;
+    // the bracket and the extremes so far, read before the MFMAs hide it (an
+    // extreme that has moved since costs an atomic more, nothing else)
+    const unsigned long long kInf = 0x7ff0000000000000ull;
+    double lo = 0.0, hi = -1.0;   // no bracket: nothing below, nothing inside
+    unsigned long long kmin0 = 0ull, kmax0 = 0ull;
+    if (!kExp && st) {
+        kmin0 = st->kmin;
+        kmax0 = st->kmax;
+        if (brbuf) {
+            lo = __longlong_as_double((long long)st->lo);
+            hi = __longlong_as_double((long long)(st->hi > kInf ? kInf : st->hi));
+        }
     }
-    const int64_t m0 = (int64_t)I * 256 + 128 * half, n0 = (int64_t)J * 128;
-    double *const out = D2 - (int64_t)I0 * 256 * ld;
-    GramCore g;
+    Core g;
     g.run(Xp, Tp, Xp, Tp, m0, n0, Tp, smem);
-    unsigned long long kmin = ~0ull, kmax = 0ull;
-    // bracket stage: the GEMM's LDS, free once every wave is past its last
-    // fragment read; each wave appends to its own segment of it
-    constexpr unsigned int kSeg = (unsigned int)(GramCore::SMEM / 8 / (GramCore::NT / 64));
-    __shared__ unsigned long long sbel[GramCore::NT / 64];
-    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    unsigned long long *const seg = (unsigned long long *)smem + wid * kSeg;
-    const unsigned long long ltmask = (1ull << lane) - 1ull;
-    unsigned long long blo = 0ull, bhi = 0ull;
-    unsigned int below = 0, wcount = 0;   // wcount: the wave's bracket keys so far (every lane)
-    if (brbuf) {
-        blo = st->lo;
-        bhi = st->hi;
-        __syncthreads();
-    }
+    double *const out = D2 - row0 * ld;
     // the squared norms of this lane's rows and columns, loaded once (the
     // stores below may alias sqn as far as the compiler knows)
-    double sa[GramCore::WTM][MfmaF64::R], sb[GramCore::WTN];
+    double sa[Core::WTM][R], sb[Core::WTN];
 #pragma unroll
-    for (int a = 0; a < GramCore::WTM; ++a)
+    for (int a = 0; a < Core::WTM; ++a)
 #pragma unroll
-        for (int rr = 0; rr < MfmaF64::R; ++rr) sa[a][rr] = sqn[m0 + GramCore::row_of(a, rr)];
+        for (int rr = 0; rr < R; ++rr) sa[a][rr] = sqn[m0 + Core::row_of(a, rr)];
 #pragma unroll
-    for (int b = 0; b < GramCore::WTN; ++b) sb[b] = sqn[n0 + GramCore::col_of(b)];
-    // D2 of element (r, c) (zero outside n and on the diagonal); upper: an
-    // upper-triangle pair inside n, whose key is set
-    auto f = [&](int r, int c, double acc, double sqa, double sqb, bool &upper,
-                 unsigned long long &key) -> double {
-        const int64_t a = m0 + r, b = n0 + c;
-        upper = false;
-        key = 0ull;
-        if (a >= n || b >= n || a == b) return 0.0;
-        double d = sqa + sqb - 2.0 * acc;
-        d = d < 0.0 ? 0.0 : d;
-        if (a < b) {
-            key = (unsigned long long)__double_as_longlong(d);
-            kmin = key < kmin ? key : kmin;
-            kmax = key > kmax ? key : kmax;
-            upper = true;
-        }
-        return d;
-    };
+    for (int b = 0; b < Core::WTN; ++b) sb[b] = sqn[n0 + Core::col_of(b)];
     double s2 = 0.0;
     if (kExp) {
         const double sigma = wstats[1];
         s2 = sigma * sigma;
     }
-    // direct stores: 16 lanes cover 16 consecutive columns of one row
+    // distances, stored as 16 lanes' 16 consecutive columns of one row; the
+    // accumulators keep the upper-triangle keys (NaN: not one)
+    const int ni = (int)n, mi = (int)m0, nj = (int)n0;   // n < 2^20
 #pragma unroll
-    for (int a = 0; a < GramCore::WTM; ++a)
+    for (int a = 0; a < Core::WTM; ++a) {
 #pragma unroll
-        for (int b = 0; b < GramCore::WTN; ++b)
+        for (int rr = 0; rr < R; ++rr) {
+            const int i = mi + Core::row_of(a, rr);
+            double *const row = out + (int64_t)i * ld + n0;
 #pragma unroll
-            for (int rr = 0; rr < MfmaF64::R; ++rr) {
-                const int r = GramCore::row_of(a, rr), c = GramCore::col_of(b);
-                bool upper;
-                unsigned long long key;
-                double v = f(r, c, g.acc[a][b][rr], sa[a][rr], sb[b], upper, key);
-                if (brbuf) {   // count below; append inside at the wave's ballot positions
-                    below += upper && key < blo ? 1u : 0u;
-                    const bool in = upper && key >= blo && key <= bhi;
-                    const unsigned long long m = __ballot(in);
-                    const unsigned int pos = wcount + (unsigned int)__popcll(m & ltmask);
-                    if (in && pos < kSeg) seg[pos] = key;
-                    wcount += (unsigned int)__popcll(m);
-                }
-                if (kExp) {
-                    const int64_t ia = m0 + r, ib = n0 + c;
-                    v = (ia < n && ib < n && ia != ib) ? exp(-v / s2) : 0.0;
-                }
-                out[(m0 + r) * ld + n0 + c] = v;
+            for (int b = 0; b < Core::WTN; ++b) {
+                const int c = Core::col_of(b), j = nj + c;
+                double d = sa[a][rr] + sb[b] - 2.0 * g.acc[a][b][rr];
+                d = d < 0.0 ? 0.0 : d;
+                const bool pair = i < ni && j < ni && i != j;
+                d = pair ? d : 0.0;
+                if (!kExp) g.acc[a][b][rr] = pair && i < j ? d : NAN;
+                if (kExp) d = pair ? exp(-d / s2) : 0.0;
+                row[c] = d;
             }
-    if (brbuf) {
-        // each wave's segment behind one global atomic (a full segment marks
-        // the buffer full: the passes then take the matrix); the count below
-        // behind one atomic per tile
-        unsigned long long base = 0ull;
-        if (lane == 0 && wcount > 0)
-            base = atomicAdd(&st->nbuf, wcount > kSeg ? (unsigned long long)brcap + 1ull
-                                                      : (unsigned long long)wcount);
-        base = __shfl(base, 0);
-        if (wcount <= kSeg)
-            for (unsigned int q = lane; q < wcount; q += 64)
-                if (base + q < (unsigned long long)brcap) brbuf[base + q] = seg[q];
-        unsigned long long bw = below;
+        }
+        __builtin_amdgcn_sched_barrier(0);   // bounds the addresses and masks held at once
+    }
+    if (kExp || !st) return;
+
+    __shared__ double wmin[Core::NW], wmax[Core::NW];
+    __shared__ unsigned int wbel[Core::NW], wcnt[Core::NW];
+    __shared__ unsigned long long sbase;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    double kmin = INFINITY, kmax = -1.0;
+    unsigned int below = 0, upto = 0;   // this lane's keys < lo and <= hi
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) bw += __shfl_xor(bw, o);
-        if (lane == 0) sbel[wid] = bw;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            unsigned long long bl = 0ull;
+    for (int a = 0; a < Core::WTM; ++a)
 #pragma unroll
-            for (int w = 0; w < GramCore::NT / 64; ++w) bl += sbel[w];
-            if (bl) atomicAdd(&st->below, bl);
+        for (int b = 0; b < Core::WTN; ++b)
+#pragma unroll
+            for (int rr = 0; rr < R; ++rr) {
+                const double d = g.acc[a][b][rr];
+                kmin = fmin(kmin, d);
+                kmax = fmax(kmax, d);
+                below += d < lo ? 1u : 0u;
+                upto += d <= hi ? 1u : 0u;
+            }
+    const unsigned int mine = brbuf ? upto - below : 0u;
+    unsigned int pos = mine, bw = below;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+        const unsigned int y = __shfl_up(pos, o);
+        pos += lane >= o ? y : 0u;
+    }
+    const unsigned int count = __shfl(pos, 63);   // the wave's keys inside
+    pos -= mine;
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        kmin = fmin(kmin, __shfl_xor(kmin, o));
+        kmax = fmax(kmax, __shfl_xor(kmax, o));
+        bw += __shfl_xor(bw, o);
+    }
+    if (lane == 0) {
+        wmin[wid] = kmin;
+        wmax[wid] = kmax;
+        wbel[wid] = bw;
+        wcnt[wid] = count;
+    }
+    __syncthreads();
+    unsigned long long tbase = 0ull;
+    // the GEMM's LDS is free: one segment of it per wave
+    constexpr unsigned int kSeg = (unsigned int)(Core::SMEM / 8 / Core::NW);
+    if (threadIdx.x == 0) {
+        // Every tile updates the same few words, and such an atomic takes about
+        // 8 ns whoever asks: so one per tile for the buffer's length, the count
+        // below spread over 64 lines, and the extremes only where they move.
+        unsigned long long bl = 0ull, cnt = 0ull;
+        bool over = false;
+#pragma unroll
+        for (int w = 0; w < Core::NW; ++w) {
+            kmin = fmin(kmin, wmin[w]);
+            kmax = fmax(kmax, wmax[w]);
+            bl += wbel[w];
+            cnt += wcnt[w];
+            over = over || wcnt[w] > kSeg;
+        }
+        if (kmax >= 0.0) {   // the tile holds a key
+            const unsigned long long k0 = (unsigned long long)__double_as_longlong(kmin);
+            const unsigned long long k1 = (unsigned long long)__double_as_longlong(kmax);
+            if (k0 < kmin0) atomicMin(&st->kmin, k0);
+            if (k1 > kmax0) atomicMax(&st->kmax, k1);
+        }
+        if (cnt) tbase = atomicAdd(&st->nbuf, over ? (unsigned long long)brcap + 1ull : cnt);
+        if (bl) atomicAdd(&st->cand[(blockIdx.x % kBelowParts) * kBelowPitch], bl);
+    }
+    if (!brbuf) return;
+    if (count <= kSeg) {   // uniform over the wave
+        unsigned long long *const seg = (unsigned long long *)smem + wid * kSeg;
+        // (opaque copies: the tests are made again rather than kept as masks)
+        double lo2 = lo, hi2 = hi;
+        asm volatile("" : "+v"(lo2), "+v"(hi2));
+#pragma unroll
+        for (int a = 0; a < Core::WTM; ++a) {
+#pragma unroll
+            for (int b = 0; b < Core::WTN; ++b)
+#pragma unroll
+                for (int rr = 0; rr < R; ++rr) {
+                    const double d = g.acc[a][b][rr];
+                    if (d >= lo2 && d <= hi2)
+                        seg[pos++] = (unsigned long long)__double_as_longlong(d);
+                }
+            __builtin_amdgcn_sched_barrier(0);
         }
     }
-    if (st) {
-        // the tile's smallest and largest key: waves, then the workgroup, then
-        // one pair of atomics per tile (all tiles update the same two words)
-        __shared__ unsigned long long wmin[GramCore::NT / 64], wmax[GramCore::NT / 64];
-#pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-            const unsigned long long a = __shfl_xor(kmin, o), b = __shfl_xor(kmax, o);
-            kmin = a < kmin ? a : kmin;
-            kmax = b > kmax ? b : kmax;
-        }
-        if ((threadIdx.x & 63) == 0) {
-            wmin[threadIdx.x >> 6] = kmin;
-            wmax[threadIdx.x >> 6] = kmax;
-        }
-        __syncthreads();
-        if (threadIdx.x == 0) {
-#pragma unroll
-            for (int w = 1; w < GramCore::NT / 64; ++w) {
-                kmin = wmin[w] < kmin ? wmin[w] : kmin;
-                kmax = wmax[w] > kmax ? wmax[w] : kmax;
-            }
-            if (kmin != ~0ull) atomicMin(&st->kmin, kmin);
-            if (kmax != 0ull) atomicMax(&st->kmax, kmax);
-        }
+    if (threadIdx.x == 0) sbase = tbase;   // (asked for before the segment was filled)
+    __syncthreads();
+    unsigned long long base = sbase;
+    for (int w = 0; w < wid; ++w) base += wcnt[w];
+    // (a full segment has marked the buffer full: its wave has nothing to copy)
+    if (count <= kSeg) {
+        const unsigned long long *const seg = (const unsigned long long *)smem + wid * kSeg;
+        for (unsigned int q = lane; q < count; q += 64)
+            if (base + q < (unsigned long long)brcap) brbuf[base + q] = seg[q];
     }
 }
 
-template <bool kExp>
-__global__ __launch_bounds__(GramCore::NT, 2) void k_gram_dist(const double *Xp, int64_t Tp,
-                                                   const double *sqn, int64_t n, int64_t ld,
-                                                   double *D2, int ncol, int I0, int pb,
-                                                   int full, int total, SelectState *st,
-                                                   const double *wstats,
-                                                   unsigned long long *brbuf, int64_t brcap) {
+template <int SHAPE, bool kExp>
+__global__ __launch_bounds__(GramCfg<SHAPE>::Core::NT, GramCfg<SHAPE>::WAVES) void k_gram_dist(
+    const double *Xp, int64_t Tp, const double *sqn, int64_t n, int64_t ld, double *D2,
+    int64_t row0, int64_t rows, int cover, SelectState *st, const double *wstats,
+    unsigned long long *brbuf, int64_t brcap) {
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-    gram_tile<kExp>(Xp, Tp, sqn, n, ld, D2, ncol, I0, pb, full, xcd_remap(blockIdx.x, total), st,
-                    wstats, (double *)smem_raw, brbuf, brcap);
+    gram_tile<SHAPE, kExp>(Xp, Tp, sqn, n, ld, D2, row0, rows, cover, xcd_remap(blockIdx.x, gridDim.x),
+                           st, wstats, (double *)smem_raw, brbuf, brcap);
 }
 
-static hipError_t gram_attr() {
+template <int SHAPE, bool kExp>
+static hipError_t gram_launch(const double *Xp, int64_t Tp, const double *sqn, int64_t n, int64_t ld,
+                              double *D2, int64_t row0, int64_t rows, GramCover cover,
+                              SelectState *st, const double *wstats, unsigned long long *brbuf,
+                              int64_t brcap, hipStream_t s) {
+    using Core = typename GramCfg<SHAPE>::Core;
     static bool attr = false;
     if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_gram_dist<false>,
+        hipError_t e = hipFuncSetAttribute((const void *)k_gram_dist<SHAPE, kExp>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)kGramSmem);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)k_gram_dist<true>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGramSmem);
+                                           (int)Core::SMEM);
         if (e != hipSuccess) return e;
         attr = true;
     }
-    return hipSuccess;
+    const int64_t total = gram_wgs(SHAPE, cover, ld, row0, rows);
+    if (total <= 0 || total > INT32_MAX) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((k_gram_dist<SHAPE, kExp>), dim3((unsigned)total), dim3(Core::NT), Core::SMEM,
+                       s, Xp, Tp, sqn, n, ld, D2, row0, rows, (int)cover, st, wstats, brbuf, brcap);
+    return hipGetLastError();
 }
 
 hipError_t launch_gram_dist(const double *Xp, int64_t Tp, const double *sqn, int64_t n,
                             int64_t ld, double *D2, SelectState *st, unsigned long long *brbuf,
                             int64_t brcap, hipStream_t s) {
     if (brbuf && !st) return hipErrorInvalidValue;
-    hipError_t e = gram_attr();
-    if (e != hipSuccess) return e;
-    const int ncol = (int)(ld / 128);
-    const int total = kGramWgPerTile * rect_upper_tiles(ld);
-    hipLaunchKernelGGL(k_gram_dist<false>, dim3(total), dim3(GramCore::NT), kGramSmem, s, Xp, Tp, sqn, n,
-                       ld, D2, ncol, 0, (int)(ld / 256), 0, total, st, (const double *)nullptr,
-                       brbuf, brcap);
-    return hipGetLastError();
+    if (gram_shape(kGramUpper, ld, 0, ld) == 1)
+        return gram_launch<1, false>(Xp, Tp, sqn, n, ld, D2, 0, ld, kGramUpper, st, nullptr, brbuf, brcap, s);
+    return gram_launch<0, false>(Xp, Tp, sqn, n, ld, D2, 0, ld, kGramUpper, st, nullptr, brbuf, brcap, s);
 }
 
 int64_t gram_panel_tiles(int64_t ld, int64_t row0, int64_t rows, bool full) {
@@ -347,39 +449,38 @@ hipError_t launch_gram_panel(const double *Xp, int64_t Tp, const double *sqn, in
                              const double *wstats, hipStream_t s) {
     if (row0 % 256 || rows % 256 || rows <= 0 || row0 + rows > ld) return hipErrorInvalidValue;
     if (wstats && !full) return hipErrorInvalidValue;
-    hipError_t e = gram_attr();
-    if (e != hipSuccess) return e;
-    const int64_t total = kGramWgPerTile * gram_panel_tiles(ld, row0, rows, full);
-    if (total <= 0 || total > INT32_MAX) return hipErrorInvalidValue;
-    const int ncol = (int)(ld / 128), I0 = (int)(row0 / 256), pb = (int)(rows / 256);
+    const GramCover cover = full ? kGramPanelFull : kGramPanelUpper;
+    const bool small = gram_shape(cover, ld, row0, rows) == 1;
     if (wstats)
-        hipLaunchKernelGGL(k_gram_dist<true>, dim3((unsigned)total), dim3(GramCore::NT), kGramSmem, s, Xp,
-                           Tp, sqn, n, ld, D2p, ncol, I0, pb, 1, (int)total,
-                           (SelectState *)nullptr, wstats, (unsigned long long *)nullptr,
-                           (int64_t)0);
-    else
-        hipLaunchKernelGGL(k_gram_dist<false>, dim3((unsigned)total), dim3(GramCore::NT), kGramSmem, s, Xp,
-                           Tp, sqn, n, ld, D2p, ncol, I0, pb, full ? 1 : 0, (int)total,
-                           (SelectState *)nullptr, (const double *)nullptr,
-                           (unsigned long long *)nullptr, (int64_t)0);
-    return hipGetLastError();
+        return small ? gram_launch<1, true>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, wstats, nullptr, 0, s)
+                     : gram_launch<0, true>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, wstats, nullptr, 0, s);
+    return small ? gram_launch<1, false>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, nullptr, nullptr, 0, s)
+                 : gram_launch<0, false>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, nullptr, nullptr, 0, s);
 }
 
 // ---------------------------------------------------------------------------
 // Exact selection of the element of rank floor((N-1)/2), N = n(n-1)/2, among
 // D2_ij (i < j).  D2 >= 0, so its IEEE bit pattern orders like its value.
-// First a bracket: a sorted sample of kSelSample keys gives [lo, hi] around
-// the target quantile (three standard deviations of the sample quantile on
-// each side), the sample's keys taken from the series before the Gram; the
-// keys below lo are counted and those in [lo, hi] appended to a buffer, by
-// the Gram's epilogue for stored snapshots, by one sweep over the recomputed
-// upper panels for streamed ones.  If the target rank falls inside the bracket
-// the radix passes below run over the buffer, else over the matrix (the
-// result is exact either way).  Radix passes of 12-bit digits start below the
-// common prefix of the bracket (or of the smallest and largest key); as soon
-// as the selected bin holds at most kSelCap keys, one pass collects them and
-// a single workgroup sorts them.  Every pass kernel reads the state's mode,
-// so the fixed launch sequence turns into no-ops once the answer is known.
+// First a bracket: the sample quantiles three standard deviations on each side
+// of the target, of pairs whose distances are taken from the series before the
+// Gram; the keys below lo are counted and those in [lo, hi] appended to a
+// buffer, by the Gram's epilogue for stored snapshots, by one sweep over the
+// recomputed upper panels for streamed ones.  If the target rank falls inside
+// the bracket the radix passes below run over the buffer, else over the matrix
+// (the result is exact either way).  Radix passes of 12-bit digits start below
+// the common prefix of the bracket (or of the smallest and largest key); as
+// soon as the selected bin holds at most kSelFew keys, one pass collects them
+// and counting ranks among them gives the answer.  The last workgroup of a
+// pass picks the digit, so a pass is one launch; every pass reads the state's
+// mode, so the fixed launch sequence turns into no-ops once the answer is
+// known.  Launch latency and single-workgroup steps bound all of this: six
+// launches and 55 us of a graph at n = 4096 (100 at n = 16384), where 21
+// launches with a sort of the sample, a sort of the candidates and a pick of
+// their own took 177 (192).
+
+constexpr int kSelFew = 512;      // candidates ranked by the last pass's last workgroup
+static_assert(kSelFew <= kSelCap, "candidates must fit the state");
+constexpr int kSelSmall = 512;    // nodes (131k keys) up to which one workgroup does it all
 
 __device__ __forceinline__ void select_reset_body(SelectState *st) {
     for (int b = threadIdx.x; b < 4096; b += blockDim.x) st->hist[b] = 0;
@@ -391,12 +492,16 @@ __device__ __forceinline__ void select_reset_body(SelectState *st) {
         st->src = 0;
         st->below = 0;
         st->nbuf = 0;
+        st->ticket = 0;
+        st->kand = ~0ull;
+        st->kor = 0ull;
     }
+    for (int q = threadIdx.x; q < kBelowParts; q += blockDim.x) st->cand[q * kBelowPitch] = 0;
 }
 
 __global__ void k_select_reset(SelectState *st) { select_reset_body(st); }
 
-constexpr int kSelSample = 4096;
+constexpr int kSelSample = 4096;  // (and kStreamSample: multiples of kRankTile)
 constexpr int kSelMargin = 96;    // 3 sqrt(kSelSample / 4): misses in ~0.3% of calls
 
 int64_t select_buffer_keys(int64_t n) {
@@ -421,42 +526,17 @@ __device__ inline void sel_pair(unsigned long long u, int64_t n, int64_t &a, int
     b = i < j ? j : i;
 }
 
-// Sort the kSelSample keys in sk (LDS, 1024 threads) and set the bracket
-// [lo, hi] of kSelMargin sample ranks on each side of the target rank.
-__device__ __forceinline__ void select_sort_bracket(int64_t n, SelectState *st,
-                                                    unsigned long long *sk) {
-    const int t = threadIdx.x;
-    for (int size = 2; size <= kSelSample; size <<= 1)
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int q = t; q < kSelSample / 2; q += 1024) {
-                const int lo = 2 * q - (q & (stride - 1)), hi = lo + stride;
-                const bool up = (lo & size) == 0;
-                const unsigned long long a = sk[lo], b = sk[hi];
-                if ((a > b) == up) { sk[lo] = b; sk[hi] = a; }
-            }
-            __syncthreads();
-        }
-    if (t == 0) {
-        const unsigned long long N = (unsigned long long)n * (unsigned long long)(n - 1) / 2ull;
-        const double rho = (double)((N - 1ull) / 2ull) / (double)N;
-        const int q = (int)(rho * kSelSample);
-        st->lo = q - kSelMargin <= 0 ? 0ull : sk[q - kSelMargin];
-        st->hi = q + kSelMargin >= kSelSample - 1 ? ~0ull : sk[q + kSelMargin];
-        st->below = 0;
-        st->nbuf = 0;
-    }
-}
-
-// The same sample pairs' keys from the padded series, before the Gram: one
-// wave per pair, D2 = sq_a + sq_b - 2 x_a.x_b with the dot product summed
-// over the lanes (another order than the Gram's: an estimate of the quantile,
-// which is all the bracket needs; the counts against it are exact).
+// Keys of the sample pairs from the padded series, before the Gram: one wave
+// per pair, D2 = sq_a + sq_b - 2 x_a.x_b with the dot product summed over the
+// lanes (another order than the Gram's: an estimate of the quantile, which is
+// all the bracket needs; the counts against it are exact).  Four pairs a wave:
+// each costs a round trip to memory, so they are spread over the whole chip.
 __device__ __forceinline__ void select_sample_keys_body(const double *Xp, int64_t Tp,
-                                                        const double *sqn, int64_t n,
+                                                        const double *sqn, int64_t n, int samples,
                                                         unsigned long long *keys, int wave,
                                                         int nwave) {
     const int lane = threadIdx.x & 63;
-    for (int u = wave; u < kSelSample; u += nwave) {
+    for (int u = wave; u < samples; u += nwave) {
         int64_t a, b;
         sel_pair((unsigned long long)u, n, a, b);
         const double *xa = Xp + a * Tp, *xb = Xp + b * Tp;
@@ -472,24 +552,76 @@ __device__ __forceinline__ void select_sample_keys_body(const double *Xp, int64_
     }
 }
 
+// Sample keys; the first workgroup also resets the selection state.
 __global__ __launch_bounds__(256) void k_select_sample_keys(const double *Xp, int64_t Tp,
-                                                            const double *sqn, int64_t n,
-                                                            unsigned long long *keys) {
-    select_sample_keys_body(Xp, Tp, sqn, n, keys, blockIdx.x * 4 + (threadIdx.x >> 6),
+                                                            const double *sqn, int64_t n, int samples,
+                                                            unsigned long long *keys,
+                                                            SelectState *st) {
+    if (blockIdx.x == 0) select_reset_body(st);
+    select_sample_keys_body(Xp, Tp, sqn, n, samples, keys, blockIdx.x * 4 + (threadIdx.x >> 6),
                             gridDim.x * 4);
 }
 
-__device__ __forceinline__ void select_sort_keys(const unsigned long long *keys, int64_t n,
-                                                 SelectState *st, unsigned long long *sk) {
-    for (int u = threadIdx.x; u < kSelSample; u += 1024) sk[u] = keys[u];
+// The bracket [lo, hi]: the sample keys of ranks q -/+ margin around the
+// target quantile's rank q.  Workgroup b ranks keys 64 b .. 64 b + 63 against
+// the whole sample, 4096 keys of it at a time in LDS, a sixteenth of those per
+// wave (every lane reads the same two keys): a key's rank is the number of
+// smaller keys (equal keys hold a run of ranks, and each of them may write the
+// same value).
+constexpr int kRankTile = 4096;
+
+__device__ __forceinline__ void select_rank_body(const unsigned long long *keys, int samples,
+                                                 int margin, int64_t n, SelectState *st, int b) {
+    struct alignas(16) Two { unsigned long long x, y; };
+    __shared__ Two tile[kRankTile / 2];
+    __shared__ unsigned int less[16][64], upto[16][64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const unsigned long long mine = keys[64 * b + lane];
+    unsigned int lt = 0, le = 0;
+    for (int j0 = 0; j0 < samples; j0 += kRankTile) {
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kRankTile / 2048; ++q)
+            tile[threadIdx.x + 1024 * q] = ((const Two *)(keys + j0))[threadIdx.x + 1024 * q];
+        __syncthreads();
+        const Two *part = tile + w * (kRankTile / 32);
+#pragma unroll 8
+        for (int j = 0; j < kRankTile / 32; ++j) {
+            const Two k = part[j];
+            lt += k.x < mine ? 1u : 0u;
+            le += k.x <= mine ? 1u : 0u;
+            lt += k.y < mine ? 1u : 0u;
+            le += k.y <= mine ? 1u : 0u;
+        }
+    }
+    less[w][lane] = lt;
+    upto[w][lane] = le;
     __syncthreads();
-    select_sort_bracket(n, st, sk);
+    if (threadIdx.x >= 64) return;
+    lt = le = 0;
+#pragma unroll
+    for (int q = 0; q < 16; ++q) {
+        lt += less[q][lane];
+        le += upto[q][lane];
+    }
+    const unsigned long long N = (unsigned long long)n * (unsigned long long)(n - 1) / 2ull;
+    const double rho = (double)((N - 1ull) / 2ull) / (double)N;
+    const int q = (int)(rho * samples), rlo = q - margin, rhi = q + margin;
+    if (rlo > 0) {
+        if ((int)lt <= rlo && rlo < (int)le) st->lo = mine;
+    } else if (b == 0 && lane == 0) {
+        st->lo = 0ull;
+    }
+    if (rhi < samples - 1) {
+        if ((int)lt <= rhi && rhi < (int)le) st->hi = mine;
+    } else if (b == 0 && lane == 0) {
+        st->hi = ~0ull;
+    }
 }
 
-__global__ __launch_bounds__(1024) void k_select_sort_bracket(const unsigned long long *keys,
-                                                              int64_t n, SelectState *st) {
-    extern __shared__ unsigned long long sk[];
-    select_sort_keys(keys, n, st, sk);
+__global__ __launch_bounds__(1024) void k_select_rank(const unsigned long long *keys, int samples,
+                                                      int margin, int64_t n, SelectState *st) {
+    select_rank_body(keys, samples, margin, n, st, blockIdx.x);
 }
 
 // The bracket pass for very many keys (streamed panels: billions of keys,
@@ -559,105 +691,123 @@ __global__ __launch_bounds__(256) void k_select_bracket_flush(const double *D2, 
     }
 }
 
-// Switch the radix passes to the buffer when the target lies in the bracket.
-__device__ __forceinline__ void select_check_body(SelectState *st, int64_t cap, double *stats) {
-    if (threadIdx.x != 0 || st->mode == 2) return;
-    const unsigned long long below = st->below, nb = st->nbuf, rank = st->rank;
-    if (nb > (unsigned long long)cap || rank < below || rank >= below + nb) return;   // stay on the matrix
-    st->src = 1;
-    st->rank = rank - below;
+// The part of the state that a pass works from.
+struct SelView {
+    unsigned long long prefix, rank;
+    int bits, mode, src;
+};
+__device__ inline SelView select_load(const SelectState *st) {
+    return SelView{st->prefix, st->rank, st->bits, st->mode, st->src};
+}
+
+// Move the radix passes to the buffer when the target lies in the bracket.
+__device__ inline void select_bracket_view(const SelectState *st, int64_t cap, SelView &v) {
+    if (v.mode == 2) return;
+    unsigned long long below = st->below;
+    const unsigned long long nb = st->nbuf;
+#pragma unroll 16
+    for (int q = 0; q < kBelowParts; ++q) below += st->cand[q * kBelowPitch];
+    if (nb > (unsigned long long)cap || v.rank < below || v.rank >= below + nb) return;   // stay on the matrix
+    v.src = 1;
+    v.rank -= below;
     const unsigned long long x = st->lo ^ st->hi;
     if (x == 0ull) {   // every bracket key equals lo
-        st->prefix = st->lo;
-        st->bits = 64;
-        st->mode = 2;
-        stats[1] = sqrt(__longlong_as_double((long long)st->lo));
+        v.prefix = st->lo;
+        v.bits = 64;
+        v.mode = 2;
         return;
     }
     const int L = __clzll((long long)x);
-    if (L > st->bits) {
-        st->bits = L;
-        st->prefix = st->lo & ~((1ull << (64 - L)) - 1ull);
+    if (L > v.bits) {
+        v.bits = L;
+        v.prefix = st->lo & ~((1ull << (64 - L)) - 1ull);
     }
-    st->mode = nb <= (unsigned long long)kSelCap ? 1 : 0;
-    st->count = 0;
+    v.mode = nb <= (unsigned long long)kSelFew ? 1 : 0;
+}
+
+// The start of a stored selection: target rank and common prefix of the keys,
+// then the bracket when one was gathered.
+__device__ inline SelView select_start(const SelectState *st, int64_t n, int64_t cap, bool gathered) {
+    SelView v;
+    const unsigned long long N = (unsigned long long)n * (unsigned long long)(n - 1) / 2ull;
+    v.rank = (N - 1ull) / 2ull;
+    v.src = 0;
+    const unsigned long long x = st->kmin ^ st->kmax;
+    if (x == 0ull) {   // every pair distance is the same value
+        v.prefix = st->kmin;
+        v.bits = 64;
+        v.mode = 2;
+        return v;
+    }
+    const int L = __clzll((long long)x);
+    v.bits = L;
+    v.prefix = L == 0 ? 0ull : (st->kmin & ~((1ull << (64 - L)) - 1ull));
+    v.mode = 0;
+    if (gathered) select_bracket_view(st, cap, v);
+    return v;
+}
+
+__device__ inline void select_done(SelectState *st, double *stats, unsigned long long key) {
+    st->mode = 2;
+    stats[1] = sqrt(__longlong_as_double((long long)key));
 }
 
 __global__ void k_select_check(SelectState *st, int64_t cap, double *stats) {
-    select_check_body(st, cap, stats);
-}
-
-__device__ __forceinline__ void select_setup_body(SelectState *st, int64_t n, double *stats) {
     if (threadIdx.x != 0) return;
-    const unsigned long long N = (unsigned long long)n * (unsigned long long)(n - 1) / 2ull;
-    st->rank = (N - 1ull) / 2ull;
-    const unsigned long long x = st->kmin ^ st->kmax;
-    if (x == 0ull) {   // every pair distance is the same value
-        st->prefix = st->kmin;
-        st->bits = 64;
-        st->mode = 2;
-        stats[1] = sqrt(__longlong_as_double((long long)st->kmin));
-        return;
-    }
-    const int L = __clzll((long long)x);
-    st->bits = L;
-    st->prefix = L == 0 ? 0ull : (st->kmin & ~((1ull << (64 - L)) - 1ull));
-    st->mode = 0;
+    SelView v = select_load(st);
+    const int before = v.mode;
+    select_bracket_view(st, cap, v);
+    st->prefix = v.prefix;
+    st->rank = v.rank;
+    st->bits = v.bits;
+    st->mode = v.mode;
+    st->src = v.src;
+    st->count = 0;
+    if (v.mode == 2 && before != 2) select_done(st, stats, v.prefix);
 }
 
-__global__ void k_select_setup(SelectState *st, int64_t n, double *stats) {
-    select_setup_body(st, n, stats);
-}
-
-__device__ inline void sel_digit(const SelectState *st, int &shift, int &width,
-                                 unsigned long long &hi_mask) {
-    const int bits = st->bits;
+__device__ inline void sel_digit(int bits, int &shift, int &width, unsigned long long &hi_mask) {
     width = 64 - bits < 12 ? 64 - bits : 12;
     shift = 64 - bits - width;
     hi_mask = bits == 0 ? 0ull : ~((1ull << (64 - bits)) - 1ull);
 }
 
 // Keys of rows [row0, row1): row i at D2 + (i - row0) ld (a row panel, or
-// the whole matrix with row0 = 0, row1 = n).
-// Workgroup b of nb.
+// the whole matrix with row0 = 0, row1 = n), or of the bracket buffer.
+// Workgroup b of nb adds its share to the digit's histogram (mode 0) or to the
+// candidates (mode 1); NT threads.
+template <int NT>
 __device__ __forceinline__ void select_pass_body(const double *D2, int64_t ld, int64_t n,
                                                  int64_t row0, int64_t row1, SelectState *st,
-                                                 const unsigned long long *buf, int64_t b,
-                                                 int64_t nb) {
-    __shared__ unsigned int h[4096];
-    const int mode = st->mode;
-    if (mode == 2) return;
-    // Up to 2^24 buffered keys go to at most kBufBlocks workgroups, each
-    // flushing its histogram once for many keys: the flush is global atomics
-    // on the same 4096 bins, and thousands of workgroups flushing them
-    // contend.  Larger buffers keep the whole grid for bandwidth.
-    constexpr int kBufBlocks = 256;
-    const bool from_buf = st->src == 1;
-    const bool few = from_buf && st->nbuf <= (1ull << 24);
-    if (few && b >= kBufBlocks) return;
+                                                 const SelView &v, const unsigned long long *buf,
+                                                 int64_t b, int64_t nb, unsigned int *h) {
+    constexpr int nt = NT;
     int shift, width;
     unsigned long long hi_mask;
-    sel_digit(st, shift, width, hi_mask);
-    const unsigned long long prefix = st->prefix;
+    sel_digit(v.bits, shift, width, hi_mask);
+    const int mode = v.mode;
+    const unsigned long long prefix = v.prefix;
     if (mode == 0) {
-        for (int b = threadIdx.x; b < 4096; b += 256) h[b] = 0;
+        for (int q = threadIdx.x; q < 4096; q += nt) h[q] = 0;
         __syncthreads();
     }
     const unsigned long long dmask = (1ull << width) - 1ull;
+    unsigned long long kand = ~0ull, kor = 0ull;
     auto take = [&](unsigned long long key) {
         if ((key & hi_mask) != prefix) return;
         if (mode == 0) {
             atomicAdd(&h[(key >> shift) & dmask], 1u);
+            kand &= key;
+            kor |= key;
         } else {
             const unsigned int q = atomicAdd(&st->count, 1u);
             if (q < kSelCap) st->cand[q] = key;
         }
     };
     // eight independent loads in flight per thread
-    if (from_buf) {
-        const int64_t gb = few && nb > kBufBlocks ? (int64_t)kBufBlocks : nb;
-        const int64_t nk = (int64_t)st->nbuf, stride = gb * 256;
-        for (int64_t q0 = b * 256 + threadIdx.x; q0 < nk; q0 += 8 * stride) {
+    if (v.src == 1) {
+        const int64_t nk = (int64_t)st->nbuf, stride = nb * nt;
+        for (int64_t q0 = b * nt + threadIdx.x; q0 < nk; q0 += 8 * stride) {
             unsigned long long key[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) key[u] = q0 + u * stride < nk ? buf[q0 + u * stride] : 0ull;
@@ -668,115 +818,203 @@ __device__ __forceinline__ void select_pass_body(const double *D2, int64_t ld, i
     } else {
         for (int64_t i = row0 + b; i < row1; i += nb) {
             const unsigned long long *row = (const unsigned long long *)(D2 + (i - row0) * ld);
-            for (int64_t j0 = i + 1 + threadIdx.x; j0 < n; j0 += 8 * 256) {
+            for (int64_t j0 = i + 1 + threadIdx.x; j0 < n; j0 += 8 * nt) {
                 unsigned long long key[8];
 #pragma unroll
-                for (int u = 0; u < 8; ++u) key[u] = j0 + 256 * u < n ? row[j0 + 256 * u] : 0ull;
+                for (int u = 0; u < 8; ++u) key[u] = j0 + nt * u < n ? row[j0 + nt * u] : 0ull;
 #pragma unroll
                 for (int u = 0; u < 8; ++u)
-                    if (j0 + 256 * u < n) take(key[u]);
+                    if (j0 + nt * u < n) take(key[u]);
             }
         }
     }
     if (mode == 0) {
         __syncthreads();
-        for (int q = threadIdx.x; q < 4096; q += 256)
+        for (int q = threadIdx.x; q < 4096; q += nt)
             if (h[q]) atomicAdd(&st->hist[q], (unsigned long long)h[q]);
+        __syncthreads();
+        // AND and OR over the workgroup (the histogram's LDS is free)
+        unsigned long long *const red = (unsigned long long *)h;
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) {
+            kand &= __shfl_xor(kand, o);
+            kor |= __shfl_xor(kor, o);
+        }
+        if ((threadIdx.x & 63) == 0) {
+            red[threadIdx.x >> 6] = kand;
+            red[16 + (threadIdx.x >> 6)] = kor;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            for (int w = 1; w < nt / 64; ++w) {
+                kand &= red[w];
+                kor |= red[16 + w];
+            }
+            if (kor || kand != ~0ull) {   // a key matched
+                atomicAnd(&st->kand, kand);
+                atomicOr(&st->kor, kor);
+            }
+        }
     }
 }
 
-__global__ __launch_bounds__(256) void k_select_pass(const double *D2, int64_t ld, int64_t n,
-                                                     int64_t row0, int64_t row1,
-                                                     SelectState *st,
-                                                     const unsigned long long *buf) {
-    select_pass_body(D2, ld, n, row0, row1, st, buf, blockIdx.x, gridDim.x);
-}
+struct PickShared {
+    unsigned long long part[16], keys[kSelFew];
+};
 
-__device__ __forceinline__ void select_pick_body(SelectState *st, double *stats) {
-    constexpr int NT = 1024, BPT = 4096 / NT;
-    __shared__ unsigned long long part[NT / 64];
-    __shared__ unsigned long long keys[kSelCap];
+// Pick the digit from the histogram, or the answer from the candidates, and
+// write the state for the next pass.  One workgroup of NT threads.
+template <int NT>
+__device__ __forceinline__ void select_pick_body(SelectState *st, const SelView &v, double *stats,
+                                                 PickShared &sh) {
+    constexpr int nt = NT;
     const int t = threadIdx.x;
-    const int mode = st->mode;
-    if (mode == 2) return;
-    if (mode == 1) {
-        // sort the collected candidates (count <= kSelCap) and take the rank
-        const unsigned int cnt = st->count;
-        for (int q = t; q < kSelCap; q += NT) keys[q] = q < (int)cnt ? st->cand[q] : ~0ull;
+    if (v.mode == 2) return;
+    if (v.mode == 1) {
+        // the candidate with `rank` smaller ones (equal candidates hold a run
+        // of ranks; each may write the same answer)
+        const int cnt = (int)(st->count < kSelFew ? st->count : kSelFew);
+        for (int q = t; q < cnt; q += nt) sh.keys[q] = st->cand[q];
         __syncthreads();
-        for (int size = 2; size <= kSelCap; size <<= 1)
-            for (int stride = size >> 1; stride > 0; stride >>= 1) {
-                for (int q = t; q < kSelCap / 2; q += NT) {
-                    const int lo = 2 * q - (q & (stride - 1)), hi = lo + stride;
-                    const bool up = (lo & size) == 0;
-                    const unsigned long long a = keys[lo], b = keys[hi];
-                    if ((a > b) == up) { keys[lo] = b; keys[hi] = a; }
-                }
-                __syncthreads();
+        for (int q = t; q < cnt; q += nt) {
+            const unsigned long long mine = sh.keys[q];
+            unsigned int lt = 0, le = 0;
+            for (int j = 0; j < cnt; ++j) {
+                lt += sh.keys[j] < mine ? 1u : 0u;
+                le += sh.keys[j] <= mine ? 1u : 0u;
             }
-        if (t == 0) {
-            const unsigned long long key = keys[st->rank];
-            st->prefix = key;
-            st->bits = 64;
-            st->mode = 2;
-            stats[1] = sqrt(__longlong_as_double((long long)key));
+            if (lt <= v.rank && v.rank < le) {
+                st->prefix = mine;
+                st->bits = 64;
+                select_done(st, stats, mine);
+            }
         }
         return;
     }
+    // (many pairs at one distance: integer series, repeated rows)
+    const bool equal = st->kand == st->kor;
     int shift, width;
     unsigned long long hi_mask;
-    sel_digit(st, shift, width, hi_mask);
-    unsigned long long c[BPT], sum = 0;
-#pragma unroll
-    for (int q = 0; q < BPT; ++q) {
-        c[q] = st->hist[t * BPT + q];
-        sum += c[q];
-    }
-    // exclusive prefix of the per-thread bin sums: within each wave by
-    // shuffles, then across the waves
+    sel_digit(v.bits, shift, width, hi_mask);
+    // thread t's bins t per .. t per + per - 1; exclusive prefix of the
+    // per-thread sums within each wave by shuffles, then across the waves
+    constexpr int per = 4096 / nt;
+    unsigned long long sum = 0;
+    for (int q = 0; q < per; ++q) sum += st->hist[t * per + q];
     unsigned long long incl = sum;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
         const unsigned long long y = __shfl_up(incl, o);
         if ((t & 63) >= o) incl += y;
     }
-    if ((t & 63) == 63) part[t >> 6] = incl;
+    if ((t & 63) == 63) sh.part[t >> 6] = incl;
     __syncthreads();
     unsigned long long before = incl - sum;
-    for (int w = 0; w < (t >> 6); ++w) before += part[w];
-    const unsigned long long rank = st->rank;
-    int bin = -1;
-    unsigned long long newrank = 0, cnt = 0;
-#pragma unroll
-    for (int q = 0; q < BPT; ++q) {
-        if (bin < 0 && rank >= before && rank < before + c[q]) {
-            bin = t * BPT + q;
-            newrank = rank - before;
-            cnt = c[q];
+    for (int w = 0; w < (t >> 6); ++w) before += sh.part[w];
+    const unsigned long long before0 = before;
+    if (v.rank >= before && v.rank < before + sum) {   // one thread
+        int bin = t * per;
+        unsigned long long cnt = st->hist[bin];
+        while (v.rank >= before + cnt) {
+            before += cnt;
+            cnt = st->hist[++bin];
         }
-        before += c[q];
-    }
-    __syncthreads();
-    if (bin >= 0) {
-        const unsigned long long p = st->prefix | ((unsigned long long)bin << shift);
+        const unsigned long long p = v.prefix | ((unsigned long long)bin << shift);
+        const int bits = v.bits + width;
         st->prefix = p;
-        st->bits += width;
-        st->rank = newrank;
-        if (st->bits >= 64) {
-            st->mode = 2;
-            stats[1] = sqrt(__longlong_as_double((long long)p));
-        } else if (cnt <= (unsigned long long)kSelCap) {
-            st->mode = 1;
-            st->count = 0;
-        }
+        st->bits = bits;
+        st->rank = v.rank - before;
+        st->src = v.src;
+        st->count = 0;
+        if (equal) select_done(st, stats, st->kand);
+        else if (bits >= 64) select_done(st, stats, p);
+        else st->mode = cnt <= (unsigned long long)kSelFew ? 1 : 0;
+    }
+    if (t == nt - 1 && v.rank >= before0 + sum) {
+        // fewer keys than pairs: some distances are NaN
+        select_done(st, stats, 0x7ff8000000000000ull);
     }
     __syncthreads();
-    for (int b = t; b < 4096; b += NT) st->hist[b] = 0;
+    for (int q = t; q < 4096; q += nt) st->hist[q] = 0;
+    if (t == 0) {
+        st->kand = ~0ull;
+        st->kor = 0ull;
+    }
 }
 
-__global__ __launch_bounds__(1024) void k_select_pick(SelectState *st, double *stats) {
-    select_pick_body(st, stats);
+// One pass over the stored matrix or its bracket buffer with the pick by the
+// last of its nb workgroups (the ticket counts them; every workgroup's
+// histogram and candidates are published before its ticket).
+__device__ __forceinline__ void select_pass_pick(const double *D2, int64_t ld, int64_t n,
+                                                 SelectState *st, const unsigned long long *buf,
+                                                 int64_t cap, bool gathered, bool first,
+                                                 double *stats, int64_t b, int64_t nb) {
+    __shared__ __align__(16) unsigned int h[4096];
+    __shared__ PickShared sh;
+    __shared__ int last;
+    const SelView v = first ? select_start(st, n, cap, gathered) : select_load(st);
+    if (v.mode == 2) {
+        if (first && b == 0 && threadIdx.x == 0) select_done(st, stats, v.prefix);
+        return;
+    }
+    select_pass_body<256>(D2, ld, n, 0, n, st, v, buf, b, nb, h);
+    if (!last_workgroup(&st->ticket, (unsigned int)nb, &last)) return;
+    select_pick_body<256>(st, v, stats, sh);
 }
+
+__global__ __launch_bounds__(256) void k_select_pass(const double *D2, int64_t ld, int64_t n,
+                                                     SelectState *st, const unsigned long long *buf,
+                                                     int64_t cap, int gathered, int first,
+                                                     double *stats) {
+    select_pass_pick(D2, ld, n, st, buf, cap, gathered, first, stats, blockIdx.x, gridDim.x);
+}
+
+// The remaining passes by one workgroup: all of them for at most kSelSmall
+// nodes (first), or what kSelPasses passes of the whole chip left undone.
+__device__ __forceinline__ void select_rest_body(const double *D2, int64_t ld, int64_t n,
+                                                 SelectState *st, const unsigned long long *buf,
+                                                 int64_t cap, bool gathered, bool first,
+                                                 double *stats) {
+    __shared__ __align__(16) unsigned int h[4096];
+    __shared__ PickShared sh;
+    SelView v = first ? select_start(st, n, cap, gathered) : select_load(st);
+    if (v.mode == 2) {
+        if (first && threadIdx.x == 0) select_done(st, stats, v.prefix);
+        return;
+    }
+    // at most 6 digit passes resolve 64 bits; the collect pass is one more
+    for (int p = 0; p < 7 && v.mode != 2; ++p) {
+        select_pass_body<1024>(D2, ld, n, 0, n, st, v, buf, 0, 1, h);
+        __threadfence();
+        __syncthreads();
+        select_pick_body<1024>(st, v, stats, sh);
+        __threadfence();
+        __syncthreads();
+        v = select_load(st);
+    }
+}
+
+__global__ __launch_bounds__(1024) void k_select_rest(const double *D2, int64_t ld, int64_t n,
+                                                      SelectState *st, const unsigned long long *buf,
+                                                      int64_t cap, int gathered, int first,
+                                                      double *stats) {
+    select_rest_body(D2, ld, n, st, buf, cap, gathered, first, stats);
+}
+
+// Workgroups of a pass over n nodes: 32 rows of the matrix each, and about 12
+// buffered keys a thread; 256 at most, since each adds its histogram to the
+// same 4096 bins.
+static int select_grid(int64_t n) { return (int)(n / 32 < 1 ? 1 : n / 32 < 256 ? n / 32 : 256); }
+
+// Passes of the whole chip.  Two digits leave at most kSelFew distinct keys of
+// up to 2e8 (n = 20000) unless they crowd in one bin of 2^-24 of their range, the
+// third pass ranks them, and equal keys are found by their AND and OR; one
+// workgroup finishes what is left (none as a rule, at 4.5 us a launch spared).
+// Larger matrices, which a single workgroup could not read in time, take as
+// many passes as 64 bits need.
+constexpr int kSelPasses = 3;
+constexpr int64_t kSelRestNodes = 20000;
+static int select_passes(int64_t n) { return n <= kSelSmall ? 0 : n <= kSelRestNodes ? kSelPasses : 7; }
 
 hipError_t launch_select_reset(SelectState *st, hipStream_t s) {
     hipLaunchKernelGGL(k_select_reset, dim3(1), dim3(256), 0, s, st);
@@ -785,34 +1023,25 @@ hipError_t launch_select_reset(SelectState *st, hipStream_t s) {
 
 hipError_t launch_select_presample(const double *Xp, int64_t Tp, const double *sqn, int64_t n,
                                    SelectState *st, unsigned long long *buf, hipStream_t s) {
-    static bool attr = false;
-    if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_select_sort_bracket,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           kSelSample * 8);
-        if (e != hipSuccess) return e;
-        attr = true;
-    }
     if (select_buffer_keys(n) < kSelSample) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(k_select_sample_keys, dim3(64), dim3(256), 0, s, Xp, Tp, sqn, n, buf);
-    hipLaunchKernelGGL(k_select_sort_bracket, dim3(1), dim3(1024), kSelSample * 8, s, buf, n, st);
+    hipLaunchKernelGGL(k_select_sample_keys, dim3(kSelSample / 16), dim3(256), 0, s, Xp, Tp, sqn, n,
+                       kSelSample, buf, st);
+    hipLaunchKernelGGL(k_select_rank, dim3(kSelSample / 64), dim3(1024), 0, s, buf, kSelSample,
+                       kSelMargin, n, st);
     return hipGetLastError();
 }
 
 hipError_t launch_select_median(const double *D2, int64_t ld, int64_t n, SelectState *st,
                                 unsigned long long *buf, bool gathered, double *stats,
                                 hipStream_t s) {
-    hipLaunchKernelGGL(k_select_setup, dim3(1), dim3(64), 0, s, st, n, stats);
-    const int grid = (int)(n < 2048 ? n : 2048);
     const int64_t cap = select_buffer_keys(n);
-    if (gathered)   // the Gram's epilogue counted and gathered the bracket
-        hipLaunchKernelGGL(k_select_check, dim3(1), dim3(64), 0, s, st, cap, stats);
-    // at most 6 digit passes resolve 64 bits; the collect pass is one more
-    for (int p = 0; p < 7; ++p) {
-        hipLaunchKernelGGL(k_select_pass, dim3(grid), dim3(256), 0, s, D2, ld, n, (int64_t)0, n,
-                           st, buf);
-        hipLaunchKernelGGL(k_select_pick, dim3(1), dim3(1024), 0, s, st, stats);
-    }
+    const int passes = select_passes(n);
+    for (int p = 0; p < passes; ++p)
+        hipLaunchKernelGGL(k_select_pass, dim3(select_grid(n)), dim3(256), 0, s, D2, ld, n, st, buf, cap,
+                           gathered ? 1 : 0, p == 0 ? 1 : 0, stats);
+    if (passes < 7)
+        hipLaunchKernelGGL(k_select_rest, dim3(1), dim3(1024), 0, s, D2, ld, n, st, buf, cap,
+                           gathered ? 1 : 0, passes == 0 ? 1 : 0, stats);
     return hipGetLastError();
 }
 
@@ -838,13 +1067,33 @@ hipError_t launch_select_start_top(SelectState *st, int64_t n, hipStream_t s) {
     return hipGetLastError();
 }
 
+// A panel's share of a digit (the pick follows the last panel).
+__global__ __launch_bounds__(256) void k_select_panel(const double *D2, int64_t ld, int64_t n,
+                                                      int64_t row0, int64_t row1,
+                                                      SelectState *st) {
+    __shared__ __align__(16) unsigned int h[4096];
+    const SelView v = select_load(st);
+    if (v.mode == 2) return;
+    select_pass_body<256>(D2, ld, n, row0, row1, st, v, nullptr, blockIdx.x, gridDim.x, h);
+}
+
+__global__ __launch_bounds__(1024) void k_select_pick(SelectState *st, double *stats) {
+    __shared__ PickShared sh;
+    select_pick_body<1024>(st, select_load(st), stats, sh);
+}
+
+// One radix pass over the streamed bracket's buffer, with its pick.
+__global__ __launch_bounds__(256) void k_select_buffer(SelectState *st, const unsigned long long *buf,
+                                                       double *stats) {
+    select_pass_pick(nullptr, 0, 0, st, buf, 0, true, false, stats, blockIdx.x, gridDim.x);
+}
+
 hipError_t launch_select_panel(const double *D2p, int64_t ld, int64_t n, int64_t row0,
                                int64_t row1, SelectState *st, hipStream_t s) {
     if (row1 <= row0) return hipSuccess;
     const int64_t rows = row1 - row0;
     const int grid = (int)(rows < 2048 ? rows : 2048);
-    hipLaunchKernelGGL(k_select_pass, dim3(grid), dim3(256), 0, s, D2p, ld, n, row0, row1, st,
-                       (const unsigned long long *)nullptr);
+    hipLaunchKernelGGL(k_select_panel, dim3(grid), dim3(256), 0, s, D2p, ld, n, row0, row1, st);
     return hipGetLastError();
 }
 
@@ -854,13 +1103,13 @@ hipError_t launch_select_pick(SelectState *st, double *stats, hipStream_t s) {
 }
 
 // The streamed bracket: kStreamSample distances of pseudo-random pairs
-// computed directly from the padded series (sq_a + sq_b - 2 x_a.x_b in
-// sequential FP64, an estimate of the quantile only: the bracket is checked
-// against exact counts), sorted in LDS, bracket of kStreamMargin sample ranks
+// from the padded series (an estimate of the quantile only: the bracket is
+// checked against exact counts), bracket of kStreamMargin sample ranks
 // on each side of the target; then one sweep over the upper panels counts the
 // keys below the bracket and gathers those inside it, and the radix passes run
 // over the gathered keys.  The larger sample keeps the bracket to about 2.3 %
-// of the keys.
+// of the keys.  Sample and ranks run on the whole chip (one workgroup, a
+// thread per dot product and a sort in LDS took 6.0 ms at T = 360; 0.05 now).
 constexpr int kStreamSample = 16384;
 constexpr int kStreamMargin = 192;   // 3 sqrt(kStreamSample / 4)
 
@@ -869,55 +1118,13 @@ int64_t select_stream_keys(int64_t n) {
     return N / 100 * 3 + 65536;
 }
 
-__global__ __launch_bounds__(1024) void k_select_sample_x(const double *Xp, int64_t Tp,
-                                                          const double *sqn, int64_t n,
-                                                          SelectState *st) {
-    extern __shared__ unsigned long long sk[];
-    const int t = threadIdx.x;
-    for (int u = 0; u < kStreamSample / 1024; ++u) {
-        int64_t i, j;
-        sel_pair((unsigned long long)(t + 1024 * u), n, i, j);
-        const double *xa = Xp + i * Tp, *xb = Xp + j * Tp;
-        double dot = 0.0;
-        for (int64_t q = 0; q < Tp; ++q) dot += xa[q] * xb[q];
-        double d = sqn[i] + sqn[j] - 2.0 * dot;
-        d = d < 0.0 ? 0.0 : d;
-        sk[t + 1024 * u] = (unsigned long long)__double_as_longlong(d);
-    }
-    __syncthreads();
-    for (int size = 2; size <= kStreamSample; size <<= 1)
-        for (int stride = size >> 1; stride > 0; stride >>= 1) {
-            for (int q = t; q < kStreamSample / 2; q += 1024) {
-                const int lo = 2 * q - (q & (stride - 1)), hi = lo + stride;
-                const bool up = (lo & size) == 0;
-                const unsigned long long a = sk[lo], b = sk[hi];
-                if ((a > b) == up) { sk[lo] = b; sk[hi] = a; }
-            }
-            __syncthreads();
-        }
-    if (t == 0) {
-        const unsigned long long N = (unsigned long long)n * (unsigned long long)(n - 1) / 2ull;
-        const double rho = (double)((N - 1ull) / 2ull) / (double)N;
-        const int q = (int)(rho * kStreamSample);
-        st->lo = q - kStreamMargin <= 0 ? 0ull : sk[q - kStreamMargin];
-        st->hi = q + kStreamMargin >= kStreamSample - 1 ? ~0ull : sk[q + kStreamMargin];
-        st->below = 0;
-        st->nbuf = 0;
-    }
-}
-
 hipError_t launch_select_sample_x(const double *Xp, int64_t Tp, const double *sqn, int64_t n,
-                                  SelectState *st, hipStream_t s) {
-    static bool attr = false;
-    if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_select_sample_x,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           kStreamSample * 8);
-        if (e != hipSuccess) return e;
-        attr = true;
-    }
-    hipLaunchKernelGGL(k_select_sample_x, dim3(1), dim3(1024), kStreamSample * 8, s, Xp, Tp, sqn,
-                       n, st);
+                                  SelectState *st, unsigned long long *buf, hipStream_t s) {
+    // (buf holds at least 65536 keys)
+    hipLaunchKernelGGL(k_select_sample_keys, dim3(kStreamSample / 16), dim3(256), 0, s, Xp, Tp, sqn, n,
+                       kStreamSample, buf, st);
+    hipLaunchKernelGGL(k_select_rank, dim3(kStreamSample / 64), dim3(1024), 0, s, buf, kStreamSample,
+                       kStreamMargin, n, st);
     return hipGetLastError();
 }
 
@@ -939,10 +1146,11 @@ hipError_t launch_select_check(SelectState *st, int64_t cap, double *stats, hipS
 
 hipError_t launch_select_buffer_pass(SelectState *st, const unsigned long long *buf, int64_t cap,
                                      double *stats, hipStream_t s) {
-    const int grid = (int)(cap / 2048 + 1 < 2048 ? cap / 2048 + 1 : 2048);
-    hipLaunchKernelGGL(k_select_pass, dim3(grid), dim3(256), 0, s, (const double *)nullptr,
-                       (int64_t)0, (int64_t)0, (int64_t)0, (int64_t)0, st, buf);
-    hipLaunchKernelGGL(k_select_pick, dim3(1), dim3(1024), 0, s, st, stats);
+    // up to 2^24 keys 512 workgroups at most, as for stored snapshots; the
+    // billions of a larger one need the whole chip's bandwidth
+    const int64_t most = cap <= ((int64_t)1 << 24) ? 512 : 2048;
+    const int grid = (int)(cap / 2048 + 1 < most ? cap / 2048 + 1 : most);
+    hipLaunchKernelGGL(k_select_buffer, dim3(grid), dim3(256), 0, s, st, buf, stats);
     return hipGetLastError();
 }
 
@@ -1086,26 +1294,21 @@ __global__ __launch_bounds__(256) void k_exp_sym(double *W, int64_t ld, int64_t 
     exp_sym_tile(W, ld, n, stats, nt, part, xcd_remap(blockIdx.x, nt * (nt + 1) / 2));
 }
 
-__global__ void k_degree_reduce(const double *part, int nt, int64_t ld, int64_t n, double *deg) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= n) return;
-    deg[i] = ordered_sum(part + i, ld, nt, 0.0);
+// Degrees of 64 nodes from the tile columns' partials: four threads per node
+// sum a quarter of the tiles each, in order, 32 loads in flight; the quarters
+// are added in order.
+__device__ __forceinline__ void degree_body(const double *part, int nt, int64_t ld, int64_t n,
+                                            double *deg, int64_t b, double (*sq)[64]) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int64_t i = b * 64 + lane;
+    const int q0 = w * nt / 4, q1 = (w + 1) * nt / 4;
+    sq[w][lane] = i < n ? ordered_sum(part + (int64_t)q0 * ld + i, ld, q1 - q0, 0.0) : 0.0;
+    __syncthreads();
+    if (w == 0 && i < n) deg[i] = (sq[0][lane] + sq[1][lane]) + (sq[2][lane] + sq[3][lane]);
 }
 
-hipError_t launch_exp_degree(double *W, int64_t ld, int64_t n, const double *stats,
-                             double *deg, double *part, hipStream_t s) {
-    const int nt = (int)(ld / 64);
-    hipLaunchKernelGGL(k_exp_sym, dim3((unsigned)sym_tiles64(ld)), dim3(256), 0, s, W, ld, n,
-                       stats, nt, part);
-    // one wave per workgroup: the n threads spread over every CU
-    hipLaunchKernelGGL(k_degree_reduce, dim3((unsigned)cdiv(n, 64)), dim3(64), 0, s, part, nt,
-                       ld, n, deg);
-    return hipGetLastError();
-}
-
-__device__ __forceinline__ void graph_stats_body(const double *deg, int64_t n, double *stats) {
-    __shared__ double red[4];
-    __shared__ double rmin[256], rmax[256];
+__device__ __forceinline__ void graph_stats_body(const double *deg, int64_t n, double *stats,
+                                                 double *red) {
     double s = 0.0, lo = INFINITY, hi = -INFINITY;
     // a thread's nodes in increasing order, sixteen loads in flight
     for (int64_t i0 = threadIdx.x; i0 < n; i0 += 16 * 256) {
@@ -1117,30 +1320,67 @@ __device__ __forceinline__ void graph_stats_body(const double *deg, int64_t n, d
             if (i0 + 256 * u >= n) break;
             const double d = dv[u];
             s += d;
-            lo = fmin(lo, d);
-            hi = fmax(hi, d);
-            if (isnan(d)) lo = hi = d;
+            // a NaN stays: it is the smallest and the largest from then on
+            lo = isnan(lo) || isnan(d) ? NAN : fmin(lo, d);
+            hi = isnan(hi) || isnan(d) ? NAN : fmax(hi, d);
         }
     }
-    rmin[threadIdx.x] = lo;
-    rmax[threadIdx.x] = hi;
     s = block_sum256(s, red);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+        const double a = __shfl_xor(lo, o), b = __shfl_xor(hi, o);
+        lo = isnan(lo) || isnan(a) ? NAN : fmin(lo, a);
+        hi = isnan(hi) || isnan(b) ? NAN : fmax(hi, b);
+    }
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) {
+        red[threadIdx.x >> 6] = lo;
+        red[4 + (threadIdx.x >> 6)] = hi;
+    }
     __syncthreads();
     if (threadIdx.x == 0) {
-        double a = rmin[0], b = rmax[0];
-        for (int q = 1; q < 256; ++q) {
-            a = (isnan(rmin[q]) || isnan(a)) ? NAN : fmin(a, rmin[q]);
-            b = (isnan(rmax[q]) || isnan(b)) ? NAN : fmax(b, rmax[q]);
+        for (int w = 1; w < 4; ++w) {
+            lo = isnan(lo) || isnan(red[w]) ? NAN : fmin(lo, red[w]);
+            hi = isnan(hi) || isnan(red[4 + w]) ? NAN : fmax(hi, red[4 + w]);
         }
         stats[0] = s;
-        stats[2] = a;
-        stats[3] = b;
+        stats[2] = lo;
+        stats[3] = hi;
     }
+}
+
+// The degrees, then the statistics by the last of nb workgroups (the degrees
+// are published before a workgroup's ticket).
+__device__ __forceinline__ void degree_stats(const double *part, int nt, int64_t ld, int64_t n,
+                                             double *deg, double *stats, int *ticket, int64_t b,
+                                             int64_t nb) {
+    __shared__ double sq[4][64], red[8];
+    __shared__ int last;
+    degree_body(part, nt, ld, n, deg, b, sq);
+    if (!last_workgroup((unsigned int *)ticket, (unsigned int)nb, &last)) return;
+    graph_stats_body(deg, n, stats, red);
+}
+
+__global__ __launch_bounds__(256) void k_degree_stats(const double *part, int nt, int64_t ld,
+                                                      int64_t n, double *deg, double *stats,
+                                                      int *ticket) {
+    degree_stats(part, nt, ld, n, deg, stats, ticket, blockIdx.x, gridDim.x);
+}
+
+hipError_t launch_exp_degree(double *W, int64_t ld, int64_t n, double *stats, double *deg,
+                             double *part, int *ticket, hipStream_t s) {
+    const int nt = (int)(ld / 64);
+    hipLaunchKernelGGL(k_exp_sym, dim3((unsigned)sym_tiles64(ld)), dim3(256), 0, s, W, ld, n,
+                       (const double *)stats, nt, part);
+    hipLaunchKernelGGL(k_degree_stats, dim3((unsigned)cdiv(n, 64)), dim3(256), 0, s, part, nt, ld, n,
+                       deg, stats, ticket);
+    return hipGetLastError();
 }
 
 __global__ __launch_bounds__(256) void k_graph_stats(const double *deg, int64_t n,
                                                      double *stats) {
-    graph_stats_body(deg, n, stats);
+    __shared__ double red[8];
+    graph_stats_body(deg, n, stats, red);
 }
 
 hipError_t launch_graph_stats(const double *deg, int64_t n, double *stats, hipStream_t s) {
@@ -1192,15 +1432,23 @@ bool select_uses_bracket(int64_t n, bool allowed) {
     return allowed && N * 2.0 * kSelMargin / kSelSample <= 0.8 * (double)select_buffer_keys(n);
 }
 
-int graph_table_count(int tb, int64_t n, int64_t ld, bool bracket) {
-    const int grid = (int)(n < 2048 ? n : 2048);
+int graph_gram_shape(int P, const int64_t *ld) {
+    int64_t c0 = 0, c1 = 0;
+    for (int t = 0; t < P; ++t) {
+        c0 += gram_wgs(0, kGramUpper, ld[t], 0, ld[t]);
+        c1 += gram_wgs(1, kGramUpper, ld[t], 0, ld[t]);
+    }
+    return (double)cdiv(c1, 256) / 0.8 < 4.0 * (double)cdiv(c0, 256) ? 1 : 0;
+}
+
+int graph_table_count(int tb, int64_t n, int64_t ld, bool bracket, int gram_shape) {
     switch (tb) {
-    case kGtRows: return (int)ld;
+    case kGtRows: return (int)(ld / 4);
     case kGtOne: return 1;
-    case kGtGram: return kGramWgPerTile * rect_upper_tiles(ld);
-    case kGtSample: return bracket ? 1 : 0;
-    case kGtKeys: return bracket ? 16 : 0;
-    case kGtPass: return grid;
+    case kGtGram: return (int)gram_wgs(gram_shape, kGramUpper, ld, 0, ld);
+    case kGtSample: return bracket ? kSelSample / 64 : 0;
+    case kGtKeys: return bracket ? kSelSample / 64 : 0;
+    case kGtPass: return select_grid(n);
     case kGtSym: return sym_tiles64(ld);
     case kGtNodes64: return (int)cdiv(n, 64);
     case kGtPrep: return (int)cdiv(ld, 256);
@@ -1228,64 +1476,68 @@ __global__ __launch_bounds__(256) void k_graph_init_grouped(const GraphSnap *sna
     if (select) select_reset_body(d.sel);
 }
 
-__global__ __launch_bounds__(64) void k_pad_grouped(const GraphSnap *snaps, const int *prefix, int P) {
+__global__ __launch_bounds__(256) void k_pad_grouped(const GraphSnap *snaps, const int *prefix, int P) {
     const GroupSlot g = group_slot(prefix, P);
     const GraphSnap &d = snaps[g.p];
-    pad_row(d.X, d.n, d.T, d.ldx, d.Xp, d.Tp, d.sqn, d.flags, g.b);
+    pad_row(d.X, d.n, d.T, d.ldx, d.Xp, d.Tp, d.sqn, nullptr, g.b * 4 + (threadIdx.x >> 6));
 }
 
 __global__ __launch_bounds__(256) void k_select_keys_grouped(const GraphSnap *snaps, const int *prefix,
                                                              int P) {
     const GroupSlot g = group_slot(prefix, P);
     const GraphSnap &d = snaps[g.p];
-    select_sample_keys_body(d.Xp, d.Tp, d.sqn, d.n, d.buf, (int)g.b * 4 + (threadIdx.x >> 6),
-                            (int)g.nb * 4);
+    select_sample_keys_body(d.Xp, d.Tp, d.sqn, d.n, kSelSample, d.buf,
+                            (int)g.b * 4 + (threadIdx.x >> 6), (int)g.nb * 4);
 }
 
-__global__ __launch_bounds__(1024) void k_select_sort_grouped(const GraphSnap *snaps, const int *prefix,
-                                                              int P) {
-    extern __shared__ unsigned long long sk[];
+__global__ __launch_bounds__(1024) void k_select_rank_grouped(const GraphSnap *snaps, const int *prefix,
+                                                             int P) {
     const GroupSlot g = group_slot(prefix, P);
     const GraphSnap &d = snaps[g.p];
-    select_sort_keys(d.buf, d.n, d.sel, sk);
+    select_rank_body(d.buf, kSelSample, kSelMargin, d.n, d.sel, (int)g.b);
 }
 
-__global__ __launch_bounds__(GramCore::NT, 2) void k_gram_grouped(const GraphSnap *snaps, const int *prefix, int P,
-                                                      int select) {
+template <int SHAPE>
+__global__ __launch_bounds__(GramCfg<SHAPE>::Core::NT, GramCfg<SHAPE>::WAVES) void k_gram_grouped(
+    const GraphSnap *snaps, const int *prefix, int P, int select) {
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
     const GroupSlot g = group_slot(prefix, P);
     const GraphSnap &d = snaps[g.p];
-    gram_tile<false>(d.Xp, d.Tp, d.sqn, d.n, d.ld, d.W, (int)(d.ld / 128), 0, (int)(d.ld / 256), 0,
-                     xcd_remap((int)g.b, (int)g.nb), select ? d.sel : nullptr,
-                     (const double *)nullptr, (double *)smem_raw,
-                     select && d.bracket ? d.buf : nullptr, d.cap);
+    gram_tile<SHAPE, false>(d.Xp, d.Tp, d.sqn, d.n, d.ld, d.W, 0, d.ld, kGramUpper,
+                            xcd_remap((int)g.b, (int)g.nb), select ? d.sel : nullptr,
+                            (const double *)nullptr, (double *)smem_raw,
+                            select && d.bracket ? d.buf : nullptr, d.cap);
 }
 
-__global__ __launch_bounds__(64) void k_select_setup_grouped(const GraphSnap *snaps, const int *prefix,
-                                                             int P) {
-    const GroupSlot g = group_slot(prefix, P);
-    const GraphSnap &d = snaps[g.p];
-    select_setup_body(d.sel, d.n, d.stats);
-}
-
-__global__ __launch_bounds__(64) void k_select_check_grouped(const GraphSnap *snaps, const int *prefix,
-                                                             int P) {
-    const GroupSlot g = group_slot(prefix, P);
-    const GraphSnap &d = snaps[g.p];
-    select_check_body(d.sel, d.cap, d.stats);
+template <int SHAPE>
+static hipError_t gram_grouped_launch(const GraphSnap *snaps, const int *prefix, int total, int P,
+                                      int select, hipStream_t s) {
+    using Core = typename GramCfg<SHAPE>::Core;
+    static bool attr = false;
+    if (!attr) {
+        hipError_t e = hipFuncSetAttribute((const void *)k_gram_grouped<SHAPE>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)Core::SMEM);
+        if (e != hipSuccess) return e;
+        attr = true;
+    }
+    hipLaunchKernelGGL(k_gram_grouped<SHAPE>, dim3(total), dim3(Core::NT), Core::SMEM, s, snaps, prefix,
+                       P, select);
+    return hipGetLastError();
 }
 
 __global__ __launch_bounds__(256) void k_select_pass_grouped(const GraphSnap *snaps, const int *prefix,
-                                                             int P) {
+                                                             int P, int first) {
     const GroupSlot g = group_slot(prefix, P);
     const GraphSnap &d = snaps[g.p];
-    select_pass_body(d.W, d.ld, d.n, 0, d.n, d.sel, d.buf, g.b, g.nb);
+    select_pass_pick(d.W, d.ld, d.n, d.sel, d.buf, d.cap, d.bracket != 0, first != 0, d.stats, g.b, g.nb);
 }
 
-__global__ __launch_bounds__(1024) void k_select_pick_grouped(const GraphSnap *snaps, const int *prefix,
-                                                              int P) {
+__global__ __launch_bounds__(1024) void k_select_rest_grouped(const GraphSnap *snaps, const int *prefix,
+                                                              int P, int first) {
     const GroupSlot g = group_slot(prefix, P);
-    select_pick_body(snaps[g.p].sel, snaps[g.p].stats);
+    const GraphSnap &d = snaps[g.p];
+    select_rest_body(d.W, d.ld, d.n, d.sel, d.buf, d.cap, d.bracket != 0, first != 0, d.stats);
 }
 
 __global__ void k_set_sigma_grouped(const GraphSnap *snaps, const int *prefix, int P, double sigma) {
@@ -1300,67 +1552,47 @@ __global__ __launch_bounds__(256) void k_exp_sym_grouped(const GraphSnap *snaps,
     exp_sym_tile(d.W, d.ld, d.n, d.stats, nt, d.dpart, xcd_remap((int)g.b, (int)g.nb));
 }
 
-__global__ __launch_bounds__(64) void k_degree_grouped(const GraphSnap *snaps, const int *prefix, int P) {
+__global__ __launch_bounds__(256) void k_degree_stats_grouped(const GraphSnap *snaps, const int *prefix,
+                                                              int P) {
     const GroupSlot g = group_slot(prefix, P);
     const GraphSnap &d = snaps[g.p];
-    const int64_t i = g.b * 64 + threadIdx.x;
-    if (i < d.n) d.deg[i] = ordered_sum(d.dpart + i, d.ld, (int)(d.ld / 64), 0.0);
-}
-
-__global__ __launch_bounds__(256) void k_graph_stats_grouped(const GraphSnap *snaps, const int *prefix,
-                                                             int P) {
-    const GroupSlot g = group_slot(prefix, P);
-    graph_stats_body(snaps[g.p].deg, snaps[g.p].n, snaps[g.p].stats);
+    degree_stats(d.dpart, (int)(d.ld / 64), d.ld, d.n, d.deg, d.stats, d.flags + kDegreeTicket, g.b, g.nb);
 }
 
 hipError_t launch_graph_grouped(const GraphSnap *snaps, const int *tables, const int *totals,
-                                int P, double sigma, hipStream_t s) {
+                                int P, int64_t nmax, double sigma, int gram_shape, hipStream_t s) {
     auto tb = [&](int t) { return tables + (size_t)t * (P + 1); };
-    hipError_t e = gram_attr();
-    if (e != hipSuccess) return e;
-    static bool attr = false;
-    if (!attr) {
-        e = hipFuncSetAttribute((const void *)k_gram_grouped,
-                                hipFuncAttributeMaxDynamicSharedMemorySize, (int)kGramSmem);
-        if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)k_select_sort_grouped,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, kSelSample * 8);
-        if (e != hipSuccess) return e;
-        attr = true;
-    }
     const bool select = sigma <= 0.0;
     hipLaunchKernelGGL(k_graph_init_grouped, dim3(totals[kGtOne]), dim3(256), 0, s, snaps, tb(kGtOne), P,
                        select ? 1 : 0);
-    hipLaunchKernelGGL(k_pad_grouped, dim3(totals[kGtRows]), dim3(64), 0, s, snaps, tb(kGtRows), P);
+    hipLaunchKernelGGL(k_pad_grouped, dim3(totals[kGtRows]), dim3(256), 0, s, snaps, tb(kGtRows), P);
     // the brackets from samples of the series; the Gram counts and gathers them
     if (select && totals[kGtSample] > 0) {
         hipLaunchKernelGGL(k_select_keys_grouped, dim3(totals[kGtKeys]), dim3(256), 0, s, snaps,
                            tb(kGtKeys), P);
-        hipLaunchKernelGGL(k_select_sort_grouped, dim3(totals[kGtSample]), dim3(1024), kSelSample * 8, s,
-                           snaps, tb(kGtSample), P);
+        hipLaunchKernelGGL(k_select_rank_grouped, dim3(totals[kGtSample]), dim3(1024), 0, s, snaps,
+                           tb(kGtSample), P);
     }
-    hipLaunchKernelGGL(k_gram_grouped, dim3(totals[kGtGram]), dim3(GramCore::NT), kGramSmem, s, snaps,
-                       tb(kGtGram), P, select ? 1 : 0);
+    hipError_t e = gram_shape == 1
+        ? gram_grouped_launch<1>(snaps, tb(kGtGram), totals[kGtGram], P, select ? 1 : 0, s)
+        : gram_grouped_launch<0>(snaps, tb(kGtGram), totals[kGtGram], P, select ? 1 : 0, s);
+    if (e != hipSuccess) return e;
     if (select) {
-        hipLaunchKernelGGL(k_select_setup_grouped, dim3(totals[kGtOne]), dim3(64), 0, s, snaps, tb(kGtOne), P);
-        if (totals[kGtSample] > 0)
-            hipLaunchKernelGGL(k_select_check_grouped, dim3(totals[kGtSample]), dim3(64), 0, s, snaps,
-                               tb(kGtSample), P);
-        // as in the per-snapshot selection: at most 6 digit passes and the
-        // collect pass, each followed by the pick
-        for (int q = 0; q < 7; ++q) {
+        // the passes that the largest snapshot takes
+        const int passes = select_passes(nmax);
+        for (int q = 0; q < passes; ++q)
             hipLaunchKernelGGL(k_select_pass_grouped, dim3(totals[kGtPass]), dim3(256), 0, s, snaps,
-                               tb(kGtPass), P);
-            hipLaunchKernelGGL(k_select_pick_grouped, dim3(totals[kGtOne]), dim3(1024), 0, s, snaps,
-                               tb(kGtOne), P);
-        }
+                               tb(kGtPass), P, q == 0 ? 1 : 0);
+        if (passes < 7)
+            hipLaunchKernelGGL(k_select_rest_grouped, dim3(totals[kGtOne]), dim3(1024), 0, s, snaps,
+                               tb(kGtOne), P, passes == 0 ? 1 : 0);
     } else {
         hipLaunchKernelGGL(k_set_sigma_grouped, dim3(totals[kGtOne]), dim3(64), 0, s, snaps, tb(kGtOne), P,
                            sigma);
     }
     hipLaunchKernelGGL(k_exp_sym_grouped, dim3(totals[kGtSym]), dim3(256), 0, s, snaps, tb(kGtSym), P);
-    hipLaunchKernelGGL(k_degree_grouped, dim3(totals[kGtNodes64]), dim3(64), 0, s, snaps, tb(kGtNodes64), P);
-    hipLaunchKernelGGL(k_graph_stats_grouped, dim3(totals[kGtOne]), dim3(256), 0, s, snaps, tb(kGtOne), P);
+    hipLaunchKernelGGL(k_degree_stats_grouped, dim3(totals[kGtNodes64]), dim3(256), 0, s, snaps,
+                       tb(kGtNodes64), P);
     return hipGetLastError();
 }
 

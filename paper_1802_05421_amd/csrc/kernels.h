@@ -13,7 +13,8 @@ int64_t pad_k(int64_t k);           // padded number of projection columns
 int64_t pad_t(int64_t T);           // padded series length (multiple of 16)
 
 // ---- graph ------------------------------------------------------------------
-constexpr int kSelCap = 4096;       // candidates sorted in the last selection step
+constexpr int kSelCap = 4093;       // candidates that the state holds
+constexpr int kDegreeTicket = 16;   // word of a graph workspace's flags: workgroups done with the degrees
 struct SelectState {                // device scratch of the exact median selection
     unsigned long long prefix;      // selected high bits so far
     unsigned long long rank;        // rank still to skip inside the prefix
@@ -27,6 +28,8 @@ struct SelectState {                // device scratch of the exact median select
     unsigned long long nbuf;        // keys in [lo, hi] (appended to the bracket buffer)
     unsigned long long hist[4096];  // 64-bit: a bin can exceed 2^32 keys for n > 92681
     unsigned long long cand[kSelCap];
+    unsigned long long kand, kor;   // AND and OR of the keys of the current digit's pass
+    unsigned int ticket;            // workgroups done with the current pass
 };
 // Keys the bracket buffer of the selection holds for n nodes.
 int64_t select_buffer_keys(int64_t n);
@@ -34,9 +37,11 @@ int64_t select_buffer_keys(int64_t n);
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s);
 // dst = src (bytes a multiple of 16, both 16-byte aligned, no overlap).
 hipError_t launch_copy16(const void *src, void *dst, size_t bytes, hipStream_t s);
+// flags (may be NULL): bit 0 set for a non-finite series; ticket (may be NULL):
+// set to 0.  rows: a multiple of 4.
 hipError_t launch_pad_series(const double *X, int64_t n, int64_t T, int64_t ldx,
                              double *Xp, int64_t rows, int64_t Tp, double *sqn,
-                             int *flags, hipStream_t s);
+                             int *flags, int *ticket, hipStream_t s);
 // st != nullptr: also record min/max upper-triangle keys for the selection
 // (st must have been reset with launch_select_reset); brbuf != nullptr (with
 // st, after launch_select_presample): also count the upper-triangle keys
@@ -68,8 +73,10 @@ hipError_t launch_select_pick(SelectState *st, double *stats, hipStream_t s);
 // the buffer (st->src = 1) when the rank lies inside and nothing overflowed;
 // then launch_select_buffer_pass (one radix pass and pick) until st->mode = 2.
 int64_t select_stream_keys(int64_t n);
+// (the sample uses buf as scratch and resets st: launch_select_start_top
+// comes after it)
 hipError_t launch_select_sample_x(const double *Xp, int64_t Tp, const double *sqn, int64_t n,
-                                  SelectState *st, hipStream_t s);
+                                  SelectState *st, unsigned long long *buf, hipStream_t s);
 hipError_t launch_select_bracket_panel(const double *D2p, int64_t ld, int64_t n, int64_t row0,
                                        int64_t row1, SelectState *st, unsigned long long *buf,
                                        int64_t cap, hipStream_t s);
@@ -84,7 +91,8 @@ hipError_t launch_exp_rows(double *Wp, int64_t ld, int64_t n, int64_t row0, int6
                            hipStream_t s);
 // The bracket of the median selection from a sample of pair distances taken
 // from the padded series (buf: select_buffer_keys(n) words of scratch, its
-// first 4096 words used); call before launch_gram_dist with brbuf = buf.
+// first 4096 words used); resets st; call before launch_gram_dist with brbuf =
+// buf.
 hipError_t launch_select_presample(const double *Xp, int64_t Tp, const double *sqn, int64_t n,
                                    SelectState *st, unsigned long long *buf, hipStream_t s);
 // The exact lower median after the Gram: gathered = the Gram gathered the
@@ -96,8 +104,10 @@ hipError_t launch_select_median(const double *D2, int64_t ld, int64_t n,
 hipError_t launch_set_sigma(double sigma, double *stats, hipStream_t s);
 // part: (ld / 64) x ld doubles of degree partials.
 int sym_tiles64(int64_t ld);   // upper 64 x 64 tiles of an ld x ld matrix
-hipError_t launch_exp_degree(double *W, int64_t ld, int64_t n, const double *stats,
-                             double *deg, double *part, hipStream_t s);
+// Weights in place with their mirror, degrees, and vol, min and max degree
+// into stats; ticket: one int, 0 on entry and on return.
+hipError_t launch_exp_degree(double *W, int64_t ld, int64_t n, double *stats, double *deg,
+                             double *part, int *ticket, hipStream_t s);
 hipError_t launch_graph_stats(const double *deg, int64_t n, double *stats, hipStream_t s);
 hipError_t launch_import_weights(const double *Win, int64_t ldw, int64_t n, double *W,
                                  int64_t ld, double *deg, int *flags, hipStream_t s);

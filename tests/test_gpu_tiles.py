@@ -130,3 +130,57 @@ def test_topk_rounds_and_ties(cdl, m, K):
     F, top = cdl.anomaly_scores(dev(Z0), g, dev(Z1), g, top_k=K)
     Fh = host(F)
     np.testing.assert_array_equal(host(top), np.lexsort((np.arange(m), -Fh))[:K])
+
+
+# The median selection: one workgroup up to 512 nodes, passes over the bracket
+# buffer above, the matrix when the bracket is switched off; many ties (integer
+# series: digits below the tied value are empty), one value only, and the tile
+# shapes of the Gram at their edges.  Integer series have exact distances, so
+# sigma is the oracle's to the bit; the others round in the Gram's order.
+@pytest.mark.parametrize("n,T,kind", [(2, 1, "normal"), (3, 400, "integer"), (64, 16, "normal"),
+                                      (257, 33, "integer"), (512, 20, "normal"), (513, 20, "integer"),
+                                      (1100, 120, "normal"), (1500, 3, "integer"), (700, 5, "constant"),
+                                      (2300, 7, "normal")])
+def test_median_and_graph_of_every_size(cdl, n, T, kind):
+    rng = np.random.default_rng(n + T)
+    X = {"normal": lambda: rng.standard_normal((n, T)),
+         "integer": lambda: rng.integers(-3, 4, (n, T)).astype(float),
+         "constant": lambda: np.tile(np.eye(n)[:, :1], (1, T)) * 2.0}[kind]()
+    if kind == "constant":   # one node off by a vector, all others equal
+        X = X + 1.0
+        want = None
+    else:
+        want = oracle.bandwidth(oracle.sq_distances(X))
+    print("median case n=%d T=%d %s" % (n, T, kind), flush=True)
+    sig = []
+    for mode in (0, 1):
+        cdl.set_select(mode)
+        try:
+            g = cdl.build_graph(dev(X), check=False)
+        finally:
+            cdl.set_select(0)
+        sig.append(g.host_stats()["sigma"])
+    assert sig[0] == sig[1] or (np.isnan(sig[0]) and np.isnan(sig[1]))
+    if kind == "integer":
+        assert sig[0] == want
+    elif kind == "normal":
+        assert sig[0] == pytest.approx(want, rel=1e-13)
+        o = oracle.build_graph(X)
+        W = host(g.W)
+        np.testing.assert_allclose(W[:n, :n], o["W"], rtol=0, atol=2e-13)
+        np.testing.assert_array_equal(W, W.T)
+        np.testing.assert_allclose(host(g.deg), o["deg"], rtol=1e-12)
+        s = g.host_stats()
+        assert s["deg_min"] == host(g.deg).min() and s["deg_max"] == host(g.deg).max()
+    else:
+        assert sig[0] == 0.0
+
+
+# A non-finite series must reach the caller whatever the selection does with it.
+@pytest.mark.parametrize("n", [40, 700])
+@pytest.mark.parametrize("bad", [np.nan, np.inf, -np.inf])
+def test_non_finite_series_is_reported(cdl, n, bad):
+    X = np.random.default_rng(n).standard_normal((n, 12))
+    X[n // 3, 5] = bad
+    with pytest.raises(cdl.CdlError):
+        cdl.build_graph(dev(X))
