@@ -295,7 +295,9 @@ ChainBuf plan_chain(Arena &a, int64_t n, int prec, int depth_max) {
     c.dmn = a.take<double>(ld);
     c.dm = a.take<double>(ld);
     c.u = a.take<double>(ld);
-    c.fro = a.take<double>(std::max<int64_t>(sym_tiles64(ld), square_tiles(prec, ld)));
+    // a squaring's norms are at most sym_tiles64(ld); the 36 of FP64 levels in 32 x
+    // 32 tiles (ld = 256) run on into fro64, which only level 0 uses
+    c.fro = a.take<double>(sym_tiles64(ld));
     c.fro64 = a.take<double>(sym_tiles64(ld));
     const size_t tb = square_tail_bytes(prec, ld, n);
     c.tail = tb ? a.take<float>(tb / sizeof(float)) : nullptr;
@@ -316,7 +318,7 @@ SolveWs plan_solve(Arena &a, int64_t n, int64_t k, int prec) {
     SolveWs w;
     // split-K partials for the largest candidate split counts
     w.part = a.take<char>(panel * std::max<size_t>(8 * (size_t)residual_splits_max(ld, kp, n),
-                                                   4 * (size_t)apply_splits(prec, ld, kp, n, 2)));
+                                                   4 * (size_t)apply_splits_max(prec, ld, kp, n)));
     w.Yt = a.take<double>(panel);
     w.Xt = a.take<double>(panel);
     w.Rt = a.take<double>(panel);
@@ -477,7 +479,7 @@ cdl_status graph_enqueue(cdl_ctx *ctx, const double *X, int64_t n, int64_t T, in
 // scaled copy is made here).  Levels l >= d are applied as 2^(l-d+1)
 // repetitions of the last stored level.  Stream-ordered, no host reads.
 cdl_status precondition_enqueue(cdl_ctx *ctx, int prec, int d, int D, const SolveWs &w,
-                                const ChainBuf &c, int64_t ld, int64_t n, int64_t kp,
+                                const ChainBuf &c, int64_t ld, int64_t n, int64_t k, int64_t kp,
                                 bool scaled, const double *inv_vs, double *Xdst,
                                 bool allow_tune = true) {
     hipStream_t s = ctx->stream;
@@ -492,17 +494,17 @@ cdl_status precondition_enqueue(cdl_ctx *ctx, int prec, int d, int D, const Solv
         std::vector<double> ms(nc);
         for (int q = 0; q < nc; ++q)
             HIPCHK(time_launch(ctx, [&] {
-                return launch_apply(prec, w.Vlo[0], c.levels, w.Vlo[2], w.T64, ld, n, kp, nullptr,
-                                    c.dm, nullptr, (float *)w.part, 0, apply_splits(prec, ld, kp, n, q), s);
+                return launch_apply(prec, w.Vlo[0], c.levels, w.Vlo[2], w.T64, ld, n, k, kp, nullptr,
+                                    c.dm, nullptr, (float *)w.part, 0, apply_splits(prec, ld, kp, n, k, q), s);
             }, &ms[q]));
         ch = cdl::tune_put(cdl::tune_arch(ctx->device), cdl::tune_key("apply", prec, ld, kp), ms);
     }
-    const int ns = apply_splits(prec, ld, kp, n, ch);
+    const int ns = apply_splits(prec, ld, kp, n, k, ch);
     int cur = 0;
     for (int l = 0; l < std::min(d, D); ++l) {
         const bool last = l + 1 == D;
         { Timed t_(ctx, "apply"); HIPCHK(launch_apply(prec, w.Vlo[cur], c.levels + c.level_bytes * l, w.Vlo[cur ^ 1],
-                            w.V64, ld, n, kp, Xdst, c.dm, last ? inv_vs : nullptr, (float *)w.part, 1, ns, s)); }
+                            w.V64, ld, n, k, kp, Xdst, c.dm, last ? inv_vs : nullptr, (float *)w.part, 1, ns, s)); }
         cur ^= 1;
     }
     for (int l = d; l < D; ++l) {
@@ -511,7 +513,7 @@ cdl_status precondition_enqueue(cdl_ctx *ctx, int prec, int d, int D, const Solv
         for (int q = 0; q < m; ++q) {
             void *dst = w.Vlo[2 + (q & 1)];
             { Timed t_(ctx, "apply"); HIPCHK(launch_apply(prec, src, c.levels + c.level_bytes * (d - 1), dst, w.T64,
-                                ld, n, kp, Xdst, c.dm, nullptr, (float *)w.part, 0, ns, s)); }
+                                ld, n, k, kp, Xdst, c.dm, nullptr, (float *)w.part, 0, ns, s)); }
             src = dst;
         }
         const bool last = l + 1 == D;
@@ -991,7 +993,7 @@ cdl_status cdl_build_chain(cdl_ctx *ctx, const double *W, const double *deg, con
         else
             more = l + 1 < depth_max && model_wants_square(prec, l, f, rho, cm);
         if (!more) break;
-        const int ntl = square_tiles(prec, ld);
+        const int ntl = square_tiles_of(prec, ld);
         {
             const cdl_status sq = square_step(ctx, prec, c.levels + c.level_bytes * l, c.levels + c.level_bytes * l,
                                               c.levels + c.level_bytes * (l + 1), ld, n, c, true);
@@ -1136,7 +1138,7 @@ static cdl_status solve_from_rhs(cdl_ctx *ctx, const WProduct &wprod, const doub
                                     : (tol == 0.0 ? d : choose_depth(prec, d, rho_model, target / rel, cm));
     };
     auto precondition = [&](int D, double *Xdst) -> cdl_status {
-        return precondition_enqueue(ctx, prec, d, D, w, c, ld, n, kp, scaled, inv_vs, Xdst);
+        return precondition_enqueue(ctx, prec, d, D, w, c, ld, n, k, kp, scaled, inv_vs, Xdst);
     };
     // max_r ||r_r|| / ||y_r|| after the norms kernel; syncs.
     auto residual_check = [&]() -> cdl_status {
@@ -1831,7 +1833,7 @@ cdl_status solve_enqueue_fixed(cdl_ctx *ctx, const double *W, const double *deg,
     HIPCHK(hipMemcpyAsync(ynorm, w.scal, kp * sizeof(double), hipMemcpyDeviceToDevice, s));
     const double *inv_vs = w.scal + kp + 1;
     for (int it = 0; it < iters; ++it) {
-        cdl_status st = precondition_enqueue(ctx, prec, depth, depth, w, c, ld, n, kp, scaled, inv_vs, w.Xt, false);
+        cdl_status st = precondition_enqueue(ctx, prec, depth, depth, w, c, ld, n, k, kp, scaled, inv_vs, w.Xt, false);
         if (st != CDL_OK) return st;
         { Timed t_(ctx, "residual"); HIPCHK(launch_residual_k(prec, w.Xt, W, w.Yt, deg, c.dm, ld, n, kp, k, 0, (double *)w.part, w.Rt,
                                  w.V64, w.Vlo[0], w.npart, w.mpart, s)); }
@@ -2046,13 +2048,13 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
     // clamped per snapshot to what its length and its workspace allow.
     auto ap_split = [&](int t, int S) {
         const int64_t n = sn[t].n, ld = pad_n(n);
-        return std::min(cdl::apply_splits_fixed(prec, n, S), apply_splits(prec, ld, kp, n, 2));
+        return std::min(cdl::apply_splits_fixed(prec, n, S), apply_splits_max(prec, ld, kp, n));
     };
     constexpr int64_t kGroupWgs = 2 * 256;
     int Sa = 1;
     auto ap_tiles = [&](int S) {
         int64_t c = 0;
-        for (int t = 0; t < P; ++t) c += cdl::apply_gemm_tiles(pad_n(sn[t].n), kp, ap_split(t, S));
+        for (int t = 0; t < P; ++t) c += (int64_t)cdl::apply_base_tiles(pad_n(sn[t].n), kp) * ap_split(t, S);
         return c;
     };
     while (Sa < 256 && ap_tiles(Sa) < kGroupWgs && ap_tiles(2 * Sa) > ap_tiles(Sa)) Sa *= 2;
@@ -2102,7 +2104,7 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
         d.npart = w.npart;
         d.mpart = w.mpart;
         d.scal = w.scal;
-        d.ap_splits = pin_ap >= 0 ? apply_splits(prec, ld, kp, n, pin_ap) : ap_split(t, Sa);
+        d.ap_splits = pin_ap >= 0 ? apply_splits(prec, ld, kp, n, k, pin_ap) : ap_split(t, Sa);
         d.res_splits = rsplit[t];
     }
     std::vector<BatchPair> hp(NP);
@@ -2148,8 +2150,12 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
         for (int i = 0; i < cnt; ++i) tb[i + 1] = tb[i] + f(i);
         return tb[cnt];
     };
-    const int tot_sq = fill(0, P, [&](int t) { return square_tiles(prec, hs[t].ld); });
-    const int tot_ag = fill(1, P, [&](int t) { return apply_gemm_tiles(hs[t].ld, kp, hs[t].ap_splits); });
+    std::vector<int> aps(P);
+    for (int t = 0; t < P; ++t) aps[t] = hs[t].ap_splits;
+    const int sq_tile = square_tile_size(prec, P, lds.data());
+    const int ap_shape = cdl::apply_shape(prec, P, ns.data(), lds.data(), aps.data(), k, kp);
+    const int tot_sq = fill(0, P, [&](int t) { return square_tiles(sq_tile, hs[t].ld); });
+    const int tot_ag = fill(1, P, [&](int t) { return apply_gemm_tiles(ap_shape, hs[t].ld, k, kp, aps[t]); });
     // element-wise kernels stride over at most 256 workgroups per snapshot, so
     // that the launches after every snapshot has converged stay cheap
     constexpr int kEltWgs = 256;
@@ -2263,7 +2269,7 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
         }
         if (st != CDL_OK) return st;
         for (int l = 0; l + 1 < depth; ++l)
-            { Timed t_(ctx, "square"); HIPCHK(cdl::launch_square_grouped(prec, dsnap, dtable(0), P, tot_sq, l, s0)); }
+            { Timed t_(ctx, "square"); HIPCHK(cdl::launch_square_grouped(prec, sq_tile, dsnap, dtable(0), P, tot_sq, l, s0)); }
         // done and iteration flags (their region is rounded up to 256 bytes)
         { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(done, (2 * (size_t)P * sizeof(int) + 15) / 16 * 16, s0)); }
         { Timed t_(ctx, "residual_init"); HIPCHK(cdl::launch_residual_grouped(prec, dsnap, res_shape, dtable(3), tot_rg, dtable(4), tot_rr, P, kp, k, 1, done, s0)); }
@@ -2272,7 +2278,7 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
             if (scaled) { Timed t_(ctx, "prep_v"); HIPCHK(cdl::launch_prep_grouped(prec, dsnap, dtable(5), tot_pv, P, kp, done, s0)); }
             int cur = 0;
             for (int l = 0; l < depth; ++l) {
-                { Timed t_(ctx, "apply"); HIPCHK(cdl::launch_apply_grouped(prec, dsnap, dtable(1), tot_ag, dtable(2), tot_ar, P, kp, l, cur, 1,
+                { Timed t_(ctx, "apply"); HIPCHK(cdl::launch_apply_grouped(prec, ap_shape, dsnap, dtable(1), tot_ag, dtable(2), tot_ar, P, k, kp, l, cur, 1,
                                                                      l + 1 == depth, done, s0)); }
                 cur ^= 1;
             }

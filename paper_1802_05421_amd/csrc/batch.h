@@ -106,21 +106,26 @@ __device__ inline int group_find(const int *prefix, int P, int b) {
 // ---- host launchers (grouped kernels; every pointer table in device memory) --
 
 // One squaring of level `level` into level + 1 for every snapshot; prefix over
-// each snapshot's upper-tile count (square_tiles).  Stream-ordered.
-hipError_t launch_square_grouped(int prec, const BatchSnap *snaps, const int *prefix, int P,
+// each snapshot's upper-tile count (square_tiles of `tile`).  Stream-ordered.
+hipError_t launch_square_grouped(int prec, int tile, const BatchSnap *snaps, const int *prefix, int P,
                                  int total, int level, hipStream_t s);
 // The chain application of one level for every unconverged snapshot: the
 // split-K product (prefix over mt * nt * ap_splits) then the update of
 // V64 / Vlo[out] / X (prefix over the reduction's workgroups, last level
 // when `last`).
-hipError_t launch_apply_grouped(int prec, const BatchSnap *snaps, const int *prefix_gemm,
-                                int total_gemm, const int *prefix_red, int total_red, int P,
+hipError_t launch_apply_grouped(int prec, int shape, const BatchSnap *snaps, const int *prefix_gemm,
+                                int total_gemm, const int *prefix_red, int total_red, int P, int64_t k,
                                 int64_t kpad, int level, int in, int accumulate, int last,
                                 const int *done, hipStream_t s);
 // Workgroups of one snapshot's share of the application's update (also the
 // FP16 operand preparation's), at most `cap`; the kernels stride over them.
 int apply_reduce_blocks(int64_t ld, int64_t kpad, int cap = 2048);
-int apply_gemm_tiles(int64_t ld, int64_t kpad, int nsplit);
+// Tile shape of the applications' products of P snapshots in one launch, a
+// snapshot's workgroups in it, and its 256-node tiles, by which split counts go.
+int apply_shape(int prec, int P, const int64_t *n, const int64_t *ld, const int *nsplit, int64_t k,
+                int64_t kpad);
+int apply_gemm_tiles(int shape, int64_t ld, int64_t k, int64_t kpad, int nsplit);
+int apply_base_tiles(int64_t ld, int64_t kpad);
 // Workgroups of a snapshot's residual product with tile shape `shape`.
 int residual_gemm_tiles(int shape, int64_t ld, int64_t k, int64_t kpad, int S);
 // Tile shape (returned) and per-snapshot split counts of the grouped residual

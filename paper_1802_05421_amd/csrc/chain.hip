@@ -18,6 +18,7 @@
 // FP16 levels hold scale * S~ (scale = a power of two near n) so entries of
 // order 1/n stay in FP16's normal range; the squaring and the application
 // divide the scale back out.
+#include <algorithm>
 #include <type_traits>
 
 #include "batch.h"
@@ -243,8 +244,10 @@ hipError_t launch_normalize_rows(int prec, const double *Wp, int64_t ld, int64_t
 // Symmetric squaring.
 
 // 16-bit levels: 256 x 256 tiles on NW = 8 waves (2 x 4 of 128 x 64) or
-// NW = 4 waves (2 x 2 of 128 x 128); FP32/FP64 levels: one configuration.
-// SH: the MFMA shape of the 16-bit cores (32: 32 x 32 x 16, 16: 16 x 16 x 32).
+// NW = 4 waves (2 x 2 of 128 x 128); SH: the MFMA shape (32: 32 x 32 x 16, 16:
+// 16 x 16 x 32).  FP32 and FP64 levels: NW = 8, and SH is the tile: 128 x 128
+// (two workgroups on a CU), 64 x 64, and 32 x 32 for the smallest FP64 levels
+// (the same bits from each; row_square_tile).
 template <typename T, int NW, int SH = 32> struct SqCfg;
 template <int NW, int SH> struct SqCfg<__bf16, NW, SH> {
     using Core = DmaCore<std::conditional_t<SH == 16, MfmaBF16x32, MfmaBF16>, 256, 256, 2, NW / 2>;
@@ -254,10 +257,37 @@ template <int NW, int SH> struct SqCfg<_Float16, NW, SH> {
     using Core = DmaCore<std::conditional_t<SH == 16, MfmaF16x32, MfmaF16>, 256, 256, 2, NW / 2>;
     static constexpr int TILE = 256;
 };
-template <int NW, int SH> struct SqCfg<float, NW, SH> { using Core = GemmCore<MfmaF32, 128, 128, 32, 2, 2>; static constexpr int TILE = 128; };
-template <int NW, int SH> struct SqCfg<double, NW, SH> { using Core = GemmCore<MfmaF64, 128, 128, 16, 2, 2>; static constexpr int TILE = 128; };
+template <int NW> struct SqCfg<float, NW, 128> { using Core = RowCore<float, 128, 128, 2, 2, 2>; static constexpr int TILE = 128; };
+template <int NW> struct SqCfg<float, NW, 64> { using Core = RowCore<float, 64, 64, 2, 2, 3>; static constexpr int TILE = 64; };
+template <int NW> struct SqCfg<double, NW, 128> { using Core = RowCore<double, 128, 128, 2, 4, 2>; static constexpr int TILE = 128; };
+template <int NW> struct SqCfg<double, NW, 64> { using Core = RowCore<double, 64, 64, 2, 2, 3>; static constexpr int TILE = 64; };
+template <int NW> struct SqCfg<double, NW, 32> { using Core = RowCore<double, 32, 32, 2, 2, 4>; static constexpr int TILE = 32; };
 
-template <typename T, int NW, int SH = 32> constexpr size_t sq_smem() {
+// Tile of an FP32 or FP64 squaring: the one whose busiest CU has the least
+// work (36 tiles of 128 x 128 at n = 1000 kept 36 CUs busy for 79 us in FP32, the
+// 136 of 64 x 64 take 23; 10 of 64 x 64 at n = 256 took 53 us in FP64, 36 of 32 x
+// 32 take 7).  The small tiles lose an eighth and a third of the matrix pipes'
+// rate.  32 x 32 only where its norm partials fit (n <= 256).
+static int row_square_tile(int prec, int P, const int64_t *ld) {
+    const int tile[3] = {128, 64, 32};
+    const double eff[3] = {1.0, 0.88, 0.67};
+    int best = 128;
+    double tb = 1e300;
+    for (int q = 0; q < (prec == 0 ? 3 : 2); ++q) {
+        int64_t tiles = 0;
+        bool fits = true;
+        for (int p = 0; p < P; ++p) {
+            const int64_t nt = ld[p] / tile[q];
+            tiles += nt * (nt + 1) / 2;
+            fits = fits && (q < 2 || ld[p] <= 256);
+        }
+        const double t = (double)cdiv(tiles, 256) * tile[q] * tile[q] / eff[q];
+        if (fits && t < tb) { tb = t; best = tile[q]; }
+    }
+    return best;
+}
+
+template <typename T, int NW, int SH> constexpr size_t sq_smem() {
     using C = typename SqCfg<T, NW, SH>::Core;
     constexpr int TL = SqCfg<T, NW, SH>::TILE;
     constexpr size_t stage = (size_t)TL * (TL + 16 / sizeof(T)) * sizeof(T);
@@ -304,7 +334,7 @@ __device__ inline void square_epilogue(Core &g, const T *A, const T *B, T *S2, i
 // tiles, or the full rounds of 256 workgroups when the last round is split
 // over k below).  The squaring is A = B = S, add = 0.
 // Upper tile `id` of C = A B and its epilogue (one workgroup).
-template <typename T, int NW, int SH = 32>
+template <typename T, int NW, int SH>
 __device__ __forceinline__ void square_tile(const T *A, const T *B, T *S2, int64_t ld, int64_t kend, int nt,
                                    int id, float inv_scale, int add, double *fro_part,
                                    char *smem_raw, double *red) {
@@ -333,19 +363,19 @@ __global__ __launch_bounds__((SqCfg<T, NW, SH>::Core::NT)) void k_square(const T
 
 // Level `level` squared into level + 1 for every snapshot of a sequence:
 // workgroup b is upper tile b - prefix[p] of snapshot p.
-template <typename T>
-__global__ __launch_bounds__((SqCfg<T, 8>::Core::NT)) void k_square_grouped(const BatchSnap *snaps,
-                                                                           const int *prefix, int P,
-                                                                           int level) {
-    using Core = typename SqCfg<T, 8>::Core;
-    constexpr int TL = SqCfg<T, 8>::TILE;
+template <typename T, int SH>
+__global__ __launch_bounds__((SqCfg<T, 8, SH>::Core::NT)) void k_square_grouped(const BatchSnap *snaps,
+                                                                               const int *prefix, int P,
+                                                                               int level) {
+    using Core = typename SqCfg<T, 8, SH>::Core;
+    constexpr int TL = SqCfg<T, 8, SH>::TILE;
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
     __shared__ double red[Core::NT / 64];
     const int p = group_find(prefix, P, blockIdx.x);
     const BatchSnap &d = snaps[p];
     const T *A = (const T *)(d.levels + d.level_bytes * level);
     T *C = (T *)(d.levels + d.level_bytes * (level + 1));
-    square_tile<T, 8>(A, A, C, d.ld, (d.n + 63) / 64 * 64, (int)(d.ld / TL), blockIdx.x - prefix[p],
+    square_tile<T, 8, SH>(A, A, C, d.ld, (d.n + 63) / 64 * 64, (int)(d.ld / TL), blockIdx.x - prefix[p],
                       d.inv_scale, 0, d.fro, smem_raw, red);
 }
 
@@ -427,11 +457,14 @@ __global__ __launch_bounds__((SqCfg<T, NW, SH>::Core::NT)) void k_square_tail(co
                        fro_part + id, (T *)smem_raw, red);
 }
 
-int square_tiles(int prec, int64_t ld) {
-    int TL = (prec == 2 || prec == 3) ? 256 : 128;
-    int nt = (int)(ld / TL);
+int square_tile_size(int prec, int P, const int64_t *ld) {
+    return prec == 2 || prec == 3 ? 256 : row_square_tile(prec, P, ld);
+}
+int square_tiles(int tile, int64_t ld) {
+    const int nt = (int)(ld / tile);
     return nt * (nt + 1) / 2;
 }
+int square_tiles_of(int prec, int64_t ld) { return square_tiles(square_tile_size(prec, 1, &ld), ld); }
 
 // Work split of one 16-bit squaring: the upper tiles fill `full` rounds of
 // one workgroup per CU; when a last round of at most half the CUs remains,
@@ -443,7 +476,7 @@ struct SqPlan {
 };
 static SqPlan square_plan(int prec, int64_t ld, int64_t n) {
     SqPlan p;
-    p.total = square_tiles(prec, ld);
+    p.total = square_tiles_of(prec, ld);
     p.kend = (n + 63) / 64 * 64;   // multiple of every BK used (64/32/16)
     p.full = p.total;
     p.rem = 0;
@@ -469,19 +502,26 @@ size_t square_tail_bytes(int prec, int64_t ld, int64_t n) {
     return (size_t)p.rem * p.splits * 256 * 256 * sizeof(float);
 }
 
-template <typename T, int NW, int SH = 32>
+template <typename T, int NW, int SH>
 static hipError_t sq_launch(const void *A, const void *B, void *S2, int64_t ld, int64_t n,
                             float inv_scale, int add, double *fro_part, float *tail, hipStream_t s) {
     using Cfg = SqCfg<T, NW, SH>;
     constexpr int TL = Cfg::TILE;
     constexpr size_t smem = sq_smem<T, NW, SH>();
+    constexpr bool k16 = sizeof(T) == 2;   // only 16-bit squarings split their last round
     static bool attr = false;
     if (!attr) {
-        for (const void *fn : {(const void *)k_square<T, NW, SH>, (const void *)k_square_part<T, NW, SH>,
-                               (const void *)k_square_tail<T, NW, SH>}) {
-            hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-            if (e != hipSuccess) return e;
+        hipError_t e = hipFuncSetAttribute((const void *)k_square<T, NW, SH>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+        if constexpr (k16) {
+            if (e == hipSuccess)
+                e = hipFuncSetAttribute((const void *)k_square_part<T, NW, SH>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
+            if (e == hipSuccess)
+                e = hipFuncSetAttribute((const void *)k_square_tail<T, NW, SH>,
+                                        hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         }
+        if (e != hipSuccess) return e;
         attr = true;
     }
     const int nt = (int)(ld / TL);
@@ -494,14 +534,17 @@ static hipError_t sq_launch(const void *A, const void *B, void *S2, int64_t ld, 
                        (const T *)B, (T *)S2, ld, p.kend, nt, p.full, inv_scale, add, fro_part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.rem == 0) return e;
-    hipLaunchKernelGGL((k_square_part<T, NW, SH>), dim3(p.rem * p.splits), dim3(NT), smem, s,
-                       (const T *)A, (const T *)B, ld, p.kend, p.ks, nt, p.full, p.splits, tail);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL((k_square_tail<T, NW, SH>), dim3(p.rem), dim3(NT), smem, s, (const T *)A,
-                       (const T *)B, (T *)S2, ld, nt, p.full, p.splits, (const float *)tail,
-                       inv_scale, add, fro_part);
-    return hipGetLastError();
+    if constexpr (k16) {
+        hipLaunchKernelGGL((k_square_part<T, NW, SH>), dim3(p.rem * p.splits), dim3(NT), smem, s,
+                           (const T *)A, (const T *)B, ld, p.kend, p.ks, nt, p.full, p.splits, tail);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_square_tail<T, NW, SH>), dim3(p.rem), dim3(NT), smem, s, (const T *)A,
+                           (const T *)B, (T *)S2, ld, nt, p.full, p.splits, (const float *)tail,
+                           inv_scale, add, fro_part);
+        return hipGetLastError();
+    }
+    return hipErrorInvalidValue;
 }
 
 int square_variants(int prec) { return prec == 2 || prec == 3 ? 6 : 1; }
@@ -526,9 +569,15 @@ static hipError_t sq_dispatch(int prec, const void *A, const void *B, void *C, i
                               int add, double *fro_part, float *tail, int variant, hipStream_t s) {
     const float inv = 1.0f / level_scale(prec, n);
     float *t = (variant & 1) ? nullptr : tail;
+    const int tile = square_tile_size(prec, 1, &ld);
     switch (prec) {
-    case 0: return sq_launch<double, 8>(A, B, C, ld, n, inv, add, fro_part, nullptr, s);
-    case 1: return sq_launch<float, 8>(A, B, C, ld, n, inv, add, fro_part, nullptr, s);
+    case 0:
+        return tile == 128 ? sq_launch<double, 8, 128>(A, B, C, ld, n, inv, add, fro_part, nullptr, s)
+             : tile == 64  ? sq_launch<double, 8, 64>(A, B, C, ld, n, inv, add, fro_part, nullptr, s)
+                           : sq_launch<double, 8, 32>(A, B, C, ld, n, inv, add, fro_part, nullptr, s);
+    case 1:
+        return tile == 128 ? sq_launch<float, 8, 128>(A, B, C, ld, n, inv, add, fro_part, nullptr, s)
+                           : sq_launch<float, 8, 64>(A, B, C, ld, n, inv, add, fro_part, nullptr, s);
     case 2: return sq_dispatch16<__bf16>(A, B, C, ld, n, inv, add, fro_part, t, variant, s);
     case 3: return sq_dispatch16<_Float16>(A, B, C, ld, n, inv, add, fro_part, t, variant, s);
     default: return hipErrorInvalidValue;
@@ -554,8 +603,8 @@ __global__ __launch_bounds__(256) void k_sym_diag(T *C, int64_t ld, int TL) {
 }
 
 template <typename T>
-static hipError_t sym_diag_launch(void *C, int64_t ld, hipStream_t s) {
-    const int TL = SqCfg<T, 8>::TILE;
+static hipError_t sym_diag_launch(int prec, void *C, int64_t ld, hipStream_t s) {
+    const int TL = square_tile_size(prec, 1, &ld);
     hipLaunchKernelGGL(k_sym_diag<T>, dim3((unsigned)(ld / TL)), dim3(256), 0, s, (T *)C, ld, TL);
     return hipGetLastError();
 }
@@ -566,44 +615,105 @@ hipError_t launch_chain_product(int prec, const void *Q, const void *L, void *C,
     hipError_t e = sq_dispatch(prec, Q, L, C, ld, n, 1, fro_part, tail, variant, s);
     if (e != hipSuccess) return e;
     switch (prec) {
-    case 0: return sym_diag_launch<double>(C, ld, s);
-    case 1: return sym_diag_launch<float>(C, ld, s);
-    case 2: return sym_diag_launch<__bf16>(C, ld, s);
-    case 3: return sym_diag_launch<_Float16>(C, ld, s);
+    case 0: return sym_diag_launch<double>(0, C, ld, s);
+    case 1: return sym_diag_launch<float>(1, C, ld, s);
+    case 2: return sym_diag_launch<__bf16>(2, C, ld, s);
+    case 3: return sym_diag_launch<_Float16>(3, C, ld, s);
     default: return hipErrorInvalidValue;
     }
 }
 
 // ---------------------------------------------------------------------------
 // Chain application: C[r][i] = sum_j Vin[r][j] S~[i][j]  (= (S~ V)_{i r}).
-// BF16/FP16/FP32 levels: split-K MFMA GEMM over 256 x 256 output tiles (8
-// waves) writing FP32 partials, then a reduction that updates V (FP64), its
-// rounded copy and, on the last level, X.  FP64 levels: one 64-wide tile
-// per workgroup, updating in the epilogue.
+// BF16/FP16/FP32 levels: split-K MFMA GEMM (tile shapes below) writing FP32
+// partials, then a reduction that updates V (FP64), its rounded copy and, on the
+// last level, X.  FP64 levels: no splits, updating in the epilogue.
 
-template <typename T> struct ApBK { static constexpr int v = 64 * 2 / (int)sizeof(T) < 16 ? 16 : 64 * 2 / (int)sizeof(T); };
-
-// 16-bit levels stream through the direct-to-LDS core, FP32 levels through
-// the register-staged one.
-template <typename T, int BM> struct ApCfg {
+// Product shapes.  16-bit levels: 0, 1, 2 = tiles of 64, 128, 256 columns of V
+// by 256 nodes on 8 waves (which by the padded column count).  FP32 levels: 3 =
+// 128 x 128 (two workgroups on a CU), 4 = 64 x 64, 5..8 = 32 (q - 4) columns by
+// 128 nodes, each wave all of the columns by 32 nodes (the same bits from each
+// at the same split count).
+template <typename T, int SHAPE> struct ApCfg {
+    static constexpr int BM = 64 << SHAPE;
     static constexpr int WM = BM / 128 > 0 ? BM / 128 : 1;
-    static constexpr int WN = 8 / WM;
-    using Mf = typename MfmaOf<T>::type;
-    using Core = std::conditional_t<sizeof(T) == 2, DmaCore<Mf, BM, 256, WM, WN>,
-                                    GemmCore<Mf, BM, 256, ApBK<T>::v, WM, WN>>;
+    using Core = DmaCore<typename MfmaOf<T>::type, BM, 256, WM, 8 / WM>;
 };
+template <int SHAPE> struct ApCfg<float, SHAPE> { using Core = RowCore<float, 32 * (SHAPE - 4), 128, 1, 4, SHAPE < 7 ? 3 : 2>; };
+template <> struct ApCfg<float, 3> { using Core = RowCore<float, 128, 128, 2, 2, 2>; };
+template <> struct ApCfg<float, 4> { using Core = RowCore<float, 64, 64, 2, 2, 3>; };
+static int64_t ap_tile_m(int shape) { return shape < 3 ? 64 << shape : shape == 3 ? 128 : shape == 4 ? 64 : 32 * (shape - 4); }
+static int64_t ap_tile_n(int shape) { return shape < 3 ? 256 : shape == 4 ? 64 : 128; }
+
+static int ap_bm(int64_t kpad) { return kpad % 256 == 0 ? 256 : (kpad % 128 == 0 ? 128 : 64); }
+// Tile rows of a shape: the whole panel, or (FP32, 5..8) the 32-column groups
+// that hold one of the k columns.
+static int64_t ap_mt(int shape, int64_t kpad, int64_t k) {
+    return shape < 5 ? kpad / ap_tile_m(shape) : cdiv(cdiv(k, 32), shape - 4);
+}
+
+int apply_live_rows(int shape, int64_t kpad, int64_t k) {
+    return (int)std::min<int64_t>(kpad, ap_mt(shape, kpad, k) * ap_tile_m(shape));
+}
+
+int apply_gemm_tiles(int shape, int64_t ld, int64_t k, int64_t kpad, int nsplit) {
+    return (int)(ap_mt(shape, kpad, k) * (ld / ap_tile_n(shape))) * nsplit;
+}
+
+// Estimated microseconds of the products of P FP32 snapshots in shape q: the
+// rounds of equal workgroups of one snapshot (of several: the whole, and the
+// longest workgroup), at a CU's FP32 rate times the shape's share of it, and
+// the partials written and read.  Fitted at (n, k) = (1000, 512), (2025, 70) and
+// (4096, 128) over shapes and 1 to 16 splits, product and reduction: 64 x 64
+// tiles at 2, 4 and 4 splits 19.9, 19.1 and 43.3 us, 128 x 128 at the best of its
+// splits 26.7, 26.5 and 46.7, each at the splits of 256-wide tiles 26, 26 and 48.
+static double apply_f32_time(int q, int P, const int64_t *n, const int64_t *ld, const int *nsplit,
+                             int64_t k, int64_t kpad) {
+    constexpr double eff[9] = {0, 0, 0, 1.0, 0.85, 0.85, 0.88, 0.93, 0.95};
+    constexpr double cu_rate = 0.586e6, bytes_us = 4.0e6;
+    double work = 0.0, longest = 0.0, bytes = 0.0;
+    int64_t wgs = 0;
+    for (int p = 0; p < P; ++p) {
+        const int64_t c = apply_gemm_tiles(q, ld[p], k, kpad, nsplit[p]);
+        const double one = 2.0 * (double)(ap_tile_m(q) * ap_tile_n(q)) * (double)cdiv(n[p], nsplit[p]);
+        work += one * (double)c;
+        longest = std::max(longest, one);
+        wgs += c;
+        bytes += 8.0 * nsplit[p] * (double)apply_live_rows(q, kpad, k) * (double)ld[p];
+    }
+    const int64_t rounds = cdiv(wgs, 256);
+    const double t = P == 1 ? (double)rounds * longest : std::max(work / 256.0 + 0.5 * longest, longest);
+    return t / cu_rate / eff[q] / (rounds > 1 && q > 3 ? 1.08 : 1.0) + bytes / bytes_us;
+}
+
+// Shape of the products of P snapshots in one launch.  FP32: the fastest by the
+// estimate (128 x 256 tiles left half the chip idle at n = 2025, k = 70 and
+// computed 128 columns: 27 us a product alone).
+int apply_shape(int prec, int P, const int64_t *n, const int64_t *ld, const int *nsplit, int64_t k,
+                int64_t kpad) {
+    if (prec != 1) return ap_bm(kpad) == 256 ? 2 : ap_bm(kpad) == 128 ? 1 : 0;
+    int best = 4;
+    double tb = 1e300;
+    for (int q = 3; q <= 8; ++q) {
+        if (kpad % ap_tile_m(q) && q < 5) continue;
+        if (ap_mt(q, kpad, k) * ap_tile_m(q) > kpad) continue;
+        const double t = apply_f32_time(q, P, n, ld, nsplit, k, kpad);
+        if (t < tb) { tb = t; best = q; }
+    }
+    return best;
+}
 
 // Split-K product tile `id` of the chain application (one workgroup).
-template <typename T, int BM>
+template <typename T, int SHAPE>
 __device__ __forceinline__ void apply_gemm_tile(const T *Vin, const T *S, int64_t ld, int64_t kend,
                                        int64_t ks, int mt, int nt, float *P, int64_t kpad, int id,
                                        char *smem_raw) {
-    using Core = typename ApCfg<T, BM>::Core;
+    using Core = typename ApCfg<T, SHAPE>::Core;
     T *smem = (T *)smem_raw;
     const int split = id / (mt * nt);
     int I, J;
     rect_tile<4>(id % (mt * nt), mt, nt, I, J);
-    const int64_t m0 = (int64_t)I * BM, n0 = (int64_t)J * 256;
+    const int64_t m0 = (int64_t)I * Core::TBM, n0 = (int64_t)J * Core::TBN;
     const int64_t k0 = (int64_t)split * ks;
     const int64_t kk = k0 < kend ? (kend - k0 < ks ? kend - k0 : ks) : 0;
     Core g;
@@ -618,16 +728,14 @@ __device__ __forceinline__ void apply_gemm_tile(const T *Vin, const T *S, int64_
                 Ps[(m0 + Core::row_of(a, r)) * ld + n0 + Core::col_of(b)] = g.acc[a][b][r];
 }
 
-template <typename T, int BM>
-__global__ __launch_bounds__(512) void k_apply_gemm(const T *Vin, const T *S, int64_t ld,
-                                                    int64_t kend, int64_t ks, int mt, int nt,
-                                                    int nsplit, float *P, int64_t kpad) {
+template <typename T, int SHAPE>
+__global__ __launch_bounds__((ApCfg<T, SHAPE>::Core::NT)) void k_apply_gemm(
+    const T *Vin, const T *S, int64_t ld, int64_t kend, int64_t ks, int mt, int nt, int nsplit,
+    float *P, int64_t kpad) {
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
     const int id = xcd_remap(blockIdx.x, mt * nt * nsplit);
-    apply_gemm_tile<T, BM>(Vin, S, ld, kend, ks, mt, nt, P, kpad, id, smem_raw);
+    apply_gemm_tile<T, SHAPE>(Vin, S, ld, kend, ks, mt, nt, P, kpad, id, smem_raw);
 }
-
-static int ap_bm(int64_t kpad) { return kpad % 256 == 0 ? 256 : (kpad % 128 == 0 ? 128 : 64); }
 
 // k-range of one split of an application's product (64-element multiples).
 __host__ __device__ inline int64_t apply_split_len(int64_t n, int nsplit) {
@@ -636,31 +744,50 @@ __host__ __device__ inline int64_t apply_split_len(int64_t n, int nsplit) {
 }
 
 // Split-K count of the chain application: choice 0 aims at >= 256
-// workgroups, 1 halves that count, 2 doubles it (at least two 64-wide
+// workgroups of the 256-node tiles (FP32 levels: is the fastest by the
+// estimate above), 1 halves that count, 2 doubles it (at least two 64-wide
 // k-tiles per split either way); FP64 levels are not split.
-int apply_splits(int prec, int64_t ld, int64_t kpad, int64_t n, int choice) {
-    if (prec == 0) return 1;
+static int64_t apply_splits_top(int64_t n) {
+    const int64_t smax = (n + 63) / 64 / 2;   // >= 2 k-tiles per split
+    return smax > 0 ? smax : 1;
+}
+static int64_t apply_splits_base(int64_t ld, int64_t kpad) {
     const int64_t base = (kpad / ap_bm(kpad)) * (ld / 256);
-    const int64_t kend = (n + 63) / 64 * 64;
-    int64_t S = (256 + base - 1) / base;
-    if (choice == 1) S = S / 2;
-    if (choice == 2) S = 2 * S;
-    const int64_t smax = kend / 128 > 0 ? kend / 128 : 1;   // >= 2 k-tiles per split
-    if (S > smax) S = smax;
-    if (S < 1) S = 1;
-    return (int)S;
+    return (256 + base - 1) / base;
+}
+int apply_splits_max(int prec, int64_t ld, int64_t kpad, int64_t n) {
+    if (prec == 0) return 1;
+    return (int)std::min(2 * apply_splits_base(ld, kpad), apply_splits_top(n));
 }
 
-// Elements first, first + step, ... (< total) of the application's update.
+int apply_splits(int prec, int64_t ld, int64_t kpad, int64_t n, int64_t k, int choice) {
+    if (prec == 0) return 1;
+    int64_t S = apply_splits_base(ld, kpad);
+    if (prec == 1) {
+        const int64_t top = std::min(S, apply_splits_top(n));
+        double tb = 1e300;
+        for (int c = 1; c <= top; ++c) {
+            const double t = apply_f32_time(apply_shape(prec, 1, &n, &ld, &c, k, kpad), 1, &n, &ld, &c, k, kpad);
+            if (t < tb) { tb = t; S = c; }
+        }
+    }
+    if (choice == 1) S = S / 2;
+    if (choice == 2) S = 2 * S;
+    return (int)std::max<int64_t>(1, std::min(S, apply_splits_top(n)));
+}
+
+// Elements first, first + step, ... (< total) of the application's update;
+// the partials hold the first `live` columns (the others are zero).
 template <typename T>
 __device__ inline void apply_reduce_range(const float *P, int nsplit, int64_t total, int64_t ld,
-                                          int64_t kpad, float inv_scale, int accumulate,
+                                          int64_t kpad, int64_t live, float inv_scale, int accumulate,
                                           double *V64, T *Vout, double *Xt, const double *dm,
                                           const double *inv_vs, int64_t first, int64_t step) {
     const double ivs = inv_vs ? *inv_vs : 0.0;
     for (int64_t o = first; o < total; o += step) {
         float acc = 0.f;
-        for (int q = 0; q < nsplit; ++q) acc += P[(int64_t)q * kpad * ld + o];
+        if (o < live * ld)
+            for (int q = 0; q < nsplit; ++q) acc += P[(int64_t)q * kpad * ld + o];
         const double v = (accumulate ? V64[o] : 0.0) + (double)acc * (double)inv_scale;
         V64[o] = v;
         Vout[o] = cvtd<T>(v);
@@ -670,94 +797,112 @@ __device__ inline void apply_reduce_range(const float *P, int nsplit, int64_t to
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_apply_reduce(const float *P, int nsplit, int64_t total,
-                                                      int64_t ld, int64_t kpad, float inv_scale,
-                                                      int accumulate, double *V64, T *Vout,
-                                                      double *Xt, const double *dm,
+                                                      int64_t ld, int64_t kpad, int64_t live,
+                                                      float inv_scale, int accumulate, double *V64,
+                                                      T *Vout, double *Xt, const double *dm,
                                                       const double *inv_vs) {
-    apply_reduce_range<T>(P, nsplit, total, ld, kpad, inv_scale, accumulate, V64, Vout, Xt, dm,
+    apply_reduce_range<T>(P, nsplit, total, ld, kpad, live, inv_scale, accumulate, V64, Vout, Xt, dm,
                           inv_vs, (int64_t)blockIdx.x * blockDim.x + threadIdx.x,
                           (int64_t)gridDim.x * blockDim.x);
 }
 
-template <typename T, int BM>
-static hipError_t apg_launch(const void *Vin, const void *S, int64_t ld, int64_t n,
+template <typename T, int SHAPE>
+static hipError_t apg_launch(const void *Vin, const void *S, int64_t ld, int64_t n, int64_t k,
                              int64_t kpad, int nsplit, float *P, hipStream_t s) {
-    using Core = typename ApCfg<T, BM>::Core;
+    using Core = typename ApCfg<T, SHAPE>::Core;
     static bool attr = false;
     if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_apply_gemm<T, BM>,
+        hipError_t e = hipFuncSetAttribute((const void *)k_apply_gemm<T, SHAPE>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)Core::SMEM);
         if (e != hipSuccess) return e;
         attr = true;
     }
-    const int mt = (int)(kpad / BM), nt = (int)(ld / 256);
-    const int64_t kend = (n + 63) / 64 * 64;
-    const int64_t ks = (cdiv(kend, nsplit) + 63) / 64 * 64;
-    hipLaunchKernelGGL((k_apply_gemm<T, BM>), dim3(mt * nt * nsplit), dim3(512), Core::SMEM, s,
-                       (const T *)Vin, (const T *)S, ld, kend, ks, mt, nt, nsplit, P, kpad);
+    const int mt = (int)ap_mt(SHAPE, kpad, k), nt = (int)(ld / Core::TBN);
+    hipLaunchKernelGGL((k_apply_gemm<T, SHAPE>), dim3(mt * nt * nsplit), dim3(Core::NT), Core::SMEM, s,
+                       (const T *)Vin, (const T *)S, ld, (n + 63) / 64 * 64, apply_split_len(n, nsplit),
+                       mt, nt, nsplit, P, kpad);
     return hipGetLastError();
 }
 
-template <typename T>
-static hipError_t ap_gemm_launch(const void *Vin, const void *S, int64_t ld, int64_t n,
-                                 int64_t kpad, int ns, float *P, hipStream_t s) {
-    switch (ap_bm(kpad)) {
-    case 256: return apg_launch<T, 256>(Vin, S, ld, n, kpad, ns, P, s);
-    case 128: return apg_launch<T, 128>(Vin, S, ld, n, kpad, ns, P, s);
-    default: return apg_launch<T, 64>(Vin, S, ld, n, kpad, ns, P, s);
+// f<SHAPE>() for the shapes that T takes.
+#define CDL_APPLY_SHAPES(CALL)                                  \
+    if constexpr (sizeof(T) == 4) {                             \
+        switch (shape) {                                        \
+        case 3: return CALL(3);                                 \
+        case 4: return CALL(4);                                 \
+        case 5: return CALL(5);                                 \
+        case 6: return CALL(6);                                 \
+        case 7: return CALL(7);                                 \
+        case 8: return CALL(8);                                 \
+        default: return hipErrorInvalidValue;                   \
+        }                                                       \
+    } else {                                                    \
+        switch (shape) {                                        \
+        case 0: return CALL(0);                                 \
+        case 1: return CALL(1);                                 \
+        case 2: return CALL(2);                                 \
+        default: return hipErrorInvalidValue;                   \
+        }                                                       \
     }
+
+template <typename T>
+static hipError_t ap_gemm_launch(int shape, const void *Vin, const void *S, int64_t ld, int64_t n,
+                                 int64_t k, int64_t kpad, int ns, float *P, hipStream_t s) {
+#define CDL_CALL(Q) (apg_launch<T, Q>(Vin, S, ld, n, k, kpad, ns, P, s))
+    CDL_APPLY_SHAPES(CDL_CALL)
+#undef CDL_CALL
 }
 
 template <typename T>
-static hipError_t ap_split_launch(const void *Vin, const void *S, void *Vout, double *V64,
-                                  int64_t ld, int64_t n, int64_t kpad, float inv_scale,
+static hipError_t ap_split_launch(int prec, const void *Vin, const void *S, void *Vout, double *V64,
+                                  int64_t ld, int64_t n, int64_t k, int64_t kpad, float inv_scale,
                                   double *Xt, const double *dm, const double *inv_vs, float *P,
                                   int accumulate, int ns, hipStream_t s) {
-    hipError_t e = ap_gemm_launch<T>(Vin, S, ld, n, kpad, ns, P, s);
+    const int shape = apply_shape(prec, 1, &n, &ld, &ns, k, kpad);
+    hipError_t e = ap_gemm_launch<T>(shape, Vin, S, ld, n, k, kpad, ns, P, s);
     if (e != hipSuccess) return e;
     const int64_t total = kpad * ld;
     const int grid = (int)(cdiv(total, 256) < 16384 ? cdiv(total, 256) : 16384);
     hipLaunchKernelGGL(k_apply_reduce<T>, dim3(grid), dim3(256), 0, s, P, ns, total, ld, kpad,
-                       inv_scale, accumulate, V64, (T *)Vout, Xt, dm, inv_vs);
+                       (int64_t)apply_live_rows(shape, kpad, k), inv_scale, accumulate, V64, (T *)Vout,
+                       Xt, dm, inv_vs);
     return hipGetLastError();
 }
 
 // ---- grouped over the snapshots of a sequence ----------------------------
 
-template <typename T, int BM>
-__global__ __launch_bounds__(512) void k_apply_gemm_grouped(const BatchSnap *snaps, const int *prefix,
-                                                            int P, int64_t kpad, int level, int in,
-                                                            const int *done) {
+template <typename T, int SHAPE>
+__global__ __launch_bounds__((ApCfg<T, SHAPE>::Core::NT)) void k_apply_gemm_grouped(
+    const BatchSnap *snaps, const int *prefix, int P, int64_t kpad, int mt, int level, int in,
+    const int *done) {
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
     const int p = group_find(prefix, P, blockIdx.x);
     if (done[p]) return;
     const BatchSnap &d = snaps[p];
-    const int mt = (int)(kpad / BM), nt = (int)(d.ld / 256);
+    const int nt = (int)(d.ld / ApCfg<T, SHAPE>::Core::TBN);
     const int count = prefix[p + 1] - prefix[p];
     const int id = xcd_remap(blockIdx.x - prefix[p], count);
-    apply_gemm_tile<T, BM>((const T *)d.Vlo[in], (const T *)(d.levels + d.level_bytes * level), d.ld,
-                           (d.n + 63) / 64 * 64, apply_split_len(d.n, d.ap_splits), mt, nt, d.Pap,
-                           kpad, id, smem_raw);
+    apply_gemm_tile<T, SHAPE>((const T *)d.Vlo[in], (const T *)(d.levels + d.level_bytes * level), d.ld,
+                              (d.n + 63) / 64 * 64, apply_split_len(d.n, d.ap_splits), mt, nt, d.Pap,
+                              kpad, id, smem_raw);
 }
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_apply_reduce_grouped(const BatchSnap *snaps, const int *prefix,
-                                                              int P, int64_t kpad, int in,
+                                                              int P, int64_t kpad, int64_t live, int in,
                                                               int accumulate, int last,
                                                               const int *done) {
     const int p = group_find(prefix, P, blockIdx.x);
     if (done[p]) return;
     const BatchSnap &d = snaps[p];
     const int64_t nb = prefix[p + 1] - prefix[p];
-    apply_reduce_range<T>(d.Pap, d.ap_splits, kpad * d.ld, d.ld, kpad, d.inv_scale, accumulate,
+    apply_reduce_range<T>(d.Pap, d.ap_splits, kpad * d.ld, d.ld, kpad, live, d.inv_scale, accumulate,
                           d.V64, (T *)d.Vlo[in ^ 1], d.Xt, d.dm, last ? d.scal + kpad + 1 : nullptr,
                           (int64_t)(blockIdx.x - prefix[p]) * 256 + threadIdx.x, nb * 256);
 }
 
-int apply_gemm_tiles(int64_t ld, int64_t kpad, int nsplit) {
-    return (int)(kpad / ap_bm(kpad) * (ld / 256)) * nsplit;
-}
+int apply_base_tiles(int64_t ld, int64_t kpad) { return (int)(kpad / ap_bm(kpad) * (ld / 256)); }
 
 int apply_reduce_blocks(int64_t ld, int64_t kpad, int cap) {
     const int64_t b = cdiv(kpad * ld, 256);
@@ -771,90 +916,90 @@ int apply_splits_fixed(int prec, int64_t n, int S) {
     return (int)(S < 1 ? 1 : S > smax ? smax : S);
 }
 
-template <typename T, int BM>
+template <typename T, int SHAPE>
 static hipError_t apply_grouped_launch(const BatchSnap *snaps, const int *prefix_gemm, int total_gemm,
-                                       const int *prefix_red, int total_red, int P, int64_t kpad,
-                                       int level, int in, int accumulate, int last, const int *done,
-                                       hipStream_t s) {
-    using Core = typename ApCfg<T, BM>::Core;
+                                       const int *prefix_red, int total_red, int P, int64_t k,
+                                       int64_t kpad, int level, int in, int accumulate, int last,
+                                       const int *done, hipStream_t s) {
+    using Core = typename ApCfg<T, SHAPE>::Core;
     static bool attr = false;
     if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_apply_gemm_grouped<T, BM>,
+        hipError_t e = hipFuncSetAttribute((const void *)k_apply_gemm_grouped<T, SHAPE>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)Core::SMEM);
         if (e != hipSuccess) return e;
         attr = true;
     }
-    hipLaunchKernelGGL((k_apply_gemm_grouped<T, BM>), dim3(total_gemm), dim3(512), Core::SMEM, s, snaps,
-                       prefix_gemm, P, kpad, level, in, done);
+    hipLaunchKernelGGL((k_apply_gemm_grouped<T, SHAPE>), dim3(total_gemm), dim3(Core::NT), Core::SMEM, s,
+                       snaps, prefix_gemm, P, kpad, (int)ap_mt(SHAPE, kpad, k), level, in, done);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_apply_reduce_grouped<T>, dim3(total_red), dim3(256), 0, s, snaps, prefix_red,
-                       P, kpad, in, accumulate, last, done);
+                       P, kpad, (int64_t)apply_live_rows(SHAPE, kpad, k), in, accumulate, last, done);
     return hipGetLastError();
 }
 
 template <typename T>
-static hipError_t apply_grouped_bm(const BatchSnap *snaps, const int *pg, int tg, const int *pr,
-                                   int tr, int P, int64_t kpad, int level, int in, int accumulate,
-                                   int last, const int *done, hipStream_t s) {
-    switch (ap_bm(kpad)) {
-    case 256: return apply_grouped_launch<T, 256>(snaps, pg, tg, pr, tr, P, kpad, level, in, accumulate, last, done, s);
-    case 128: return apply_grouped_launch<T, 128>(snaps, pg, tg, pr, tr, P, kpad, level, in, accumulate, last, done, s);
-    default: return apply_grouped_launch<T, 64>(snaps, pg, tg, pr, tr, P, kpad, level, in, accumulate, last, done, s);
-    }
+static hipError_t apply_grouped_shape(int shape, const BatchSnap *snaps, const int *pg, int tg,
+                                      const int *pr, int tr, int P, int64_t k, int64_t kpad, int level,
+                                      int in, int accumulate, int last, const int *done, hipStream_t s) {
+#define CDL_CALL(Q) (apply_grouped_launch<T, Q>(snaps, pg, tg, pr, tr, P, k, kpad, level, in, accumulate, last, done, s))
+    CDL_APPLY_SHAPES(CDL_CALL)
+#undef CDL_CALL
 }
 
-hipError_t launch_apply_grouped(int prec, const BatchSnap *snaps, const int *prefix_gemm,
-                                int total_gemm, const int *prefix_red, int total_red, int P,
+hipError_t launch_apply_grouped(int prec, int shape, const BatchSnap *snaps, const int *prefix_gemm,
+                                int total_gemm, const int *prefix_red, int total_red, int P, int64_t k,
                                 int64_t kpad, int level, int in, int accumulate, int last,
                                 const int *done, hipStream_t s) {
     switch (prec) {
-    case 1: return apply_grouped_bm<float>(snaps, prefix_gemm, total_gemm, prefix_red, total_red, P, kpad, level, in, accumulate, last, done, s);
-    case 2: return apply_grouped_bm<__bf16>(snaps, prefix_gemm, total_gemm, prefix_red, total_red, P, kpad, level, in, accumulate, last, done, s);
-    case 3: return apply_grouped_bm<_Float16>(snaps, prefix_gemm, total_gemm, prefix_red, total_red, P, kpad, level, in, accumulate, last, done, s);
+    case 1: return apply_grouped_shape<float>(shape, snaps, prefix_gemm, total_gemm, prefix_red, total_red, P, k, kpad, level, in, accumulate, last, done, s);
+    case 2: return apply_grouped_shape<__bf16>(shape, snaps, prefix_gemm, total_gemm, prefix_red, total_red, P, k, kpad, level, in, accumulate, last, done, s);
+    case 3: return apply_grouped_shape<_Float16>(shape, snaps, prefix_gemm, total_gemm, prefix_red, total_red, P, k, kpad, level, in, accumulate, last, done, s);
     default: return hipErrorInvalidValue;   // FP64 chains are not grouped
     }
 }
 
-template <typename T>
+template <typename T, int SH>
 static hipError_t square_grouped_launch(const BatchSnap *snaps, const int *prefix, int P, int total,
                                         int level, hipStream_t s) {
-    constexpr size_t smem = sq_smem<T, 8>();
+    constexpr size_t smem = sq_smem<T, 8, SH>();
     static bool attr = false;
     if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_square_grouped<T>,
+        hipError_t e = hipFuncSetAttribute((const void *)k_square_grouped<T, SH>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if (e != hipSuccess) return e;
         attr = true;
     }
-    hipLaunchKernelGGL(k_square_grouped<T>, dim3(total), dim3(SqCfg<T, 8>::Core::NT), smem, s, snaps,
-                       prefix, P, level);
+    hipLaunchKernelGGL((k_square_grouped<T, SH>), dim3(total), dim3(SqCfg<T, 8, SH>::Core::NT), smem, s,
+                       snaps, prefix, P, level);
     return hipGetLastError();
 }
 
-hipError_t launch_square_grouped(int prec, const BatchSnap *snaps, const int *prefix, int P,
+hipError_t launch_square_grouped(int prec, int tile, const BatchSnap *snaps, const int *prefix, int P,
                                  int total, int level, hipStream_t s) {
     switch (prec) {
-    case 1: return square_grouped_launch<float>(snaps, prefix, P, total, level, s);
-    case 2: return square_grouped_launch<__bf16>(snaps, prefix, P, total, level, s);
-    case 3: return square_grouped_launch<_Float16>(snaps, prefix, P, total, level, s);
+    case 1: return tile == 128 ? square_grouped_launch<float, 128>(snaps, prefix, P, total, level, s)
+                               : square_grouped_launch<float, 64>(snaps, prefix, P, total, level, s);
+    case 2: return square_grouped_launch<__bf16, 32>(snaps, prefix, P, total, level, s);
+    case 3: return square_grouped_launch<_Float16, 32>(snaps, prefix, P, total, level, s);
     default: return hipErrorInvalidValue;
     }
 }
 
-// FP64 levels: in-epilogue update (small n only in practice).
-template <int BM>
-__global__ __launch_bounds__(BM) void k_apply_f64(const double *Vin, const double *S, double *Vout,
-                                                  double *V64, int64_t ld, int64_t kend, int mt,
-                                                  int nt, double *Xt, const double *dm,
-                                                  const double *inv_vs, int accumulate) {
-    using Core = GemmCore<MfmaF64, BM, 64, 16, BM / 64, 1>;
+// FP64 levels: in-epilogue update (small n only in practice), in square tiles
+// of 128, 64 or 32 by the busiest CU's work: a tile's k loop is a serial chain
+// (four tiles of 64 took 61 us a launch at n = 256, k = 32; 16 of 32 take 7).
+template <int TL>
+__global__ __launch_bounds__((SqCfg<double, 8, TL>::Core::NT)) void k_apply_f64(
+    const double *Vin, const double *S, double *Vout, double *V64, int64_t ld, int64_t kend, int mt,
+    int nt, double *Xt, const double *dm, const double *inv_vs, int accumulate) {
+    using Core = typename SqCfg<double, 8, TL>::Core;
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
     double *smem = (double *)smem_raw;
     int I, J;
     rect_tile<4>(xcd_remap(blockIdx.x, mt * nt), mt, nt, I, J);
-    const int64_t m0 = (int64_t)I * BM, n0 = (int64_t)J * 64;
+    const int64_t m0 = (int64_t)I * TL, n0 = (int64_t)J * TL;
     Core g;
     g.run(Vin, ld, S, ld, m0, n0, kend, smem);
     const double ivs = inv_vs ? *inv_vs : 0.0;
@@ -873,50 +1018,55 @@ __global__ __launch_bounds__(BM) void k_apply_f64(const double *Vin, const doubl
             }
 }
 
-template <int BM>
+template <int TL>
 static hipError_t apf64_launch(const void *Vin, const void *S, void *Vout, double *V64,
                                int64_t ld, int64_t n, int64_t kpad, double *Xt, const double *dm,
                                const double *inv_vs, int accumulate, hipStream_t s) {
-    using Core = GemmCore<MfmaF64, BM, 64, 16, BM / 64, 1>;
+    using Core = typename SqCfg<double, 8, TL>::Core;
     static bool attr = false;
     if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_apply_f64<BM>,
+        hipError_t e = hipFuncSetAttribute((const void *)k_apply_f64<TL>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)Core::SMEM);
         if (e != hipSuccess) return e;
         attr = true;
     }
-    const int mt = (int)(kpad / BM), nt = (int)(ld / 64);
+    const int mt = (int)(kpad / TL), nt = (int)(ld / TL);
     const int64_t kend = (n + 63) / 64 * 64;
-    hipLaunchKernelGGL(k_apply_f64<BM>, dim3(mt * nt), dim3(BM), Core::SMEM, s,
+    hipLaunchKernelGGL(k_apply_f64<TL>, dim3(mt * nt), dim3(Core::NT), Core::SMEM, s,
                        (const double *)Vin, (const double *)S, (double *)Vout, V64, ld, kend, mt,
                        nt, Xt, dm, inv_vs, accumulate);
     return hipGetLastError();
 }
 
+static int apply_f64_tile(int64_t ld, int64_t kpad) {
+    const double eff[3] = {1.0, 0.88, 0.67};
+    int best = 64;
+    double tb = 1e300;
+    for (int q = 0; q < 3; ++q) {
+        const int64_t tl = 128 >> q;
+        if (kpad % tl) continue;
+        const double t = (double)cdiv(kpad / tl * (ld / tl), 256) * (double)(tl * tl) / eff[q];
+        if (t < tb) { tb = t; best = (int)tl; }
+    }
+    return best;
+}
+
 hipError_t launch_apply(int prec, const void *Vin, const void *S, void *Vout, double *V64,
-                        int64_t ld, int64_t n, int64_t kpad, double *Xt, const double *dm,
+                        int64_t ld, int64_t n, int64_t k, int64_t kpad, double *Xt, const double *dm,
                         const double *inv_vs, float *P, int accumulate, int nsplit, hipStream_t s) {
     const float inv = 1.0f / level_scale(prec, n);
     const int ns = nsplit;
     switch (prec) {
     case 0:
-        if (kpad % 256 == 0) return apf64_launch<256>(Vin, S, Vout, V64, ld, n, kpad, Xt, dm, inv_vs, accumulate, s);
-        if (kpad % 128 == 0) return apf64_launch<128>(Vin, S, Vout, V64, ld, n, kpad, Xt, dm, inv_vs, accumulate, s);
-        return apf64_launch<64>(Vin, S, Vout, V64, ld, n, kpad, Xt, dm, inv_vs, accumulate, s);
-    case 1: return ap_split_launch<float>(Vin, S, Vout, V64, ld, n, kpad, inv, Xt, dm, inv_vs, P, accumulate, ns, s);
-    case 2: return ap_split_launch<__bf16>(Vin, S, Vout, V64, ld, n, kpad, inv, Xt, dm, inv_vs, P, accumulate, ns, s);
-    case 3: return ap_split_launch<_Float16>(Vin, S, Vout, V64, ld, n, kpad, inv, Xt, dm, inv_vs, P, accumulate, ns, s);
-    default: return hipErrorInvalidValue;
-    }
-}
-
-hipError_t launch_apply_gemm(int prec, const void *Vin, const void *S, int64_t ld, int64_t n,
-                             int64_t kpad, int nsplit, float *P, hipStream_t s) {
-    switch (prec) {
-    case 1: return ap_gemm_launch<float>(Vin, S, ld, n, kpad, nsplit, P, s);
-    case 2: return ap_gemm_launch<__bf16>(Vin, S, ld, n, kpad, nsplit, P, s);
-    case 3: return ap_gemm_launch<_Float16>(Vin, S, ld, n, kpad, nsplit, P, s);
+        switch (apply_f64_tile(ld, kpad)) {
+        case 128: return apf64_launch<128>(Vin, S, Vout, V64, ld, n, kpad, Xt, dm, inv_vs, accumulate, s);
+        case 64: return apf64_launch<64>(Vin, S, Vout, V64, ld, n, kpad, Xt, dm, inv_vs, accumulate, s);
+        default: return apf64_launch<32>(Vin, S, Vout, V64, ld, n, kpad, Xt, dm, inv_vs, accumulate, s);
+        }
+    case 1: return ap_split_launch<float>(1, Vin, S, Vout, V64, ld, n, k, kpad, inv, Xt, dm, inv_vs, P, accumulate, ns, s);
+    case 2: return ap_split_launch<__bf16>(2, Vin, S, Vout, V64, ld, n, k, kpad, inv, Xt, dm, inv_vs, P, accumulate, ns, s);
+    case 3: return ap_split_launch<_Float16>(3, Vin, S, Vout, V64, ld, n, k, kpad, inv, Xt, dm, inv_vs, P, accumulate, ns, s);
     default: return hipErrorInvalidValue;
     }
 }

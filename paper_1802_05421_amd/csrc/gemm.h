@@ -1,129 +1,13 @@
 // LDS-tiled MFMA cores for C = A * B^T (both operands row-major along the
 // reduction index k), used by every dense contraction of the path.  Callers
 // supply padded operands (K a multiple of BK, tile rows inside the
-// allocation), so the cores have no bounds checks.  GemmCore stages through
-// registers (FP32 levels); DmaCore (16-bit levels) and Dma64Core (FP64) load
-// straight into LDS.
+// allocation), so the cores have no bounds checks.  Operands go straight from
+// global memory into LDS: RowCore for FP64 and FP32, DmaCore for 16-bit levels.
 #pragma once
 
 #include "common.h"
 
 namespace cdl {
-
-template <class Mf, int BM, int BN, int BK, int WM, int WN>
-struct GemmCore {
-    using T = typename Mf::T;
-    using Frag = typename Mf::Frag;
-    using AccV = typename Mf::AccV;
-    using MF = Mf;
-    static constexpr int TBM = BM, TBN = BN;
-    static constexpr int NT = WM * WN * 64;
-    static constexpr int CE = 16 / (int)sizeof(T);     // elements per 16-byte chunk
-    static constexpr int LDSK = BK + CE;                // padded LDS row (elements)
-    static constexpr int CPR = BK / CE;                 // chunks per tile row
-    static constexpr int A_CH = BM * CPR / NT;
-    static constexpr int B_CH = BN * CPR / NT;
-    static constexpr int WTM = BM / WM / Mf::M;
-    static constexpr int WTN = BN / WN / Mf::M;
-    static constexpr int STAGE = (BM + BN) * LDSK;     // elements per stage
-    static constexpr size_t SMEM = 2 * (size_t)STAGE * sizeof(T);
-    static_assert(BM * CPR % NT == 0 && BN * CPR % NT == 0, "tile/thread mismatch");
-    static_assert(WTM >= 1 && WTN >= 1, "wave tile too small");
-    static_assert(BK % Mf::KI == 0 && BK % CE == 0, "bad BK");
-
-    AccV acc[WTM][WTN];
-    uint4 ra[A_CH], rb[B_CH];
-
-    __device__ inline void zero() {
-#pragma unroll
-        for (int i = 0; i < WTM; ++i)
-#pragma unroll
-            for (int j = 0; j < WTN; ++j)
-#pragma unroll
-                for (int r = 0; r < Mf::R; ++r) acc[i][j][r] = 0;
-    }
-
-    __device__ inline void load_global(const T *A, int64_t lda, const T *B, int64_t ldb,
-                                       int64_t m0, int64_t n0, int64_t k0) {
-        const int tid = threadIdx.x;
-#pragma unroll
-        for (int c = 0; c < A_CH; ++c) {
-            int ch = tid + c * NT, row = ch / CPR, kc = ch % CPR;
-            ra[c] = *(const uint4 *)(A + (m0 + row) * lda + k0 + kc * CE);
-        }
-#pragma unroll
-        for (int c = 0; c < B_CH; ++c) {
-            int ch = tid + c * NT, row = ch / CPR, kc = ch % CPR;
-            rb[c] = *(const uint4 *)(B + (n0 + row) * ldb + k0 + kc * CE);
-        }
-    }
-
-    __device__ inline void store_lds(T *s) {
-        const int tid = threadIdx.x;
-        T *sA = s, *sB = s + BM * LDSK;
-#pragma unroll
-        for (int c = 0; c < A_CH; ++c) {
-            int ch = tid + c * NT, row = ch / CPR, kc = ch % CPR;
-            *(uint4 *)(sA + row * LDSK + kc * CE) = ra[c];
-        }
-#pragma unroll
-        for (int c = 0; c < B_CH; ++c) {
-            int ch = tid + c * NT, row = ch / CPR, kc = ch % CPR;
-            *(uint4 *)(sB + row * LDSK + kc * CE) = rb[c];
-        }
-    }
-
-    __device__ inline void compute(const T *s) {
-        const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-        const int wm = wid % WM, wn = wid / WM;
-        const T *sA = s + (wm * WTM * Mf::M) * LDSK;
-        const T *sB = s + BM * LDSK + (wn * WTN * Mf::M) * LDSK;
-        const int fr = lane % Mf::M, fk = Mf::E * (lane / Mf::M);
-#pragma unroll
-        for (int kk = 0; kk < BK; kk += Mf::KI) {
-            Frag a[WTM], b[WTN];
-#pragma unroll
-            for (int i = 0; i < WTM; ++i)
-                a[i] = *(const Frag *)(sA + (i * Mf::M + fr) * LDSK + kk + fk);
-#pragma unroll
-            for (int j = 0; j < WTN; ++j)
-                b[j] = *(const Frag *)(sB + (j * Mf::M + fr) * LDSK + kk + fk);
-#pragma unroll
-            for (int i = 0; i < WTM; ++i)
-#pragma unroll
-                for (int j = 0; j < WTN; ++j) acc[i][j] = Mf::mma(a[i], b[j], acc[i][j]);
-        }
-    }
-
-    // Full K loop with a two-stage LDS ring; K is a multiple of BK.
-    __device__ inline void run(const T *A, int64_t lda, const T *B, int64_t ldb,
-                               int64_t m0, int64_t n0, int64_t K, T *smem) {
-        zero();
-        const int nk = (int)(K / BK);
-        if (nk == 0) return;
-        load_global(A, lda, B, ldb, m0, n0, 0);
-        store_lds(smem);
-        __syncthreads();
-        for (int kt = 0; kt < nk; ++kt) {
-            T *cur = smem + (kt & 1) * STAGE;
-            T *nxt = smem + ((kt + 1) & 1) * STAGE;
-            if (kt + 1 < nk) load_global(A, lda, B, ldb, m0, n0, (int64_t)(kt + 1) * BK);
-            compute(cur);
-            if (kt + 1 < nk) store_lds(nxt);
-            __syncthreads();
-        }
-    }
-
-    // Tile-local coordinates of accumulator element (i, j, r) of this lane.
-    __device__ static inline int row_of(int i, int r) {
-        const int lane = threadIdx.x & 63, wm = (threadIdx.x >> 6) % WM;
-        return wm * WTM * Mf::M + i * Mf::M + Mf::crow(lane, r);
-    }
-    __device__ static inline int col_of(int j) {
-        const int lane = threadIdx.x & 63, wn = (threadIdx.x >> 6) / WM;
-        return wn * WTN * Mf::M + j * Mf::M + Mf::ccol(lane);
-    }
-};
 
 // Stage the BM x BN tile of values f(row, col, acc) (tile-local row, col) of
 // type O in LDS (row stride BN + 16/sizeof(O)), then copy it to global
@@ -409,55 +293,74 @@ struct DmaCore {
 };
 
 // ---------------------------------------------------------------------------
-// FP64 core fed by direct global->LDS loads, for every FP64 contraction
-// (distance Gram, score Gram, residual and panel products, FP64 levels).
-// An FP64 MFMA holds its matrix pipe for 64 cycles, so neither LDS nor L2
-// bandwidth bounds a tile; what costs time is every cycle in which all waves
-// of a SIMD wait at once: the register-staged core stored the next k-tile and
-// met a barrier after its last MFMA (MFMA pipes 74-84 % busy).  Here the loads
-// go straight into LDS, the fragments of k-step q + 1 are read while the MFMAs
-// of k-step q run, and the barrier lies before the last k-step's MFMAs, whose
-// fragments are already in registers, so the next k-tile's first fragments
-// arrive under them.
+// FP64 and FP32 core fed by direct global->LDS loads, for every contraction of
+// those types (distance Gram, score Gram, residual and panel products, FP64 and
+// FP32 levels).  One of their MFMAs holds its matrix pipe for 64 cycles, so
+// neither LDS nor L2 bandwidth bounds a tile; what costs time is every cycle in
+// which all waves of a SIMD wait at once: a register-staged core stored the
+// next k-tile and met a barrier after its last MFMA (FP64 matrix pipes 74-84 %
+// busy).  Here the fragments of k-group q + 1 are read while the MFMAs of group
+// q run, and the barrier lies before the last group's MFMAs, whose fragments
+// are already in registers, so the next k-tile's first fragments arrive under
+// them.
 //
-// Rows of 16 doubles (128 bytes) with the 16-byte chunks XOR-swizzled by
-// (row >> 1) & 7: the 16 rows x 2 k that a half-wave reads cover the 64 banks
-// once.  NS: LDS stages (2 for the large tiles, whose k-tile takes
-// microseconds; 3 where a k-tile is nearer the load latency).  The k order of
-// every sum is that of GemmCore, so the results are the same bits for every
-// tile shape.
+// LDS rows of 128 bytes (16 doubles, 32 floats) with the 16-byte chunks
+// XOR-swizzled by (row >> 1) & 7.  A k-tile is four groups of 32 bytes of every
+// row; of group q, lane l reads chunk 2 q + (l >> 5) of row l % M: for FP64 the
+// half (l >> 4) & 1 of it (one MFMA of 4 k), for FP32 the whole (four MFMAs of
+// two k each, k and k + 4 together).  Each phase of such a read covers the 64
+// banks once.  NS: LDS stages (2 for the large tiles, whose k-tile takes
+// microseconds; 3 or 4 where it is nearer the load latency).  The k order of
+// every sum is the same for every tile shape, so the results are the same bits.
 //
-// Measured at 256 x 16384 x 16384 (the residual product's shape) on one card,
-// in bursts: 256 x 128 tiles of 8 waves 1.86 ms (74 TFLOP/s), 128 x 128 of 8
-// waves 1.89, 128 x 64 of 4 waves 1.95, 64 x 64 of 4 waves 2.02; the
+// Measured at 256 x 16384 x 16384 in FP64 (the residual product's shape) on one
+// card, in bursts: 256 x 128 tiles of 8 waves 1.86 ms (74 TFLOP/s), 128 x 128 of
+// 8 waves 1.89, 128 x 64 of 4 waves 1.95, 64 x 64 of 4 waves 2.02; the
 // register-staged core 2.08-2.30.  Reading a symmetric B as B^T (k-tiles of 1 KB
 // rows), which had paid there, gives nothing here (1.88).
-template <int BM, int BN, int WM, int WN, int NS = 2>
-struct Dma64Core {
-    using T = double;
+template <typename T> struct RowMf;
+template <> struct RowMf<double> : MfmaF64 {
     using Frag = double;
-    using AccV = f64x4;
-    using MF = MfmaF64;
-    static constexpr int BK = 16;
+    static constexpr int STEPS = 1;
+    __device__ static inline int within(int lane) { return 8 * ((lane >> 4) & 1); }   // byte of the chunk
+    __device__ static inline AccV step(const Frag &a, const Frag &b, const AccV &c, int) {
+        return MfmaF64::mma(a, b, c);
+    }
+};
+template <> struct RowMf<float> : MfmaF32 {
+    using Frag = f32x4;
+    static constexpr int STEPS = 4;
+    __device__ static inline int within(int) { return 0; }
+    __device__ static inline AccV step(const Frag &a, const Frag &b, const AccV &c, int s) {
+        return MfmaF32::mma(a[s], b[s], c);
+    }
+};
+
+template <typename E, int BM, int BN, int WM, int WN, int NS = 2>
+struct RowCore {
+    using T = E;
+    using MF = RowMf<T>;
+    using Frag = typename MF::Frag;
+    using AccV = typename MF::AccV;
+    static constexpr int M = MF::M;
+    static constexpr int ROWB = 128;                 // bytes per LDS row
+    static constexpr int BK = ROWB / (int)sizeof(T);
     static constexpr int TBM = BM, TBN = BN;
     static constexpr int NW = WM * WN, NT = NW * 64;
-    static constexpr int ROWB = BK * 8;              // bytes per LDS row
     static constexpr int STAGE = (BM + BN) * ROWB;
     static constexpr size_t SMEM = (size_t)NS * STAGE;
-    static constexpr int WTM = BM / WM / 16, WTN = BN / WN / 16;
+    static constexpr int WTM = BM / WM / M, WTN = BN / WN / M;
     // 1 KB loads (8 rows) per wave and stage; where they do not divide evenly
     // the last block is loaded more than once (the same bytes to the same
     // place), so that every wave counts the same number
     static constexpr int AB = BM / 8, BB = BN / 8;
     static constexpr int AI = (AB + NW - 1) / NW, BI = (BB + NW - 1) / NW;
-    static constexpr int NKK = BK / 4;
-    static constexpr int NF = WTM + WTN, NM = WTM * WTN;
-    static_assert(WTM * WM * 16 == BM && WTN * WN * 16 == BN, "wave tiles of 16");
+    static constexpr int NKK = 4;
+    static constexpr int NF = WTM + WTN, NM = WTM * WTN * MF::STEPS;
+    static_assert(WTM * WM * M == BM && WTN * WN * M == BN, "whole wave tiles");
     static_assert(WTM >= 1 && WTN >= 1 && NS >= 2, "tile shape");
 
     AccV acc[WTM][WTN];
-
-    __device__ static inline int swz(int c, int row) { return c ^ ((row >> 1) & 7); }
 
     // Loads of the k-tile starting at element k0 into the LDS stage at byte
     // offset `stage`.
@@ -470,7 +373,7 @@ struct Dma64Core {
             if (AB % NW) blk = blk < AB ? blk : AB - 1;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
                 ra, (lds_void *)(uintptr_t)(stage + blk * 1024), 16, blk & 1 ? va1 : va0,
-                (uint32_t)(((int64_t)(blk * 8) * lda + k0) * 8), 0, 0);
+                (uint32_t)(((int64_t)(blk * 8) * lda + k0) * (int)sizeof(T)), 0, 0);
         }
 #pragma unroll
         for (int q = 0; q < BI; ++q) {
@@ -478,32 +381,34 @@ struct Dma64Core {
             if (BB % NW) blk = blk < BB ? blk : BB - 1;
             __builtin_amdgcn_raw_ptr_buffer_load_lds(
                 rb, (lds_void *)(uintptr_t)(stage + BM * ROWB + blk * 1024), 16, blk & 1 ? vb1 : vb0,
-                (uint32_t)(((int64_t)(blk * 8) * ldb + k0) * 8), 0, 0);
+                (uint32_t)(((int64_t)(blk * 8) * ldb + k0) * (int)sizeof(T)), 0, 0);
         }
     }
 
-    __device__ inline void load_frags(const char *s, int kk, Frag *f) {
+    __device__ inline void load_frags(const char *s, int q, Frag *f) {
         const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
         const int wm = wid % WM, wn = wid / WM;
-        const int k = kk + (lane >> 4), r16 = lane & 15;
         const char *sA = s, *sB = s + BM * ROWB;
+        const int c = 2 * q + (lane >> 5), in = MF::within(lane);
 #pragma unroll
         for (int i = 0; i < WTM; ++i) {
-            const int row = (wm * WTM + i) * 16 + r16;
-            f[i] = *(const double *)(sA + row * ROWB + 16 * swz(k >> 1, row) + 8 * (k & 1));
+            const int row = (wm * WTM + i) * M + lane % M;
+            f[i] = *(const Frag *)(sA + row * ROWB + 16 * (c ^ ((row >> 1) & 7)) + in);
         }
 #pragma unroll
         for (int j = 0; j < WTN; ++j) {
-            const int row = (wn * WTN + j) * 16 + r16;
-            f[WTM + j] = *(const double *)(sB + row * ROWB + 16 * swz(k >> 1, row) + 8 * (k & 1));
+            const int row = (wn * WTN + j) * M + lane % M;
+            f[WTM + j] = *(const Frag *)(sB + row * ROWB + 16 * (c ^ ((row >> 1) & 7)) + in);
         }
     }
 
     __device__ inline void mmas(const Frag *f) {
 #pragma unroll
-        for (int i = 0; i < WTM; ++i)
+        for (int s = 0; s < MF::STEPS; ++s)
 #pragma unroll
-            for (int j = 0; j < WTN; ++j) acc[i][j] = MF::mma(f[i], f[WTM + j], acc[i][j]);
+            for (int i = 0; i < WTM; ++i)
+#pragma unroll
+                for (int j = 0; j < WTN; ++j) acc[i][j] = MF::step(f[i], f[WTM + j], acc[i][j], s);
     }
 
     template <int I = 0> __device__ static inline void interleave() {
@@ -524,10 +429,10 @@ struct Dma64Core {
                 for (int r = 0; r < MF::R; ++r) acc[i][j][r] = -acc[i][j][r];
     }
 
-    // Full K loop (K a multiple of 16; rows m0.. and n0.. inside the
+    // Full K loop (K a multiple of BK; rows m0.. and n0.. inside the
     // allocations).  smem holds SMEM bytes and is free again on return.
     // DIFF: the second half of the k range minus the first (the sums are
-    // negated half way, which is exact; K a multiple of 32).
+    // negated half way, which is exact; K a multiple of 2 BK).
     template <bool DIFF = false>
     __device__ inline void run(const T *A, int64_t lda, const T *B, int64_t ldb, int64_t m0,
                                int64_t n0, int64_t K, T *smem_t) {
@@ -543,14 +448,14 @@ struct Dma64Core {
         const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const uint32_t s0 = (uint32_t)(uintptr_t)(lds_void *)smem;
         __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(A + m0 * lda), 0, (int)(BM * lda * 8), 0x00020000);
+            (void *)(A + m0 * lda), 0, (int)(BM * lda * (int)sizeof(T)), 0x00020000);
         __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(B + n0 * ldb), 0, (int)(BN * ldb * 8), 0x00020000);
+            (void *)(B + n0 * ldb), 0, (int)(BN * ldb * (int)sizeof(T)), 0x00020000);
         // this lane's offset within a block of 8 rows: even and odd blocks
         const int rl = (threadIdx.x & 63) >> 3, sl = threadIdx.x & 7;
         const uint32_t c0 = 16 * (sl ^ (rl >> 1)), c1 = 16 * (sl ^ ((rl >> 1) + 4));
-        const uint32_t va0 = (uint32_t)(rl * lda * 8) + c0, va1 = (uint32_t)(rl * lda * 8) + c1;
-        const uint32_t vb0 = (uint32_t)(rl * ldb * 8) + c0, vb1 = (uint32_t)(rl * ldb * 8) + c1;
+        const uint32_t oa = (uint32_t)(rl * lda * (int)sizeof(T)), ob = (uint32_t)(rl * ldb * (int)sizeof(T));
+        const uint32_t va0 = oa + c0, va1 = oa + c1, vb0 = ob + c0, vb1 = ob + c1;
         // the first NS stages, then wait for stage 0
 #pragma unroll
         for (int p = 0; p < NS; ++p)
@@ -567,7 +472,7 @@ struct Dma64Core {
             if (DIFF && 2 * kt == nk) negate();
 #pragma unroll
             for (int q = 0; q < NKK - 1; ++q) {
-                load_frags(sc, (q + 1) * 4, f[(q + 1) & 1]);
+                load_frags(sc, q + 1, f[(q + 1) & 1]);
                 mmas(f[q & 1]);
                 interleave();
             }
@@ -589,7 +494,7 @@ struct Dma64Core {
         if (DIFF && nk == 2) negate();
 #pragma unroll
         for (int q = 0; q < NKK - 1; ++q) {
-            load_frags(sc, (q + 1) * 4, f[(q + 1) & 1]);
+            load_frags(sc, q + 1, f[(q + 1) & 1]);
             mmas(f[q & 1]);
             interleave();
         }
@@ -600,12 +505,14 @@ struct Dma64Core {
 
     __device__ static inline int row_of(int i, int r) {
         const int lane = threadIdx.x & 63, wm = (threadIdx.x >> 6) % WM;
-        return (wm * WTM + i) * 16 + MF::crow(lane, r);
+        return (wm * WTM + i) * M + MF::crow(lane, r);
     }
     __device__ static inline int col_of(int j) {
         const int lane = threadIdx.x & 63, wn = (threadIdx.x >> 6) / WM;
-        return (wn * WTN + j) * 16 + MF::ccol(lane);
+        return (wn * WTN + j) * M + MF::ccol(lane);
     }
 };
+
+template <int BM, int BN, int WM, int WN, int NS = 2> using Dma64Core = RowCore<double, BM, BN, WM, WN, NS>;
 
 } // namespace cdl

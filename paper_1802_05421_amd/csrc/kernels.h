@@ -124,7 +124,11 @@ float level_scale(int prec, int64_t n);   // storage scale of FP16 levels (1 oth
 hipError_t launch_normalize(int prec, const double *W, int64_t ld, int64_t n,
                             const double *dmn, const double *u, int lazy, void *S0,
                             double *fro_part, double *fro64_part, hipStream_t s);
-int square_tiles(int prec, int64_t ld);   // number of partial norms written
+// Tile of a squaring (of P levels in one launch), and the partial norms that
+// a tile size, or the tile of one level, writes.
+int square_tile_size(int prec, int P, const int64_t *ld);
+int square_tiles(int tile, int64_t ld);
+int square_tiles_of(int prec, int64_t ld);
 // Level 0 from a row panel of W (rows [row0, row0 + rows), full rows): the
 // values of launch_normalize; per-row sums of squares (rounded, exact) into
 // fro_part[q], fro64_part[q].
@@ -148,18 +152,15 @@ hipError_t launch_chain_product(int prec, const void *Q, const void *L, void *C,
 // inv_vs != nullptr marks the last level: X += dm * V * (*inv_vs).  P is the
 // split-K partial buffer (nsplit x kpad x ld floats; unused for FP64).
 hipError_t launch_apply(int prec, const void *Vin, const void *S, void *Vout, double *V64,
-                        int64_t ld, int64_t n, int64_t kpad, double *Xt, const double *dm,
-                        const double *inv_vs, float *P, int accumulate, int nsplit,
-                        hipStream_t s);
-// The split-K product of one application alone (partials into P), for timing.
-hipError_t launch_apply_gemm(int prec, const void *Vin, const void *S, int64_t ld, int64_t n,
-                             int64_t kpad, int nsplit, float *P, hipStream_t s);
+                        int64_t ld, int64_t n, int64_t k, int64_t kpad, double *Xt, const double *dm,
+                        const double *inv_vs, float *P, int accumulate, int nsplit, hipStream_t s);
 // V64 += T64, Vout = V64 rounded, last level: X += dm * V64 * (*inv_vs).
 hipError_t launch_axpy_v(int prec, const double *T64, int64_t ld, int64_t kpad, double *V64,
                          void *Vout, double *Xt, const double *dm, const double *inv_vs,
                          hipStream_t s);
 // Split-K count of the chain application (choices as for residual_splits).
-int apply_splits(int prec, int64_t ld, int64_t kpad, int64_t n, int choice);
+int apply_splits(int prec, int64_t ld, int64_t kpad, int64_t n, int64_t k, int choice);
+int apply_splits_max(int prec, int64_t ld, int64_t kpad, int64_t n);   // of every choice and k
 
 // ---- solve ------------------------------------------------------------------
 hipError_t launch_rhs(const double *W, int64_t ld, int64_t n, const int32_t *gid, int64_t k,

@@ -184,3 +184,34 @@ def test_non_finite_series_is_reported(cdl, n, bad):
     X[n // 3, 5] = bad
     with pytest.raises(cdl.CdlError):
         cdl.build_graph(dev(X))
+
+
+# FP32 and FP64 levels are squared in tiles of 128, 64 or (FP64, one tile row)
+# 32 by their count, and applied in tiles by the live 32-column groups, the
+# column padding and n.  A level is the product of its predecessor with itself:
+# a sum of nonnegative products rounded at most ld + 2 times.  A depth of 8
+# leaves rho^256 < 1e-11 on these graphs (kappa < 10) and a sum's rounding, at
+# most 8 ld 2^-24 < 1e-3 in FP32, of an application, so four corrections reach
+# 1e-12; a missing or misplaced tile would leave its nodes uncorrected.
+@pytest.mark.parametrize("prec", ["fp32", "fp64"])
+@pytest.mark.parametrize("n,k", [(2, 1), (200, 32), (256, 33), (300, 70), (520, 112), (1000, 160),
+                                 (1300, 96), (1800, 260), (700, 512)])
+def test_levels_and_applications_of_every_tile_shape(cdl, prec, n, k):
+    X = np.random.default_rng(n + k).standard_normal((n, 24))
+    o = oracle.build_graph(X, sigma=6.0)
+    want = oracle.solve_embedding(o["W"], oracle.rhs(o["W"], k, SEED))
+    print("level case n=%d k=%d %s" % (n, k, prec), flush=True)
+    g = cdl.build_graph(dev(X), sigma=6.0)
+    ch = cdl.build_chain(g, prec=prec, depth=8, depth_max=8, lazy=n == 2)
+    eps = 2.0 ** (-24 if prec == "fp32" else -53)
+    for l in (0, 3):
+        A, B = (host(cdl.level(ch, q)).astype(np.float64) for q in (l, l + 1))
+        ref = A @ A
+        assert np.abs(B - ref).max() <= (cdl.ld(n) + 2) * eps * np.abs(ref).max()
+        np.testing.assert_array_equal(B, B.T)
+    cdl.set_solve_depth(8)   # all eight, also where fewer would do
+    try:
+        Z, info = cdl.solve_embedding(g, ch, k, SEED, tol=1e-12, max_iter=4)
+    finally:
+        cdl.set_solve_depth(0)
+    assert info.converged and rel(host(Z), want) <= 1e-10
