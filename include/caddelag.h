@@ -300,6 +300,13 @@ cdl_status cdl_k_rp(int64_t n, double eps_rp, int64_t *k);
  *   scale   host output.
  * Errors: CDL_E_ARG for n < 1, an invalid prec or a NULL scale. */
 cdl_status cdl_level_scale(int64_t n, cdl_prec prec, double *scale);
+/* Number of ids that two ascending id lists share: the length of the scores of
+ * consecutive snapshots (cdl_score_sequence).  Host memory, no device work.
+ *   gid0, gid1   host, n0 and n1 strictly increasing ids.
+ *   count        host output.
+ * Errors: CDL_E_ARG for a negative length or a NULL pointer. */
+cdl_status cdl_common_nodes(int64_t n0, const int32_t *gid0, int64_t n1, const int32_t *gid1,
+                            int64_t *count);
 /* Plain device-to-device copy on the context's stream (one 16-byte
  * nontemporal load and store per lane over a grid that covers the buffer):
  * the reference stream against which the hot kernels' HBM traffic and

@@ -101,6 +101,7 @@ def load():
         "cdl_autotune_entries": (C.c_int32, []),
         "cdl_ld": (i64, [i64]),
         "cdl_k_rp": (I, [i64, d, C.POINTER(i64)]),
+        "cdl_common_nodes": (I, [i64, P, i64, P, C.POINTER(i64)]),
         "cdl_level_scale": (I, [i64, I, C.POINTER(d)]),
         "cdl_device_copy": (I, [P, P, P, sz]),
         "cdl_matrix_bytes": (sz, [i64, I]),

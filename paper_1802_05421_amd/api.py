@@ -591,10 +591,13 @@ def score_sequence(Xs: Sequence[torch.Tensor], gids: Sequence[torch.Tensor], p: 
         Fs, tops = out
         tops = [t._base if t._base is not None else t for t in tops]
     else:
-        Fs, tops = [], []
+        # sizes of the common node sets (sets of Python integers took 0.3 ms a
+        # pair of 5000 nodes, more than the pair's kernels)
+        Fs, tops, count = [], [], C.c_int64()
         for t in range(n_snap - 1):
-            a = set(gid_host[t].tolist())
-            m = sum(1 for v in gid_host[t + 1].tolist() if v in a)
+            a, b = gid_host[t], gid_host[t + 1]
+            _check(_lib().cdl_common_nodes(a.numel(), _ptr(a), b.numel(), _ptr(b), C.byref(count)))
+            m = count.value
             Fs.append(torch.empty(m, dtype=torch.float64, device=dev))
             tops.append(torch.empty(max(1, min(p.top_k, m)), dtype=torch.int32, device=dev))
     Fp = (C.c_void_p * (n_snap - 1))(*[f.data_ptr() for f in Fs])

@@ -828,6 +828,20 @@ cdl_status cdl_device_copy(cdl_ctx *ctx, const void *src, void *dst, size_t byte
     return CDL_OK;
 }
 
+cdl_status cdl_common_nodes(int64_t n0, const int32_t *gid0, int64_t n1, const int32_t *gid1,
+                            int64_t *count) {
+    if (!gid0 || !gid1 || !count || n0 < 0 || n1 < 0) return CDL_E_ARG;
+    int64_t i = 0, j = 0, c = 0;
+    while (i < n0 && j < n1) {
+        const int32_t a = gid0[i], b = gid1[j];
+        c += a == b;
+        i += a <= b;
+        j += b <= a;
+    }
+    *count = c;
+    return CDL_OK;
+}
+
 cdl_status cdl_level_scale(int64_t n, cdl_prec prec, double *scale) {
     if (!scale || n < 1 || !valid_prec(prec)) return CDL_E_ARG;
     *scale = (double)level_scale(prec, n);
@@ -1779,17 +1793,25 @@ SeqPlan seq_plan(int32_t n_snap, const cdl_snapshot *sn) {
     return p;
 }
 
-// Common nodes of snapshots y and x (ascending global id): row indices.
+// Common nodes of snapshots y and x (ascending global id): row indices.  The
+// steps of the merge are arithmetic: which list goes on is a coin toss on random
+// subsets, and a wrong guess costs more than the step.
 void common_maps(const cdl_snapshot &y, const cdl_snapshot &x, std::vector<int32_t> &m0,
                  std::vector<int32_t> &m1) {
-    m0.clear();
-    m1.clear();
-    int64_t i = 0, j = 0;
+    const int64_t most = std::min(y.n, x.n);
+    m0.resize(most);
+    m1.resize(most);
+    int64_t i = 0, j = 0, c = 0;
     while (i < y.n && j < x.n) {
-        if (y.gid_host[i] == x.gid_host[j]) { m0.push_back((int32_t)i); m1.push_back((int32_t)j); ++i; ++j; }
-        else if (y.gid_host[i] < x.gid_host[j]) ++i;
-        else ++j;
+        const int32_t a = y.gid_host[i], b = x.gid_host[j];
+        m0[c] = (int32_t)i;   // (c < most: every match moves both on)
+        m1[c] = (int32_t)j;
+        c += a == b;
+        i += a <= b;
+        j += b <= a;
     }
+    m0.resize(c);
+    m1.resize(c);
 }
 
 // Chain with a fixed number of levels, no host reads.
