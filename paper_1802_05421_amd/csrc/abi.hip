@@ -126,31 +126,47 @@ struct HostRead {
     size_t bytes;
 };
 
-// Enqueues the reads on `stream` into the context's pinned staging buffer,
-// synchronises that stream and copies the results out (every read in one
-// round trip).
-hipError_t read_to_host(cdl_ctx *c, hipStream_t stream, std::initializer_list<HostRead> reads) {
-    size_t total = 0;
-    for (const auto &r : reads) total += (r.bytes + 255) / 256 * 256;
-    if (total > c->stage_bytes) {
-        // no copy into the old buffer is pending: every read ends with a sync
+// The context's pinned staging buffer with room for `bytes`: its host address,
+// and in *dev its device address, which kernels write results through.
+hipError_t stage_reserve(cdl_ctx *c, hipStream_t stream, size_t bytes, char **dev) {
+    if (bytes > c->stage_bytes) {
+        // an earlier call that failed half way may have left writes pending
+        hipError_t e = hipStreamSynchronize(stream);
+        if (e == hipSuccess && stream != c->stream) e = hipStreamSynchronize(c->stream);
+        if (e != hipSuccess) return e;
         if (c->stage) (void)hipHostFree(c->stage);
         c->stage = nullptr;
         c->stage_bytes = 0;
         void *p = nullptr;
-        const hipError_t e = hipHostMalloc(&p, total, hipHostMallocDefault);
+        e = hipHostMalloc(&p, bytes, hipHostMallocDefault);
         if (e != hipSuccess) return e;
         c->stage = p;
-        c->stage_bytes = total;
+        c->stage_bytes = bytes;
     }
+    return hipHostGetDevicePointer((void **)dev, c->stage, 0);
+}
+
+// Copies the reads (4-byte multiples) through the staging buffer with one
+// launch on `stream`, synchronises that stream and hands the results out.
+hipError_t read_to_host(cdl_ctx *c, hipStream_t stream, std::initializer_list<HostRead> reads) {
+    size_t total = 0;
+    for (const auto &r : reads) total += (r.bytes + 255) / 256 * 256;
+    hipError_t e = hipSetDevice(c->device);
+    if (e != hipSuccess) return e;
+    char *dev = nullptr;
+    e = stage_reserve(c, stream, total, &dev);
+    if (e != hipSuccess) return e;
+    cdl::ReadOut out{};
     size_t off = 0;
     for (const auto &r : reads) {
-        const hipError_t e = hipMemcpyAsync((char *)c->stage + off, r.src, r.bytes,
-                                            hipMemcpyDeviceToHost, stream);
-        if (e != hipSuccess) return e;
+        if (out.count == 4 || r.bytes % 4) return hipErrorInvalidValue;
+        out.src[out.count] = (const uint32_t *)r.src;
+        out.dst[out.count] = (uint32_t *)(dev + off);
+        out.words[out.count++] = r.bytes / 4;
         off += (r.bytes + 255) / 256 * 256;
     }
-    const hipError_t e = hipStreamSynchronize(stream);
+    e = cdl::launch_read_out(out, stream);
+    if (e == hipSuccess) e = hipStreamSynchronize(stream);
     if (e != hipSuccess) return e;
     off = 0;
     for (const auto &r : reads) {
@@ -934,17 +950,17 @@ cdl_status cdl_graph_from_weights(cdl_ctx *ctx, const double *Win, int64_t n, in
 // ---- chain ---------------------------------------------------------------------
 
 // One squaring (or dense-chain product when A != B) with the tuned tile
-// variant; a tuning context times every variant first (each leaves a
-// complete, correct output).
+// variant, its norm partials into `fro`; a tuning context times every variant
+// first (each leaves a complete, correct output).
 static cdl_status square_step(cdl_ctx *ctx, int prec, const void *A, const void *B, void *C,
-                              int64_t ld, int64_t n, const ChainBuf &c, bool allow_tune) {
+                              int64_t ld, int64_t n, const ChainBuf &c, double *fro, bool allow_tune) {
     const bool product = A != B;
     bool tune = false;
     const int nv = square_variants(prec);
     int v = pick_choice(ctx, "square", prec, ld, 0, nv, allow_tune, &tune);
     auto go = [&](int var) {
-        return product ? launch_chain_product(prec, A, B, C, ld, n, c.fro, c.tail, var, ctx->stream)
-                       : launch_square(prec, A, C, ld, n, c.fro, c.tail, var, ctx->stream);
+        return product ? launch_chain_product(prec, A, B, C, ld, n, fro, c.tail, var, ctx->stream)
+                       : launch_square(prec, A, C, ld, n, fro, c.tail, var, ctx->stream);
     };
     if (tune) {
         std::vector<double> ms(nv);
@@ -956,11 +972,17 @@ static cdl_status square_step(cdl_ctx *ctx, int prec, const void *A, const void 
     return CDL_OK;
 }
 
-static double host_sum(const std::vector<double> &v) {
+static double host_sum(const double *v, int count) {
     double s = 0.0;
-    for (double x : v) s += x;
+    for (int q = 0; q < count; ++q) s += v[q];
     return s;
 }
+static double host_sum(const std::vector<double> &v) { return host_sum(v.data(), (int)v.size()); }
+
+// Up to this many norm partials a level's workgroups write straight into pinned
+// memory (8 bytes each over the bus, behind the kernel's own work); more are
+// gathered by a launch of their own.
+constexpr int kHostNorms = 2112;
 
 cdl_status cdl_build_chain(cdl_ctx *ctx, const double *W, const double *deg, const double *stats,
                            int64_t n, cdl_prec prec, int depth, int depth_max, double chain_eps,
@@ -986,13 +1008,54 @@ cdl_status cdl_build_chain(cdl_ctx *ctx, const double *W, const double *deg, con
     info->prec = prec;
 
     { Timed t_(ctx, "chain_prep"); HIPCHK(launch_chain_prep(deg, stats, n, ld, info->lazy, c.dmn, c.dm, c.u, s)); }
-    { Timed t_(ctx, "normalize"); HIPCHK(launch_normalize(prec, W, ld, n, c.dmn, c.u, info->lazy, c.levels, c.fro, c.fro64, s)); }
-    const int nst = sym_tiles64(ld);
-    std::vector<double> part(nst), part64(nst);
-    HIPCHK(read_to_host(ctx, s, {{part.data(), c.fro, nst * sizeof(double)},
-                              {part64.data(), c.fro64, nst * sizeof(double)}}));
-    info->rho_bound = std::sqrt(host_sum(part64));
-    double f = std::sqrt(host_sum(part));
+    // The partial norms of level 0 (rounded and exact) and of every further
+    // level, each in its own place of the staging buffer.  A chain of given depth
+    // is built without a look at them (at n = 256 a read after each of its levels
+    // took three times as long as the squarings), then they are checked in order.
+    const int nst = sym_tiles64(ld), ntl = square_tiles_of(prec, ld);
+    const size_t place0 = ((size_t)nst * sizeof(double) + 255) / 256 * 256;
+    const size_t place = ((size_t)ntl * sizeof(double) + 255) / 256 * 256;
+    const int ahead = depth > 0 ? depth - 1 : 1;   // levels in flight at once
+    char *stage_dev = nullptr;
+    HIPCHK(stage_reserve(ctx, s, 2 * place0 + (size_t)ahead * place, &stage_dev));
+    const char *stage = (const char *)ctx->stage;
+    // copies partials that the device kept to their place
+    auto gather = [&](double *p0, int n0, size_t off0, double *p1, size_t off1) {
+        cdl::ReadOut out{};
+        out.count = p1 ? 2 : 1;
+        out.src[0] = (const uint32_t *)p0;
+        out.dst[0] = (uint32_t *)(stage_dev + off0);
+        out.src[1] = (const uint32_t *)p1;
+        out.dst[1] = (uint32_t *)(stage_dev + off1);
+        out.words[0] = out.words[1] = (size_t)n0 * 2;
+        return cdl::launch_read_out(out, s);
+    };
+    {
+        const bool host = nst <= kHostNorms;
+        { Timed t_(ctx, "normalize"); HIPCHK(launch_normalize(prec, W, ld, n, c.dmn, c.u, info->lazy, c.levels,
+                                       host ? (double *)stage_dev : c.fro,
+                                       host ? (double *)(stage_dev + place0) : c.fro64, s)); }
+        if (!host) HIPCHK(gather(c.fro, nst, 0, c.fro64, place0));
+    }
+    // level l + 1 from level l, its norms into place `q`
+    auto next_level = [&](int l, int q) -> cdl_status {
+        const size_t off = 2 * place0 + (size_t)q * place;
+        const bool host = ntl <= kHostNorms;
+        const cdl_status sq = square_step(ctx, prec, c.levels + c.level_bytes * l, c.levels + c.level_bytes * l,
+                                          c.levels + c.level_bytes * (l + 1), ld, n, c,
+                                          host ? (double *)(stage_dev + off) : c.fro, true);
+        if (sq != CDL_OK) return sq;
+        if (!host) HIPCHK(gather(c.fro, ntl, off, nullptr, 0));
+        return CDL_OK;
+    };
+    if (depth > 0)
+        for (int l = 0; l + 1 < depth; ++l) {
+            const cdl_status sq = next_level(l, l);
+            if (sq != CDL_OK) return sq;
+        }
+    HIPCHK(hipStreamSynchronize(s));
+    info->rho_bound = std::sqrt(host_sum((const double *)(stage + place0), nst));
+    double f = std::sqrt(host_sum((const double *)stage, nst));
     if (!std::isfinite(f)) return fail(ctx, CDL_E_NONFINITE, "non-finite chain level");
     info->fro[0] = f;
     int l = 0;
@@ -1007,16 +1070,15 @@ cdl_status cdl_build_chain(cdl_ctx *ctx, const double *W, const double *deg, con
         else
             more = l + 1 < depth_max && model_wants_square(prec, l, f, rho, cm);
         if (!more) break;
-        const int ntl = square_tiles_of(prec, ld);
-        {
-            const cdl_status sq = square_step(ctx, prec, c.levels + c.level_bytes * l, c.levels + c.level_bytes * l,
-                                              c.levels + c.level_bytes * (l + 1), ld, n, c, true);
+        int q = l;
+        if (depth == 0) {
+            q = 0;
+            const cdl_status sq = next_level(l, q);
             if (sq != CDL_OK) return sq;
+            HIPCHK(hipStreamSynchronize(s));
         }
-        part.resize(ntl);
-        HIPCHK(read_to_host(ctx, s, {{part.data(), c.fro, ntl * sizeof(double)}}));
         const double fprev = f;
-        f = std::sqrt(host_sum(part));
+        f = std::sqrt(host_sum((const double *)(stage + 2 * place0 + (size_t)q * place), ntl));
         if (!std::isfinite(f)) return fail(ctx, CDL_E_NONFINITE, "non-finite chain level");
         ++l;
         info->fro[l] = f;
@@ -1063,11 +1125,11 @@ cdl_status cdl_chain_densify(cdl_ctx *ctx, int64_t n, void *chain, size_t chain_
         // Q_{j} = Q_{j-1} + L_j + Q_{j-1} L_j alternating between the spare
         // slot and slot 0 (free once L_0 is consumed); Q ends in slot 0.
         char *spare = slot(d), *cur = spare;
-        cdl_status st = square_step(ctx, info->prec, slot(0), slot(1), spare, ld, n, c, true);
+        cdl_status st = square_step(ctx, info->prec, slot(0), slot(1), spare, ld, n, c, c.fro, true);
         if (st != CDL_OK) return st;
         for (int j = 2; j < d; ++j) {
             char *dst = cur == spare ? slot(0) : spare;
-            if ((st = square_step(ctx, info->prec, cur, slot(j), dst, ld, n, c, true)) != CDL_OK) return st;
+            if ((st = square_step(ctx, info->prec, cur, slot(j), dst, ld, n, c, c.fro, true)) != CDL_OK) return st;
             cur = dst;
         }
         if (cur != slot(0)) HIPCHK(hipMemcpyAsync(slot(0), cur, c.level_bytes, hipMemcpyDeviceToDevice, s));
@@ -1269,7 +1331,6 @@ cdl_status cdl_solve_embedding(cdl_ctx *ctx, const double *W, const double *deg,
     HIPCHK(hipSetDevice(ctx->device));
     if (info) std::memset(info, 0, sizeof(*info));
 
-    { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w.Yt, panel * sizeof(double), s)); }
     { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w.Xt, panel * sizeof(double), s)); }
     { Timed t_(ctx, "rhs"); HIPCHK(launch_rhs(W, ld, n, gid, k, kp, seed, w.Yt, s)); }
     return solve_from_rhs(ctx, stored_product(ctx, W, n, k), deg, stats, n, c, ci, k, solver, tol,
@@ -1301,9 +1362,7 @@ cdl_status cdl_solve_embedding_pair(cdl_ctx *ctx, const double *W0, const double
     HIPCHK(hipSetDevice(ctx->device));
     if (info0) std::memset(info0, 0, sizeof(*info0));
     if (info1) std::memset(info1, 0, sizeof(*info1));
-    { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w0.Yt, pbytes, s)); }
     { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w0.Xt, pbytes, s)); }
-    { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w1.Yt, pbytes, s)); }
     { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w1.Xt, pbytes, s)); }
     { Timed t_(ctx, "rhs_pair"); HIPCHK(launch_rhs_pair(W0, W1, ld, n, gid, k, kp, seed, w0.Yt, w1.Yt, s)); }
     st = solve_from_rhs(ctx, stored_product(ctx, W0, n, k), deg0, stats0, n, c0, ci0, k, solver,
@@ -1452,7 +1511,6 @@ cdl_status cdl_stream_embedding(cdl_ctx *ctx, const double *X, int64_t n, int64_
     }
 
     // Weights, degrees and right-hand sides: one sweep over the full row panels.
-    { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w.Yt, kbytes, s)); }
     { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w.Xt, kbytes, s)); }
     for (int64_t r0 = 0; r0 < n; r0 += P) {
         const int64_t rows = std::min(P, ld - r0);
@@ -1825,7 +1883,7 @@ cdl_status chain_enqueue(cdl_ctx *ctx, const double *W, const double *deg, const
     { Timed t_(ctx, "normalize"); HIPCHK(launch_normalize(prec, W, ld, n, c.dmn, c.u, 0, c.levels, c.fro, c.fro64, s)); }
     for (int l = 0; l + 1 < depth; ++l) {
         const cdl_status sq = square_step(ctx, prec, c.levels + c.level_bytes * l, c.levels + c.level_bytes * l,
-                                          c.levels + c.level_bytes * (l + 1), ld, n, c, false);
+                                          c.levels + c.level_bytes * (l + 1), ld, n, c, c.fro, false);
         if (sq != CDL_OK) return sq;
     }
     return CDL_OK;
@@ -1847,7 +1905,6 @@ cdl_status solve_enqueue_fixed(cdl_ctx *ctx, const double *W, const double *deg,
     hipStream_t s = ctx->stream;
     const int nparts = residual_parts(ld), ntiles = residual_tiles(ld, kp);
     const bool scaled = prec == 3;
-    { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w.Yt, panel * sizeof(double), s)); }
     { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w.Xt, panel * sizeof(double), s)); }
     { Timed t_(ctx, "rhs"); HIPCHK(launch_rhs(W, ld, n, gid, k, kp, seed, w.Yt, s)); }
     { Timed t_(ctx, "residual_init"); HIPCHK(launch_residual_k(prec, w.Xt, W, w.Yt, deg, c.dm, ld, n, kp, k, 1, (double *)w.part, w.Rt, w.V64, w.Vlo[0], w.npart, w.mpart, s)); }
@@ -2278,7 +2335,6 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
             double *stats = (double *)(base + L.st[t]);
             const SolveWs &w = solves[t];
             const size_t panel = (size_t)kp * hs[t].ld * sizeof(double);
-            { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w.Yt, panel, es)); }
             { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w.Xt, panel, es)); }
             { Timed t_(ctx, "rhs"); HIPCHK(launch_rhs(W, hs[t].ld, x.n, x.gid, k, kp, q->seed, w.Yt, es)); }
             HIPCHK(hipMemcpyAsync(status + (size_t)t * CDL_GRAPH_STATS, stats,

@@ -88,6 +88,24 @@ hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s) {
     return hipGetLastError();
 }
 
+// Small results into pinned host memory, every read in one launch: a copy
+// command waits about 10 us before it starts, this kernel as long as any other.
+__global__ __launch_bounds__(256) void k_read_out(ReadOut r) {
+    const uint32_t *src = r.src[blockIdx.y];
+    uint32_t *dst = r.dst[blockIdx.y];
+    for (size_t q = (size_t)blockIdx.x * 256 + threadIdx.x; q < r.words[blockIdx.y]; q += (size_t)gridDim.x * 256)
+        dst[q] = src[q];
+}
+
+hipError_t launch_read_out(const ReadOut &r, hipStream_t s) {
+    size_t most = 0;
+    for (int q = 0; q < r.count; ++q) most = r.words[q] > most ? r.words[q] : most;
+    if (most == 0) return hipSuccess;
+    const unsigned blocks = (unsigned)((most + 1023) / 1024 < 64 ? (most + 1023) / 1024 : 64);
+    hipLaunchKernelGGL(k_read_out, dim3(blocks, (unsigned)r.count), dim3(256), 0, s, r);
+    return hipGetLastError();
+}
+
 // Plain device copy: one 16-byte element per lane, a grid covering the whole
 // buffer (consecutive workgroups stream consecutive memory), nontemporal
 // loads and stores (the data is touched once).  The reference stream for HBM

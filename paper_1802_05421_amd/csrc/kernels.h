@@ -35,6 +35,14 @@ struct SelectState {                // device scratch of the exact median select
 int64_t select_buffer_keys(int64_t n);
 
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s);
+// Device ranges to copy, in 4-byte words, and their places in pinned memory.
+struct ReadOut {
+    const uint32_t *src[4];
+    uint32_t *dst[4];
+    size_t words[4];
+    int count;
+};
+hipError_t launch_read_out(const ReadOut &r, hipStream_t s);
 // dst = src (bytes a multiple of 16, both 16-byte aligned, no overlap).
 hipError_t launch_copy16(const void *src, void *dst, size_t bytes, hipStream_t s);
 // flags (may be NULL): bit 0 set for a non-finite series; ticket (may be NULL):
