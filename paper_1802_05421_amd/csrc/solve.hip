@@ -77,11 +77,45 @@ static uint64_t splitmix64_mix_host(uint64_t z) {
     return z ^ (z >> 31);
 }
 
-__device__ __forceinline__ uint64_t rhs_sign_word(uint64_t mseed, uint64_t key) {
-    uint64_t z = mseed ^ key;
-    z = (z ^ (z >> 30)) * 0xbf58476d1ce4e5b9ull;
-    z = (z ^ (z >> 27)) * 0x94d049bb133111ebull;
-    return z ^ (z >> 31);
+// The sign word of ids a < b (below 2^20): the mixer of mseed ^ block << 40 |
+// a << 20 | b.  Its first shift-and-xor is linear over the bits, so the part of
+// seed and block comes in as `base`, that xor done (base ^ base >> 30), and the
+// ids' part needs no 64-bit shift; the other shifts are v_alignbit pairs.  Most
+// of the word's time goes to its six quarter-rate multiplies.
+__device__ __forceinline__ void rhs_sign_word(uint64_t base, uint32_t a, uint32_t b, uint32_t &lo,
+                                              uint32_t &hi) {
+    lo = (uint32_t)base ^ ((a << 20) | b) ^ (a >> 10);
+    hi = (uint32_t)(base >> 32) ^ (a >> 12);
+    uint64_t z = ((uint64_t)hi << 32 | lo) * 0xbf58476d1ce4e5b9ull;
+    lo = (uint32_t)z ^ __builtin_amdgcn_alignbit((uint32_t)(z >> 32), (uint32_t)z, 27);
+    hi = (uint32_t)(z >> 32) ^ ((uint32_t)(z >> 32) >> 27);
+    z = ((uint64_t)hi << 32 | lo) * 0x94d049bb133111ebull;
+    lo = (uint32_t)z ^ __builtin_amdgcn_alignbit((uint32_t)(z >> 32), (uint32_t)z, 31);
+    hi = (uint32_t)(z >> 32) ^ ((uint32_t)(z >> 32) >> 31);
+}
+
+// Correctly rounded square root of 2^-767 <= x < infinity: the steps that also
+// follow the scaling of smaller numbers, without it.
+__device__ __forceinline__ double rhs_sqrt(double x) {
+    const double y = __builtin_amdgcn_rsq(x);
+    double g = x * y, h = 0.5 * y;
+    const double r = fma(-h, g, 0.5);
+    g = fma(g, r, g);
+    h = fma(h, r, h);
+    g = fma(fma(-g, g, x), h, g);
+    return fma(fma(-g, g, x), h, g);
+}
+
+// Largest value of a wave, in lane 63.
+__device__ __forceinline__ uint32_t rhs_wave_max(uint32_t x) {
+    auto step = [&](uint32_t y) { x = x > y ? x : y; };
+    step(__builtin_amdgcn_update_dpp(0, x, 0x111, 0xf, 0xf, false));   // row_shr 1, 2, 4, 8
+    step(__builtin_amdgcn_update_dpp(0, x, 0x112, 0xf, 0xf, false));
+    step(__builtin_amdgcn_update_dpp(0, x, 0x114, 0xf, 0xf, false));
+    step(__builtin_amdgcn_update_dpp(0, x, 0x118, 0xf, 0xf, false));
+    step(__builtin_amdgcn_update_dpp(0, x, 0x142, 0xa, 0xf, false));   // row_bcast 15
+    step(__builtin_amdgcn_update_dpp(0, x, 0x143, 0xc, 0xf, false));   // row_bcast 31
+    return x;
 }
 
 // out[b] = byte b of a0, a1, a2, a3 (in that order from the low byte): a
@@ -137,7 +171,7 @@ __global__ __launch_bounds__(256 * NB) void k_rhs(const double *W0, const double
     // roles
     const int q = t & 255, bw = t >> 8;                        // sign words
     const bool word_on = bgrp * NB + bw < nb;
-    const uint64_t kbeta = (uint64_t)(bgrp * NB + bw) << 40;
+    const uint64_t sbeta = mseed ^ (uint64_t)(bgrp * NB + bw) << 40, base = sbeta ^ sbeta >> 30;
     const int mb = wv >> 2, kq = wv & 3, m16 = lane & 15, g4 = lane >> 4;   // MFMAs
     const bool mfma_on = bgrp * NB + mb < nb;
     const int sn = S == 2 ? (m16 >> 3) : 0;                     // snapshot of this lane's slot
@@ -184,21 +218,33 @@ __global__ __launch_bounds__(256 * NB) void k_rhs(const double *W0, const double
         for (int d = 0; d < DG; ++d) {
             const int gx = t + d * NT;
             if (gx >= S * 256) continue;
+            // zero, tiny, non-finite or negative weights (the diagonal, ends of
+            // rows) take the general root, for the whole wave
+            uint32_t most = 0;
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const uint32_t x = (uint32_t)__double2hiint(vn[d][e]) - 0x10000000u;
+                most = most > x ? most : x;
+            }
+            if (__any(most >= 0x6ff00000u)) {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) vn[d][e] = sqrt(vn[d][e]);
+            } else {
+#pragma unroll
+                for (int e = 0; e < 4; ++e) vn[d][e] = rhs_sqrt(vn[d][e]);
+            }
             uint32_t h = 0;
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                const double r = sqrt(vn[d][e]);
-                vn[d][e] = gi > gn[e] ? -r : r;
-                tp[d] += vn[d][e];
-                const uint32_t hv = (uint32_t)__double2hiint(r) & 0x7fffffffu;
+                const uint32_t hv = (uint32_t)__double2hiint(vn[d][e]) & 0x7fffffffu;
                 h = h > hv ? h : hv;
+                // negative if the neighbour's id is the lower one
+                vn[d][e] = __hiloint2double((int)(hv | ((gn[e] - gi) & 0x80000000u)),
+                                            __double2loint(vn[d][e]));
+                tp[d] += vn[d][e];
             }
-#pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) {
-                const uint32_t x = (uint32_t)__shfl_xor((int)h, o);
-                h = h > x ? h : x;
-            }
-            if (lane == 0) wmax[slot][gx >> 6] = h;
+            h = rhs_wave_max(h);
+            if (lane == 63) wmax[slot][gx >> 6] = h;
         }
     };
 
@@ -274,17 +320,20 @@ __global__ __launch_bounds__(256 * NB) void k_rhs(const double *W0, const double
             const int gx = t + d * NT;
             if (gx >= S * 256) continue;
             const int s = gx >> 8;
-            const double Q = rhs_pow2(S == 2 && s ? qs[S - 1] : qs[0]);
+            // V = rint(2^q v) = xh 2^32 + rl, both read off the low bits of
+            // sums with 1.5 2^52 (non-finite roots leave meaningless digits in
+            // range; T carries them)
+            const int qd = S == 2 && s ? qs[S - 1] : qs[0];
+            const double Q = rhs_pow2(qd), Qh = rhs_pow2(qd - 32);
+            constexpr double kMagic = 0x1.8p52;
             uint32_t lo[4], hi[4];
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                // (clamped, so that non-finite weights convert without
-                // overflow; T carries them)
-                const double x = fmin(fmax(rint(vn[d][e] * Q), -0x1p54), 0x1p54);
-                const double xh = floor(x * 0x1p-32);
-                const double xl = fma(xh, -0x1p32, x);
-                const uint64_t u = (((uint64_t)(uint32_t)(int)xh << 32) | (uint32_t)xl) +
-                                   0x80808080808080ull;
+                const double tm = fma(vn[d][e], Qh, kMagic);
+                const double um = fma(tm - kMagic, -0x1p32, vn[d][e] * Q) + kMagic;
+                const uint64_t u = (uint64_t)__double_as_longlong(um) +
+                                   ((uint64_t)(uint32_t)__double2loint(tm) << 32) +
+                                   (0x0080808080808080ull - 0x4338000000000000ull);
                 lo[e] = (uint32_t)u ^ 0x80808080u;
                 hi[e] = (uint32_t)(u >> 32) ^ 0x808080u;
             }
@@ -303,9 +352,7 @@ __global__ __launch_bounds__(256 * NB) void k_rhs(const double *W0, const double
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 const uint32_t a = gi < gn[e] ? gi : gn[e], b = gi < gn[e] ? gn[e] : gi;
-                const uint64_t wd = rhs_sign_word(mseed, kbeta | ((uint64_t)a << 20) | b);
-                lo[e] = (uint32_t)wd;
-                hi[e] = (uint32_t)(wd >> 32);
+                rhs_sign_word(base, a, b, lo[e], hi[e]);
             }
             uint32_t o[4];
             unsigned char *pp = planes + (buf * NB + bw) * 8 * kRhsPitch + 4 * q;
