@@ -290,34 +290,36 @@ static int row_square_tile(int prec, int P, const int64_t *ld) {
 template <typename T, int NW, int SH> constexpr size_t sq_smem() {
     using C = typename SqCfg<T, NW, SH>::Core;
     constexpr int TL = SqCfg<T, NW, SH>::TILE;
-    constexpr size_t stage = (size_t)TL * (TL + 16 / sizeof(T)) * sizeof(T);
+    constexpr size_t stage = sizeof(T) == 2 ? (size_t)TL * TL * 2 : (size_t)TL * (TL + 16 / sizeof(T)) * sizeof(T);
     return C::SMEM > stage ? C::SMEM : stage;
 }
 
 // Epilogue of one output tile of C = A B (tile rows m0.., columns n0..):
-// scale back by inv_scale, with add != 0 also add A + B (the next factor of
+// scale back by inv_scale, with ADD also add A + B (the next factor of
 // the dense chain product, below), round to T, store the tile and (off the
 // diagonal) its mirror, and write the squared Frobenius norm of the stored
 // values (doubled off the diagonal) to *fro_out.  A and B are polynomials in
 // the same symmetric matrix, so they commute and C is symmetric.
-template <typename T, class Core>
+template <typename T, bool ADD, class Core>
 __device__ inline void square_epilogue(Core &g, const T *A, const T *B, T *S2, int64_t ld,
                                        int64_t m0, int64_t n0, bool mirror, float inv_scale,
-                                       int add, double *fro_out, T *smem, double *red) {
+                                       double *fro_out, T *smem, double *red) {
     using Acc = typename Core::MF::Acc;
     double fro = 0.0;
     auto f = [&](int r, int c, Acc acc) -> T {
         Acc v = acc * (Acc)inv_scale;
-        if (add) {
-            const int64_t o = (m0 + r) * ld + n0 + c;
-            v += (Acc)tod<T>(A[o]) + (Acc)tod<T>(B[o]);
+        if constexpr (ADD) {
+            // (32-bit lane offsets from the tile's corner)
+            const uint32_t o = (uint32_t)r * (uint32_t)ld + (uint32_t)c;
+            v += (Acc)tod<T>((A + m0 * ld + n0)[o]) + (Acc)tod<T>((B + m0 * ld + n0)[o]);
         }
-        T t = (T)v;
-        double tv = tod<T>(t) * (double)inv_scale;
-        fro += tv * tv;
+        const T t = (T)v;
+        const double tv = tod<T>(t);
+        fro = fma(tv, tv, fro);   // (the scale is a power of two: the sum takes it)
         return t;
     };
-    stage_and_store(g, smem, f, S2, ld, m0, n0, mirror);
+    if constexpr (sizeof(T) == 2) stage_and_store16(g, (char *)smem, f, S2, ld, m0, n0, mirror);
+    else stage_and_store(g, smem, f, S2, ld, m0, n0, mirror);
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) fro += __shfl_xor(fro, o);
     __syncthreads();
@@ -326,17 +328,17 @@ __device__ inline void square_epilogue(Core &g, const T *A, const T *B, T *S2, i
     if (threadIdx.x == 0) {
         double t = 0.0;
         for (int q = 0; q < Core::NT / 64; ++q) t += red[q];
-        *fro_out = (mirror ? 2.0 : 1.0) * t;
+        *fro_out = (mirror ? 2.0 : 1.0) * t * ((double)inv_scale * (double)inv_scale);
     }
 }
 
 // C = A B over the upper tiles with logical ids [0, count) (count = all
 // tiles, or the full rounds of 256 workgroups when the last round is split
-// over k below).  The squaring is A = B = S, add = 0.
+// over k below).  The squaring is A = B = S, ADD = false.
 // Upper tile `id` of C = A B and its epilogue (one workgroup).
-template <typename T, int NW, int SH>
+template <typename T, int NW, int SH, bool ADD>
 __device__ __forceinline__ void square_tile(const T *A, const T *B, T *S2, int64_t ld, int64_t kend, int nt,
-                                   int id, float inv_scale, int add, double *fro_part,
+                                   int id, float inv_scale, double *fro_part,
                                    char *smem_raw, double *red) {
     using Core = typename SqCfg<T, NW, SH>::Core;
     constexpr int TL = SqCfg<T, NW, SH>::TILE;
@@ -345,20 +347,20 @@ __device__ __forceinline__ void square_tile(const T *A, const T *B, T *S2, int64
     const int64_t m0 = (int64_t)I * TL, n0 = (int64_t)J * TL;
     Core g;
     g.run(A, ld, B, ld, m0, n0, kend, (T *)smem_raw);
-    square_epilogue<T>(g, A, B, S2, ld, m0, n0, I != J, inv_scale, add, fro_part + id,
-                       (T *)smem_raw, red);
+    square_epilogue<T, ADD>(g, A, B, S2, ld, m0, n0, I != J, inv_scale, fro_part + id,
+                            (T *)smem_raw, red);
 }
 
-template <typename T, int NW, int SH>
+template <typename T, int NW, int SH, bool ADD>
 __global__ __launch_bounds__((SqCfg<T, NW, SH>::Core::NT)) void k_square(const T *A, const T *B, T *S2, int64_t ld,
                                                 int64_t kend, int nt, int count, float inv_scale,
-                                                int add, double *fro_part) {
+                                                double *fro_part) {
     using Core = typename SqCfg<T, NW, SH>::Core;
     constexpr int TL = SqCfg<T, NW, SH>::TILE;
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
     __shared__ double red[Core::NT / 64];
     const int id = TL == 256 ? round_remap(blockIdx.x, count) : xcd_remap(blockIdx.x, count);
-    square_tile<T, NW, SH>(A, B, S2, ld, kend, nt, id, inv_scale, add, fro_part, smem_raw, red);
+    square_tile<T, NW, SH, ADD>(A, B, S2, ld, kend, nt, id, inv_scale, fro_part, smem_raw, red);
 }
 
 // Level `level` squared into level + 1 for every snapshot of a sequence:
@@ -375,8 +377,10 @@ __global__ __launch_bounds__((SqCfg<T, 8, SH>::Core::NT)) void k_square_grouped(
     const BatchSnap &d = snaps[p];
     const T *A = (const T *)(d.levels + d.level_bytes * level);
     T *C = (T *)(d.levels + d.level_bytes * (level + 1));
-    square_tile<T, 8, SH>(A, A, C, d.ld, (d.n + 63) / 64 * 64, (int)(d.ld / TL), blockIdx.x - prefix[p],
-                      d.inv_scale, 0, d.fro, smem_raw, red);
+    const int count = prefix[p + 1] - prefix[p], b = blockIdx.x - prefix[p];
+    const int id = TL == 256 ? round_remap(b, count) : xcd_remap(b, count);
+    square_tile<T, 8, SH, false>(A, A, C, d.ld, (d.n + 63) / 64 * 64, (int)(d.ld / TL), id,
+                             d.inv_scale, d.fro, smem_raw, red);
 }
 
 // The tiles of the last, partial round of workgroups (logical ids
@@ -407,20 +411,37 @@ __global__ __launch_bounds__((SqCfg<T, NW, SH>::Core::NT)) void k_square_part(co
             for (int r = 0; r < Core::MF::R; ++r, ++e) Pb[(size_t)e * Core::NT + threadIdx.x] = g.acc[i][j][r];
 }
 
-// One workgroup per tile of the split round: the partial tiles summed in
-// split order into the accumulator layout of the core, then the epilogue.
-// Loads go out sixteen elements by four splits at a time, so a thread has
-// 64 in flight instead of one round trip per element and split.
-template <typename T, int NW, int SH>
+// The partial tiles of the split round summed in split order into each tile's
+// first.  On its own because a tile's epilogue needs the whole tile, and 16 to
+// 32 workgroups that also read every partial took 94 us for 16 tiles of 16 splits
+// (64 MB); spread over the chip the sum takes 12 and the epilogue 12.
+__global__ __launch_bounds__(256) void k_square_sum(float *P, int splits, int64_t tile4) {
+    f32x4 *Pt = (f32x4 *)P + (int64_t)blockIdx.y * splits * tile4;
+    const int64_t o = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    constexpr int SB = 8;   // loads in flight
+    for (int sp0 = 0; sp0 < splits; sp0 += SB) {
+        f32x4 w[SB];
+#pragma unroll
+        for (int u = 0; u < SB; ++u)
+            if (sp0 + u < splits) w[u] = Pt[(int64_t)(sp0 + u) * tile4 + o];
+#pragma unroll
+        for (int u = 0; u < SB; ++u)
+            if (sp0 + u < splits) v += w[u];
+    }
+    Pt[o] = v;
+}
+
+// One workgroup per tile of the split round: the summed tile in the accumulator
+// layout of the core (in the first of the tile's partials), then the epilogue.
+template <typename T, int NW, int SH, bool ADD>
 __global__ __launch_bounds__((SqCfg<T, NW, SH>::Core::NT)) void k_square_tail(const T *A, const T *B, T *S2,
                                                      int64_t ld, int nt, int first, int splits,
-                                                     const float *P, float inv_scale, int add,
+                                                     const float *P, float inv_scale,
                                                      double *fro_part) {
     using Core = typename SqCfg<T, NW, SH>::Core;
     constexpr int TL = SqCfg<T, NW, SH>::TILE;
     constexpr int R = Core::MF::R, E = Core::WTM * Core::WTN * R;
-    constexpr int G = 16, SB = 4;   // elements per group, splits per batch
-    static_assert(E % G == 0, "accumulator count");
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
     __shared__ double red[Core::NT / 64];
     const int id = first + blockIdx.x;
@@ -429,32 +450,10 @@ __global__ __launch_bounds__((SqCfg<T, NW, SH>::Core::NT)) void k_square_tail(co
     Core g;
     const float *Pt = P + (size_t)blockIdx.x * splits * TL * TL + threadIdx.x;
 #pragma unroll
-    for (int e0 = 0; e0 < E; e0 += G) {
-        float v[G];
-#pragma unroll
-        for (int q = 0; q < G; ++q) v[q] = 0.f;
-        for (int sp0 = 0; sp0 < splits; sp0 += SB) {
-            float w[SB][G];
-#pragma unroll
-            for (int u = 0; u < SB; ++u)
-                if (sp0 + u < splits)
-#pragma unroll
-                    for (int q = 0; q < G; ++q)
-                        w[u][q] = Pt[(size_t)(sp0 + u) * TL * TL + (size_t)(e0 + q) * Core::NT];
-#pragma unroll
-            for (int u = 0; u < SB; ++u)
-                if (sp0 + u < splits)
-#pragma unroll
-                    for (int q = 0; q < G; ++q) v[q] += w[u][q];
-        }
-#pragma unroll
-        for (int q = 0; q < G; ++q) {
-            const int e = e0 + q, r = e % R, ij = e / R;
-            g.acc[ij / Core::WTN][ij % Core::WTN][r] = v[q];
-        }
-    }
-    square_epilogue<T>(g, A, B, S2, ld, (int64_t)I * TL, (int64_t)J * TL, I != J, inv_scale, add,
-                       fro_part + id, (T *)smem_raw, red);
+    for (int e = 0; e < E; ++e)
+        g.acc[e / R / Core::WTN][e / R % Core::WTN][e % R] = Pt[(size_t)e * Core::NT];
+    square_epilogue<T, ADD>(g, A, B, S2, ld, (int64_t)I * TL, (int64_t)J * TL, I != J, inv_scale,
+                            fro_part + id, (T *)smem_raw, red);
 }
 
 int square_tile_size(int prec, int P, const int64_t *ld) {
@@ -502,23 +501,23 @@ size_t square_tail_bytes(int prec, int64_t ld, int64_t n) {
     return (size_t)p.rem * p.splits * 256 * 256 * sizeof(float);
 }
 
-template <typename T, int NW, int SH>
+template <typename T, int NW, int SH, bool ADD>
 static hipError_t sq_launch(const void *A, const void *B, void *S2, int64_t ld, int64_t n,
-                            float inv_scale, int add, double *fro_part, float *tail, hipStream_t s) {
+                            float inv_scale, double *fro_part, float *tail, hipStream_t s) {
     using Cfg = SqCfg<T, NW, SH>;
     constexpr int TL = Cfg::TILE;
     constexpr size_t smem = sq_smem<T, NW, SH>();
     constexpr bool k16 = sizeof(T) == 2;   // only 16-bit squarings split their last round
     static bool attr = false;
     if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_square<T, NW, SH>,
+        hipError_t e = hipFuncSetAttribute((const void *)k_square<T, NW, SH, ADD>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         if constexpr (k16) {
             if (e == hipSuccess)
                 e = hipFuncSetAttribute((const void *)k_square_part<T, NW, SH>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
             if (e == hipSuccess)
-                e = hipFuncSetAttribute((const void *)k_square_tail<T, NW, SH>,
+                e = hipFuncSetAttribute((const void *)k_square_tail<T, NW, SH, ADD>,
                                         hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
         }
         if (e != hipSuccess) return e;
@@ -530,8 +529,8 @@ static hipError_t sq_launch(const void *A, const void *B, void *S2, int64_t ld, 
     SqPlan p = square_plan(prec, ld, n);
     if (!tail) p = SqPlan{p.total, p.total, 0, 0, p.kend, 0};
     constexpr int NT = Cfg::Core::NT;
-    hipLaunchKernelGGL((k_square<T, NW, SH>), dim3(p.full), dim3(NT), smem, s, (const T *)A,
-                       (const T *)B, (T *)S2, ld, p.kend, nt, p.full, inv_scale, add, fro_part);
+    hipLaunchKernelGGL((k_square<T, NW, SH, ADD>), dim3(p.full), dim3(NT), smem, s, (const T *)A,
+                       (const T *)B, (T *)S2, ld, p.kend, nt, p.full, inv_scale, fro_part);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess || p.rem == 0) return e;
     if constexpr (k16) {
@@ -539,9 +538,14 @@ static hipError_t sq_launch(const void *A, const void *B, void *S2, int64_t ld, 
                            (const T *)A, (const T *)B, ld, p.kend, p.ks, nt, p.full, p.splits, tail);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((k_square_tail<T, NW, SH>), dim3(p.rem), dim3(NT), smem, s, (const T *)A,
+        constexpr int64_t tile4 = (int64_t)TL * TL / 4;
+        hipLaunchKernelGGL(k_square_sum, dim3((unsigned)(tile4 / 256), (unsigned)p.rem), dim3(256), 0, s,
+                           tail, p.splits, tile4);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((k_square_tail<T, NW, SH, ADD>), dim3(p.rem), dim3(NT), smem, s, (const T *)A,
                            (const T *)B, (T *)S2, ld, nt, p.full, p.splits, (const float *)tail,
-                           inv_scale, add, fro_part);
+                           inv_scale, fro_part);
         return hipGetLastError();
     }
     return hipErrorInvalidValue;
@@ -551,42 +555,43 @@ int square_variants(int prec) { return prec == 2 || prec == 3 ? 6 : 1; }
 
 // (the 4-wave core with 16 x 16 x 32 MFMAs needs more than its 512
 // registers and is not a candidate)
-template <typename T>
+template <typename T, bool ADD>
 static hipError_t sq_dispatch16(const void *A, const void *B, void *C, int64_t ld, int64_t n,
-                                float inv, int add, double *fro_part, float *t, int variant,
+                                float inv, double *fro_part, float *t, int variant,
                                 hipStream_t s) {
     switch (variant >> 1) {
-    case 0: return sq_launch<T, 8, 32>(A, B, C, ld, n, inv, add, fro_part, t, s);
-    case 1: return sq_launch<T, 4, 32>(A, B, C, ld, n, inv, add, fro_part, t, s);
-    default: return sq_launch<T, 8, 16>(A, B, C, ld, n, inv, add, fro_part, t, s);
+    case 0: return sq_launch<T, 8, 32, ADD>(A, B, C, ld, n, inv, fro_part, t, s);
+    case 1: return sq_launch<T, 4, 32, ADD>(A, B, C, ld, n, inv, fro_part, t, s);
+    default: return sq_launch<T, 8, 16, ADD>(A, B, C, ld, n, inv, fro_part, t, s);
     }
 }
 
 // variant (16-bit levels, 0..5): bit 0 set = no k-split of the last round;
 // variant >> 1 = 0: 8-wave core, 32 x 32 x 16 MFMAs; 1: 4-wave core, 32 x 32
 // x 16; 2: 8-wave core, 16 x 16 x 32.  Other types have one variant.
+template <bool ADD>
 static hipError_t sq_dispatch(int prec, const void *A, const void *B, void *C, int64_t ld, int64_t n,
-                              int add, double *fro_part, float *tail, int variant, hipStream_t s) {
+                              double *fro_part, float *tail, int variant, hipStream_t s) {
     const float inv = 1.0f / level_scale(prec, n);
     float *t = (variant & 1) ? nullptr : tail;
     const int tile = square_tile_size(prec, 1, &ld);
     switch (prec) {
     case 0:
-        return tile == 128 ? sq_launch<double, 8, 128>(A, B, C, ld, n, inv, add, fro_part, nullptr, s)
-             : tile == 64  ? sq_launch<double, 8, 64>(A, B, C, ld, n, inv, add, fro_part, nullptr, s)
-                           : sq_launch<double, 8, 32>(A, B, C, ld, n, inv, add, fro_part, nullptr, s);
+        return tile == 128 ? sq_launch<double, 8, 128, ADD>(A, B, C, ld, n, inv, fro_part, nullptr, s)
+             : tile == 64  ? sq_launch<double, 8, 64, ADD>(A, B, C, ld, n, inv, fro_part, nullptr, s)
+                           : sq_launch<double, 8, 32, ADD>(A, B, C, ld, n, inv, fro_part, nullptr, s);
     case 1:
-        return tile == 128 ? sq_launch<float, 8, 128>(A, B, C, ld, n, inv, add, fro_part, nullptr, s)
-                           : sq_launch<float, 8, 64>(A, B, C, ld, n, inv, add, fro_part, nullptr, s);
-    case 2: return sq_dispatch16<__bf16>(A, B, C, ld, n, inv, add, fro_part, t, variant, s);
-    case 3: return sq_dispatch16<_Float16>(A, B, C, ld, n, inv, add, fro_part, t, variant, s);
+        return tile == 128 ? sq_launch<float, 8, 128, ADD>(A, B, C, ld, n, inv, fro_part, nullptr, s)
+                           : sq_launch<float, 8, 64, ADD>(A, B, C, ld, n, inv, fro_part, nullptr, s);
+    case 2: return sq_dispatch16<__bf16, ADD>(A, B, C, ld, n, inv, fro_part, t, variant, s);
+    case 3: return sq_dispatch16<_Float16, ADD>(A, B, C, ld, n, inv, fro_part, t, variant, s);
     default: return hipErrorInvalidValue;
     }
 }
 
 hipError_t launch_square(int prec, const void *S, void *S2, int64_t ld, int64_t n,
                          double *fro_part, float *tail, int variant, hipStream_t s) {
-    return sq_dispatch(prec, S, S, S2, ld, n, 0, fro_part, tail, variant, s);
+    return sq_dispatch<false>(prec, S, S, S2, ld, n, fro_part, tail, variant, s);
 }
 
 // Inside a diagonal tile both triangles come out of the GEMM, and for A != B
@@ -612,7 +617,7 @@ static hipError_t sym_diag_launch(int prec, void *C, int64_t ld, hipStream_t s) 
 hipError_t launch_chain_product(int prec, const void *Q, const void *L, void *C, int64_t ld,
                                 int64_t n, double *fro_part, float *tail, int variant,
                                 hipStream_t s) {
-    hipError_t e = sq_dispatch(prec, Q, L, C, ld, n, 1, fro_part, tail, variant, s);
+    hipError_t e = sq_dispatch<true>(prec, Q, L, C, ld, n, fro_part, tail, variant, s);
     if (e != hipSuccess) return e;
     switch (prec) {
     case 0: return sym_diag_launch<double>(0, C, ld, s);

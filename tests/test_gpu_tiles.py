@@ -215,3 +215,30 @@ def test_levels_and_applications_of_every_tile_shape(cdl, prec, n, k):
     finally:
         cdl.set_solve_depth(0)
     assert info.converged and rel(host(Z), want) <= 1e-10
+
+
+# 16-bit levels go through 256 x 256 tiles whose rows and mirrored rows leave
+# through one transposed copy.  An element is a sum of products (exact in FP32)
+# rounded at most ld times in FP32 and once to its type; the dense product adds
+# the two factors first, and its lower triangle is the upper one's copy (rounded
+# factors do not quite commute).
+@pytest.mark.parametrize("prec", ["bf16", "fp16"])
+@pytest.mark.parametrize("n", [2, 255, 257, 900])
+def test_16bit_levels_and_dense_product(cdl, prec, n):
+    print("16-bit level case n=%d %s" % (n, prec), flush=True)
+    X = np.random.default_rng(n).standard_normal((n, 24))
+    g = cdl.build_graph(dev(X), sigma=4.0)
+    ch = cdl.build_chain(g, prec=prec, depth=2, depth_max=3, lazy=n == 2)
+    sc = cdl.level_scale(ch)
+    A, B = (host(cdl.level(ch, q).double()) / sc for q in (0, 1))
+    ulp, least = (2.0 ** -8, 0.0) if prec == "bf16" else (2.0 ** -11, 2.0 ** -25 / sc)
+    acc = (cdl.ld(n) + 3) * 2.0 ** -24
+    ref, mag = A @ A, np.abs(A) @ np.abs(A)
+    assert np.all(np.abs(B - ref) <= ulp * np.abs(ref) + 2 * acc * mag + least)
+    np.testing.assert_array_equal(B, B.T)
+    cdl.chain_densify(ch)
+    Q = host(cdl.level(ch, 0).double()) / sc
+    ref, mag = A + B + A @ B, np.abs(A) + np.abs(B) + np.abs(A) @ np.abs(B)
+    ref, mag = (np.triu(m) + np.triu(m, 1).T for m in (ref, mag))
+    assert np.all(np.abs(Q - ref) <= ulp * np.abs(ref) + 2 * acc * mag + least)
+    np.testing.assert_array_equal(Q, Q.T)
