@@ -187,7 +187,10 @@ template <> struct GramCfg<1> {
 constexpr int kBelowParts = 64, kBelowPitch = 16;
 static_assert(kBelowParts * kBelowPitch <= kSelCap, "counts must fit the candidates");
 // What a launch covers: the upper triangle of the whole matrix, the upper
-// triangle's part of a row panel, or every tile of a row panel.
+// triangle's part of a row panel, or a whole row panel: its upper part, whose
+// tiles in the panel's own square are also stored mirrored (the same bits; half
+// of a sweep's Gram where one panel holds every row, a fifth at n = 20000 with
+// panels of 8192), and the columns before that square.
 enum GramCover { kGramUpper, kGramPanelUpper, kGramPanelFull };
 
 // Workgroups of shape `shape` on rows [row0, row0 + rows) (multiples of 256).
@@ -195,7 +198,7 @@ static int64_t gram_wgs(int shape, GramCover cover, int64_t ld, int64_t row0, in
     if (shape == 0) return 2 * gram_panel_tiles(ld, row0, rows, cover == kGramPanelFull);
     const int64_t nt = ld / 64;
     if (cover == kGramUpper) return nt * (nt + 1) / 2;
-    return rows / 64 * (cover == kGramPanelFull ? nt : (ld - row0) / 64);
+    return rows / 64 * (cover == kGramPanelFull ? nt : (ld - row0) / 64);   // (some without a tile)
 }
 
 // The busiest CU's work in 64 x 64 tiles: the small tiles' rate is 0.8 of the
@@ -213,28 +216,35 @@ __device__ inline bool gram_place(int cover, int id, int64_t ld, int64_t row0, i
     int I, J;
     if (SHAPE == 0) {
         const int tile = id >> 1, half = id & 1, I0 = (int)(row0 / 256), pb = (int)(rows / 256);
-        const int ncol = (int)(ld / 128);
-        if (cover == kGramPanelFull) {
-            rect_tile<4>(tile, pb, ncol, I, J);
-            I += I0;
-        } else {
+        const int ncol = (int)(ld / 128), upper = pb * ncol - 2 * (I0 * pb + pb * (pb - 1) / 2);
+        if (tile < upper) {
             upper_band_tile<4>(tile, I0, pb, ncol, I, J);
+        } else {
+            rect_tile<4>(tile - upper, pb, 2 * I0, I, J);
+            I += I0;
         }
         m0 = (int64_t)I * 256 + 128 * half;
         n0 = (int64_t)J * 128;
-        return true;
+        // (the lower halves of a panel's 256-row diagonal tiles: their mirror)
+        return cover != kGramPanelFull || tile >= upper || n0 >= m0;
     }
     if (cover == kGramUpper) {
         sym_tile<8>(id, (int)(ld / 64), I, J);
-    } else {
-        const int64_t first = cover == kGramPanelFull ? 0 : row0;
-        rect_tile<8>(id, (int)(rows / 64), (int)((ld - first) / 64), I, J);
-        I += (int)(row0 / 64);
-        J += (int)(first / 64);
+        m0 = (int64_t)I * 64;
+        n0 = (int64_t)J * 64;
+        return true;
     }
+    const int pb = (int)(rows / 64), I0 = (int)(row0 / 64), right = (int)(ld / 64) - I0;
+    if (id < pb * right) {
+        rect_tile<8>(id, pb, right, I, J);
+        J += I0;
+    } else {
+        rect_tile<8>(id - pb * right, pb, I0, I, J);
+    }
+    I += I0;
     m0 = (int64_t)I * 64;
     n0 = (int64_t)J * 64;
-    return cover == kGramPanelFull || I <= J;
+    return id >= pb * right || I <= J;
 }
 
 // One tile.  Row i is stored at D2 + (i - row0) ld, so a row panel needs a
@@ -254,7 +264,8 @@ __device__ inline bool gram_place(int cover, int id, int64_t ld, int64_t row0, i
 // kExp: store the weights exp(-D2 / sigma^2) instead (zero on the diagonal and
 // outside n; sigma = wstats[1]), the expression of the separate exponential
 // kernels, so the values are the same bits.
-template <int SHAPE, bool kExp>
+// kPanel: a whole row panel (kGramPanelFull).
+template <int SHAPE, bool kExp, bool kPanel>
 __device__ __forceinline__ void gram_tile(const double *Xp, int64_t Tp, const double *sqn,
                                           int64_t n, int64_t ld, double *D2, int64_t row0,
                                           int64_t rows, int cover, int id, SelectState *st,
@@ -311,12 +322,27 @@ __device__ __forceinline__ void gram_tile(const double *Xp, int64_t Tp, const do
                 d = d < 0.0 ? 0.0 : d;
                 const bool pair = i < ni && j < ni && i != j;
                 d = pair ? d : 0.0;
-                if (!kExp) g.acc[a][b][rr] = pair && i < j ? d : NAN;
                 if (kExp) d = pair ? exp(-d / s2) : 0.0;
+                g.acc[a][b][rr] = kPanel || (pair && i < j) ? d : NAN;
                 row[c] = d;
             }
         }
         __builtin_amdgcn_sched_barrier(0);   // bounds the addresses and masks held at once
+    }
+    if (kPanel) {
+        // (four lanes make 32 consecutive bytes of the mirror, the four stores of a
+        // lane a line of it)
+        if (n0 > m0 && n0 < row0 + rows)
+#pragma unroll
+            for (int b = 0; b < Core::WTN; ++b) {
+                double *const row = out + (n0 + Core::col_of(b)) * ld + m0;
+#pragma unroll
+                for (int a = 0; a < Core::WTM; ++a)
+#pragma unroll
+                    for (int rr = 0; rr < R; ++rr) row[Core::row_of(a, rr)] = g.acc[a][b][rr];
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        return;
     }
     if (kExp || !st) return;
 
@@ -417,17 +443,17 @@ __device__ __forceinline__ void gram_tile(const double *Xp, int64_t Tp, const do
     }
 }
 
-template <int SHAPE, bool kExp>
+template <int SHAPE, bool kExp, bool kPanel>
 __global__ __launch_bounds__(GramCfg<SHAPE>::Core::NT, GramCfg<SHAPE>::WAVES) void k_gram_dist(
     const double *Xp, int64_t Tp, const double *sqn, int64_t n, int64_t ld, double *D2,
     int64_t row0, int64_t rows, int cover, SelectState *st, const double *wstats,
     unsigned long long *brbuf, int64_t brcap) {
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
-    gram_tile<SHAPE, kExp>(Xp, Tp, sqn, n, ld, D2, row0, rows, cover, xcd_remap(blockIdx.x, gridDim.x),
+    gram_tile<SHAPE, kExp, kPanel>(Xp, Tp, sqn, n, ld, D2, row0, rows, cover, xcd_remap(blockIdx.x, gridDim.x),
                            st, wstats, (double *)smem_raw, brbuf, brcap);
 }
 
-template <int SHAPE, bool kExp>
+template <int SHAPE, bool kExp, bool kPanel>
 static hipError_t gram_launch(const double *Xp, int64_t Tp, const double *sqn, int64_t n, int64_t ld,
                               double *D2, int64_t row0, int64_t rows, GramCover cover,
                               SelectState *st, const double *wstats, unsigned long long *brbuf,
@@ -435,7 +461,7 @@ static hipError_t gram_launch(const double *Xp, int64_t Tp, const double *sqn, i
     using Core = typename GramCfg<SHAPE>::Core;
     static bool attr = false;
     if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_gram_dist<SHAPE, kExp>,
+        hipError_t e = hipFuncSetAttribute((const void *)k_gram_dist<SHAPE, kExp, kPanel>,
                                            hipFuncAttributeMaxDynamicSharedMemorySize,
                                            (int)Core::SMEM);
         if (e != hipSuccess) return e;
@@ -443,7 +469,7 @@ static hipError_t gram_launch(const double *Xp, int64_t Tp, const double *sqn, i
     }
     const int64_t total = gram_wgs(SHAPE, cover, ld, row0, rows);
     if (total <= 0 || total > INT32_MAX) return hipErrorInvalidValue;
-    hipLaunchKernelGGL((k_gram_dist<SHAPE, kExp>), dim3((unsigned)total), dim3(Core::NT), Core::SMEM,
+    hipLaunchKernelGGL((k_gram_dist<SHAPE, kExp, kPanel>), dim3((unsigned)total), dim3(Core::NT), Core::SMEM,
                        s, Xp, Tp, sqn, n, ld, D2, row0, rows, (int)cover, st, wstats, brbuf, brcap);
     return hipGetLastError();
 }
@@ -453,13 +479,13 @@ hipError_t launch_gram_dist(const double *Xp, int64_t Tp, const double *sqn, int
                             int64_t brcap, hipStream_t s) {
     if (brbuf && !st) return hipErrorInvalidValue;
     if (gram_shape(kGramUpper, ld, 0, ld) == 1)
-        return gram_launch<1, false>(Xp, Tp, sqn, n, ld, D2, 0, ld, kGramUpper, st, nullptr, brbuf, brcap, s);
-    return gram_launch<0, false>(Xp, Tp, sqn, n, ld, D2, 0, ld, kGramUpper, st, nullptr, brbuf, brcap, s);
+        return gram_launch<1, false, false>(Xp, Tp, sqn, n, ld, D2, 0, ld, kGramUpper, st, nullptr, brbuf, brcap, s);
+    return gram_launch<0, false, false>(Xp, Tp, sqn, n, ld, D2, 0, ld, kGramUpper, st, nullptr, brbuf, brcap, s);
 }
 
 int64_t gram_panel_tiles(int64_t ld, int64_t row0, int64_t rows, bool full) {
     const int64_t ncol = ld / 128, I0 = row0 / 256, pb = rows / 256;
-    return full ? pb * ncol : pb * ncol - 2 * (I0 * pb + pb * (pb - 1) / 2);
+    return pb * ncol - 2 * (I0 * pb + pb * (pb - 1) / 2) + (full ? 2 * I0 * pb : 0);
 }
 
 hipError_t launch_gram_panel(const double *Xp, int64_t Tp, const double *sqn, int64_t n,
@@ -470,10 +496,13 @@ hipError_t launch_gram_panel(const double *Xp, int64_t Tp, const double *sqn, in
     const GramCover cover = full ? kGramPanelFull : kGramPanelUpper;
     const bool small = gram_shape(cover, ld, row0, rows) == 1;
     if (wstats)
-        return small ? gram_launch<1, true>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, wstats, nullptr, 0, s)
-                     : gram_launch<0, true>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, wstats, nullptr, 0, s);
-    return small ? gram_launch<1, false>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, nullptr, nullptr, 0, s)
-                 : gram_launch<0, false>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, nullptr, nullptr, 0, s);
+        return small ? gram_launch<1, true, true>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, wstats, nullptr, 0, s)
+                     : gram_launch<0, true, true>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, wstats, nullptr, 0, s);
+    if (full)
+        return small ? gram_launch<1, false, true>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, nullptr, nullptr, 0, s)
+                     : gram_launch<0, false, true>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, nullptr, nullptr, 0, s);
+    return small ? gram_launch<1, false, false>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, nullptr, nullptr, 0, s)
+                 : gram_launch<0, false, false>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, nullptr, nullptr, 0, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -1521,7 +1550,7 @@ __global__ __launch_bounds__(GramCfg<SHAPE>::Core::NT, GramCfg<SHAPE>::WAVES) vo
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
     const GroupSlot g = group_slot(prefix, P);
     const GraphSnap &d = snaps[g.p];
-    gram_tile<SHAPE, false>(d.Xp, d.Tp, d.sqn, d.n, d.ld, d.W, 0, d.ld, kGramUpper,
+    gram_tile<SHAPE, false, false>(d.Xp, d.Tp, d.sqn, d.n, d.ld, d.W, 0, d.ld, kGramUpper,
                             xcd_remap((int)g.b, (int)g.nb), select ? d.sel : nullptr,
                             (const double *)nullptr, (double *)smem_raw,
                             select && d.bracket ? d.buf : nullptr, d.cap);

@@ -242,3 +242,23 @@ def test_16bit_levels_and_dense_product(cdl, prec, n):
     ref, mag = (np.triu(m) + np.triu(m, 1).T for m in (ref, mag))
     assert np.all(np.abs(Q - ref) <= ulp * np.abs(ref) + 2 * acc * mag + least)
     np.testing.assert_array_equal(Q, Q.T)
+
+
+# A whole row panel computes the upper tiles of its own square once and stores
+# them mirrored: with one panel, panels whose square ends in the padding, and
+# either tile shape (a few tiles or many), the sweeps must see the stored path's
+# weights: degrees agree to the rounding of their sums, (n + 2) 2^-53, and Z, each
+# solved to a relative residual of 1e-12 with kappa below 10, to 2e-11.
+@pytest.mark.parametrize("n,panel", [(256, 256), (700, 256), (700, 512), (1300, 1536), (3000, 1024),
+                                     (5000, 5120)])
+def test_panels_mirror_their_own_square(cdl, n, panel):
+    print("panel case n=%d panel=%d" % (n, panel), flush=True)
+    X = np.random.default_rng(n).standard_normal((n, 24))
+    ref = cdl.build_graph(dev(X), sigma=6.0)
+    g, Z, info = cdl.stream_embedding(dev(X), 3, SEED, sigma=6.0, tol=1e-12, max_iter=60, panel_rows=panel)
+    assert info.converged
+    d0, d1 = host(ref.deg), host(g.deg)
+    assert np.abs(d1 - d0).max() <= (n + 2) * 2.0 ** -53 * d0.max()
+    ch = cdl.build_chain(ref, prec="fp32", depth_max=8)
+    Z0, info = cdl.solve_embedding(ref, ch, 3, SEED, tol=1e-12, max_iter=60)
+    assert info.converged and rel(host(Z), host(Z0)) <= 2e-11
