@@ -1016,6 +1016,87 @@ __global__ __launch_bounds__(256) void k_select_pass(const double *D2, int64_t l
     select_pass_pick(D2, ld, n, st, buf, cap, gathered, first, stats, blockIdx.x, gridDim.x);
 }
 
+// The whole selection from the bracket buffer by one workgroup of 1024 threads,
+// histogram and candidates in LDS: through the state in memory, as between
+// launches, two passes with their fences took 26 us at n = 256, this takes 9.
+__device__ __forceinline__ void select_buffer_alone(SelectState *st, const SelView &v,
+                                                    const unsigned long long *buf, double *stats,
+                                                    unsigned int *h, PickShared &sh) {
+    __shared__ unsigned long long s_prefix, s_rank;
+    __shared__ unsigned int s_left;
+    const int t = threadIdx.x;
+    const int64_t nk = (int64_t)st->nbuf;
+    unsigned long long prefix = v.prefix, rank = v.rank;
+    int64_t left = nk;   // keys under the prefix
+    int bits = v.bits, shift, width;
+    unsigned long long hi_mask;
+    while (bits < 64 && left > kSelFew) {
+        sel_digit(bits, shift, width, hi_mask);
+        ((uint4 *)h)[t] = make_uint4(0, 0, 0, 0);
+        __syncthreads();
+        for (int64_t q = t; q < nk; q += 1024) {
+            const unsigned long long key = buf[q];
+            if ((key & hi_mask) == prefix) atomicAdd(&h[(key >> shift) & ((1ull << width) - 1ull)], 1u);
+        }
+        __syncthreads();
+        // thread t's bins 4 t .. 4 t + 3 behind the bins of the threads before it
+        const uint4 c = ((const uint4 *)h)[t];
+        const unsigned int sum = c.x + c.y + c.z + c.w;
+        unsigned int incl = sum;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const unsigned int y = __shfl_up(incl, o);
+            if ((t & 63) >= o) incl += y;
+        }
+        if ((t & 63) == 63) sh.part[t >> 6] = incl;
+        __syncthreads();
+        unsigned long long before = incl - sum;
+        for (int w = 0; w < (t >> 6); ++w) before += sh.part[w];
+        if (rank >= before && rank < before + sum) {   // one thread
+            const unsigned int cq[4] = {c.x, c.y, c.z, c.w};
+            int q = 0;
+            while (rank >= before + cq[q]) before += cq[q++];
+            s_prefix = prefix | ((unsigned long long)(4 * t + q) << shift);
+            s_rank = rank - before;
+            s_left = cq[q];
+        }
+        __syncthreads();
+        prefix = s_prefix;
+        rank = s_rank;
+        left = s_left;
+        bits += width;
+    }
+    if (bits >= 64) {
+        if (t == 0) {
+            st->prefix = prefix;
+            select_done(st, stats, prefix);
+        }
+        return;
+    }
+    sel_digit(bits, shift, width, hi_mask);
+    __syncthreads();
+    if (t == 0) s_left = 0;
+    __syncthreads();
+    for (int64_t q = t; q < nk; q += 1024) {
+        const unsigned long long key = buf[q];
+        if ((key & hi_mask) == prefix) sh.keys[atomicAdd(&s_left, 1u)] = key;   // at most kSelFew
+    }
+    __syncthreads();
+    const unsigned int cnt = s_left;
+    if (t < (int)cnt) {
+        const unsigned long long mine = sh.keys[t];
+        unsigned int lt = 0, le = 0;
+        for (unsigned int j = 0; j < cnt; ++j) {
+            lt += sh.keys[j] < mine ? 1u : 0u;
+            le += sh.keys[j] <= mine ? 1u : 0u;
+        }
+        if (lt <= rank && rank < le) {
+            st->prefix = mine;
+            select_done(st, stats, mine);
+        }
+    }
+}
+
 // The remaining passes by one workgroup: all of them for at most kSelSmall
 // nodes (first), or what kSelPasses passes of the whole chip left undone.
 __device__ __forceinline__ void select_rest_body(const double *D2, int64_t ld, int64_t n,
@@ -1027,6 +1108,10 @@ __device__ __forceinline__ void select_rest_body(const double *D2, int64_t ld, i
     SelView v = first ? select_start(st, n, cap, gathered) : select_load(st);
     if (v.mode == 2) {
         if (first && threadIdx.x == 0) select_done(st, stats, v.prefix);
+        return;
+    }
+    if (first && v.src == 1) {
+        select_buffer_alone(st, v, buf, stats, h, sh);
         return;
     }
     // at most 6 digit passes resolve 64 bits; the collect pass is one more
