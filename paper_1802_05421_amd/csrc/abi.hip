@@ -1166,7 +1166,7 @@ static WProduct stored_product(cdl_ctx *ctx, const double *W, int64_t n, int64_t
     };
 }
 
-// The solve from the right-hand sides in w.Yt (X = 0 in w.Xt): norms, the
+// The solve from the right-hand sides in w.Yt (X starts as 0): norms, the
 // refinement iterations and the centred Z.  Syncs once per iteration.
 static cdl_status solve_from_rhs(cdl_ctx *ctx, const WProduct &wprod, const double *deg,
                                  const double *stats, int64_t n, const ChainBuf &c,
@@ -1326,12 +1326,10 @@ cdl_status cdl_solve_embedding(cdl_ctx *ctx, const double *W, const double *deg,
     Arena ac((void *)chain);
     ChainBuf c = plan_chain(ac, n, ci->prec, ci->depth);
     const int64_t ld = pad_n(n), kp = pad_k(k);
-    const size_t panel = (size_t)kp * ld;
     hipStream_t s = ctx->stream;
     HIPCHK(hipSetDevice(ctx->device));
     if (info) std::memset(info, 0, sizeof(*info));
 
-    { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w.Xt, panel * sizeof(double), s)); }
     { Timed t_(ctx, "rhs"); HIPCHK(launch_rhs(W, ld, n, gid, k, kp, seed, w.Yt, s)); }
     return solve_from_rhs(ctx, stored_product(ctx, W, n, k), deg, stats, n, c, ci, k, solver, tol,
                           max_iter, Z, w, info);
@@ -1357,13 +1355,10 @@ cdl_status cdl_solve_embedding_pair(cdl_ctx *ctx, const double *W0, const double
     Arena ac0((void *)chain0), ac1((void *)chain1);
     ChainBuf c0 = plan_chain(ac0, n, ci0->prec, ci0->depth), c1 = plan_chain(ac1, n, ci1->prec, ci1->depth);
     const int64_t ld = pad_n(n), kp = pad_k(k);
-    const size_t pbytes = (size_t)kp * ld * sizeof(double);
     hipStream_t s = ctx->stream;
     HIPCHK(hipSetDevice(ctx->device));
     if (info0) std::memset(info0, 0, sizeof(*info0));
     if (info1) std::memset(info1, 0, sizeof(*info1));
-    { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w0.Xt, pbytes, s)); }
-    { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w1.Xt, pbytes, s)); }
     { Timed t_(ctx, "rhs_pair"); HIPCHK(launch_rhs_pair(W0, W1, ld, n, gid, k, kp, seed, w0.Yt, w1.Yt, s)); }
     st = solve_from_rhs(ctx, stored_product(ctx, W0, n, k), deg0, stats0, n, c0, ci0, k, solver,
                         tol, max_iter, Z0, w0, info0);
@@ -1461,7 +1456,6 @@ cdl_status cdl_stream_embedding(cdl_ctx *ctx, const double *X, int64_t n, int64_
     Arena a(ws);
     const StreamWs w = plan_stream(a, n, T, k, panel_rows, level_prec);
     const int64_t ld = pad_n(n), Tp = pad_t(T), kp = pad_k(k), P = w.prow;
-    const size_t kbytes = (size_t)kp * ld * sizeof(double);
     hipStream_t s = ctx->stream;
 
     { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w.flags, 256, s)); }
@@ -1511,7 +1505,6 @@ cdl_status cdl_stream_embedding(cdl_ctx *ctx, const double *X, int64_t n, int64_
     }
 
     // Weights, degrees and right-hand sides: one sweep over the full row panels.
-    { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w.Xt, kbytes, s)); }
     for (int64_t r0 = 0; r0 < n; r0 += P) {
         const int64_t rows = std::min(P, ld - r0);
         { Timed t_(ctx, "stream_gram"); HIPCHK(launch_gram_panel(w.Xp, Tp, w.sqn, n, ld, r0, rows, true, w.panel, nullptr, s)); }
@@ -1901,11 +1894,9 @@ cdl_status solve_enqueue_fixed(cdl_ctx *ctx, const double *W, const double *deg,
     Arena ac((void *)chain);
     ChainBuf c = plan_chain(ac, n, prec, depth);
     const int64_t ld = pad_n(n), kp = pad_k(k);
-    const size_t panel = (size_t)kp * ld;
     hipStream_t s = ctx->stream;
     const int nparts = residual_parts(ld), ntiles = residual_tiles(ld, kp);
     const bool scaled = prec == 3;
-    { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w.Xt, panel * sizeof(double), s)); }
     { Timed t_(ctx, "rhs"); HIPCHK(launch_rhs(W, ld, n, gid, k, kp, seed, w.Yt, s)); }
     { Timed t_(ctx, "residual_init"); HIPCHK(launch_residual_k(prec, w.Xt, W, w.Yt, deg, c.dm, ld, n, kp, k, 1, (double *)w.part, w.Rt, w.V64, w.Vlo[0], w.npart, w.mpart, s)); }
     { Timed t_(ctx, "col_norms"); HIPCHK(launch_col_norms2(w.npart, nparts, kp, w.mpart, ntiles, scaled, w.scal, s)); }
@@ -2334,8 +2325,6 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
             const double *W = hs[t].W;
             double *stats = (double *)(base + L.st[t]);
             const SolveWs &w = solves[t];
-            const size_t panel = (size_t)kp * hs[t].ld * sizeof(double);
-            { Timed t_(ctx, "fill_zero"); HIPCHK(launch_fill_zero(w.Xt, panel, es)); }
             { Timed t_(ctx, "rhs"); HIPCHK(launch_rhs(W, hs[t].ld, x.n, x.gid, k, kp, q->seed, w.Yt, es)); }
             HIPCHK(hipMemcpyAsync(status + (size_t)t * CDL_GRAPH_STATS, stats,
                                   CDL_GRAPH_STATS * sizeof(double), hipMemcpyDeviceToDevice, es));

@@ -188,9 +188,9 @@ hipError_t launch_rhs_rows(const double *Wp, int64_t ld, int64_t n, int64_t row0
 hipError_t launch_panel_product(const double *Vt, const double *Wp, int64_t ld, int64_t n,
                                 int64_t k, int64_t kpad, int64_t row0, int64_t rows, double *Prod,
                                 hipStream_t s);
-// The residual reduction with S explicit split partials (S = 1: P is W X);
-// dm (ld entries) scales the maxima written to mpart.
-hipError_t launch_residual_reduce(const double *P, int S, const double *Yt, const double *Xt,
+// The residual reduction with S explicit split partials (S = 1: P is W X; S = 0:
+// X = 0, written here); dm (ld entries) scales the maxima written to mpart.
+hipError_t launch_residual_reduce(const double *P, int S, const double *Yt, double *Xt,
                                   const double *deg, const double *dm, int64_t ld, int64_t n,
                                   int64_t kpad, int64_t k, double *Rt, double *npart,
                                   double *mpart, hipStream_t s);
@@ -202,10 +202,10 @@ hipError_t launch_stream_scale(const double *Rt, const double *rdeg, int64_t ld,
                                double *Ut, hipStream_t s);
 hipError_t launch_stream_update(const double *Ut, const double *Prod, const double *rdeg,
                                 int64_t ld, int64_t k, double *Xt, hipStream_t s);
-// R = Y - deg * X + W X (skip_gemm: R = Y - deg * X).  P: residual_splits()
+// R = Y - deg * X + W X (skip_gemm: X = 0, written here, and R = Y).  P: residual_splits()
 // x kpad x ld doubles of split-K partials.  For prec 0..2 the reduction also
 // writes V = dm * R (V64) and its rounded copy (Vlo); prec 3 leaves V alone.
-hipError_t launch_residual_k(int prec, const double *Xt, const double *W, const double *Yt,
+hipError_t launch_residual_k(int prec, double *Xt, const double *W, const double *Yt,
                              const double *deg, const double *dm, int64_t ld, int64_t n,
                              int64_t kpad, int64_t k, int skip_gemm, double *P, double *Rt,
                              double *V64, void *Vlo, double *npart, double *mpart,
@@ -221,7 +221,7 @@ int residual_splits(int64_t ld, int64_t kpad, int64_t n, int choice);
 hipError_t launch_residual_gemm(const double *Xt, const double *W, int64_t ld, int64_t n,
                                 int64_t k, int64_t kpad, int S, double *P, hipStream_t s);
 hipError_t launch_residual_reduce_k(int prec, const double *P, int S, const double *Yt,
-                                    const double *Xt, const double *deg, const double *dm,
+                                    double *Xt, const double *deg, const double *dm,
                                     int64_t ld, int64_t n, int64_t kpad, int64_t k, double *Rt,
                                     double *V64, void *Vlo, double *npart, double *mpart,
                                     hipStream_t s);

@@ -631,21 +631,23 @@ hipError_t launch_panel_product(const double *Vt, const double *Wp, int64_t ld, 
 // reads as zero, giving -L X); optional
 // V = dm R (FP64) and V rounded to the chain type; per (256-node block, r)
 // partial sums of R^2 and per-block maxima of |dm R|.
+// skip_gemm: X = 0, which is written here (no product).
 // Node block bx, column r of the residual's reduction (one workgroup).
 template <typename T>
 __device__ inline void residual_reduce_block(
-    const double *P, int S, const double *Yt, const double *Xt, const double *deg,
+    const double *P, int S, const double *Yt, double *Xt, const double *deg,
     const double *dm, int64_t ld, int64_t n, int64_t k, int64_t kpad, int skip_gemm,
     double *Rt, double *V64, T *Vlo, double *npart, double *mpart, int64_t bx, int64_t r,
     double *red, double *redm) {
     const int64_t i = bx * 256 + threadIdx.x;
     const int64_t o = r * ld + i;
     double R = 0.0;
+    if (skip_gemm) Xt[o] = 0.0;
     if (r < k && i < n) {
         double acc = 0.0;
         if (!skip_gemm)
             for (int q = 0; q < S; ++q) acc += P[(int64_t)q * kpad * ld + o];
-        R = (Yt ? Yt[o] : 0.0) - deg[i] * Xt[o] + acc;
+        R = (Yt ? Yt[o] : 0.0) - deg[i] * (skip_gemm ? 0.0 : Xt[o]) + acc;
     }
     Rt[o] = R;
     const double v = dm[i] * R;
@@ -672,7 +674,7 @@ __device__ inline void residual_reduce_block(
 
 template <typename T>
 __global__ __launch_bounds__(256) void k_residual_reduce(
-    const double *P, int S, const double *Yt, const double *Xt, const double *deg,
+    const double *P, int S, const double *Yt, double *Xt, const double *deg,
     const double *dm, int64_t ld, int64_t n, int64_t k, int64_t kpad, int skip_gemm,
     double *Rt, double *V64, T *Vlo, double *npart, double *mpart) {
     __shared__ double red[4], redm[4];
@@ -680,13 +682,13 @@ __global__ __launch_bounds__(256) void k_residual_reduce(
                              mpart, blockIdx.x, blockIdx.y, red, redm);
 }
 
-hipError_t launch_residual_reduce(const double *P, int S, const double *Yt, const double *Xt,
+hipError_t launch_residual_reduce(const double *P, int S, const double *Yt, double *Xt,
                                   const double *deg, const double *dm, int64_t ld, int64_t n,
                                   int64_t kpad, int64_t k, double *Rt, double *npart,
                                   double *mpart, hipStream_t s) {
     dim3 grid((unsigned)(ld / 256), (unsigned)kpad), blk(256);
     hipLaunchKernelGGL(k_residual_reduce<double>, grid, blk, 0, s, P, S, Yt, Xt, deg, dm, ld, n,
-                       k, kpad, 0, Rt, (double *)nullptr, (double *)nullptr, npart, mpart);
+                       k, kpad, S == 0, Rt, (double *)nullptr, (double *)nullptr, npart, mpart);
     return hipGetLastError();
 }
 
@@ -749,7 +751,7 @@ hipError_t launch_residual_gemm(const double *Xt, const double *W, int64_t ld, i
 }
 
 hipError_t launch_residual_reduce_k(int prec, const double *P, int S, const double *Yt,
-                                    const double *Xt, const double *deg, const double *dm,
+                                    double *Xt, const double *deg, const double *dm,
                                     int64_t ld, int64_t n, int64_t kpad, int64_t k, double *Rt,
                                     double *V64, void *Vlo, double *npart, double *mpart,
                                     hipStream_t s) {
@@ -765,7 +767,7 @@ hipError_t launch_residual_reduce_k(int prec, const double *P, int S, const doub
 }
 
 // prec < 0: no fused operand (FP16 chains scale it separately).
-hipError_t launch_residual_k(int prec, const double *Xt, const double *W, const double *Yt,
+hipError_t launch_residual_k(int prec, double *Xt, const double *W, const double *Yt,
                              const double *deg, const double *dm, int64_t ld, int64_t n,
                              int64_t kpad, int64_t k, int skip_gemm, double *P, double *Rt,
                              double *V64, void *Vlo, double *npart, double *mpart,
