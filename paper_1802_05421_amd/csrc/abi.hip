@@ -118,6 +118,7 @@ bool timing_selected(const cdl_ctx *c, const char *nm) {
 }
 
 constexpr size_t kStageInitBytes = 4096;
+static_assert(cdl::kGraphStats == CDL_GRAPH_STATS, "statistics of a graph");
 
 // One device-to-host read: `bytes` from device `src` into host `dst`.
 struct HostRead {
@@ -1167,7 +1168,8 @@ static WProduct stored_product(cdl_ctx *ctx, const double *W, int64_t n, int64_t
 }
 
 // The solve from the right-hand sides in w.Yt (X starts as 0): norms, the
-// refinement iterations and the centred Z.  Syncs once per iteration.
+// refinement iterations and the centred Z.  Syncs once per iteration (and, for a
+// certified tolerance, once before).
 static cdl_status solve_from_rhs(cdl_ctx *ctx, const WProduct &wprod, const double *deg,
                                  const double *stats, int64_t n, const ChainBuf &c,
                                  const cdl_chain_info *ci, int64_t k, cdl_solver solver,
@@ -1180,13 +1182,15 @@ static cdl_status solve_from_rhs(cdl_ctx *ctx, const WProduct &wprod, const doub
     const int nparts = residual_parts(ld), ntiles = residual_tiles(ld, kp);
     const int scaled = prec == 3;   // FP16 operands need a power-of-two scale
     { Timed t_(ctx, "residual_init"); HIPCHK(launch_residual_reduce_k(prec, nullptr, 0, w.Yt, w.Xt, deg, c.dm, ld, n, kp, k, w.Rt, w.V64, w.Vlo[0], w.npart, w.mpart, s)); }
-    { Timed t_(ctx, "col_norms"); HIPCHK(launch_col_norms2(w.npart, nparts, kp, w.mpart, ntiles, scaled, w.scal, s)); }
-    std::vector<double> ynorm(kp), rnorm(kp);
-    double hstats[CDL_GRAPH_STATS];
-    HIPCHK(read_to_host(ctx, s, {{ynorm.data(), w.scal, kp * sizeof(double)},
-                              {hstats, stats, sizeof(hstats)}}));
-    for (int64_t r = 0; r < k; ++r)
-        if (!std::isfinite(ynorm[r])) return fail(ctx, CDL_E_NONFINITE, "non-finite right-hand side");
+    // the norms of Y and the statistics, then those of every residual, as the
+    // kernel writes them into the staging buffer
+    const size_t place = ((size_t)(kp + CDL_GRAPH_STATS) * sizeof(double) + 255) / 256 * 256;
+    char *stage_dev = nullptr;
+    HIPCHK(stage_reserve(ctx, s, 2 * place, &stage_dev));
+    const double *const ynorm = (const double *)ctx->stage, *const hstats = ynorm + kp;
+    const double *const rnorm = (const double *)((const char *)ctx->stage + place);
+    double *const rnorm_dev = (double *)(stage_dev + place);
+    { Timed t_(ctx, "col_norms"); HIPCHK(launch_col_norms2(w.npart, nparts, kp, w.mpart, ntiles, scaled, w.scal, (double *)stage_dev, stats, s)); }
     // kappa bounds ||e|| / ||z|| per unit relative residual: the nonzero
     // spectrum of L = D^{1/2} (I - S) D^{1/2} lies in
     // [deg_min (1 - rho), deg_max (1 + rho)], rho = rho(S~) <= ||S~||_F.
@@ -1194,9 +1198,22 @@ static cdl_status solve_from_rhs(cdl_ctx *ctx, const WProduct &wprod, const doub
     // and <= 2, so kappa = deg_max / (deg_min (1 - ||S~'||_F)).
     const double rb = ci->rho_bound;
     double kappa = INFINITY;
-    if (rb < 1.0 && hstats[2] > 0.0)
-        kappa = ci->lazy ? hstats[3] / (hstats[2] * (1.0 - rb))
-                         : hstats[3] * (1.0 + rb) / (hstats[2] * (1.0 - rb));
+    // once Y's norms are there
+    auto first_norms = [&]() -> cdl_status {
+        for (int64_t r = 0; r < k; ++r)
+            if (!std::isfinite(ynorm[r])) return fail(ctx, CDL_E_NONFINITE, "non-finite right-hand side");
+        if (rb < 1.0 && hstats[2] > 0.0)
+            kappa = ci->lazy ? hstats[3] / (hstats[2] * (1.0 - rb))
+                             : hstats[3] * (1.0 + rb) / (hstats[2] * (1.0 - rb));
+        return CDL_OK;
+    };
+    // Only a certified tolerance needs them before the first iteration; otherwise
+    // they are looked at with its residual, one wait fewer.
+    if (tol < 0.0) {
+        HIPCHK(hipStreamSynchronize(s));
+        const cdl_status fst = first_norms();
+        if (fst != CDL_OK) return fst;
+    }
     const double target = tol > 0.0 ? tol : (tol < 0.0 ? -tol / kappa : 0.0);
     if (tol < 0.0 && !std::isfinite(kappa))
         return fail(ctx, CDL_E_ARG, "certified tolerance needs ||S~||_F < 1; use tol > 0");
@@ -1218,7 +1235,14 @@ static cdl_status solve_from_rhs(cdl_ctx *ctx, const WProduct &wprod, const doub
     };
     // max_r ||r_r|| / ||y_r|| after the norms kernel; syncs.
     auto residual_check = [&]() -> cdl_status {
-        HIPCHK(read_to_host(ctx, s, {{rnorm.data(), w.scal, kp * sizeof(double)}}));
+        HIPCHK(hipStreamSynchronize(s));
+        if (it == 1 && !(tol < 0.0)) {
+            const cdl_status fst = first_norms();
+            if (fst != CDL_OK) {
+                if (info) info->depth_used[0] = 0;
+                return fst;
+            }
+        }
         rel = 0.0;
         for (int64_t r = 0; r < k; ++r) {
             if (!std::isfinite(rnorm[r])) return fail(ctx, CDL_E_NONFINITE, "non-finite residual");
@@ -1240,7 +1264,7 @@ static cdl_status solve_from_rhs(cdl_ctx *ctx, const WProduct &wprod, const doub
             if ((st = wprod(w.Xt, (double *)w.part, S)) != CDL_OK) return st;
             { Timed t_(ctx, "residual_reduce"); HIPCHK(launch_residual_reduce_k(prec, (double *)w.part, S, w.Yt, w.Xt, deg, c.dm, ld, n, kp, k,
                                      w.Rt, w.V64, w.Vlo[0], w.npart, w.mpart, s)); }
-            { Timed t_(ctx, "col_norms"); HIPCHK(launch_col_norms2(w.npart, nparts, kp, w.mpart, ntiles, scaled, w.scal, s)); }
+            { Timed t_(ctx, "col_norms"); HIPCHK(launch_col_norms2(w.npart, nparts, kp, w.mpart, ntiles, scaled, w.scal, rnorm_dev, nullptr, s)); }
             if ((st = residual_check()) != CDL_OK) return st;
             if (conv) break;
         }
@@ -1267,7 +1291,7 @@ static cdl_status solve_from_rhs(cdl_ctx *ctx, const WProduct &wprod, const doub
             { Timed t_(ctx, "pcg_vec"); HIPCHK(launch_pcg_scalars(w.dots, ld, kp, 1, 0, w.pcg, s)); }
             { Timed t_(ctx, "pcg_update"); HIPCHK(launch_pcg_update(prec, w.Pt, w.Qt, alpha, c.dm, ld, kp, w.Xt, w.Rt, w.V64,
                                        w.Vlo[0], w.npart, w.mpart, s)); }
-            { Timed t_(ctx, "col_norms"); HIPCHK(launch_col_norms2(w.npart, nparts, kp, w.mpart, ntiles, scaled, w.scal, s)); }
+            { Timed t_(ctx, "col_norms"); HIPCHK(launch_col_norms2(w.npart, nparts, kp, w.mpart, ntiles, scaled, w.scal, rnorm_dev, nullptr, s)); }
             if ((st = residual_check()) != CDL_OK) return st;
             if (conv) break;
         }
@@ -1560,7 +1584,7 @@ cdl_status cdl_stream_embedding(cdl_ctx *ctx, const double *X, int64_t n, int64_
     const int nparts = residual_parts(ld), ntiles = residual_tiles(ld, kp);
     // R = Y (X = 0) and the norms of Y's columns
     { Timed t_(ctx, "residual_init"); HIPCHK(launch_residual_reduce(nullptr, 0, w.Yt, w.Xt, deg, w.rdeg, ld, n, kp, k, w.Rt, w.npart, w.mpart, s)); }
-    { Timed t_(ctx, "col_norms"); HIPCHK(launch_col_norms2(w.npart, nparts, kp, w.mpart, ntiles, 0, w.scal, s)); }
+    { Timed t_(ctx, "col_norms"); HIPCHK(launch_col_norms2(w.npart, nparts, kp, w.mpart, ntiles, 0, w.scal, nullptr, nullptr, s)); }
     std::vector<double> ynorm(kp), rnorm(kp);
     double hstats[CDL_GRAPH_STATS];
     HIPCHK(read_to_host(ctx, s, {{ynorm.data(), w.scal, kp * sizeof(double)}, {hstats, stats, sizeof(hstats)}}));
@@ -1615,7 +1639,7 @@ cdl_status cdl_stream_embedding(cdl_ctx *ctx, const double *X, int64_t n, int64_
         // R = Y - D X + W X
         if ((st = product_sweep(w.Xt, false)) != CDL_OK) return st;
         { Timed t_(ctx, "residual"); HIPCHK(launch_residual_reduce(w.Prod, 1, w.Yt, w.Xt, deg, w.rdeg, ld, n, kp, k, w.Rt, w.npart, w.mpart, s)); }
-        { Timed t_(ctx, "col_norms"); HIPCHK(launch_col_norms2(w.npart, nparts, kp, w.mpart, ntiles, 0, w.scal, s)); }
+        { Timed t_(ctx, "col_norms"); HIPCHK(launch_col_norms2(w.npart, nparts, kp, w.mpart, ntiles, 0, w.scal, nullptr, nullptr, s)); }
         HIPCHK(read_to_host(ctx, s, {{rnorm.data(), w.scal, kp * sizeof(double)}}));
         rel = 0.0;
         for (int64_t r = 0; r < k; ++r) {
@@ -1899,7 +1923,7 @@ cdl_status solve_enqueue_fixed(cdl_ctx *ctx, const double *W, const double *deg,
     const bool scaled = prec == 3;
     { Timed t_(ctx, "rhs"); HIPCHK(launch_rhs(W, ld, n, gid, k, kp, seed, w.Yt, s)); }
     { Timed t_(ctx, "residual_init"); HIPCHK(launch_residual_k(prec, w.Xt, W, w.Yt, deg, c.dm, ld, n, kp, k, 1, (double *)w.part, w.Rt, w.V64, w.Vlo[0], w.npart, w.mpart, s)); }
-    { Timed t_(ctx, "col_norms"); HIPCHK(launch_col_norms2(w.npart, nparts, kp, w.mpart, ntiles, scaled, w.scal, s)); }
+    { Timed t_(ctx, "col_norms"); HIPCHK(launch_col_norms2(w.npart, nparts, kp, w.mpart, ntiles, scaled, w.scal, nullptr, nullptr, s)); }
     HIPCHK(hipMemcpyAsync(ynorm, w.scal, kp * sizeof(double), hipMemcpyDeviceToDevice, s));
     const double *inv_vs = w.scal + kp + 1;
     for (int it = 0; it < iters; ++it) {
@@ -1907,7 +1931,7 @@ cdl_status solve_enqueue_fixed(cdl_ctx *ctx, const double *W, const double *deg,
         if (st != CDL_OK) return st;
         { Timed t_(ctx, "residual"); HIPCHK(launch_residual_k(prec, w.Xt, W, w.Yt, deg, c.dm, ld, n, kp, k, 0, (double *)w.part, w.Rt,
                                  w.V64, w.Vlo[0], w.npart, w.mpart, s)); }
-        { Timed t_(ctx, "col_norms"); HIPCHK(launch_col_norms2(w.npart, nparts, kp, w.mpart, ntiles, scaled, w.scal, s)); }
+        { Timed t_(ctx, "col_norms"); HIPCHK(launch_col_norms2(w.npart, nparts, kp, w.mpart, ntiles, scaled, w.scal, nullptr, nullptr, s)); }
     }
     HIPCHK(hipMemcpyAsync(rnorm, w.scal, kp * sizeof(double), hipMemcpyDeviceToDevice, s));
     { Timed t_(ctx, "finalize_z"); HIPCHK(launch_finalize_z2(w.Xt, ld, n, kp, k, w.mean, Z, s)); }

@@ -35,6 +35,7 @@ struct SelectState {                // device scratch of the exact median select
 int64_t select_buffer_keys(int64_t n);
 
 hipError_t launch_fill_zero(void *p, size_t bytes, hipStream_t s);
+constexpr int kGraphStats = 4;   // doubles of a graph's statistics
 // Device ranges to copy, in 4-byte words, and their places in pinned memory.
 struct ReadOut {
     const uint32_t *src[4];
@@ -228,7 +229,8 @@ hipError_t launch_residual_reduce_k(int prec, const double *P, int S, const doub
 int residual_parts(int64_t ld);               // column-norm partials per column
 int residual_tiles(int64_t ld, int64_t kpad); // maxima written
 hipError_t launch_col_norms2(const double *npart, int nparts, int64_t kpad, const double *mpart,
-                             int ntiles, int scaled, double *out, hipStream_t s);
+                             int ntiles, int scaled, double *out, double *host, const double *stats,
+                             hipStream_t s);
 hipError_t launch_prep_v2(int prec, const double *Rt, const double *dm, int64_t ld, int64_t kpad,
                           const double *scal, double *V64, void *Vlo, hipStream_t s);
 // Z[i][r] = Xt[r][i] for i < n, r < k (Z n x k row-major).
