@@ -378,6 +378,9 @@ struct DmaCore {
 // banks once.  NS: LDS stages (2 for the large tiles, whose k-tile takes
 // microseconds; 3 or 4 where it is nearer the load latency).  The k order of
 // every sum is the same for every tile shape, so the results are the same bits.
+// WK = 2 (panel products of one workgroup per CU): twice the waves, each half of
+// them taking two of a stage's four groups, so that a SIMD has another wave's
+// MFMAs while one waits.
 //
 // Measured at 256 x 16384 x 16384 in FP64 (the residual product's shape) on one
 // card, in bursts: 256 x 128 tiles of 8 waves 1.86 ms (74 TFLOP/s), 128 x 128 of
@@ -402,7 +405,7 @@ template <> struct RowMf<float> : MfmaF32 {
     }
 };
 
-template <typename E, int BM, int BN, int WM, int WN, int NS = 2>
+template <typename E, int BM, int BN, int WM, int WN, int NS = 2, int WK = 1>
 struct RowCore {
     using T = E;
     using MF = RowMf<T>;
@@ -412,7 +415,7 @@ struct RowCore {
     static constexpr int ROWB = 128;                 // bytes per LDS row
     static constexpr int BK = ROWB / (int)sizeof(T);
     static constexpr int TBM = BM, TBN = BN;
-    static constexpr int NW = WM * WN, NT = NW * 64;
+    static constexpr int NW = WM * WN * WK, NT = NW * 64;
     static constexpr int STAGE = (BM + BN) * ROWB;
     static constexpr size_t SMEM = (size_t)NS * STAGE;
     static constexpr int WTM = BM / WM / M, WTN = BN / WN / M;
@@ -421,10 +424,10 @@ struct RowCore {
     // place), so that every wave counts the same number
     static constexpr int AB = BM / 8, BB = BN / 8;
     static constexpr int AI = (AB + NW - 1) / NW, BI = (BB + NW - 1) / NW;
-    static constexpr int NKK = 4;
+    static constexpr int NKK = 4 / WK;               // k-groups of a stage per wave
     static constexpr int NF = WTM + WTN, NM = WTM * WTN * MF::STEPS;
     static_assert(WTM * WM * M == BM && WTN * WN * M == BN, "whole wave tiles");
-    static_assert(WTM >= 1 && WTN >= 1 && NS >= 2, "tile shape");
+    static_assert(WTM >= 1 && WTN >= 1 && NS >= 2 && (WK == 1 || WK == 2), "tile shape");
 
     AccV acc[WTM][WTN];
 
@@ -453,9 +456,9 @@ struct RowCore {
 
     __device__ inline void load_frags(const char *s, int q, Frag *f) {
         const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-        const int wm = wid % WM, wn = wid / WM;
+        const int wm = wid % WM, wn = wid / WM % WN;
         const char *sA = s, *sB = s + BM * ROWB;
-        const int c = 2 * q + (lane >> 5), in = MF::within(lane);
+        const int c = 2 * (NKK * half() + q) + (lane >> 5), in = MF::within(lane);
 #pragma unroll
         for (int i = 0; i < WTM; ++i) {
             const int row = (wm * WTM + i) * M + lane % M;
@@ -567,14 +570,40 @@ struct RowCore {
         mmas(f[1]);
         wait_vmcnt_lds<0>();
         lds_barrier();
+        if constexpr (WK == 2) {
+            static_assert(WTM * WTN * MF::R * WM * WN * 64 * sizeof(T) <= SMEM, "the other half's sums");
+            T *const other = (T *)smem + threadIdx.x % (WM * WN * 64);
+            if (half()) {
+#pragma unroll
+                for (int i = 0; i < WTM; ++i)
+#pragma unroll
+                    for (int j = 0; j < WTN; ++j)
+#pragma unroll
+                        for (int r = 0; r < MF::R; ++r)
+                            other[((i * WTN + j) * MF::R + r) * (WM * WN * 64)] = acc[i][j][r];
+            }
+            __syncthreads();
+            if (!half()) {
+#pragma unroll
+                for (int i = 0; i < WTM; ++i)
+#pragma unroll
+                    for (int j = 0; j < WTN; ++j)
+#pragma unroll
+                        for (int r = 0; r < MF::R; ++r)
+                            acc[i][j][r] += other[((i * WTN + j) * MF::R + r) * (WM * WN * 64)];
+            }
+        }
     }
 
+    // WK = 2: which half of every stage's k-groups this wave sums; the sums are
+    // those of the waves of half 0 after run().
+    __device__ static inline int half() { return WK == 1 ? 0 : (int)(threadIdx.x >> 6) / (WM * WN); }
     __device__ static inline int row_of(int i, int r) {
         const int lane = threadIdx.x & 63, wm = (threadIdx.x >> 6) % WM;
         return (wm * WTM + i) * M + MF::crow(lane, r);
     }
     __device__ static inline int col_of(int j) {
-        const int lane = threadIdx.x & 63, wn = (threadIdx.x >> 6) / WM;
+        const int lane = threadIdx.x & 63, wn = (threadIdx.x >> 6) / WM % WN;
         return (wn * WTN + j) * M + MF::ccol(lane);
     }
 };

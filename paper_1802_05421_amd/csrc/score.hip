@@ -11,8 +11,8 @@
 //               partial per (column block, node) and per column into one
 //               partial per (row block, node)
 //   reduce      F_a = sum of exactly the written partials (fixed order)
-//   topk        bitonic sort of chunks in registers, keep the best K per chunk,
-//               repeat on the candidates (order: value desc, index asc)
+//   topk        the best K of every chunk in order, repeated on the candidates
+//               (order: value desc, index asc)
 //   edges       the K largest edge scores (a < b) exactly: maxima per 256 x 128
 //               tile from k_score, threshold = K-th largest tile maximum, only
 //               tiles reaching it recomputed and their edges collected

@@ -619,11 +619,64 @@ static hipError_t residual_product(const double *Xt, const double *W, int64_t ld
     }
 }
 
+// Panel products of at most one workgroup per CU in column-group tiles: eight
+// waves, half of them on each half of every k-tile (one wave per SIMD alone left
+// its matrix pipe idle at every wait: 1080 -> 910 us on average over panels of n = 20000,
+// k = 200).
+template <int C>
+__global__ __launch_bounds__(512) void k_panel_product(const double *Vt, const double *Wp, int64_t ld,
+                                                       int64_t kend, int mt, int nt, double *Prod,
+                                                       int64_t row0) {
+    using Core = RowCore<double, 16 * C, 64, 1, 4, 3, 2>;
+    extern __shared__ __attribute__((aligned(16))) char smem_raw[];
+    int I, J;
+    rect_tile<4>(xcd_remap(blockIdx.x, mt * nt), mt, nt, I, J);
+    const int64_t m0 = (int64_t)I * Core::TBM, n0 = (int64_t)J * Core::TBN;
+    Core g;
+    g.run(Vt, ld, Wp, ld, m0, n0, kend, (double *)smem_raw);
+    if (Core::half()) return;
+    double *const out = Prod + row0;
+#pragma unroll
+    for (int a = 0; a < Core::WTM; ++a)
+#pragma unroll
+        for (int b = 0; b < Core::WTN; ++b)
+#pragma unroll
+            for (int rr = 0; rr < MfmaF64::R; ++rr)
+                out[(m0 + Core::row_of(a, rr)) * ld + n0 + Core::col_of(b)] = g.acc[a][b][rr];
+}
+
+template <int C>
+static hipError_t panel_launch(const double *Vt, const double *Wp, int64_t ld, int64_t n, int64_t rows,
+                               int64_t row0, int64_t k, int64_t kpad, double *Prod, hipStream_t s) {
+    using Core = RowCore<double, 16 * C, 64, 1, 4, 3, 2>;
+    static bool attr = false;
+    if (!attr) {
+        hipError_t e = hipFuncSetAttribute((const void *)k_panel_product<C>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize, (int)Core::SMEM);
+        if (e != hipSuccess) return e;
+        attr = true;
+    }
+    const int mt = (int)res_mt(C, kpad, k), nt = (int)(rows / 64);
+    hipLaunchKernelGGL(k_panel_product<C>, dim3(mt * nt), dim3(Core::NT), Core::SMEM, s, Vt, Wp, ld,
+                       (n + 63) / 64 * 64, mt, nt, Prod, row0);
+    return hipGetLastError();
+}
+
 hipError_t launch_panel_product(const double *Vt, const double *Wp, int64_t ld, int64_t n,
                                 int64_t k, int64_t kpad, int64_t row0, int64_t rows, double *Prod,
                                 hipStream_t s) {
     if (rows <= 0 || rows % 128 || row0 < 0 || row0 + rows > ld || kpad % 64 || k < 1 || k > kpad)
         return hipErrorInvalidValue;
+    const int shape = residual_shape(k, kpad, rows, (n + 63) / 64 * 64, 1);
+    if (shape >= 4 && res_mt(shape, kpad, k) * (rows / 64) <= 256) {
+        switch (shape) {
+        case 4: return panel_launch<4>(Vt, Wp, ld, n, rows, row0, k, kpad, Prod, s);
+        case 5: return panel_launch<5>(Vt, Wp, ld, n, rows, row0, k, kpad, Prod, s);
+        case 6: return panel_launch<6>(Vt, Wp, ld, n, rows, row0, k, kpad, Prod, s);
+        case 7: return panel_launch<7>(Vt, Wp, ld, n, rows, row0, k, kpad, Prod, s);
+        default: return panel_launch<8>(Vt, Wp, ld, n, rows, row0, k, kpad, Prod, s);
+        }
+    }
     return residual_product(Vt, Wp, ld, n, rows, row0, k, kpad, 1, Prod, s);
 }
 
