@@ -247,7 +247,10 @@ hipError_t launch_normalize_rows(int prec, const double *Wp, int64_t ld, int64_t
 // NW = 4 waves (2 x 2 of 128 x 128); SH: the MFMA shape (32: 32 x 32 x 16, 16:
 // 16 x 16 x 32).  FP32 and FP64 levels: NW = 8, and SH is the tile: 128 x 128
 // (two workgroups on a CU), 64 x 64, and 32 x 32 for the smallest FP64 levels
-// (the same bits from each; row_square_tile).
+// (row_square_tile), eight waves each.  Those of FP32 and of the small FP64 tiles
+// share every stage's k-groups between two halves, for the launches of one
+// workgroup on a CU (conjugate gradients at 2025 nodes 719 -> 699 us, a pair of
+// 256 in FP64 531 -> 496); every FP32 tile gives the same bits.
 template <typename T, int NW, int SH = 32> struct SqCfg;
 template <int NW, int SH> struct SqCfg<__bf16, NW, SH> {
     using Core = DmaCore<std::conditional_t<SH == 16, MfmaBF16x32, MfmaBF16>, 256, 256, 2, NW / 2>;
@@ -257,11 +260,11 @@ template <int NW, int SH> struct SqCfg<_Float16, NW, SH> {
     using Core = DmaCore<std::conditional_t<SH == 16, MfmaF16x32, MfmaF16>, 256, 256, 2, NW / 2>;
     static constexpr int TILE = 256;
 };
-template <int NW> struct SqCfg<float, NW, 128> { using Core = RowCore<float, 128, 128, 2, 2, 2>; static constexpr int TILE = 128; };
-template <int NW> struct SqCfg<float, NW, 64> { using Core = RowCore<float, 64, 64, 2, 2, 3>; static constexpr int TILE = 64; };
+template <int NW> struct SqCfg<float, NW, 128> { using Core = RowCore<float, 128, 128, 2, 2, 2, 2>; static constexpr int TILE = 128; };
+template <int NW> struct SqCfg<float, NW, 64> { using Core = RowCore<float, 64, 64, 2, 2, 3, 2>; static constexpr int TILE = 64; };
 template <int NW> struct SqCfg<double, NW, 128> { using Core = RowCore<double, 128, 128, 2, 4, 2>; static constexpr int TILE = 128; };
-template <int NW> struct SqCfg<double, NW, 64> { using Core = RowCore<double, 64, 64, 2, 2, 3>; static constexpr int TILE = 64; };
-template <int NW> struct SqCfg<double, NW, 32> { using Core = RowCore<double, 32, 32, 2, 2, 4>; static constexpr int TILE = 32; };
+template <int NW> struct SqCfg<double, NW, 64> { using Core = RowCore<double, 64, 64, 2, 2, 3, 2>; static constexpr int TILE = 64; };
+template <int NW> struct SqCfg<double, NW, 32> { using Core = RowCore<double, 32, 32, 2, 2, 4, 2>; static constexpr int TILE = 32; };
 
 // Tile of an FP32 or FP64 squaring: the one whose busiest CU has the least
 // work (36 tiles of 128 x 128 at n = 1000 kept 36 CUs busy for 79 us in FP32, the
@@ -644,9 +647,9 @@ template <typename T, int SHAPE> struct ApCfg {
     static constexpr int WM = BM / 128 > 0 ? BM / 128 : 1;
     using Core = DmaCore<typename MfmaOf<T>::type, BM, 256, WM, 8 / WM>;
 };
-template <int SHAPE> struct ApCfg<float, SHAPE> { using Core = RowCore<float, 32 * (SHAPE - 4), 128, 1, 4, SHAPE < 7 ? 3 : 2>; };
-template <> struct ApCfg<float, 3> { using Core = RowCore<float, 128, 128, 2, 2, 2>; };
-template <> struct ApCfg<float, 4> { using Core = RowCore<float, 64, 64, 2, 2, 3>; };
+template <int SHAPE> struct ApCfg<float, SHAPE> { using Core = RowCore<float, 32 * (SHAPE - 4), 128, 1, 4, SHAPE < 7 ? 3 : 2, 2>; };
+template <> struct ApCfg<float, 3> { using Core = RowCore<float, 128, 128, 2, 2, 2, 2>; };
+template <> struct ApCfg<float, 4> { using Core = RowCore<float, 64, 64, 2, 2, 3, 2>; };
 static int64_t ap_tile_m(int shape) { return shape < 3 ? 64 << shape : shape == 3 ? 128 : shape == 4 ? 64 : 32 * (shape - 4); }
 static int64_t ap_tile_n(int shape) { return shape < 3 ? 256 : shape == 4 ? 64 : 128; }
 
@@ -723,6 +726,7 @@ __device__ __forceinline__ void apply_gemm_tile(const T *Vin, const T *S, int64_
     const int64_t kk = k0 < kend ? (kend - k0 < ks ? kend - k0 : ks) : 0;
     Core g;
     g.run(Vin + k0, ld, S + k0, ld, m0, n0, kk, smem);
+    if (Core::half()) return;
     float *Ps = P + (int64_t)split * kpad * ld;
 #pragma unroll
     for (int a = 0; a < Core::WTM; ++a)
@@ -1007,6 +1011,7 @@ __global__ __launch_bounds__((SqCfg<double, 8, TL>::Core::NT)) void k_apply_f64(
     const int64_t m0 = (int64_t)I * TL, n0 = (int64_t)J * TL;
     Core g;
     g.run(Vin, ld, S, ld, m0, n0, kend, smem);
+    if (Core::half()) return;
     const double ivs = inv_vs ? *inv_vs : 0.0;
 #pragma unroll
     for (int a = 0; a < Core::WTM; ++a)

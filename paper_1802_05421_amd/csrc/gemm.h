@@ -22,15 +22,17 @@ __device__ inline void stage_and_store(Core &g, O *sC, F f, O *C, int64_t ldc,
     constexpr int CEo = 16 / (int)sizeof(O);
     constexpr int LDC = BN + CEo;
     __syncthreads();
+    if (!Core::half()) {
 #pragma unroll
-    for (int i = 0; i < Core::WTM; ++i)
+        for (int i = 0; i < Core::WTM; ++i)
 #pragma unroll
-        for (int j = 0; j < Core::WTN; ++j)
+            for (int j = 0; j < Core::WTN; ++j)
 #pragma unroll
-            for (int r = 0; r < Core::MF::R; ++r) {
-                int row = Core::row_of(i, r), col = Core::col_of(j);
-                sC[row * LDC + col] = f(row, col, g.acc[i][j][r]);
-            }
+                for (int r = 0; r < Core::MF::R; ++r) {
+                    int row = Core::row_of(i, r), col = Core::col_of(j);
+                    sC[row * LDC + col] = f(row, col, g.acc[i][j][r]);
+                }
+    }
     __syncthreads();
     constexpr int CPR = BN / CEo;
     for (int ch = threadIdx.x; ch < BM * CPR; ch += NT) {
@@ -348,6 +350,7 @@ struct DmaCore {
         lds_barrier();
     }
 
+    __device__ static inline int half() { return 0; }
     __device__ static inline int row_of(int i, int r) {
         const int lane = threadIdx.x & 63, wm = (threadIdx.x >> 6) % WM;
         return wm * WTM * Mf::M + i * Mf::M + Mf::crow(lane, r);
@@ -378,9 +381,9 @@ struct DmaCore {
 // banks once.  NS: LDS stages (2 for the large tiles, whose k-tile takes
 // microseconds; 3 or 4 where it is nearer the load latency).  The k order of
 // every sum is the same for every tile shape, so the results are the same bits.
-// WK = 2 (panel products of one workgroup per CU): twice the waves, each half of
-// them taking two of a stage's four groups, so that a SIMD has another wave's
-// MFMAs while one waits.
+// WK = 2 (FP32 levels, small FP64 levels, panel products of one workgroup per
+// CU): twice the waves, each half of them taking two of a stage's four groups, so
+// that a SIMD has another wave's MFMAs while one waits; these have their own order.
 //
 // Measured at 256 x 16384 x 16384 in FP64 (the residual product's shape) on one
 // card, in bursts: 256 x 128 tiles of 8 waves 1.86 ms (74 TFLOP/s), 128 x 128 of
