@@ -619,10 +619,10 @@ static hipError_t residual_product(const double *Xt, const double *W, int64_t ld
     }
 }
 
-// Panel products of at most one workgroup per CU in column-group tiles: eight
-// waves, half of them on each half of every k-tile (one wave per SIMD alone left
-// its matrix pipe idle at every wait: 1080 -> 910 us on average over panels of n = 20000,
-// k = 200).
+// Panel products in column-group tiles: eight waves, half of them on each half of
+// every k-tile.  A panel of 8192 rows at k = 200 is 256 workgroups, and with four
+// waves the matrix pipes stood still at every wait: 1080 -> 910 us on average over
+// panels of n = 20000.
 template <int C>
 __global__ __launch_bounds__(512) void k_panel_product(const double *Vt, const double *Wp, int64_t ld,
                                                        int64_t kend, int mt, int nt, double *Prod,
@@ -667,9 +667,20 @@ hipError_t launch_panel_product(const double *Vt, const double *Wp, int64_t ld, 
                                 hipStream_t s) {
     if (rows <= 0 || rows % 128 || row0 < 0 || row0 + rows > ld || kpad % 64 || k < 1 || k > kpad)
         return hipErrorInvalidValue;
-    const int shape = residual_shape(k, kpad, rows, (n + 63) / 64 * 64, 1);
-    if (shape >= 4 && res_mt(shape, kpad, k) * (rows / 64) <= 256) {
-        switch (shape) {
+    // By the columns alone, so that the order of the sums, and with it every bit
+    // of the embedding, is the same for every panel size: whole 128-column tiles
+    // keep the shapes that serve them.
+    if (cdiv(k, 16) % 8 != 0) {
+        int best = 4;
+        double tb = 1e300;
+        for (int c = 2; c <= 8; ++c) {
+            if (!res_inside(c, kpad, k)) continue;
+            const double t = (double)cdiv(res_mt(c, kpad, k) * (rows / 64), 256) * (double)c / res_eff(c, false);
+            if (t < tb) { tb = t; best = c; }
+        }
+        switch (best) {
+        case 2: return panel_launch<2>(Vt, Wp, ld, n, rows, row0, k, kpad, Prod, s);
+        case 3: return panel_launch<3>(Vt, Wp, ld, n, rows, row0, k, kpad, Prod, s);
         case 4: return panel_launch<4>(Vt, Wp, ld, n, rows, row0, k, kpad, Prod, s);
         case 5: return panel_launch<5>(Vt, Wp, ld, n, rows, row0, k, kpad, Prod, s);
         case 6: return panel_launch<6>(Vt, Wp, ld, n, rows, row0, k, kpad, Prod, s);

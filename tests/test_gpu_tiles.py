@@ -262,3 +262,16 @@ def test_panels_mirror_their_own_square(cdl, n, panel):
     ch = cdl.build_chain(ref, prec="fp32", depth_max=8)
     Z0, info = cdl.solve_embedding(ref, ch, 3, SEED, tol=1e-12, max_iter=60)
     assert info.converged and rel(host(Z), host(Z0)) <= 2e-11
+
+
+# The panel products' tiles differ with the panel's size, the order of their sums
+# does not: the same bits for every panel size, at column counts of every tile
+# and at whole 128-column panels.
+@pytest.mark.parametrize("n,k", [(300, 5), (700, 48), (1100, 70), (1300, 112), (900, 128), (600, 200)])
+def test_panel_size_leaves_every_bit(cdl, n, k):
+    print("panel bits n=%d k=%d" % (n, k), flush=True)
+    X = dev(np.random.default_rng(n + k).standard_normal((n, 24)))
+    Z = [host(cdl.stream_embedding(X, k, SEED, sigma=6.0, tol=1e-12, max_iter=60, panel_rows=p)[1])
+         for p in (256, 768, 0)]
+    np.testing.assert_array_equal(Z[0], Z[1])
+    np.testing.assert_array_equal(Z[0], Z[2])
