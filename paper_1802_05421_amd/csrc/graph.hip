@@ -54,10 +54,13 @@ __device__ inline double block_sum256(double v, double *red) {
 
 // Whether this workgroup is the last of nb to come here (the ticket is 0
 // before the first and after the last); what the others wrote before is then
-// visible to it.  One thread's fences cover its workgroup (the barriers order
-// the rest): a fence per wave writes the L2 back as often (25 against 8 us for
-// 256 workgroups).  Every thread must call; `last` is a shared word.
+// visible to it.  Every wave first waits until its own stores and atomics have
+// reached the L2 (the barrier alone waits for LDS only); one thread's release
+// then publishes them for the whole workgroup, since a release per wave writes
+// the L2 back as often (25 against 8 us for 256 workgroups).  Every thread must
+// call; `last` is a shared word.
 __device__ __forceinline__ bool last_workgroup(unsigned int *ticket, unsigned int nb, int *last) {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
     if (threadIdx.x == 0) {
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
