@@ -185,10 +185,6 @@ template <> struct GramCfg<1> {
     using Core = Dma64Core<64, 64, 2, 2, 3>;
     static constexpr int WAVES = 3;
 };
-// The tiles' counts of keys below the bracket: words of the selection state's
-// candidate array (free until the last pass), one per 128 bytes.
-constexpr int kBelowParts = 64, kBelowPitch = 16;
-static_assert(kBelowParts * kBelowPitch <= kSelCap, "counts must fit the candidates");
 // What a launch covers: the upper triangle of the whole matrix, the upper
 // triangle's part of a row panel, or a whole row panel: its upper part, whose
 // tiles in the panel's own square are also stored mirrored (the same bits; half
@@ -413,7 +409,7 @@ __device__ __forceinline__ void gram_tile(const double *Xp, int64_t Tp, const do
             if (k1 > kmax0) atomicMax(&st->kmax, k1);
         }
         if (cnt) tbase = atomicAdd(&st->nbuf, over ? (unsigned long long)brcap + 1ull : cnt);
-        if (bl) atomicAdd(&st->cand[(blockIdx.x % kBelowParts) * kBelowPitch], bl);
+        if (bl) atomicAdd(&st->part[(blockIdx.x % kBelowParts) * kBelowPitch], bl);
     }
     if (!brbuf) return;
     if (count <= kSeg) {   // uniform over the wave
@@ -546,7 +542,7 @@ __device__ __forceinline__ void select_reset_body(SelectState *st) {
         st->kand = ~0ull;
         st->kor = 0ull;
     }
-    for (int q = threadIdx.x; q < kBelowParts; q += blockDim.x) st->cand[q * kBelowPitch] = 0;
+    for (int q = threadIdx.x; q < kBelowParts; q += blockDim.x) st->part[q * kBelowPitch] = 0;
 }
 
 __global__ void k_select_reset(SelectState *st) { select_reset_body(st); }
@@ -756,7 +752,7 @@ __device__ inline void select_bracket_view(const SelectState *st, int64_t cap, S
     unsigned long long below = st->below;
     const unsigned long long nb = st->nbuf;
 #pragma unroll 16
-    for (int q = 0; q < kBelowParts; ++q) below += st->cand[q * kBelowPitch];
+    for (int q = 0; q < kBelowParts; ++q) below += st->part[q * kBelowPitch];
     if (nb > (unsigned long long)cap || v.rank < below || v.rank >= below + nb) return;   // stay on the matrix
     v.src = 1;
     v.rank -= below;
@@ -776,7 +772,9 @@ __device__ inline void select_bracket_view(const SelectState *st, int64_t cap, S
 }
 
 // The start of a stored selection: target rank and common prefix of the keys,
-// then the bracket when one was gathered.
+// then the bracket when one was gathered.  Every workgroup of the first pass
+// makes it from the state while others of its launch may be passing already, so
+// it reads nothing that a pass writes.
 __device__ inline SelView select_start(const SelectState *st, int64_t n, int64_t cap, bool gathered) {
     SelView v;
     const unsigned long long N = (unsigned long long)n * (unsigned long long)(n - 1) / 2ull;

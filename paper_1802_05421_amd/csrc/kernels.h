@@ -13,7 +13,8 @@ int64_t pad_k(int64_t k);           // padded number of projection columns
 int64_t pad_t(int64_t T);           // padded series length (multiple of 16)
 
 // ---- graph ------------------------------------------------------------------
-constexpr int kSelCap = 4093;       // candidates that the state holds
+constexpr int kSelCap = 3069;       // candidates that the state holds
+constexpr int kBelowParts = 64, kBelowPitch = 16;   // counts of the Gram's tiles, a line each
 constexpr int kDegreeTicket = 16;   // word of a graph workspace's flags: workgroups done with the degrees
 struct SelectState {                // device scratch of the exact median selection
     unsigned long long prefix;      // selected high bits so far
@@ -27,6 +28,7 @@ struct SelectState {                // device scratch of the exact median select
     unsigned long long below;       // keys < lo
     unsigned long long nbuf;        // keys in [lo, hi] (appended to the bracket buffer)
     unsigned long long hist[4096];  // 64-bit: a bin can exceed 2^32 keys for n > 92681
+    unsigned long long part[kBelowParts * kBelowPitch];   // keys < lo counted by the Gram's tiles
     unsigned long long cand[kSelCap];
     unsigned long long kand, kor;   // AND and OR of the keys of the current digit's pass
     unsigned int ticket;            // workgroups done with the current pass

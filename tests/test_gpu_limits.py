@@ -1,0 +1,68 @@
+"""Calls at the ends of their ranges: groups that mix very small and large
+snapshots, edge scores that are no numbers, sizes past 32-bit offsets and launch
+limits."""
+
+import numpy as np
+import pytest
+import torch
+
+import gen
+
+pytestmark = pytest.mark.gpu
+
+SEED = gen.grid.PROJ_SEED
+
+
+@pytest.fixture(scope="module")
+def cdl():
+    import paper_1802_05421_amd as cdl
+    return cdl
+
+
+def dev(x):
+    return torch.from_numpy(np.ascontiguousarray(x)).cuda()
+
+
+def host(t):
+    torch.cuda.synchronize()
+    return t.cpu().numpy()
+
+
+def mixed_snapshots(sizes, T, seed):
+    """Random series on random subsets of one range of ids that share its ids 0..9."""
+    rng = np.random.default_rng(seed)
+    top = max(sizes) + 10
+    Xs, gids = [], []
+    for n in sizes:
+        ids = np.sort(np.append(np.arange(10), 10 + rng.choice(top - 10, n - 10, replace=False)))
+        Xs.append(dev(rng.standard_normal((n, T))))
+        gids.append(torch.from_numpy(ids.astype(np.int32)).cuda())
+    return Xs, gids
+
+
+def batched_equals_per_snapshot(cdl, Xs, gids, **kw):
+    """The one-pass sequence with its choices pinned: the per-snapshot path's bits."""
+    base = dict(k=16, seed=SEED, depth=2, tol=0.0, max_iter=3, top_k=5, **kw)
+    cdl.force_choice("apply", 0)
+    cdl.force_choice("residual", 0)
+    try:
+        wF, wT, _ = cdl.score_sequence(Xs, gids, cdl.SeqParams(**base))
+        Fb, Tb, _ = cdl.score_sequence(Xs, gids, cdl.SeqParams(**base, asynchronous=True, batched=True))
+    finally:
+        cdl.force_choice("apply", -1)
+        cdl.force_choice("residual", -1)
+    for t in range(len(wF)):
+        np.testing.assert_array_equal(host(Fb[t]), host(wF[t]), err_msg="pair %d" % t)
+        np.testing.assert_array_equal(host(Tb[t]), host(wT[t]), err_msg="pair %d" % t)
+
+
+# Beside a snapshot of more than 512 nodes the small ones' medians take the passes
+# of the whole chip.  Up to about 148 nodes a bracket holds at most 512 keys, which
+# the first pass already collects, while the snapshot's other workgroups may still
+# be reading the counts that say so.  The scores depend on every snapshot's
+# bandwidth, so equal bits mean equal bandwidths.
+@pytest.mark.parametrize("sizes", [[70, 3000, 100, 140], [600, 64, 148, 149, 70, 128] + [96, 127, 65, 141] * 5])
+def test_small_snapshots_beside_large_ones(cdl, sizes):
+    print("mixed group", sizes, flush=True)
+    Xs, gids = mixed_snapshots(sizes, 20, len(sizes))
+    batched_equals_per_snapshot(cdl, Xs, gids, prec="fp32")
