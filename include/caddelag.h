@@ -624,7 +624,9 @@ cdl_status cdl_anomaly_scores_noalloc(cdl_ctx *ctx, const double *Z0, const doub
  *   top_k       1..CDL_MAX_TOPK, at most m(m-1)/2.
  *   edge_a, edge_b  device outputs, top_k int32 common-node indices (a < b),
  *               sorted by descending score, ties by ascending (a, b).
- *   edge_val    device output, top_k FP64 scores.
+ *   edge_val    device output, top_k FP64 scores.  An edge whose score is not
+ *               a number has no place; where fewer than top_k are left, the
+ *               last entries are -infinity and their edge indices unspecified.
  *   ws          device workspace of cdl_edges_workspace_bytes(m, k, top_k).
  * Exact: the per-tile maxima of the fused score give a lower bound on the
  * K-th largest edge score (the K-th largest tile maximum); only tiles reaching

@@ -635,9 +635,10 @@ __global__ __launch_bounds__(kChunk) void k_topk(const double *val_in, const I *
 
 int64_t topk_scratch_elems(int64_t m, int K) { return cdiv(m, kChunk) * (int64_t)K; }
 
-// Rounds of k_topk on `count` pairs; the last round's K best go to val_out
-// (may be NULL) and idx_out.  scratch: 2 * topk_scratch_elems(count, K)
-// doubles and as many indices.
+// Rounds of k_topk on `count` pairs (none: one round of padding alone); the last
+// round's K best go to val_out (may be NULL) and idx_out, padded with -infinity
+// and the largest index.  scratch: 2 * topk_scratch_elems(count, K) doubles and as
+// many indices.
 template <typename I>
 static hipError_t topk_rounds(const double *val, const I *idx, int64_t count, int K, void *scratch,
                               double *val_out, I *idx_out, hipStream_t s) {
@@ -645,11 +646,12 @@ static hipError_t topk_rounds(const double *val, const I *idx, int64_t count, in
     double *v[2] = {(double *)scratch, (double *)scratch + sc};
     I *ix[2] = {(I *)((double *)scratch + 2 * sc), (I *)((double *)scratch + 2 * sc) + sc};
     for (int side = 0;; side ^= 1) {
-        const int64_t blocks = cdiv(count, kChunk);
+        const int64_t blocks = count > 0 ? cdiv(count, kChunk) : 1;
         const bool last = blocks == 1;
         hipLaunchKernelGGL(k_topk<I>, dim3((unsigned)blocks), dim3(kChunk), 0, s, val, idx, count, K,
                            last ? val_out : v[side], last ? idx_out : ix[side]);
-        if (last) return hipGetLastError();
+        const hipError_t e = hipGetLastError();
+        if (last || e != hipSuccess) return e;
         val = v[side];
         idx = ix[side];
         count = blocks * K;

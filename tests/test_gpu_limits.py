@@ -66,3 +66,28 @@ def test_small_snapshots_beside_large_ones(cdl, sizes):
     print("mixed group", sizes, flush=True)
     Xs, gids = mixed_snapshots(sizes, 20, len(sizes))
     batched_equals_per_snapshot(cdl, Xs, gids, prec="fp32")
+
+
+# Edge scores that are no numbers: the finite ones come first, in order, and
+# -infinity fills the rest.  With k = 1, vol = 1 and Z1 = 0 the score of (a, b) is
+# (z_a - z_b)^2, exact for small integers.
+@pytest.mark.parametrize("m,finite,K", [(300, 0, 20), (2, 0, 1), (300, 2, 20), (300, 5, 256), (700, 40, 50)])
+def test_edges_without_enough_numbers(cdl, m, finite, K):
+    print("edges m=%d with %d finite nodes, K=%d" % (m, finite, K), flush=True)
+    rng = np.random.default_rng(m + finite)
+    z = np.full(m, np.nan)
+    at = np.sort(rng.choice(m, finite, replace=False))
+    z[at] = rng.permutation(finite).astype(float)
+    st = dev(np.ones(4))
+    g = cdl.Graph(W=None, deg=dev(np.ones(m)), stats=st, n=m)
+    F, a, b, v = cdl.anomaly_edges(dev(z[:, None]), g, dev(np.zeros((m, 1))), g, top_k=K)
+    a, b, v = host(a), host(b), host(v)
+    i, j = np.triu_indices(finite, 1)
+    score = (z[at[i]] - z[at[j]]) ** 2
+    order = np.argsort(-score, kind="stable")[:K]   # ascending (a, b) among equals
+    c = len(order)
+    np.testing.assert_array_equal(v[:c], score[order])
+    np.testing.assert_array_equal(a[:c], at[i[order]])
+    np.testing.assert_array_equal(b[:c], at[j[order]])
+    assert np.all(v[c:] == -np.inf)
+    assert np.isnan(host(F)).all()
