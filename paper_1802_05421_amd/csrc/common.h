@@ -190,6 +190,15 @@ __host__ __device__ inline int rect_upper_tiles(int64_t ld) {
     return nrow * ncol - nrow * (nrow - 1);
 }
 
+// Launches whose workgroups may be so many that their work-items pass 2^32 along x
+// (such a launch is refused or, worse, wraps): a grid of rows of kGridRow, whose
+// workgroups at or past the total return.
+constexpr int64_t kGridRow = (int64_t)1 << 21;   // a multiple of the XCDs, times 1024 threads below 2^32
+inline dim3 grid_rows(int64_t total) {
+    return total <= kGridRow ? dim3((unsigned)total) : dim3((unsigned)kGridRow, (unsigned)cdiv(total, kGridRow));
+}
+__device__ inline int grid_row_id() { return (int)(blockIdx.y * gridDim.x + blockIdx.x); }
+
 __device__ inline int xcd_remap(int w, int total) {
     int x = w % kNumXcd, j = w / kNumXcd;
     int base = total / kNumXcd, rem = total % kNumXcd;

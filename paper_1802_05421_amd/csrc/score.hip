@@ -287,11 +287,13 @@ template <int SHAPE, bool WT>
 __global__ __launch_bounds__(ScoreCfg<SHAPE>::Core::NT, ScoreCfg<SHAPE>::WAVES) void k_score(
     const double *Zh, int64_t ldz, const double *sq, int64_t m, int64_t mpad, const double *W0,
     int64_t ld0, const double *W1, int64_t ld1, const int32_t *map0, const int32_t *map1,
-    double *part, double *tmax) {
+    double *part, double *tmax, int total) {
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
     __shared__ ScoreShared<SHAPE> sh;
+    const int w = grid_row_id();
+    if (w >= total) return;
     score_tile<SHAPE, WT>(Zh, ldz, sq, m, mpad, W0, ld0, W1, ld1, map0, map1, part, tmax,
-                          xcd_remap(blockIdx.x, gridDim.x), smem_raw, sh);
+                          xcd_remap(w, total), smem_raw, sh);
 }
 
 template <int SHAPE, bool WT>
@@ -308,8 +310,9 @@ static hipError_t score_launch(const double *Zh, int64_t ldz, const double *sq, 
         if (e != hipSuccess) return e;
         attr = true;
     }
-    hipLaunchKernelGGL((k_score<SHAPE, WT>), dim3(score_tile_count(SHAPE, mpad)), dim3(Core::NT),
-                       Core::SMEM, s, Zh, ldz, sq, m, mpad, W0, ld0, W1, ld1, map0, map1, part, tmax);
+    const int total = score_tile_count(SHAPE, mpad);
+    hipLaunchKernelGGL((k_score<SHAPE, WT>), grid_rows(total), dim3(Core::NT), Core::SMEM, s, Zh, ldz, sq,
+                       m, mpad, W0, ld0, W1, ld1, map0, map1, part, tmax, total);
     return hipGetLastError();
 }
 

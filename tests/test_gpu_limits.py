@@ -91,3 +91,27 @@ def test_edges_without_enough_numbers(cdl, m, finite, K):
     np.testing.assert_array_equal(b[:c], at[j[order]])
     assert np.all(v[c:] == -np.inf)
     assert np.isnan(host(F)).all()
+
+
+# With k = 1, vol = 1 and Z1 = 0 the score of (a, b) is (z_a - z_b)^2: F_a = m z_a^2 -
+# 2 z_a S1 + S2, every sum an integer below 2^53 and so exact.
+def one_column(cdl, z):
+    m = len(z)
+    g = cdl.Graph(W=None, deg=dev(np.ones(m)), stats=dev(np.ones(4)), n=m)
+    return dev(z[:, None]), g, dev(np.zeros((m, 1))), g
+
+
+def one_column_scores(z):
+    z = z.astype(np.int64)
+    return (len(z) * z * z - 2 * z * z.sum() + (z * z).sum()).astype(np.float64)
+
+
+# The tiles of the score Gram of 525000 common nodes have 2^32 work-items and more.
+def test_scores_past_a_launch_of_32_bits(cdl):
+    m = 525000
+    print("scores m=%d" % m, flush=True)
+    z = np.random.default_rng(m).integers(0, 4096, m).astype(float)
+    F, top = cdl.anomaly_scores(*one_column(cdl, z), top_k=50)
+    want = one_column_scores(z)
+    np.testing.assert_array_equal(host(F), want)
+    np.testing.assert_array_equal(host(top), np.lexsort((np.arange(m), -want))[:50])
