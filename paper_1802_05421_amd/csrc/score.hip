@@ -348,7 +348,7 @@ __global__ void k_edge_threshold(const double *tmax, const int32_t *tile_order, 
     *count = 0;
 }
 
-// Workgroup b: 64 x 64 part b % 8 of tile b / 8 (a reached tile's eight parts
+// Workgroup w: 64 x 64 part w % 8 of tile w / 8 (a reached tile's eight parts
 // on eight CUs: about K tiles are reached, so whole tiles left most of the
 // chip idle: 85 us with the threshold kernel against 43 at m = 9216, k = 128).
 __global__ __launch_bounds__(ScoreCfg<2>::Core::NT) void k_edge_collect(
@@ -359,7 +359,8 @@ __global__ __launch_bounds__(ScoreCfg<2>::Core::NT) void k_edge_collect(
     using Core = typename ScoreCfg<2>::Core;
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
     double *smem = (double *)smem_raw;
-    const int id = blockIdx.x >> 3, sub = blockIdx.x & 7, ncol = (int)(mpad / 128);
+    const int w = grid_row_id(), id = w >> 3, sub = w & 7, ncol = (int)(mpad / 128);
+    if (id >= rect_upper_tiles(mpad)) return;
     const double th = *tau;
     if (tmax[id] < th) return;   // uniform over the workgroup
     int I, J;
@@ -414,7 +415,7 @@ hipError_t launch_edge_collect(const double *Zh, int64_t k,
     const int total = rect_upper_tiles(mpad);
     hipLaunchKernelGGL(k_edge_threshold, dim3(1), dim3(64), 0, s, tmax, tile_order, K, total, tau,
                        count);
-    hipLaunchKernelGGL(k_edge_collect, dim3((unsigned)total * 8), dim3(Core::NT), Core::SMEM, s, Zh,
+    hipLaunchKernelGGL(k_edge_collect, grid_rows((int64_t)total * 8), dim3(Core::NT), Core::SMEM, s, Zh,
                        score_ldz(k), sq, m, W0, ld0, W1, ld1, map0, map1, weighted, mpad,
                        tmax, tau, cap, count, cval, cidx);
     return hipGetLastError();

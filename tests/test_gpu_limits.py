@@ -115,3 +115,18 @@ def test_scores_past_a_launch_of_32_bits(cdl):
     want = one_column_scores(z)
     np.testing.assert_array_equal(host(F), want)
     np.testing.assert_array_equal(host(top), np.lexsort((np.arange(m), -want))[:50])
+
+
+# So have the eight parts of every 256 x 128 tile of 371000 nodes, of which the
+# collection keeps those that reach the threshold.  The largest score is that of a
+# 0 and a 4095, which many pairs share: the first fifty in order of (a, b).
+def test_edges_past_a_launch_of_32_bits(cdl):
+    m, K = 371000, 50
+    print("edges m=%d" % m, flush=True)
+    z = np.random.default_rng(m).integers(0, 4096, m).astype(float)
+    F, a, b, v = cdl.anomaly_edges(*one_column(cdl, z), top_k=K)
+    np.testing.assert_array_equal(host(F), one_column_scores(z))
+    ends = np.flatnonzero((z == 0) | (z == 4095))
+    pairs = [(i, j) for i in ends for j in ends if i < j and z[i] != z[j]][:K]
+    assert len(pairs) == K and np.all(host(v) == 4095.0 ** 2)
+    assert list(zip(host(a).tolist(), host(b).tolist())) == pairs
