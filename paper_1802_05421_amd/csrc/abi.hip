@@ -2273,7 +2273,9 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
     HIPCHK(hipMemcpyAsync(dpre, pre.data(), pre.size() * sizeof(int), hipMemcpyHostToDevice, s));
     // the graph build and level-0 chains of all snapshots: descriptors and
     // prefix tables of the grouped launches
-    const int gram_shape = cdl::graph_gram_shape(P, lds.data());
+    std::vector<int64_t> lengths(P);
+    for (int t = 0; t < P; ++t) lengths[t] = sn[t].T;
+    const int gram_shape = cdl::graph_gram_shape(P, lds.data(), lengths.data());
     std::vector<cdl::GraphSnap> hg(P);
     std::vector<int> gpre((size_t)cdl::kGraphTables * (P + 1), 0), gtot(cdl::kGraphTables, 0);
     for (int t = 0; t < P; ++t) {

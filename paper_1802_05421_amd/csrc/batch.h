@@ -66,7 +66,7 @@ enum GraphTable {
 // starts with the sampled bracket).
 int graph_table_count(int tb, int64_t n, int64_t ld, bool bracket, int gram_shape);
 // Tile shape of the group's distance Gram.
-int graph_gram_shape(int P, const int64_t *ld);
+int graph_gram_shape(int P, const int64_t *ld, const int64_t *T);
 // Whether the stored selection of n keys' matrix starts with a sampled
 // bracket (the bracket must fit the buffer).
 bool select_uses_bracket(int64_t n, bool allowed);

@@ -177,6 +177,7 @@ __device__ inline void stage_and_store_rows(Core &g, O *sC, F f, O *C, int64_t l
 // just released.  The loop body is uniform; the last stage is peeled.
 
 typedef __attribute__((address_space(3))) void lds_void;
+typedef __attribute__((address_space(1))) void glb_void;
 
 template <int N> __device__ inline void wait_vmcnt() {
     static_assert(N >= 0 && N < 64, "vmcnt range");
@@ -408,7 +409,10 @@ template <> struct RowMf<float> : MfmaF32 {
     }
 };
 
-template <typename E, int BM, int BN, int WM, int WN, int NS = 2, int WK = 1>
+// FAR: the operands' rows lie more than 2^32 bytes apart from a tile's first to its
+// last, which the buffer loads' 32-bit offsets do not reach: the same loads by
+// 64-bit addresses.
+template <typename E, int BM, int BN, int WM, int WN, int NS = 2, int WK = 1, bool FAR = false>
 struct RowCore {
     using T = E;
     using MF = RowMf<T>;
@@ -434,26 +438,52 @@ struct RowCore {
 
     AccV acc[WTM][WTN];
 
+    // One operand panel as its loads address it: the resource, and this lane's
+    // offset in an even and an odd block of 8 rows (FAR: from its row's start).
+    struct Panel {
+        __amdgpu_buffer_rsrc_t rsrc;
+        const char *row;
+        int64_t ld;
+        uint32_t v0, v1;
+    };
+    __device__ static inline Panel panel(const T *A, int64_t ld, int64_t first, int rows) {
+        const int rl = (threadIdx.x & 63) >> 3, sl = threadIdx.x & 7;
+        const uint32_t o = FAR ? 0 : (uint32_t)(rl * ld * (int)sizeof(T));
+        Panel p;
+        if (!FAR)
+            p.rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)(A + first * ld), 0,
+                                                       (int)(rows * ld * (int)sizeof(T)), 0x00020000);
+        p.row = (const char *)(A + (first + rl) * ld);
+        p.ld = ld;
+        p.v0 = o + 16 * (sl ^ (rl >> 1));
+        p.v1 = o + 16 * (sl ^ ((rl >> 1) + 4));
+        return p;
+    }
+    // Block `blk` of 8 rows of the k-tile starting at element k0 into LDS at `dst`.
+    __device__ static inline void load_block(const Panel &p, uint32_t dst, int blk, int64_t k0) {
+        const int64_t o = ((int64_t)(blk * 8) * p.ld + k0) * (int)sizeof(T);
+        if constexpr (FAR)
+            __builtin_amdgcn_global_load_lds((const glb_void *)(p.row + o + (blk & 1 ? p.v1 : p.v0)),
+                                             (lds_void *)(uintptr_t)dst, 16, 0, 0);
+        else
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(p.rsrc, (lds_void *)(uintptr_t)dst, 16,
+                                                     blk & 1 ? p.v1 : p.v0, (uint32_t)o, 0, 0);
+    }
+
     // Loads of the k-tile starting at element k0 into the LDS stage at byte
     // offset `stage`.
-    __device__ inline void issue(uint32_t stage, __amdgpu_buffer_rsrc_t ra, __amdgpu_buffer_rsrc_t rb,
-                                 int64_t lda, int64_t ldb, int64_t k0, int w, uint32_t va0,
-                                 uint32_t va1, uint32_t vb0, uint32_t vb1) {
+    __device__ inline void issue(uint32_t stage, const Panel &pa, const Panel &pb, int64_t k0, int w) {
 #pragma unroll
         for (int q = 0; q < AI; ++q) {
             int blk = w + q * NW;
             if (AB % NW) blk = blk < AB ? blk : AB - 1;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                ra, (lds_void *)(uintptr_t)(stage + blk * 1024), 16, blk & 1 ? va1 : va0,
-                (uint32_t)(((int64_t)(blk * 8) * lda + k0) * (int)sizeof(T)), 0, 0);
+            load_block(pa, stage + blk * 1024, blk, k0);
         }
 #pragma unroll
         for (int q = 0; q < BI; ++q) {
             int blk = w + q * NW;
             if (BB % NW) blk = blk < BB ? blk : BB - 1;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(
-                rb, (lds_void *)(uintptr_t)(stage + BM * ROWB + blk * 1024), 16, blk & 1 ? vb1 : vb0,
-                (uint32_t)(((int64_t)(blk * 8) * ldb + k0) * (int)sizeof(T)), 0, 0);
+            load_block(pb, stage + BM * ROWB + blk * 1024, blk, k0);
         }
     }
 
@@ -519,19 +549,11 @@ struct RowCore {
         if (nk == 0) return;
         const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
         const uint32_t s0 = (uint32_t)(uintptr_t)(lds_void *)smem;
-        __amdgpu_buffer_rsrc_t ra = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(A + m0 * lda), 0, (int)(BM * lda * (int)sizeof(T)), 0x00020000);
-        __amdgpu_buffer_rsrc_t rb = __builtin_amdgcn_make_buffer_rsrc(
-            (void *)(B + n0 * ldb), 0, (int)(BN * ldb * (int)sizeof(T)), 0x00020000);
-        // this lane's offset within a block of 8 rows: even and odd blocks
-        const int rl = (threadIdx.x & 63) >> 3, sl = threadIdx.x & 7;
-        const uint32_t c0 = 16 * (sl ^ (rl >> 1)), c1 = 16 * (sl ^ ((rl >> 1) + 4));
-        const uint32_t oa = (uint32_t)(rl * lda * (int)sizeof(T)), ob = (uint32_t)(rl * ldb * (int)sizeof(T));
-        const uint32_t va0 = oa + c0, va1 = oa + c1, vb0 = ob + c0, vb1 = ob + c1;
+        const Panel pa = panel(A, lda, m0, BM), pb = panel(B, ldb, n0, BN);
         // the first NS stages, then wait for stage 0
 #pragma unroll
         for (int p = 0; p < NS; ++p)
-            if (p < nk) issue(s0 + p * STAGE, ra, rb, lda, ldb, (int64_t)p * BK, w, va0, va1, vb0, vb1);
+            if (p < nk) issue(s0 + p * STAGE, pa, pb, (int64_t)p * BK, w);
         if (nk >= NS) wait_vmcnt<(NS - 1) * (AI + BI)>();
         else wait_vmcnt<0>();
         lds_barrier();
@@ -558,8 +580,7 @@ struct RowCore {
             mmas(f[1]);
             interleave();
             // nobody reads stage kt any more
-            if (kt + NS < nk)
-                issue(s0 + cur * STAGE, ra, rb, lda, ldb, (int64_t)(kt + NS) * BK, w, va0, va1, vb0, vb1);
+            if (kt + NS < nk) issue(s0 + cur * STAGE, pa, pb, (int64_t)(kt + NS) * BK, w);
             cur = nxt;
         }
         const char *sc = smem + cur * STAGE;
@@ -611,6 +632,7 @@ struct RowCore {
     }
 };
 
-template <int BM, int BN, int WM, int WN, int NS = 2> using Dma64Core = RowCore<double, BM, BN, WM, WN, NS>;
+template <int BM, int BN, int WM, int WN, int NS = 2, bool FAR = false>
+using Dma64Core = RowCore<double, BM, BN, WM, WN, NS, 1, FAR>;
 
 } // namespace cdl

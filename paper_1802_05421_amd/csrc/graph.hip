@@ -173,7 +173,7 @@ hipError_t launch_pad_series(const double *X, int64_t n, int64_t T, int64_t ldx,
 // workgroups on a CU; the cover's 256 x 128 tiles (whose order shares operand
 // panels in an XCD's L2) are each computed as two such halves.  1: 64 x 64 by
 // four waves, three on a CU, for sizes that 128 x 128 tiles cannot spread over
-// the CUs.  What a tile costs beside its MFMAs (2 n^2 T / 2 flop in all) is
+// the CUs.  2: the same with 64-bit addresses, for very long series.  What a tile costs beside its MFMAs (2 n^2 T / 2 flop in all) is
 // the first loads and the epilogue: distances, median bracket, stores; other
 // workgroups' MFMAs run beside them.
 template <int SHAPE> struct GramCfg;
@@ -185,6 +185,13 @@ template <> struct GramCfg<1> {
     using Core = Dma64Core<64, 64, 2, 2, 3>;
     static constexpr int WAVES = 3;
 };
+template <> struct GramCfg<2> {
+    using Core = Dma64Core<64, 64, 2, 2, 3, true>;
+    static constexpr int WAVES = 3;
+};
+// Padded series lengths from which shape 2 takes over: 128 rows of 2^22 values
+// are 2^32 bytes, the reach of the other shapes' offsets.
+constexpr int64_t kGramFar = (int64_t)1 << 22;
 // What a launch covers: the upper triangle of the whole matrix, the upper
 // triangle's part of a row panel, or a whole row panel: its upper part, whose
 // tiles in the panel's own square are also stored mirrored (the same bits; half
@@ -202,7 +209,8 @@ static int64_t gram_wgs(int shape, GramCover cover, int64_t ld, int64_t row0, in
 
 // The busiest CU's work in 64 x 64 tiles: the small tiles' rate is 0.8 of the
 // large ones' (twice the first loads and operand traffic per flop).
-static int gram_shape(GramCover cover, int64_t ld, int64_t row0, int64_t rows) {
+static int gram_shape(GramCover cover, int64_t ld, int64_t Tp, int64_t row0, int64_t rows) {
+    if (Tp >= kGramFar) return 2;
     const double t0 = 4.0 * (double)cdiv(gram_wgs(0, cover, ld, row0, rows), 256);
     const double t1 = (double)cdiv(gram_wgs(1, cover, ld, row0, rows), 256) / 0.8;
     return t1 < t0 ? 1 : 0;
@@ -473,13 +481,22 @@ static hipError_t gram_launch(const double *Xp, int64_t Tp, const double *sqn, i
     return hipGetLastError();
 }
 
+template <bool kExp, bool kPanel>
+static hipError_t gram_any(const double *Xp, int64_t Tp, const double *sqn, int64_t n, int64_t ld, double *D2,
+                           int64_t row0, int64_t rows, GramCover cover, SelectState *st,
+                           const double *wstats, unsigned long long *brbuf, int64_t brcap, hipStream_t s) {
+    switch (gram_shape(cover, ld, Tp, row0, rows)) {
+    case 0: return gram_launch<0, kExp, kPanel>(Xp, Tp, sqn, n, ld, D2, row0, rows, cover, st, wstats, brbuf, brcap, s);
+    case 1: return gram_launch<1, kExp, kPanel>(Xp, Tp, sqn, n, ld, D2, row0, rows, cover, st, wstats, brbuf, brcap, s);
+    default: return gram_launch<2, kExp, kPanel>(Xp, Tp, sqn, n, ld, D2, row0, rows, cover, st, wstats, brbuf, brcap, s);
+    }
+}
+
 hipError_t launch_gram_dist(const double *Xp, int64_t Tp, const double *sqn, int64_t n,
                             int64_t ld, double *D2, SelectState *st, unsigned long long *brbuf,
                             int64_t brcap, hipStream_t s) {
     if (brbuf && !st) return hipErrorInvalidValue;
-    if (gram_shape(kGramUpper, ld, 0, ld) == 1)
-        return gram_launch<1, false, false>(Xp, Tp, sqn, n, ld, D2, 0, ld, kGramUpper, st, nullptr, brbuf, brcap, s);
-    return gram_launch<0, false, false>(Xp, Tp, sqn, n, ld, D2, 0, ld, kGramUpper, st, nullptr, brbuf, brcap, s);
+    return gram_any<false, false>(Xp, Tp, sqn, n, ld, D2, 0, ld, kGramUpper, st, nullptr, brbuf, brcap, s);
 }
 
 int64_t gram_panel_tiles(int64_t ld, int64_t row0, int64_t rows, bool full) {
@@ -493,15 +510,9 @@ hipError_t launch_gram_panel(const double *Xp, int64_t Tp, const double *sqn, in
     if (row0 % 256 || rows % 256 || rows <= 0 || row0 + rows > ld) return hipErrorInvalidValue;
     if (wstats && !full) return hipErrorInvalidValue;
     const GramCover cover = full ? kGramPanelFull : kGramPanelUpper;
-    const bool small = gram_shape(cover, ld, row0, rows) == 1;
-    if (wstats)
-        return small ? gram_launch<1, true, true>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, wstats, nullptr, 0, s)
-                     : gram_launch<0, true, true>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, wstats, nullptr, 0, s);
-    if (full)
-        return small ? gram_launch<1, false, true>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, nullptr, nullptr, 0, s)
-                     : gram_launch<0, false, true>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, nullptr, nullptr, 0, s);
-    return small ? gram_launch<1, false, false>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, nullptr, nullptr, 0, s)
-                 : gram_launch<0, false, false>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, nullptr, nullptr, 0, s);
+    if (wstats) return gram_any<true, true>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, wstats, nullptr, 0, s);
+    if (full) return gram_any<false, true>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, nullptr, nullptr, 0, s);
+    return gram_any<false, false>(Xp, Tp, sqn, n, ld, D2p, row0, rows, cover, nullptr, nullptr, nullptr, 0, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -1565,7 +1576,9 @@ bool select_uses_bracket(int64_t n, bool allowed) {
     return allowed && N * 2.0 * kSelMargin / kSelSample <= 0.8 * (double)select_buffer_keys(n);
 }
 
-int graph_gram_shape(int P, const int64_t *ld) {
+int graph_gram_shape(int P, const int64_t *ld, const int64_t *T) {
+    for (int t = 0; t < P; ++t)
+        if (pad_t(T[t]) >= kGramFar) return 2;
     int64_t c0 = 0, c1 = 0;
     for (int t = 0; t < P; ++t) {
         c0 += gram_wgs(0, kGramUpper, ld[t], 0, ld[t]);
@@ -1706,9 +1719,12 @@ hipError_t launch_graph_grouped(const GraphSnap *snaps, const int *tables, const
         hipLaunchKernelGGL(k_select_rank_grouped, dim3(totals[kGtSample]), dim3(1024), 0, s, snaps,
                            tb(kGtSample), P);
     }
-    hipError_t e = gram_shape == 1
-        ? gram_grouped_launch<1>(snaps, tb(kGtGram), totals[kGtGram], P, select ? 1 : 0, s)
-        : gram_grouped_launch<0>(snaps, tb(kGtGram), totals[kGtGram], P, select ? 1 : 0, s);
+    hipError_t e;
+    switch (gram_shape) {
+    case 0: e = gram_grouped_launch<0>(snaps, tb(kGtGram), totals[kGtGram], P, select ? 1 : 0, s); break;
+    case 1: e = gram_grouped_launch<1>(snaps, tb(kGtGram), totals[kGtGram], P, select ? 1 : 0, s); break;
+    default: e = gram_grouped_launch<2>(snaps, tb(kGtGram), totals[kGtGram], P, select ? 1 : 0, s); break;
+    }
     if (e != hipSuccess) return e;
     if (select) {
         // the passes that the largest snapshot takes

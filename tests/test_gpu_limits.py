@@ -130,3 +130,36 @@ def test_edges_past_a_launch_of_32_bits(cdl):
     pairs = [(i, j) for i in ends for j in ends if i < j and z[i] != z[j]][:K]
     assert len(pairs) == K and np.all(host(v) == 4095.0 ** 2)
     assert list(zip(host(a).tolist(), host(b).tolist())) == pairs
+
+
+# Series so long that a tile's rows lie 2^32 bytes apart (64 rows of 2^23 values).
+# Small integers: every distance is exact, whatever the order of its sum.
+@pytest.mark.parametrize("n,T", [(70, (1 << 23) + 5), (3, (1 << 22) + 7)])
+def test_series_past_32_bit_offsets(cdl, n, T):
+    print("long series n=%d T=%d" % (n, T), flush=True)
+    g = torch.Generator(device="cuda").manual_seed(n)
+    X = torch.randint(-2, 3, (n, T), generator=g, device="cuda").double()
+    G = torch.zeros((n, n), dtype=torch.float64, device="cuda")
+    for c in range(0, T, 1 << 21):
+        G += X[:, c:c + (1 << 21)] @ X[:, c:c + (1 << 21)].T.contiguous()
+    D2 = host(G.diag()[:, None] + G.diag()[None, :] - 2.0 * G)
+    d = np.sort(D2[np.triu_indices(n, 1)])
+    sigma = np.sqrt(d[(len(d) - 1) // 2])
+    W = np.exp(-D2 / sigma ** 2)
+    np.fill_diagonal(W, 0.0)
+    for mode in (0, 1):
+        cdl.set_select(mode)
+        try:
+            got = cdl.build_graph(X)
+        finally:
+            cdl.set_select(0)
+        assert got.host_stats()["sigma"] == sigma
+        np.testing.assert_allclose(host(got.W)[:n, :n], W, rtol=1e-14)
+        del got
+    st, Z, info = cdl.stream_embedding(X, 2, SEED, tol=1e-9, max_iter=60)
+    assert info.converged and st.host_stats()["sigma"] == sigma
+    np.testing.assert_allclose(host(st.deg), W.sum(1), rtol=1e-13)
+    del st, Z
+    if n > 4:
+        gid = torch.arange(n, dtype=torch.int32, device="cuda")
+        batched_equals_per_snapshot(cdl, [X, X], [gid, gid], prec="fp32")
