@@ -1833,7 +1833,7 @@ cdl_status cdl_anomaly_edges(cdl_ctx *ctx, const double *Z0, const double *W0,
     { Timed t_(ctx, "score_reduce"); HIPCHK(launch_score_reduce(shape, w.part, m, mp, F, s)); }
     const int nt2 = score_tiles_2d(mp);
     { Timed t_(ctx, "topk"); HIPCHK(launch_topk(e.tmax, nt2, std::min(top_k, nt2), e.tscratch, e.order, s)); }
-    { Timed t_(ctx, "edge_collect"); HIPCHK(launch_edge_collect(w.Zh, k, w.sq, m, mp, W0, pad_n(n0), W1, pad_n(n1),
+    { Timed t_(ctx, "edge_collect"); HIPCHK(launch_edge_collect(shape, w.Zh, k, w.sq, m, mp, W0, pad_n(n0), W1, pad_n(n1),
                                map0, map1, weighted, e.tmax, e.order, top_k, e.tau, e.cap,
                                e.count, e.cval, e.cidx, s)); }
     // the number of candidates (a few times top_k out of e.cap) sets the

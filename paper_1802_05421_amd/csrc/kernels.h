@@ -268,8 +268,8 @@ hipError_t launch_score(int shape, const double *Zh, int64_t k, const double *sq
 int score_tiles_2d(int64_t mpad);
 // tile_order: tile indices by descending maximum (first K used); sets tau
 // and clears *count, then appends the edges with score >= tau to
-// (cval, cidx) through *count (at most cap stored).
-hipError_t launch_edge_collect(const double *Zh, int64_t k,
+// (cval, cidx) through *count (at most cap stored).  shape: the scores'.
+hipError_t launch_edge_collect(int shape, const double *Zh, int64_t k,
                                const double *sq, int64_t m, int64_t mpad, const double *W0,
                                int64_t ld0, const double *W1, int64_t ld1,
                                const int32_t *map0, const int32_t *map1, int weighted,

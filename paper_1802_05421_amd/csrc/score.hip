@@ -81,19 +81,20 @@ hipError_t launch_build_zhat(const double *Z0, const double *Z1, const int32_t *
 
 // Tile shapes of the score Gram (the same edge scores from each).  0: 256 x
 // 128 in bands of four row blocks; 1 and 2: square tiles, two or three
-// workgroups on a CU.  Only pairs a < b count: a tile straddling the diagonal
+// workgroups on a CU; 3: as 2 with 64-bit addresses, for very many columns.  Only pairs a < b count: a tile straddling the diagonal
 // also holds pairs a > b, whose mirror images another element covers.
 constexpr int kScoreShapes = 3;
+constexpr int kScoreFar = 3;
 template <int SHAPE> struct ScoreCfg {
     static constexpr int WM = SHAPE == 0 ? 4 : 2, WN = SHAPE == 1 ? 4 : 2;
-    static constexpr int TM = SHAPE == 0 ? 256 : SHAPE == 1 ? 128 : 64, TN = SHAPE == 2 ? 64 : 128;
+    static constexpr int TM = SHAPE == 0 ? 256 : SHAPE == 1 ? 128 : 64, TN = SHAPE >= 2 ? 64 : 128;
     // waves per SIMD that the registers must leave room for: one, two and
     // three workgroups on a CU
     static constexpr int WAVES = SHAPE == 0 ? 2 : SHAPE == 1 ? 4 : 3;
-    using Core = Dma64Core<TM, TN, WM, WN, SHAPE == 2 ? 3 : 2>;
+    using Core = Dma64Core<TM, TN, WM, WN, SHAPE >= 2 ? 3 : 2, SHAPE == kScoreFar>;
 };
 static int64_t score_tm(int shape) { return shape == 0 ? 256 : shape == 1 ? 128 : 64; }
-static int64_t score_tn(int shape) { return shape == 2 ? 64 : 128; }
+static int64_t score_tn(int shape) { return shape >= 2 ? 64 : 128; }
 
 int score_tile_count(int shape, int64_t mpad) {
     if (shape == 0) return rect_upper_tiles(mpad);
@@ -118,7 +119,10 @@ int64_t score_part_doubles(int64_t mpad, int64_t kpad) {
 // large products); on 20 to 600 large tiles the last round of CUs costs more
 // than that.  Weighted scores are bound by the gathers of the weights as well,
 // which only the 64 x 64 tiles keep in flight (a tenth more for the others).
+// From 2^20 columns on the rows of a 256-row tile take 2^32 bytes, which the
+// first three shapes' offsets do not.
 int score_shape(int P, const int64_t *mpad, int64_t kpad, int weighted) {
+    if (score_ldz(kpad) >= (int64_t)1 << 21) return kScoreFar;
     int best = 0;
     double tb = 1e300;
     for (int q = 0; q < kScoreShapes; ++q) {
@@ -193,7 +197,7 @@ __device__ __forceinline__ void score_tile(const double *Zh, int64_t ldz,
         j0[b] = WT && map0 ? map0[c] : c;
         j1[b] = WT && map1 ? map1[c] : c;
     }
-    constexpr bool PRE = WT && SHAPE == 2;   // (the larger shapes have no registers for it)
+    constexpr bool PRE = WT && SHAPE >= 2;   // (the larger shapes have no registers for it)
 #pragma unroll
     for (int a = 0; a < Core::WTM; ++a) {
         // the weights of four rows, all loads in flight (indices clamped into
@@ -325,7 +329,7 @@ hipError_t launch_score(int shape, const double *Zh, int64_t k, const double *sq
     switch (2 * shape + (weighted ? 1 : 0)) {
 #define CDL_CASE(q, w) \
     case 2 * q + w: return score_launch<q, w>(Zh, ldz, sq, m, mpad, W0, ld0, W1, ld1, map0, map1, part, tmax, s);
-    CDL_CASE(0, 0) CDL_CASE(0, 1) CDL_CASE(1, 0) CDL_CASE(2, 0) CDL_CASE(2, 1)
+    CDL_CASE(0, 0) CDL_CASE(0, 1) CDL_CASE(1, 0) CDL_CASE(2, 0) CDL_CASE(2, 1) CDL_CASE(3, 0) CDL_CASE(3, 1)
 #undef CDL_CASE
     default: return hipErrorInvalidValue;
     }
@@ -351,12 +355,13 @@ __global__ void k_edge_threshold(const double *tmax, const int32_t *tile_order, 
 // Workgroup w: 64 x 64 part w % 8 of tile w / 8 (a reached tile's eight parts
 // on eight CUs: about K tiles are reached, so whole tiles left most of the
 // chip idle: 85 us with the threshold kernel against 43 at m = 9216, k = 128).
-__global__ __launch_bounds__(ScoreCfg<2>::Core::NT) void k_edge_collect(
+template <int SHAPE>
+__global__ __launch_bounds__(ScoreCfg<SHAPE>::Core::NT) void k_edge_collect(
     const double *Zh, int64_t ldz, const double *sq, int64_t m,
     const double *W0, int64_t ld0, const double *W1, int64_t ld1, const int32_t *map0,
     const int32_t *map1, int weighted, int64_t mpad, const double *tmax,
     const double *tau, int64_t cap, unsigned int *count, double *cval, int64_t *cidx) {
-    using Core = typename ScoreCfg<2>::Core;
+    using Core = typename ScoreCfg<SHAPE>::Core;
     extern __shared__ __attribute__((aligned(16))) char smem_raw[];
     double *smem = (double *)smem_raw;
     const int w = grid_row_id(), id = w >> 3, sub = w & 7, ncol = (int)(mpad / 128);
@@ -396,29 +401,41 @@ __global__ __launch_bounds__(ScoreCfg<2>::Core::NT) void k_edge_collect(
         }
 }
 
-hipError_t launch_edge_collect(const double *Zh, int64_t k,
+template <int SHAPE>
+static hipError_t edge_collect_launch(const double *Zh, int64_t ldz, const double *sq, int64_t m,
+                                      int64_t mpad, const double *W0, int64_t ld0, const double *W1,
+                                      int64_t ld1, const int32_t *map0, const int32_t *map1,
+                                      int weighted, const double *tmax, const double *tau, int64_t cap,
+                                      unsigned int *count, double *cval, int64_t *cidx, hipStream_t s) {
+    using Core = typename ScoreCfg<SHAPE>::Core;
+    static bool attr = false;
+    if (!attr) {
+        hipError_t e = hipFuncSetAttribute((const void *)k_edge_collect<SHAPE>,
+                                           hipFuncAttributeMaxDynamicSharedMemorySize,
+                                           (int)Core::SMEM);
+        if (e != hipSuccess) return e;
+        attr = true;
+    }
+    hipLaunchKernelGGL(k_edge_collect<SHAPE>, grid_rows((int64_t)rect_upper_tiles(mpad) * 8), dim3(Core::NT),
+                       Core::SMEM, s, Zh, ldz, sq, m, W0, ld0, W1, ld1, map0, map1, weighted, mpad,
+                       tmax, tau, cap, count, cval, cidx);
+    return hipGetLastError();
+}
+
+hipError_t launch_edge_collect(int shape, const double *Zh, int64_t k,
                                const double *sq, int64_t m, int64_t mpad, const double *W0,
                                int64_t ld0, const double *W1, int64_t ld1,
                                const int32_t *map0, const int32_t *map1, int weighted,
                                const double *tmax, const int32_t *tile_order, int K,
                                double *tau, int64_t cap, unsigned int *count, double *cval,
                                int64_t *cidx, hipStream_t s) {
-    using Core = typename ScoreCfg<2>::Core;
-    static bool attr = false;
-    if (!attr) {
-        hipError_t e = hipFuncSetAttribute((const void *)k_edge_collect,
-                                           hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           (int)Core::SMEM);
-        if (e != hipSuccess) return e;
-        attr = true;
-    }
-    const int total = rect_upper_tiles(mpad);
-    hipLaunchKernelGGL(k_edge_threshold, dim3(1), dim3(64), 0, s, tmax, tile_order, K, total, tau,
-                       count);
-    hipLaunchKernelGGL(k_edge_collect, grid_rows((int64_t)total * 8), dim3(Core::NT), Core::SMEM, s, Zh,
-                       score_ldz(k), sq, m, W0, ld0, W1, ld1, map0, map1, weighted, mpad,
-                       tmax, tau, cap, count, cval, cidx);
-    return hipGetLastError();
+    hipLaunchKernelGGL(k_edge_threshold, dim3(1), dim3(64), 0, s, tmax, tile_order, K,
+                       rect_upper_tiles(mpad), tau, count);
+    if (shape == kScoreFar)
+        return edge_collect_launch<kScoreFar>(Zh, score_ldz(k), sq, m, mpad, W0, ld0, W1, ld1, map0, map1,
+                                              weighted, tmax, tau, cap, count, cval, cidx, s);
+    return edge_collect_launch<2>(Zh, score_ldz(k), sq, m, mpad, W0, ld0, W1, ld1, map0, map1, weighted,
+                                  tmax, tau, cap, count, cval, cidx, s);
 }
 
 // flag = 1 if some entry of map0 lies outside [0, n0) or of map1 outside
@@ -526,7 +543,7 @@ hipError_t launch_score_grouped(int shape, const BatchPair *pairs, const int *pr
     switch (2 * shape + (weighted ? 1 : 0)) {
 #define CDL_CASE(q, w) \
     case 2 * q + w: e = score_grouped_launch<q, w>(pairs, prefix_score, total_score, P, ldz, s); break;
-    CDL_CASE(0, 0) CDL_CASE(0, 1) CDL_CASE(1, 0) CDL_CASE(2, 0) CDL_CASE(2, 1)
+    CDL_CASE(0, 0) CDL_CASE(0, 1) CDL_CASE(1, 0) CDL_CASE(2, 0) CDL_CASE(2, 1) CDL_CASE(3, 0) CDL_CASE(3, 1)
 #undef CDL_CASE
     default: return hipErrorInvalidValue;
     }

@@ -163,3 +163,35 @@ def test_series_past_32_bit_offsets(cdl, n, T):
     if n > 4:
         gid = torch.arange(n, dtype=torch.int32, device="cuda")
         batched_equals_per_snapshot(cdl, [X, X], [gid, gid], prec="fp32")
+
+
+# Embeddings of so many columns that a score tile's rows lie 2^32 bytes apart; small
+# integers, so that every score is exact.
+@pytest.mark.parametrize("mode", ["unweighted", "delta_a"])
+def test_scores_past_32_bit_offsets(cdl, mode):
+    n, k, K = 70, (1 << 22) + 3, 20
+    print("scores of %d columns, %s" % (k, mode), flush=True)
+    gen_ = torch.Generator(device="cuda").manual_seed(k)
+    Z, C, W, gs = [], [], [], []
+    for t in range(2):
+        z = torch.randint(-1, 2, (n, k), generator=gen_, device="cuda").double()
+        G = z @ z.T.contiguous()
+        C.append(host(G.diag()[:, None] + G.diag()[None, :] - 2.0 * G))
+        A = np.zeros((cdl.ld(n), cdl.ld(n)))
+        B = np.triu(np.random.default_rng(t).integers(1, 9, (n, n)), 1).astype(float)
+        A[:n, :n] = B + B.T
+        Z.append(z)
+        W.append(A[:n, :n])
+        gs.append(cdl.Graph(W=dev(A), deg=dev(np.ones(n)), stats=dev(np.ones(4)), n=n))
+    E = np.abs(C[0] - C[1])
+    if mode == "delta_a":
+        E = E * np.abs(W[1] - W[0])
+    F, top = cdl.anomaly_scores(Z[0], gs[0], Z[1], gs[1], mode=mode, top_k=K)
+    np.testing.assert_array_equal(host(F), E.sum(1))
+    F, a, b, v = cdl.anomaly_edges(Z[0], gs[0], Z[1], gs[1], mode=mode, top_k=K)
+    np.testing.assert_array_equal(host(F), E.sum(1))
+    i, j = np.triu_indices(n, 1)
+    order = np.argsort(-E[i, j], kind="stable")[:K]
+    np.testing.assert_array_equal(host(v), E[i, j][order])
+    np.testing.assert_array_equal(host(a), i[order])
+    np.testing.assert_array_equal(host(b), j[order])
