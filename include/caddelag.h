@@ -164,7 +164,10 @@ typedef struct {
  * whole group (the smallest that gives two workgroups per CU), so the
  * results equal the per-snapshot path's to rounding; with the "apply" and
  * "residual" choices pinned on the context (cdl_ctx_force_choice) each
- * snapshot keeps its own counts and the results are bit for bit the same. */
+ * snapshot keeps its own counts and each pair its own score tiles, and the
+ * results are bit for bit the same (16-bit levels of more than 5632 nodes:
+ * with "square" pinned to 1 as well, since the groups' squarings do not split
+ * their last round). */
 #define CDL_SEQ_BATCHED 4
 
 typedef struct {

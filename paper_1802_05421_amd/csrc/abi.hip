@@ -1957,7 +1957,8 @@ struct BatchLayout {
 // Streams of a one-pass sequence's right-hand sides: the context's stream,
 // its second stream and two more.
 constexpr int kSeqStreams = 4;
-constexpr int kBatchTables = 10;   // prefix tables of the grouped launches
+constexpr int kTableScore = 8;     // the score tiles' tables, one per shape
+constexpr int kBatchTables = kTableScore + cdl::kScoreShapes;   // prefix tables of the grouped launches
 
 BatchLayout batch_layout(int32_t n_snap, const cdl_snapshot *sn, const cdl_seq_params *q) {
     BatchLayout L;
@@ -2235,7 +2236,7 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
     }
     // prefix tables: 0 squaring, 1 apply product, 2 apply update, 3 residual
     // product, 4 residual reduction, 5 FP16 operand, 6 signature rows,
-    // 7 score tiles, 8 score reduction
+    // 7 score reduction, then the score tiles by shape
     std::vector<int> pre((size_t)kBatchTables * (P + 1), 0);
     auto table = [&](int id) { return pre.data() + (size_t)id * (P + 1); };
     auto fill = [&](int id, int cnt, const std::function<int(int)> &f) {
@@ -2260,9 +2261,17 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
     const int tot_zh = fill(6, NP, [&](int t) { return (int)hp[t].mpad; });
     std::vector<int64_t> mpads(NP);
     for (int t = 0; t < NP; ++t) mpads[t] = hp[t].mpad;
-    const int sc_shape = score_shape(NP, mpads.data(), kp, q->mode == CDL_SCORE_DELTA_A);
-    const int tot_sc = fill(7, NP, [&](int t) { return score_tile_count(sc_shape, mpads[t]); });
-    const int tot_sr = fill(8, NP, [&](int t) { return (int)((hp[t].m + 63) / 64); });
+    // One tile shape for all pairs; with the splits pinned each pair's own, since
+    // the order in which a node's partial sums are added goes by the tiles.
+    const int weighted_sc = q->mode == CDL_SCORE_DELTA_A;
+    const bool own = pin_ap >= 0 && pin_res >= 0;
+    const int sc_shape = score_shape(NP, mpads.data(), kp, weighted_sc);
+    for (int t = 0; t < NP; ++t) hp[t].shape = own ? score_shape(1, &mpads[t], kp, weighted_sc) : sc_shape;
+    int tot_sc[cdl::kScoreShapes];
+    for (int c = 0; c < cdl::kScoreShapes; ++c)
+        tot_sc[c] = fill(kTableScore + c, NP,
+                         [&](int t) { return hp[t].shape == c ? score_tile_count(c, mpads[t]) : 0; });
+    const int tot_sr = fill(7, NP, [&](int t) { return (int)((hp[t].m + 63) / 64); });
     BatchSnap *dsnap = (BatchSnap *)(base + L.snaps);
     BatchPair *dpair = (BatchPair *)(base + L.pairs);
     int *dpre = (int *)(base + L.prefix);
@@ -2381,7 +2390,7 @@ static cdl_status score_sequence_batched(cdl_ctx *ctx, int32_t n_snap, const cdl
         for (int t = 0; t < P; ++t)
             { Timed t_(ctx, "finalize_z"); HIPCHK(launch_finalize_z2(solves[t].Xt, hs[t].ld, sn[t].n, kp, k, solves[t].mean,
                                                              (double *)(base + L.Z[t]), s0)); }
-        { Timed t_(ctx, "score"); HIPCHK(cdl::launch_score_grouped(sc_shape, dpair, dtable(6), tot_zh, dtable(7), tot_sc, dtable(8), tot_sr, NP, k,
+        { Timed t_(ctx, "score"); HIPCHK(cdl::launch_score_grouped(dpair, dtable(6), tot_zh, dtable(kTableScore), P + 1, tot_sc, dtable(7), tot_sr, NP, k,
                                                              weighted, s0)); }
         if (top_idx && q->top_k > 0)
             { Timed t_(ctx, "topk"); HIPCHK(cdl::launch_topk_grouped(dpair, mcnt.data(), NP, q->top_k, s0)); }

@@ -94,6 +94,7 @@ struct BatchPair {
     double *Zh, *sq, *part;
     double *F;
     int32_t *top;              // min(top_k, m) best nodes (NULL: not asked for)
+    int shape;                 // tile shape of its score Gram
 };
 
 // Problem index of workgroup b: prefix[p] <= b < prefix[p + 1] (P problems).
@@ -152,12 +153,13 @@ hipError_t launch_norms_grouped(const BatchSnap *snaps, int P, int64_t kpad, int
 // FP16 operand: V = scale * dm R and its rounded copy, unconverged snapshots.
 hipError_t launch_prep_grouped(int prec, const BatchSnap *snaps, const int *prefix, int total,
                                int P, int64_t kpad, const int *done, hipStream_t s);
-// Scores of every pair: signature embeddings, the FP64 Gram tiles (shape:
-// score_shape) over the upper triangles and the row sums.
-hipError_t launch_score_grouped(int shape, const BatchPair *pairs, const int *prefix_zhat,
-                                int total_zhat, const int *prefix_score, int total_score,
-                                const int *prefix_red, int total_red, int P, int64_t k,
-                                int weighted, hipStream_t s);
+// Scores of every pair: signature embeddings, the FP64 Gram tiles over the upper
+// triangles (kScoreShapes prefix tables, `pitch` entries apart, and totals: the
+// pairs of each shape) and the row sums.
+hipError_t launch_score_grouped(const BatchPair *pairs, const int *prefix_zhat,
+                                int total_zhat, const int *prefix_score, int pitch,
+                                const int *total_score, const int *prefix_red, int total_red, int P,
+                                int64_t k, int weighted, hipStream_t s);
 // The min(top_k, m[p]) best nodes of every pair (m: host copy), after the
 // scores.
 hipError_t launch_topk_grouped(const BatchPair *pairs, const int64_t *m, int P, int top_k,

@@ -252,6 +252,7 @@ hipError_t launch_build_zhat(const double *Z0, const double *Z1, const int32_t *
 // Doubles that a score workspace holds for partial sums.
 int64_t score_part_doubles(int64_t mpad, int64_t kpad);
 // Tile shape of the score Gram of P pairs in one launch, and a shape's tiles.
+constexpr int kScoreShapes = 4;
 int score_shape(int P, const int64_t *mpad, int64_t kpad, int weighted);
 int score_tile_count(int shape, int64_t mpad);
 // *flag = 1 if an entry of map0 (map1) is outside [0, n0) ([0, n1)), else 0.

@@ -83,8 +83,8 @@ hipError_t launch_build_zhat(const double *Z0, const double *Z1, const int32_t *
 // 128 in bands of four row blocks; 1 and 2: square tiles, two or three
 // workgroups on a CU; 3: as 2 with 64-bit addresses, for very many columns.  Only pairs a < b count: a tile straddling the diagonal
 // also holds pairs a > b, whose mirror images another element covers.
-constexpr int kScoreShapes = 3;
 constexpr int kScoreFar = 3;
+static_assert(kScoreFar + 1 == kScoreShapes, "score shapes");
 template <int SHAPE> struct ScoreCfg {
     static constexpr int WM = SHAPE == 0 ? 4 : 2, WN = SHAPE == 1 ? 4 : 2;
     static constexpr int TM = SHAPE == 0 ? 256 : SHAPE == 1 ? 128 : 64, TN = SHAPE >= 2 ? 64 : 128;
@@ -93,8 +93,8 @@ template <int SHAPE> struct ScoreCfg {
     static constexpr int WAVES = SHAPE == 0 ? 2 : SHAPE == 1 ? 4 : 3;
     using Core = Dma64Core<TM, TN, WM, WN, SHAPE >= 2 ? 3 : 2, SHAPE == kScoreFar>;
 };
-static int64_t score_tm(int shape) { return shape == 0 ? 256 : shape == 1 ? 128 : 64; }
-static int64_t score_tn(int shape) { return shape >= 2 ? 64 : 128; }
+__host__ __device__ static int64_t score_tm(int shape) { return shape == 0 ? 256 : shape == 1 ? 128 : 64; }
+__host__ __device__ static int64_t score_tn(int shape) { return shape >= 2 ? 64 : 128; }
 
 int score_tile_count(int shape, int64_t mpad) {
     if (shape == 0) return rect_upper_tiles(mpad);
@@ -125,7 +125,7 @@ int score_shape(int P, const int64_t *mpad, int64_t kpad, int weighted) {
     if (score_ldz(kpad) >= (int64_t)1 << 21) return kScoreFar;
     int best = 0;
     double tb = 1e300;
-    for (int q = 0; q < kScoreShapes; ++q) {
+    for (int q = 0; q < kScoreFar; ++q) {
         if (weighted && q == 1) continue;
         int64_t tiles = 0;
         bool fits = true;
@@ -506,11 +506,10 @@ __global__ __launch_bounds__(ScoreCfg<SHAPE>::Core::NT, ScoreCfg<SHAPE>::WAVES) 
                           q.part, nullptr, id, smem_raw, sh);
 }
 
-__global__ void k_score_reduce_grouped(const BatchPair *pairs, const int *prefix, int P, int64_t tm,
-                                       int64_t tn) {
+__global__ void k_score_reduce_grouped(const BatchPair *pairs, const int *prefix, int P) {
     const int p = group_find(prefix, P, blockIdx.x);
     const BatchPair &q = pairs[p];
-    score_reduce_node(q.part, tm, tn, q.m, q.mpad, q.F,
+    score_reduce_node(q.part, score_tm(q.shape), score_tn(q.shape), q.m, q.mpad, q.F,
                       (int64_t)(blockIdx.x - prefix[p]) * blockDim.x + threadIdx.x);
 }
 
@@ -531,25 +530,27 @@ static hipError_t score_grouped_launch(const BatchPair *pairs, const int *prefix
     return hipGetLastError();
 }
 
-hipError_t launch_score_grouped(int shape, const BatchPair *pairs, const int *prefix_zhat,
-                                int total_zhat, const int *prefix_score, int total_score,
-                                const int *prefix_red, int total_red, int P, int64_t k,
-                                int weighted, hipStream_t s) {
+hipError_t launch_score_grouped(const BatchPair *pairs, const int *prefix_zhat,
+                                int total_zhat, const int *prefix_score, int pitch,
+                                const int *total_score, const int *prefix_red, int total_red, int P,
+                                int64_t k, int weighted, hipStream_t s) {
     const int64_t ldz = score_ldz(k);
     hipLaunchKernelGGL(k_build_zhat_grouped, dim3(total_zhat), dim3(64), 0, s, pairs, prefix_zhat, P,
                        k, ldz);
     hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    switch (2 * shape + (weighted ? 1 : 0)) {
+    for (int shape = 0; shape < kScoreShapes && e == hipSuccess; ++shape) {
+        const int total = total_score[shape], *prefix = prefix_score + (size_t)shape * pitch;
+        if (total == 0) continue;
+        switch (2 * shape + (weighted ? 1 : 0)) {
 #define CDL_CASE(q, w) \
-    case 2 * q + w: e = score_grouped_launch<q, w>(pairs, prefix_score, total_score, P, ldz, s); break;
-    CDL_CASE(0, 0) CDL_CASE(0, 1) CDL_CASE(1, 0) CDL_CASE(2, 0) CDL_CASE(2, 1) CDL_CASE(3, 0) CDL_CASE(3, 1)
+        case 2 * q + w: e = score_grouped_launch<q, w>(pairs, prefix, total, P, ldz, s); break;
+        CDL_CASE(0, 0) CDL_CASE(0, 1) CDL_CASE(1, 0) CDL_CASE(2, 0) CDL_CASE(2, 1) CDL_CASE(3, 0) CDL_CASE(3, 1)
 #undef CDL_CASE
-    default: return hipErrorInvalidValue;
+        default: return hipErrorInvalidValue;
+        }
     }
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_score_reduce_grouped, dim3(total_red), dim3(64), 0, s, pairs, prefix_red, P,
-                       score_tm(shape), score_tn(shape));
+    hipLaunchKernelGGL(k_score_reduce_grouped, dim3(total_red), dim3(64), 0, s, pairs, prefix_red, P);
     return hipGetLastError();
 }
 

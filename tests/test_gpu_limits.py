@@ -195,3 +195,14 @@ def test_scores_past_32_bit_offsets(cdl, mode):
     np.testing.assert_array_equal(host(v), E[i, j][order])
     np.testing.assert_array_equal(host(a), i[order])
     np.testing.assert_array_equal(host(b), j[order])
+
+
+# The score tiles' shape goes by the whole group, and the order in which a node's
+# partial sums are added by the shape: with the choices pinned each pair takes the
+# shape that it takes alone (3000 nodes: 64 x 64, five such pairs 128 x 128).
+@pytest.mark.parametrize("mode,sizes", [("unweighted", [3000, 2900, 3100, 2950, 3050, 500]),
+                                        ("delta_a", [700, 5200, 5100, 5000, 300])])
+def test_pinned_groups_score_as_their_pairs_alone(cdl, mode, sizes):
+    print("pinned group", mode, sizes, flush=True)
+    Xs, gids = mixed_snapshots(sizes, 20, len(sizes))
+    batched_equals_per_snapshot(cdl, Xs, gids, prec="fp32", mode=mode)
