@@ -1491,8 +1491,8 @@ cdl_status cdl_stream_embedding(cdl_ctx *ctx, const double *X, int64_t n, int64_
     // Bandwidth: exact lower median of the upper-triangle distances.  One
     // sweep over the recomputed upper row panels counts the keys below a
     // sampled bracket and gathers those inside; the radix passes then run over
-    // the gathered keys.  If the bracket misses the rank (or the buffer
-    // overflows), one 12-bit digit per sweep from the top bit instead.
+    // the gathered keys.  If the buffer overflows, one 12-bit digit of the keys
+    // inside the bracket per sweep; if the bracket misses the rank, of all keys.
     if (sigma > 0.0) {
         { Timed t_(ctx, "set_sigma"); HIPCHK(launch_set_sigma(sigma, stats, s)); }
     } else {

@@ -56,7 +56,7 @@ enum GraphTable {
     kGtGram,      // upper-triangle tiles of the group's shape
     kGtSample,    // 64 per snapshot whose selection starts with a sampled bracket (ranks)
     kGtKeys,      // 64 per such snapshot (its sample's keys from the series)
-    kGtPass,      // n / 32, 1 to 256, per snapshot
+    kGtPass,      // workgroups of a selection's pass over the snapshot
     kGtSym,       // upper 64 x 64 tiles
     kGtNodes64,   // ceil(n / 64)
     kGtPrep,      // ceil(ld / 256)

@@ -262,8 +262,8 @@ __device__ inline bool gram_place(int cover, int id, int64_t ld, int64_t row0, i
 // on the tile's upper-triangle keys: count those below st->lo into st->below
 // and append those in [lo, hi] to brbuf (capacity brcap) through an LDS
 // stage in the GEMM's staging memory, one segment per wave (a wave with more
-// of them than its segment holds marks the buffer full, which sends the
-// selection to its passes over the matrix: exact either way).  Each lane counts
+// of them than its segment holds counts them, marks the buffer unusable and the
+// selection passes over the matrix: exact either way).  Each lane counts
 // its own keys below and up to the bracket's end, one scan over the wave gives
 // its place, and a second walk over its registers appends them (a ballot and a
 // popcount per element before: the epilogue took half of a launch at T = 120).
@@ -416,7 +416,8 @@ __device__ __forceinline__ void gram_tile(const double *Xp, int64_t Tp, const do
             if (k0 < kmin0) atomicMin(&st->kmin, k0);
             if (k1 > kmax0) atomicMax(&st->kmax, k1);
         }
-        if (cnt) tbase = atomicAdd(&st->nbuf, over ? (unsigned long long)brcap + 1ull : cnt);
+        if (cnt) tbase = atomicAdd(&st->nbuf, cnt);
+        if (over) atomicOr(&st->over, 1u);
         if (bl) atomicAdd(&st->part[(blockIdx.x % kBelowParts) * kBelowPitch], bl);
     }
     if (!brbuf) return;
@@ -442,7 +443,7 @@ __device__ __forceinline__ void gram_tile(const double *Xp, int64_t Tp, const do
     __syncthreads();
     unsigned long long base = sbase;
     for (int w = 0; w < wid; ++w) base += wcnt[w];
-    // (a full segment has marked the buffer full: its wave has nothing to copy)
+    // (a full segment has marked the buffer unusable: its wave has nothing to copy)
     if (count <= kSeg) {
         const unsigned long long *const seg = (const unsigned long long *)smem + wid * kSeg;
         for (unsigned int q = lane; q < count; q += 64)
@@ -520,12 +521,17 @@ hipError_t launch_gram_panel(const double *Xp, int64_t Tp, const double *sqn, in
 // D2_ij (i < j).  D2 >= 0, so its IEEE bit pattern orders like its value.
 // First a bracket: the sample quantiles three standard deviations on each side
 // of the target, of pairs whose distances are taken from the series before the
-// Gram; the keys below lo are counted and those in [lo, hi] appended to a
+// Gram, widened by what the rounding of two orders of summation can differ; the
+// keys below lo are counted and those in [lo, hi] counted and appended to a
 // buffer, by the Gram's epilogue for stored snapshots, by one sweep over the
 // recomputed upper panels for streamed ones.  If the target rank falls inside
-// the bracket the radix passes below run over the buffer, else over the matrix
-// (the result is exact either way).  Radix passes of 12-bit digits start below
-// the common prefix of the bracket (or of the smallest and largest key); as
+// the bracket the radix passes below run over the buffer, or, where many keys
+// crowd there and it does not hold them, over the matrix's keys inside the
+// bracket; else over the whole matrix (the result is exact either way).  Inside a
+// bracket a pass takes its digit from key - lo, of which hi - lo leaves few bits:
+// distances that differ by rounding alone (patterns that repeat) are resolved by
+// one digit, where digits of the keys themselves took a pass over the matrix for
+// every 12 of the 40 leading bits that such keys share.  A digit has 12 bits; as
 // soon as the selected bin holds at most kSelFew keys, one pass collects them
 // and counting ranks among them gives the answer.  The last workgroup of a
 // pass picks the digit, so a pass is one launch; every pass reads the state's
@@ -550,6 +556,7 @@ __device__ __forceinline__ void select_reset_body(SelectState *st) {
         st->below = 0;
         st->nbuf = 0;
         st->ticket = 0;
+        st->over = 0;
         st->kand = ~0ull;
         st->kor = 0ull;
     }
@@ -557,6 +564,14 @@ __device__ __forceinline__ void select_reset_body(SelectState *st) {
 }
 
 __global__ void k_select_reset(SelectState *st) { select_reset_body(st); }
+
+// Before the ranks of a sample: the bracket's ends are found as minima and maxima.
+__device__ __forceinline__ void select_bracket_reset(SelectState *st) {
+    if (threadIdx.x == 0) {
+        st->lo = ~0ull;
+        st->hi = 0ull;
+    }
+}
 
 constexpr int kSelSample = 4096;  // (and kStreamSample: multiples of kRankTile)
 constexpr int kSelMargin = 96;    // 3 sqrt(kSelSample / 4): misses in ~0.3% of calls
@@ -614,21 +629,35 @@ __global__ __launch_bounds__(256) void k_select_sample_keys(const double *Xp, in
                                                             const double *sqn, int64_t n, int samples,
                                                             unsigned long long *keys,
                                                             SelectState *st) {
-    if (blockIdx.x == 0) select_reset_body(st);
+    if (blockIdx.x == 0) {
+        select_reset_body(st);
+        select_bracket_reset(st);
+    }
     select_sample_keys_body(Xp, Tp, sqn, n, samples, keys, blockIdx.x * 4 + (threadIdx.x >> 6),
                             gridDim.x * 4);
 }
 
 // The bracket [lo, hi]: the sample keys of ranks q -/+ margin around the
-// target quantile's rank q.  Workgroup b ranks keys 64 b .. 64 b + 63 against
+// target quantile's rank q, moved outwards by the difference that the rounding of
+// the sample's and of the Gram's order of summation can make (without that, a
+// crowd of distances that are equal but for rounding could lie beside its own
+// sample's bracket).  Workgroup b ranks keys 64 b .. 64 b + 63 against
 // the whole sample, 4096 keys of it at a time in LDS, a sixteenth of those per
 // wave (every lane reads the same two keys): a key's rank is the number of
-// smaller keys (equal keys hold a run of ranks, and each of them may write the
-// same value).
+// smaller keys (equal keys hold a run of ranks, and the outermost end counts).
 constexpr int kRankTile = 4096;
 
+// Bound of that difference for pair u: each order rounds a sum of Tp products at
+// most Tp + 16 times, |x_a| |x_b| <= (sq_a + sq_b) / 2.
+__device__ inline double select_slack(int64_t u, int64_t n, const double *sqn, int64_t Tp) {
+    int64_t a, b;
+    sel_pair((unsigned long long)u, n, a, b);
+    return (double)(Tp + 16) * 0x1p-52 * (sqn[a] + sqn[b]);
+}
+
 __device__ __forceinline__ void select_rank_body(const unsigned long long *keys, int samples,
-                                                 int margin, int64_t n, SelectState *st, int b) {
+                                                 int margin, int64_t n, const double *sqn, int64_t Tp,
+                                                 SelectState *st, int b) {
     struct alignas(16) Two { unsigned long long x, y; };
     __shared__ Two tile[kRankTile / 2];
     __shared__ unsigned int less[16][64], upto[16][64];
@@ -664,21 +693,30 @@ __device__ __forceinline__ void select_rank_body(const unsigned long long *keys,
     const unsigned long long N = (unsigned long long)n * (unsigned long long)(n - 1) / 2ull;
     const double rho = (double)((N - 1ull) / 2ull) / (double)N;
     const int q = (int)(rho * samples), rlo = q - margin, rhi = q + margin;
+    // (a NaN among the ends stays what it is)
+    const double d = __longlong_as_double((long long)mine);
     if (rlo > 0) {
-        if ((int)lt <= rlo && rlo < (int)le) st->lo = mine;
+        if ((int)lt <= rlo && rlo < (int)le) {
+            const double x = d - select_slack(64 * b + lane, n, sqn, Tp);
+            atomicMin(&st->lo, x > 0.0 ? (unsigned long long)__double_as_longlong(x) : x <= 0.0 ? 0ull : mine);
+        }
     } else if (b == 0 && lane == 0) {
-        st->lo = 0ull;
+        atomicMin(&st->lo, 0ull);
     }
     if (rhi < samples - 1) {
-        if ((int)lt <= rhi && rhi < (int)le) st->hi = mine;
+        if ((int)lt <= rhi && rhi < (int)le) {
+            const double x = d + select_slack(64 * b + lane, n, sqn, Tp);
+            atomicMax(&st->hi, x >= d ? (unsigned long long)__double_as_longlong(x) : mine);
+        }
     } else if (b == 0 && lane == 0) {
-        st->hi = ~0ull;
+        atomicMax(&st->hi, ~0ull);
     }
 }
 
 __global__ __launch_bounds__(1024) void k_select_rank(const unsigned long long *keys, int samples,
-                                                      int margin, int64_t n, SelectState *st) {
-    select_rank_body(keys, samples, margin, n, st, blockIdx.x);
+                                                      int margin, int64_t n, const double *sqn,
+                                                      int64_t Tp, SelectState *st) {
+    select_rank_body(keys, samples, margin, n, sqn, Tp, st, blockIdx.x);
 }
 
 // The bracket pass for very many keys (streamed panels: billions of keys,
@@ -748,38 +786,40 @@ __global__ __launch_bounds__(256) void k_select_bracket_flush(const double *D2, 
     }
 }
 
-// The part of the state that a pass works from.
+// The part of the state that a pass works from.  It selects among x = key - base
+// of the keys with x <= span.
 struct SelView {
-    unsigned long long prefix, rank;
+    unsigned long long prefix, rank, base, span;
     int bits, mode, src;
 };
 __device__ inline SelView select_load(const SelectState *st) {
-    return SelView{st->prefix, st->rank, st->bits, st->mode, st->src};
+    const int src = st->src;
+    const unsigned long long lo = st->lo, hi = st->hi;
+    return SelView{st->prefix, st->rank, src ? lo : 0ull, src == 2 ? hi - lo : ~0ull, st->bits, st->mode, src};
 }
 
-// Move the radix passes to the buffer when the target lies in the bracket.
+// Move the radix passes into the bracket when the target lies there: to the
+// buffer, or to the matrix's keys inside when the buffer does not hold them all.
 __device__ inline void select_bracket_view(const SelectState *st, int64_t cap, SelView &v) {
     if (v.mode == 2) return;
     unsigned long long below = st->below;
     const unsigned long long nb = st->nbuf;
 #pragma unroll 16
     for (int q = 0; q < kBelowParts; ++q) below += st->part[q * kBelowPitch];
-    if (nb > (unsigned long long)cap || v.rank < below || v.rank >= below + nb) return;   // stay on the matrix
-    v.src = 1;
+    if (v.rank < below || v.rank >= below + nb) return;   // stay on the whole matrix
+    const unsigned long long x = st->hi - st->lo;
+    v.src = nb > (unsigned long long)cap || st->over ? 2 : 1;
     v.rank -= below;
-    const unsigned long long x = st->lo ^ st->hi;
+    v.base = st->lo;
+    v.span = v.src == 2 ? x : ~0ull;
+    v.prefix = 0ull;
     if (x == 0ull) {   // every bracket key equals lo
-        v.prefix = st->lo;
         v.bits = 64;
         v.mode = 2;
         return;
     }
-    const int L = __clzll((long long)x);
-    if (L > v.bits) {
-        v.bits = L;
-        v.prefix = st->lo & ~((1ull << (64 - L)) - 1ull);
-    }
-    v.mode = nb <= (unsigned long long)kSelFew ? 1 : 0;
+    v.bits = __clzll((long long)x);
+    v.mode = v.src == 1 && nb <= (unsigned long long)kSelFew ? 1 : 0;
 }
 
 // The start of a stored selection: target rank and common prefix of the keys,
@@ -791,6 +831,8 @@ __device__ inline SelView select_start(const SelectState *st, int64_t n, int64_t
     const unsigned long long N = (unsigned long long)n * (unsigned long long)(n - 1) / 2ull;
     v.rank = (N - 1ull) / 2ull;
     v.src = 0;
+    v.base = 0ull;
+    v.span = ~0ull;
     const unsigned long long x = st->kmin ^ st->kmax;
     if (x == 0ull) {   // every pair distance is the same value
         v.prefix = st->kmin;
@@ -822,7 +864,7 @@ __global__ void k_select_check(SelectState *st, int64_t cap, double *stats) {
     st->mode = v.mode;
     st->src = v.src;
     st->count = 0;
-    if (v.mode == 2 && before != 2) select_done(st, stats, v.prefix);
+    if (v.mode == 2 && before != 2) select_done(st, stats, v.base + v.prefix);
 }
 
 __device__ inline void sel_digit(int bits, int &shift, int &width, unsigned long long &hi_mask) {
@@ -853,14 +895,15 @@ __device__ __forceinline__ void select_pass_body(const double *D2, int64_t ld, i
     const unsigned long long dmask = (1ull << width) - 1ull;
     unsigned long long kand = ~0ull, kor = 0ull;
     auto take = [&](unsigned long long key) {
-        if ((key & hi_mask) != prefix) return;
+        const unsigned long long x = key - v.base;
+        if (x > v.span || (x & hi_mask) != prefix) return;
         if (mode == 0) {
-            atomicAdd(&h[(key >> shift) & dmask], 1u);
-            kand &= key;
-            kor |= key;
+            atomicAdd(&h[(x >> shift) & dmask], 1u);
+            kand &= x;
+            kor |= x;
         } else {
             const unsigned int q = atomicAdd(&st->count, 1u);
-            if (q < kSelCap) st->cand[q] = key;
+            if (q < kSelCap) st->cand[q] = x;
         }
     };
     // eight independent loads in flight per thread
@@ -945,7 +988,7 @@ __device__ __forceinline__ void select_pick_body(SelectState *st, const SelView 
             if (lt <= v.rank && v.rank < le) {
                 st->prefix = mine;
                 st->bits = 64;
-                select_done(st, stats, mine);
+                select_done(st, stats, v.base + mine);
             }
         }
         return;
@@ -985,8 +1028,8 @@ __device__ __forceinline__ void select_pick_body(SelectState *st, const SelView 
         st->rank = v.rank - before;
         st->src = v.src;
         st->count = 0;
-        if (equal) select_done(st, stats, st->kand);
-        else if (bits >= 64) select_done(st, stats, p);
+        if (equal) select_done(st, stats, v.base + st->kand);
+        else if (bits >= 64) select_done(st, stats, v.base + p);
         else st->mode = cnt <= (unsigned long long)kSelFew ? 1 : 0;
     }
     if (t == nt - 1 && v.rank >= before0 + sum) {
@@ -1001,9 +1044,28 @@ __device__ __forceinline__ void select_pick_body(SelectState *st, const SelView 
     }
 }
 
+// Digit passes and the last collection by one workgroup of NT threads (at most 6
+// digits resolve 64 bits), from the state as it stands.
+template <int NT>
+__device__ __forceinline__ void select_alone(const double *D2, int64_t ld, int64_t n, SelectState *st,
+                                             SelView v, const unsigned long long *buf, double *stats,
+                                             unsigned int *h, PickShared &sh) {
+    for (int p = 0; p < 7 && v.mode != 2; ++p) {
+        select_pass_body<NT>(D2, ld, n, 0, n, st, v, buf, 0, 1, h);
+        __threadfence();
+        __syncthreads();
+        select_pick_body<NT>(st, v, stats, sh);
+        __threadfence();
+        __syncthreads();
+        v = select_load(st);
+    }
+}
+
 // One pass over the stored matrix or its bracket buffer with the pick by the
 // last of its nb workgroups (the ticket counts them; every workgroup's
-// histogram and candidates are published before its ticket).
+// histogram and candidates are published before its ticket).  kFinish: the last
+// pass, whose last workgroup goes on alone if the answer is still not known.
+template <bool kFinish>
 __device__ __forceinline__ void select_pass_pick(const double *D2, int64_t ld, int64_t n,
                                                  SelectState *st, const unsigned long long *buf,
                                                  int64_t cap, bool gathered, bool first,
@@ -1013,19 +1075,25 @@ __device__ __forceinline__ void select_pass_pick(const double *D2, int64_t ld, i
     __shared__ int last;
     const SelView v = first ? select_start(st, n, cap, gathered) : select_load(st);
     if (v.mode == 2) {
-        if (first && b == 0 && threadIdx.x == 0) select_done(st, stats, v.prefix);
+        if (first && b == 0 && threadIdx.x == 0) select_done(st, stats, v.base + v.prefix);
         return;
     }
     select_pass_body<256>(D2, ld, n, 0, n, st, v, buf, b, nb, h);
     if (!last_workgroup(&st->ticket, (unsigned int)nb, &last)) return;
     select_pick_body<256>(st, v, stats, sh);
+    if constexpr (kFinish) {
+        __threadfence();
+        __syncthreads();
+        select_alone<256>(D2, ld, n, st, select_load(st), buf, stats, h, sh);
+    }
 }
 
+template <bool kFinish>
 __global__ __launch_bounds__(256) void k_select_pass(const double *D2, int64_t ld, int64_t n,
                                                      SelectState *st, const unsigned long long *buf,
                                                      int64_t cap, int gathered, int first,
                                                      double *stats) {
-    select_pass_pick(D2, ld, n, st, buf, cap, gathered, first, stats, blockIdx.x, gridDim.x);
+    select_pass_pick<kFinish>(D2, ld, n, st, buf, cap, gathered, first, stats, blockIdx.x, gridDim.x);
 }
 
 // The whole selection from the bracket buffer by one workgroup of 1024 threads,
@@ -1047,8 +1115,8 @@ __device__ __forceinline__ void select_buffer_alone(SelectState *st, const SelVi
         ((uint4 *)h)[t] = make_uint4(0, 0, 0, 0);
         __syncthreads();
         for (int64_t q = t; q < nk; q += 1024) {
-            const unsigned long long key = buf[q];
-            if ((key & hi_mask) == prefix) atomicAdd(&h[(key >> shift) & ((1ull << width) - 1ull)], 1u);
+            const unsigned long long x = buf[q] - v.base;
+            if ((x & hi_mask) == prefix) atomicAdd(&h[(x >> shift) & ((1ull << width) - 1ull)], 1u);
         }
         __syncthreads();
         // thread t's bins 4 t .. 4 t + 3 behind the bins of the threads before it
@@ -1081,7 +1149,7 @@ __device__ __forceinline__ void select_buffer_alone(SelectState *st, const SelVi
     if (bits >= 64) {
         if (t == 0) {
             st->prefix = prefix;
-            select_done(st, stats, prefix);
+            select_done(st, stats, v.base + prefix);
         }
         return;
     }
@@ -1090,8 +1158,8 @@ __device__ __forceinline__ void select_buffer_alone(SelectState *st, const SelVi
     if (t == 0) s_left = 0;
     __syncthreads();
     for (int64_t q = t; q < nk; q += 1024) {
-        const unsigned long long key = buf[q];
-        if ((key & hi_mask) == prefix) sh.keys[atomicAdd(&s_left, 1u)] = key;   // at most kSelFew
+        const unsigned long long x = buf[q] - v.base;
+        if ((x & hi_mask) == prefix) sh.keys[atomicAdd(&s_left, 1u)] = x;   // at most kSelFew
     }
     __syncthreads();
     const unsigned int cnt = s_left;
@@ -1104,61 +1172,53 @@ __device__ __forceinline__ void select_buffer_alone(SelectState *st, const SelVi
         }
         if (lt <= rank && rank < le) {
             st->prefix = mine;
-            select_done(st, stats, mine);
+            select_done(st, stats, v.base + mine);
         }
     }
 }
 
-// The remaining passes by one workgroup: all of them for at most kSelSmall
-// nodes (first), or what kSelPasses passes of the whole chip left undone.
-__device__ __forceinline__ void select_rest_body(const double *D2, int64_t ld, int64_t n,
-                                                 SelectState *st, const unsigned long long *buf,
-                                                 int64_t cap, bool gathered, bool first,
-                                                 double *stats) {
+// The whole selection by one workgroup, for at most kSelSmall nodes.
+__device__ __forceinline__ void select_small_body(const double *D2, int64_t ld, int64_t n,
+                                                  SelectState *st, const unsigned long long *buf,
+                                                  int64_t cap, bool gathered, double *stats) {
     __shared__ __align__(16) unsigned int h[4096];
     __shared__ PickShared sh;
-    SelView v = first ? select_start(st, n, cap, gathered) : select_load(st);
+    const SelView v = select_start(st, n, cap, gathered);
     if (v.mode == 2) {
-        if (first && threadIdx.x == 0) select_done(st, stats, v.prefix);
+        if (threadIdx.x == 0) select_done(st, stats, v.base + v.prefix);
         return;
     }
-    if (first && v.src == 1) {
-        select_buffer_alone(st, v, buf, stats, h, sh);
-        return;
-    }
-    // at most 6 digit passes resolve 64 bits; the collect pass is one more
-    for (int p = 0; p < 7 && v.mode != 2; ++p) {
-        select_pass_body<1024>(D2, ld, n, 0, n, st, v, buf, 0, 1, h);
-        __threadfence();
-        __syncthreads();
-        select_pick_body<1024>(st, v, stats, sh);
-        __threadfence();
-        __syncthreads();
-        v = select_load(st);
-    }
+    if (v.src == 1) select_buffer_alone(st, v, buf, stats, h, sh);
+    else select_alone<1024>(D2, ld, n, st, v, buf, stats, h, sh);
 }
 
-__global__ __launch_bounds__(1024) void k_select_rest(const double *D2, int64_t ld, int64_t n,
-                                                      SelectState *st, const unsigned long long *buf,
-                                                      int64_t cap, int gathered, int first,
-                                                      double *stats) {
-    select_rest_body(D2, ld, n, st, buf, cap, gathered, first, stats);
+__global__ __launch_bounds__(1024) void k_select_small(const double *D2, int64_t ld, int64_t n,
+                                                       SelectState *st, const unsigned long long *buf,
+                                                       int64_t cap, int gathered, double *stats) {
+    select_small_body(D2, ld, n, st, buf, cap, gathered, stats);
 }
 
-// Workgroups of a pass over n nodes: 32 rows of the matrix each, and about 12
-// buffered keys a thread; 256 at most, since each adds its histogram to the
-// same 4096 bins.
-static int select_grid(int64_t n) { return (int)(n / 32 < 1 ? 1 : n / 32 < 256 ? n / 32 : 256); }
+// Workgroups of a pass over n nodes.  With a bracket: 32 rows of the matrix each,
+// and about 12 buffered keys a thread; 256 at most, since each adds its histogram
+// to the same 4096 bins.  Over the whole matrix twice as many keep more loads in
+// flight (seven passes at n = 4096 103 us, with 1024 workgroups 134, 128 163; at
+// 16384 0.72 ms, 0.76, with 256 1.14).
+static int select_grid(int64_t n, bool gathered) {
+    const int64_t g = gathered ? n / 32 : n / 8, most = gathered ? 256 : 512;
+    return (int)(g < 1 ? 1 : g < most ? g : most);
+}
 
-// Passes of the whole chip.  Two digits leave at most kSelFew distinct keys of
-// up to 2e8 (n = 20000) unless they crowd in one bin of 2^-24 of their range, the
-// third pass ranks them, and equal keys are found by their AND and OR; one
-// workgroup finishes what is left (none as a rule, at 4.5 us a launch spared).
-// Larger matrices, which a single workgroup could not read in time, take as
-// many passes as 64 bits need.
-constexpr int kSelPasses = 3;
-constexpr int64_t kSelRestNodes = 20000;
-static int select_passes(int64_t n) { return n <= kSelSmall ? 0 : n <= kSelRestNodes ? kSelPasses : 7; }
+// Passes of the whole chip.  With a bracket the third digit leaves at most kSelFew
+// distinct keys unless they crowd in one bin of 2^-36 of the bracket, the fourth
+// pass ranks them, equal keys are found by their AND and OR, and the last
+// workgroup of the fourth finishes what is left (a bracket wider than 2^48 units
+// in the last place, and that crowd).  Without one, and for matrices that a
+// single workgroup could not read in time, as many passes as 64 bits need.
+constexpr int kSelPasses = 4, kSelAllPasses = 7;
+constexpr int64_t kSelFinishNodes = 20000;
+static int select_passes(int64_t n, bool gathered) {
+    return n <= kSelSmall ? 0 : n <= kSelFinishNodes && gathered ? kSelPasses : kSelAllPasses;
+}
 
 hipError_t launch_select_reset(SelectState *st, hipStream_t s) {
     hipLaunchKernelGGL(k_select_reset, dim3(1), dim3(256), 0, s, st);
@@ -1171,7 +1231,7 @@ hipError_t launch_select_presample(const double *Xp, int64_t Tp, const double *s
     hipLaunchKernelGGL(k_select_sample_keys, dim3(kSelSample / 16), dim3(256), 0, s, Xp, Tp, sqn, n,
                        kSelSample, buf, st);
     hipLaunchKernelGGL(k_select_rank, dim3(kSelSample / 64), dim3(1024), 0, s, buf, kSelSample,
-                       kSelMargin, n, st);
+                       kSelMargin, n, sqn, Tp, st);
     return hipGetLastError();
 }
 
@@ -1179,20 +1239,25 @@ hipError_t launch_select_median(const double *D2, int64_t ld, int64_t n, SelectS
                                 unsigned long long *buf, bool gathered, double *stats,
                                 hipStream_t s) {
     const int64_t cap = select_buffer_keys(n);
-    const int passes = select_passes(n);
-    for (int p = 0; p < passes; ++p)
-        hipLaunchKernelGGL(k_select_pass, dim3(select_grid(n)), dim3(256), 0, s, D2, ld, n, st, buf, cap,
-                           gathered ? 1 : 0, p == 0 ? 1 : 0, stats);
-    if (passes < 7)
-        hipLaunchKernelGGL(k_select_rest, dim3(1), dim3(1024), 0, s, D2, ld, n, st, buf, cap,
-                           gathered ? 1 : 0, passes == 0 ? 1 : 0, stats);
+    const int passes = select_passes(n, gathered);
+    if (passes == 0) {
+        hipLaunchKernelGGL(k_select_small, dim3(1), dim3(1024), 0, s, D2, ld, n, st, buf, cap,
+                           gathered ? 1 : 0, stats);
+        return hipGetLastError();
+    }
+    const dim3 grid(select_grid(n, gathered)), blk(256);
+    for (int p = 0; p + 1 < passes; ++p)
+        hipLaunchKernelGGL(k_select_pass<false>, grid, blk, 0, s, D2, ld, n, st, buf, cap, gathered ? 1 : 0,
+                           p == 0 ? 1 : 0, stats);
+    hipLaunchKernelGGL(k_select_pass<true>, grid, blk, 0, s, D2, ld, n, st, buf, cap, gathered ? 1 : 0, 0,
+                       stats);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
 // Streamed selection (no stored matrix): radix digits from the top bit, each
-// digit one k_select_pass per recomputed row panel of the upper triangle and
-// one pick; the collect pass and the final sort are those of the stored path.
+// digit one k_select_panel per recomputed row panel of the upper triangle and
+// one pick; the collect pass and the final ranks are those of the stored path.
 
 __global__ void k_select_start_top(SelectState *st, int64_t n) {
     if (threadIdx.x != 0) return;
@@ -1229,7 +1294,7 @@ __global__ __launch_bounds__(1024) void k_select_pick(SelectState *st, double *s
 // One radix pass over the streamed bracket's buffer, with its pick.
 __global__ __launch_bounds__(256) void k_select_buffer(SelectState *st, const unsigned long long *buf,
                                                        double *stats) {
-    select_pass_pick(nullptr, 0, 0, st, buf, 0, true, false, stats, blockIdx.x, gridDim.x);
+    select_pass_pick<false>(nullptr, 0, 0, st, buf, 0, true, false, stats, blockIdx.x, gridDim.x);
 }
 
 hipError_t launch_select_panel(const double *D2p, int64_t ld, int64_t n, int64_t row0,
@@ -1268,7 +1333,7 @@ hipError_t launch_select_sample_x(const double *Xp, int64_t Tp, const double *sq
     hipLaunchKernelGGL(k_select_sample_keys, dim3(kStreamSample / 16), dim3(256), 0, s, Xp, Tp, sqn, n,
                        kStreamSample, buf, st);
     hipLaunchKernelGGL(k_select_rank, dim3(kStreamSample / 64), dim3(1024), 0, s, buf, kStreamSample,
-                       kStreamMargin, n, st);
+                       kStreamMargin, n, sqn, Tp, st);
     return hipGetLastError();
 }
 
@@ -1594,7 +1659,7 @@ int graph_table_count(int tb, int64_t n, int64_t ld, bool bracket, int gram_shap
     case kGtGram: return (int)gram_wgs(gram_shape, kGramUpper, ld, 0, ld);
     case kGtSample: return bracket ? kSelSample / 64 : 0;
     case kGtKeys: return bracket ? kSelSample / 64 : 0;
-    case kGtPass: return select_grid(n);
+    case kGtPass: return select_grid(n, bracket);
     case kGtSym: return sym_tiles64(ld);
     case kGtNodes64: return (int)cdiv(n, 64);
     case kGtPrep: return (int)cdiv(ld, 256);
@@ -1619,7 +1684,10 @@ __global__ __launch_bounds__(256) void k_graph_init_grouped(const GraphSnap *sna
     const GroupSlot g = group_slot(prefix, P);
     const GraphSnap &d = snaps[g.p];
     if (threadIdx.x < 64) d.flags[threadIdx.x] = 0;
-    if (select) select_reset_body(d.sel);
+    if (select) {
+        select_reset_body(d.sel);
+        select_bracket_reset(d.sel);
+    }
 }
 
 __global__ __launch_bounds__(256) void k_pad_grouped(const GraphSnap *snaps, const int *prefix, int P) {
@@ -1640,7 +1708,7 @@ __global__ __launch_bounds__(1024) void k_select_rank_grouped(const GraphSnap *s
                                                              int P) {
     const GroupSlot g = group_slot(prefix, P);
     const GraphSnap &d = snaps[g.p];
-    select_rank_body(d.buf, kSelSample, kSelMargin, d.n, d.sel, (int)g.b);
+    select_rank_body(d.buf, kSelSample, kSelMargin, d.n, d.sqn, d.Tp, d.sel, (int)g.b);
 }
 
 template <int SHAPE>
@@ -1672,18 +1740,20 @@ static hipError_t gram_grouped_launch(const GraphSnap *snaps, const int *prefix,
     return hipGetLastError();
 }
 
+template <bool kFinish>
 __global__ __launch_bounds__(256) void k_select_pass_grouped(const GraphSnap *snaps, const int *prefix,
                                                              int P, int first) {
     const GroupSlot g = group_slot(prefix, P);
     const GraphSnap &d = snaps[g.p];
-    select_pass_pick(d.W, d.ld, d.n, d.sel, d.buf, d.cap, d.bracket != 0, first != 0, d.stats, g.b, g.nb);
+    select_pass_pick<kFinish>(d.W, d.ld, d.n, d.sel, d.buf, d.cap, d.bracket != 0, first != 0, d.stats, g.b,
+                              g.nb);
 }
 
-__global__ __launch_bounds__(1024) void k_select_rest_grouped(const GraphSnap *snaps, const int *prefix,
-                                                              int P, int first) {
+__global__ __launch_bounds__(1024) void k_select_small_grouped(const GraphSnap *snaps, const int *prefix,
+                                                               int P) {
     const GroupSlot g = group_slot(prefix, P);
     const GraphSnap &d = snaps[g.p];
-    select_rest_body(d.W, d.ld, d.n, d.sel, d.buf, d.cap, d.bracket != 0, first != 0, d.stats);
+    select_small_body(d.W, d.ld, d.n, d.sel, d.buf, d.cap, d.bracket != 0, d.stats);
 }
 
 __global__ void k_set_sigma_grouped(const GraphSnap *snaps, const int *prefix, int P, double sigma) {
@@ -1727,14 +1797,18 @@ hipError_t launch_graph_grouped(const GraphSnap *snaps, const int *tables, const
     }
     if (e != hipSuccess) return e;
     if (select) {
-        // the passes that the largest snapshot takes
-        const int passes = select_passes(nmax);
-        for (int q = 0; q < passes; ++q)
-            hipLaunchKernelGGL(k_select_pass_grouped, dim3(totals[kGtPass]), dim3(256), 0, s, snaps,
+        // the passes that the largest snapshot takes (one of few enough nodes for
+        // kSelPasses has a bracket whenever another has)
+        const int passes = select_passes(nmax, totals[kGtSample] > 0);
+        for (int q = 0; q + 1 < passes; ++q)
+            hipLaunchKernelGGL(k_select_pass_grouped<false>, dim3(totals[kGtPass]), dim3(256), 0, s, snaps,
                                tb(kGtPass), P, q == 0 ? 1 : 0);
-        if (passes < 7)
-            hipLaunchKernelGGL(k_select_rest_grouped, dim3(totals[kGtOne]), dim3(1024), 0, s, snaps,
-                               tb(kGtOne), P, passes == 0 ? 1 : 0);
+        if (passes > 0)
+            hipLaunchKernelGGL(k_select_pass_grouped<true>, dim3(totals[kGtPass]), dim3(256), 0, s, snaps,
+                               tb(kGtPass), P, 0);
+        else
+            hipLaunchKernelGGL(k_select_small_grouped, dim3(totals[kGtOne]), dim3(1024), 0, s, snaps,
+                               tb(kGtOne), P);
     } else {
         hipLaunchKernelGGL(k_set_sigma_grouped, dim3(totals[kGtOne]), dim3(64), 0, s, snaps, tb(kGtOne), P,
                            sigma);

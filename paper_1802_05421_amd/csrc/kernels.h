@@ -23,15 +23,17 @@ struct SelectState {                // device scratch of the exact median select
     int bits;                       // number of resolved high bits
     int mode;                       // 0 histogram, 1 collect, 2 done
     unsigned int count;             // collected candidates
-    int src;                        // keys read from 0: the matrix, 1: the bracket buffer
+    int src;                        // keys read from 0: the matrix, 1: the bracket buffer, 2: the
+                                    // matrix's keys inside the bracket (1, 2: less lo)
     unsigned long long lo, hi;      // sampled bracket [lo, hi] around the target rank
     unsigned long long below;       // keys < lo
-    unsigned long long nbuf;        // keys in [lo, hi] (appended to the bracket buffer)
+    unsigned long long nbuf;        // keys in [lo, hi] (appended to the bracket buffer while they fit)
     unsigned long long hist[4096];  // 64-bit: a bin can exceed 2^32 keys for n > 92681
     unsigned long long part[kBelowParts * kBelowPitch];   // keys < lo counted by the Gram's tiles
     unsigned long long cand[kSelCap];
     unsigned long long kand, kor;   // AND and OR of the keys of the current digit's pass
     unsigned int ticket;            // workgroups done with the current pass
+    unsigned int over;              // a Gram tile had more keys inside than it could append
 };
 // Keys the bracket buffer of the selection holds for n nodes.
 int64_t select_buffer_keys(int64_t n);

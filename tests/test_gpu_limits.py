@@ -206,3 +206,41 @@ def test_pinned_groups_score_as_their_pairs_alone(cdl, mode, sizes):
     print("pinned group", mode, sizes, flush=True)
     Xs, gids = mixed_snapshots(sizes, 20, len(sizes))
     batched_equals_per_snapshot(cdl, Xs, gids, prec="fp32", mode=mode)
+
+
+# Distances that crowd without being equal: 200 patterns at the corners of a rotated
+# simplex are 2 apart but for rounding, and every node repeats one of them.  More
+# keys than the bracket's buffer holds lie within a few units in the last place of
+# the median; beside them some spread ones, or none.  The selection is exact: its
+# result is one of the matrix's own distances, with the median's rank among them.
+# The Gram's distances are not kept, but W = exp(-D2 / sigma^2) falls with them: the
+# rank of sigma is bracketed by the weights above and below 1/e.
+@pytest.mark.parametrize("n", [300, 513, 2100, 5000])
+@pytest.mark.parametrize("spread", [0.0, 0.3])
+def test_median_of_crowded_distances(cdl, n, spread):
+    print("crowded n=%d spread=%.1f" % (n, spread), flush=True)
+    rng = np.random.default_rng(n)
+    C = 200
+    Q = np.linalg.qr(rng.standard_normal((C, C)))[0]
+    X = Q[rng.integers(0, C, n)]
+    far = rng.random(n) < spread
+    X[far] += 0.3 * rng.standard_normal((far.sum(), C)) / np.sqrt(C)
+    sig, Ws = [], []
+    for mode in (0, 1):
+        cdl.set_select(mode)
+        try:
+            g = cdl.build_graph(dev(X))
+        finally:
+            cdl.set_select(0)
+        sig.append(g.host_stats()["sigma"])
+        Ws.append(host(g.W)[:n, :n])
+    assert sig[0] == sig[1]
+    np.testing.assert_array_equal(Ws[0], Ws[1])
+    st, _, _ = cdl.stream_embedding(dev(X), 2, SEED, tol=1e-6, max_iter=64, panel_rows=512)
+    assert st.host_stats()["sigma"] == sig[0]
+    D2 = (X * X).sum(1)[:, None] + (X * X).sum(1)[None, :] - 2.0 * X @ X.T
+    d = np.sort(D2[np.triu_indices(n, 1)])
+    assert sig[0] ** 2 == pytest.approx(d[(len(d) - 1) // 2], rel=1e-13)
+    w = Ws[0][np.triu_indices(n, 1)]
+    rank, e1 = (len(d) - 1) // 2, np.exp(-1.0)
+    assert (w > e1 * (1 + 1e-15)).sum() <= rank < (w >= e1 * (1 - 1e-15)).sum()

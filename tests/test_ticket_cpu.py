@@ -41,7 +41,9 @@ def test_waves_wait_for_their_stores_before_the_ticket(tmp_path):
     funcs = {k: v for k, v in _functions(tmp_path).items() if any(n in k for n in KERNELS)}
     assert all(any(n in k for k in funcs) for n in KERNELS)
     for name, ins in funcs.items():
-        release = [i for i, x in enumerate(ins) if x.startswith("buffer_wbl2")]
+        # (releases that an atomic with its old value returned follows)
+        release = [i for i, x in enumerate(ins) if x.startswith("buffer_wbl2")
+                   and any(re.match(r"(global|flat)_atomic_add .* sc0", y) for y in ins[i:i + 15])]
         assert len(release) == 1, name
         barrier = max(i for i, x in enumerate(ins[:release[0]]) if x.startswith("s_barrier"))
         wait = [i for i, x in enumerate(ins[:barrier]) if x.startswith("s_waitcnt") and "vmcnt(0)" in x]
