@@ -2002,10 +2002,26 @@ BatchLayout batch_layout(int32_t n_snap, const cdl_snapshot *sn, const cdl_seq_p
     return L;
 }
 
-size_t seq_bytes(const SeqPlan &p, const cdl_seq_params *q) {
+// Workspaces that hold every snapshot's calls in turn: a smaller snapshot can need
+// more than the largest (split counts and split rounds fall as n grows).
+void seq_needs(int32_t n_snap, const cdl_snapshot *sn, const SeqPlan &p, const cdl_seq_params *q,
+               size_t *graph, size_t *chain, size_t *solve, size_t *score) {
     const int dmax = q->depth > 0 ? q->depth : q->depth_max;
-    size_t g = 0, c = 0, so = 0, sc = 0;
-    cdl_workspace_bytes(p.nmax, p.Tmax, q->k, dmax, q->prec, &g, &c, &so, &sc);
+    *graph = *chain = *solve = *score = 0;
+    cdl_workspace_bytes(p.nmax, p.Tmax, q->k, dmax, q->prec, graph, chain, solve, score);
+    for (int t = 0; t < n_snap; ++t) {
+        size_t g = 0, c = 0, so = 0, sc = 0;
+        cdl_workspace_bytes(sn[t].n, sn[t].T, q->k, dmax, q->prec, &g, &c, &so, &sc);
+        *graph = std::max(*graph, g);
+        *chain = std::max(*chain, c);
+        *solve = std::max(*solve, so);
+        *score = std::max(*score, sc);
+    }
+}
+
+size_t seq_bytes(int32_t n_snap, const cdl_snapshot *sn, const SeqPlan &p, const cdl_seq_params *q) {
+    size_t g, c, so, sc;
+    seq_needs(n_snap, sn, p, q, &g, &c, &so, &sc);
     const size_t ld = (size_t)pad_n(p.nmax);
     size_t tot = 0;
     tot += 2 * al(ld * ld * sizeof(double));                    // W ping-pong
@@ -2453,7 +2469,7 @@ cdl_status cdl_sequence_workspace_bytes(int32_t n_snap, const cdl_snapshot *snap
     for (int t = 0; t < n_snap; ++t)
         if (snaps[t].n < 2 || snaps[t].T < 1) return CDL_E_ARG;
     *bytes = (p->flags & CDL_SEQ_BATCHED) ? batch_layout(n_snap, snaps, p).total
-                                           : seq_bytes(seq_plan(n_snap, snaps), p);
+                                           : seq_bytes(n_snap, snaps, seq_plan(n_snap, snaps), p);
     return CDL_OK;
 }
 
@@ -2477,7 +2493,7 @@ cdl_status cdl_score_sequence(cdl_ctx *ctx, int32_t n_snap, const cdl_snapshot *
     if ((q->flags & ~(CDL_SEQ_ASYNC | CDL_SEQ_GRAPH | CDL_SEQ_BATCHED)) != 0 ||
         ((q->flags & (CDL_SEQ_GRAPH | CDL_SEQ_BATCHED)) && !async))
         return fail(ctx, CDL_E_ARG, "bad sequence flags");
-    if (ws_bytes < (batched ? batch_layout(n_snap, sn, q).total : seq_bytes(plan, q)))
+    if (ws_bytes < (batched ? batch_layout(n_snap, sn, q).total : seq_bytes(n_snap, sn, plan, q)))
         return fail(ctx, CDL_E_WORKSPACE, "sequence workspace too small");
     if (async) {
         // the enqueue helpers check nothing: every argument is checked here
@@ -2502,8 +2518,8 @@ cdl_status cdl_score_sequence(cdl_ctx *ctx, int32_t n_snap, const cdl_snapshot *
         }
     }
     const int dmax = q->depth > 0 ? q->depth : q->depth_max;
-    size_t gB = 0, cB = 0, soB = 0, scB = 0;
-    cdl_workspace_bytes(plan.nmax, plan.Tmax, q->k, dmax, q->prec, &gB, &cB, &soB, &scB);
+    size_t gB, cB, soB, scB;
+    seq_needs(n_snap, sn, plan, q, &gB, &cB, &soB, &scB);
     Arena a(ws);
     const size_t ld = (size_t)pad_n(plan.nmax);
     double *Wb[2] = {a.take<double>(ld * ld), a.take<double>(ld * ld)};

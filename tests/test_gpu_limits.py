@@ -244,3 +244,16 @@ def test_median_of_crowded_distances(cdl, n, spread):
     w = Ws[0][np.triu_indices(n, 1)]
     rank, e1 = (len(d) - 1) // 2, np.exp(-1.0)
     assert (w > e1 * (1 + 1e-15)).sum() <= rank < (w >= e1 * (1 - 1e-15)).sum()
+
+
+# Sequences whose smaller snapshots need larger workspaces than the largest one.
+@pytest.mark.parametrize("prec,k,sizes", [("fp32", 128, [2560, 2304, 2500, 2250]), ("bf16", 16, [7100, 6900, 7000])])
+def test_sequences_of_uneven_needs(cdl, prec, k, sizes):
+    print("uneven needs", prec, k, sizes, flush=True)
+    Xs, gids = mixed_snapshots(sizes, 20, len(sizes))
+    base = dict(k=k, seed=SEED, prec=prec, depth=2, tol=0.0, max_iter=3, top_k=5)
+    wF, wT, _ = cdl.score_sequence(Xs, gids, cdl.SeqParams(**base))
+    F, T, _ = cdl.score_sequence(Xs, gids, cdl.SeqParams(**base, asynchronous=True))
+    for t in range(len(wF)):
+        np.testing.assert_array_equal(host(F[t]), host(wF[t]))
+        np.testing.assert_array_equal(host(T[t]), host(wT[t]))
