@@ -312,9 +312,9 @@ ChainBuf plan_chain(Arena &a, int64_t n, int prec, int depth_max) {
     c.dmn = a.take<double>(ld);
     c.dm = a.take<double>(ld);
     c.u = a.take<double>(ld);
-    // a squaring's norms are at most sym_tiles64(ld); the 36 of FP64 levels in 32 x
-    // 32 tiles (ld = 256) run on into fro64, which only level 0 uses
-    c.fro = a.take<double>(sym_tiles64(ld));
+    // the norms of level 0's 64 x 64 tiles, or of a squaring's (FP64 at ld = 256: 36
+    // of 32 x 32)
+    c.fro = a.take<double>(std::max(sym_tiles64(ld), square_tiles_of(prec, ld)));
     c.fro64 = a.take<double>(sym_tiles64(ld));
     const size_t tb = square_tail_bytes(prec, ld, n);
     c.tail = tb ? a.take<float>(tb / sizeof(float)) : nullptr;

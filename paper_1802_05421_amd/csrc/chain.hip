@@ -270,7 +270,7 @@ template <int NW> struct SqCfg<double, NW, 32> { using Core = RowCore<double, 32
 // work (36 tiles of 128 x 128 at n = 1000 kept 36 CUs busy for 79 us in FP32, the
 // 136 of 64 x 64 take 23; 10 of 64 x 64 at n = 256 took 53 us in FP64, 36 of 32 x
 // 32 take 7).  The small tiles lose an eighth and a third of the matrix pipes'
-// rate.  32 x 32 only where its norm partials fit (n <= 256).
+// rate.  32 x 32 only up to n = 256, where they were measured.
 static int row_square_tile(int prec, int P, const int64_t *ld) {
     const int tile[3] = {128, 64, 32};
     const double eff[3] = {1.0, 0.88, 0.67};

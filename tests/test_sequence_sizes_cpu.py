@@ -41,3 +41,11 @@ def test_small_snapshots_fit(prec, k, depth, big, small):
     # one set of workspaces; two with the asynchronous flag
     for flags, sets in ((0, 1), (1, 2)):
         assert sequence([big, small], flags) - sequence([big, big], flags) + maps >= sets * more
+
+
+def test_chain_buffers_hold_every_norm():
+    # FP64 levels of up to 256 nodes are squared in 36 tiles of 32 x 32, one norm
+    # each, beside the 10 exact norms of level 0 and three vectors of 256
+    import paper_1802_05421_amd._lib as L
+    off = L.load().cdl_chain_level_offset(256, L.PREC["fp64"])
+    assert off >= 3 * aligned(8 * 256) + aligned(8 * 36) + aligned(8 * 10)
