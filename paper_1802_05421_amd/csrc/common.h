@@ -273,4 +273,21 @@ __device__ inline double ordered_sum(const double *p, int64_t stride, int cnt, d
     return acc;
 }
 
+// s[u] += p[u stride] + p[(u + 4) stride] + ... (below cnt), each in index order,
+// with 32 loads in flight at a time.
+__device__ inline void quarter_sums(const double *p, int64_t stride, int cnt, double (&s)[4]) {
+    int b = 0;
+    for (; b + 32 <= cnt; b += 32) {
+        double v[32];
+#pragma unroll
+        for (int u = 0; u < 32; ++u) v[u] = p[(int64_t)(b + u) * stride];
+#pragma unroll
+        for (int u = 0; u < 32; ++u) s[u & 3] += v[u];
+    }
+    for (; b < cnt; b += 4)
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (b + u < cnt) s[u] += p[(int64_t)(b + u) * stride];
+}
+
 } // namespace cdl

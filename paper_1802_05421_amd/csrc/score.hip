@@ -461,15 +461,27 @@ hipError_t launch_check_maps(const int32_t *map0, const int32_t *map1, int64_t m
 
 // F_a = its row partials over the column blocks from its row block's diagonal
 // on, then its column partials over the row blocks down to its column block:
-// exactly the slots the score tiles (tm x tn) wrote, summed in a fixed order.
+// exactly the slots the score tiles (tm x tn) wrote, summed in a fixed order: of
+// more than 8 column blocks every fourth slot in a chain of its own, so that the 80
+// of 5003 nodes in small tiles do not round one sum 80 times (error against 64 bits
+// 1.2e-16 of the scores, one chain 2.6e-16; 256 x 128 tiles in one chain 1.7e-16).
 __device__ inline void score_reduce_node(const double *part, int64_t tm, int64_t tn, int64_t m,
                                          int64_t mpad, double *F, int64_t a) {
     if (a >= m) return;
     const int ncol = (int)(mpad / tn), J0 = (int)(a / tm * (tm / tn));
-    double s = ordered_sum(part + (int64_t)J0 * mpad + a, mpad, ncol - J0, 0.0);
     const int Imax = (int)(a / tn * tn / tm);
-    s = ordered_sum(part + (int64_t)ncol * mpad + a, mpad, Imax + 1, s);
-    F[a] = s;
+    const double *const rows = part + (int64_t)J0 * mpad + a, *const cols = part + (int64_t)ncol * mpad + a;
+    if (ncol <= 8) {
+        double f = 0.0;
+        for (int q = 0; q < ncol - J0; ++q) f += rows[q * mpad];
+        for (int q = 0; q <= Imax; ++q) f += cols[q * mpad];
+        F[a] = f;
+        return;
+    }
+    double s[4] = {0.0, 0.0, 0.0, 0.0};
+    quarter_sums(rows, mpad, ncol - J0, s);
+    quarter_sums(cols, mpad, Imax + 1, s);
+    F[a] = (s[0] + s[1]) + (s[2] + s[3]);
 }
 
 __global__ void k_score_reduce(const double *part, int64_t tm, int64_t tn, int64_t m, int64_t mpad,

@@ -257,3 +257,24 @@ def test_sequences_of_uneven_needs(cdl, prec, k, sizes):
     for t in range(len(wF)):
         np.testing.assert_array_equal(host(F[t]), host(wF[t]))
         np.testing.assert_array_equal(host(T[t]), host(wT[t]))
+
+
+# Rounding of a node's sum over the tiles alone: with one column of integers below
+# 2^23 and weights that differ by 1 every edge score and every sum over 64 of them is
+# exact, and F's error is that of adding its 80 partial sums.  A rounding is
+# uniform over half a unit in the last place, at most 0.58 2^-53 of the sum (rms).  In
+# four chains the i-th of 20 sums is i / 80 of F: 4 sum (i / 80)^2 = 1.8, and the last
+# additions are 2 / 4 and 1: rms at most 0.58 sqrt(1.8 + 0.5 + 1) 2^-53 = 1.06 2^-53.
+# (One chain of 80: at least 0.29 sqrt(27) 2^-53 = 1.5 2^-53.)
+def test_node_sums_round_little(cdl):
+    m = 5003
+    print("node sums m=%d" % m, flush=True)
+    z = np.random.default_rng(m).integers(0, 1 << 23, m)
+    A = np.zeros((cdl.ld(m), cdl.ld(m)))
+    B = A.copy()
+    B[:m, :m] = 1.0 - np.eye(m)
+    g = [cdl.Graph(W=dev(w), deg=dev(np.ones(m)), stats=dev(np.ones(4)), n=m) for w in (A, B)]
+    F, _ = cdl.anomaly_scores(dev(z[:, None].astype(float)), g[0], dev(np.zeros((m, 1))), g[1], mode="delta_a", top_k=0)
+    want = m * z * z - 2 * z * z.sum() + (z * z).sum()
+    err = (host(F).astype(np.int64) - want) / want.astype(float)
+    assert np.sqrt((err * err).mean()) <= 1.1 * 2.0 ** -53
