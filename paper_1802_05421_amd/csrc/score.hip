@@ -587,10 +587,11 @@ template <typename I> struct TopkShared {
 __device__ inline int32_t shfl_xor_idx(int32_t x, int o) { return __shfl_xor(x, o); }
 __device__ inline int64_t shfl_xor_idx(int64_t x, int o) { return __shfl_xor((long long)x, o); }
 
-// Keys in the order of the values (both zeros alike; a NaN has a place of its
-// own, so no pair is lost).
+// Keys in the order of the values (both zeros alike; a NaN of either sign before
+// all numbers, so that no pair is lost behind the padding).
 __device__ inline unsigned long long topk_key(double v) {
-    const unsigned long long u = (unsigned long long)__double_as_longlong(v + 0.0);
+    unsigned long long u = (unsigned long long)__double_as_longlong(v + 0.0);
+    if (v != v) u &= 0x7fffffffffffffffull;
     return u >> 63 ? ~u : u | 0x8000000000000000ull;
 }
 

@@ -278,3 +278,14 @@ def test_node_sums_round_little(cdl):
     want = m * z * z - 2 * z * z.sum() + (z * z).sum()
     err = (host(F).astype(np.int64) - want) / want.astype(float)
     assert np.sqrt((err * err).mean()) <= 1.1 * 2.0 ** -53
+
+
+# Scores that are no numbers come first, in order of their index; none gives its
+# place to the padding of a chunk.
+@pytest.mark.parametrize("m,K", [(300, 256), (1300, 50)])
+def test_top_nodes_of_nan_scores(cdl, m, K):
+    z = np.arange(m, dtype=float)
+    z[m // 2] = -np.nan
+    F, top = cdl.anomaly_scores(*one_column(cdl, z), top_k=K)
+    assert np.isnan(host(F)).all()
+    np.testing.assert_array_equal(host(top), np.arange(K))
