@@ -161,7 +161,7 @@ __global__ __launch_bounds__(256 * NB) void k_rhs(const double *W0, const double
     const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
     const int nbg = (nb + NB - 1) / NB;
     // The projection groups of one row take ids kNumXcd apart (one XCD).
-    const int w = blockIdx.x, per = kNumXcd * nbg, l = w % per;
+    const int w = grid_row_id(), per = kNumXcd * nbg, l = w % per;
     const int64_t i = row0 + (int64_t)(w / per) * kNumXcd + l % kNumXcd;
     const int bgrp = l / kNumXcd;
     if (i >= row1) return;
@@ -432,7 +432,7 @@ static hipError_t launch_rhs_k(const double *W0, const double *W1, int64_t ld, i
     const int NB = nb >= 3 ? 4 : nb;
     const int nbg = (nb + NB - 1) / NB;
     const int64_t rows = cdiv(row1 - row0, kNumXcd) * kNumXcd;
-    const dim3 grid((unsigned)(rows * nbg));
+    const dim3 grid = grid_rows(rows * nbg);   // (ids past the rows find none)
     const double isk = 1.0 / sqrt((double)k);
     switch (NB) {
     case 4: hipLaunchKernelGGL((k_rhs<4, S>), grid, dim3(1024), 0, s, W0, W1, ld, n, row0, row1, gid, k, mseed, isk, nb, Y0t, Y1t); break;
@@ -781,7 +781,7 @@ hipError_t launch_stream_prep(const double *deg, int64_t n, int64_t ld, double *
 // rdeg is zero beyond n and R is zero beyond k).
 __global__ void k_stream_scale(const double *Rt, const double *rdeg, int64_t ld, int64_t total,
                                double *Ut) {
-    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t o = (int64_t)grid_row_id() * blockDim.x + threadIdx.x;
     if (o >= total) return;
     Ut[o] = Rt[o] * rdeg[o % ld];
 }
@@ -789,14 +789,14 @@ __global__ void k_stream_scale(const double *Rt, const double *rdeg, int64_t ld,
 hipError_t launch_stream_scale(const double *Rt, const double *rdeg, int64_t ld, int64_t kpad,
                                double *Ut, hipStream_t s) {
     const int64_t total = ld * kpad;
-    hipLaunchKernelGGL(k_stream_scale, dim3((unsigned)cdiv(total, 256)), dim3(256), 0, s, Rt,
+    hipLaunchKernelGGL(k_stream_scale, grid_rows(cdiv(total, 256)), dim3(256), 0, s, Rt,
                        rdeg, ld, total, Ut);
     return hipGetLastError();
 }
 
 __global__ void k_stream_update(const double *Ut, const double *Prod, const double *rdeg,
                                 int64_t ld, int64_t total, double *Xt) {
-    const int64_t o = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t o = (int64_t)grid_row_id() * blockDim.x + threadIdx.x;
     if (o >= total) return;
     Xt[o] += Ut[o] + rdeg[o % ld] * Prod[o];
 }
@@ -804,7 +804,7 @@ __global__ void k_stream_update(const double *Ut, const double *Prod, const doub
 hipError_t launch_stream_update(const double *Ut, const double *Prod, const double *rdeg,
                                 int64_t ld, int64_t k, double *Xt, hipStream_t s) {
     const int64_t total = ld * k;
-    hipLaunchKernelGGL(k_stream_update, dim3((unsigned)cdiv(total, 256)), dim3(256), 0, s, Ut,
+    hipLaunchKernelGGL(k_stream_update, grid_rows(cdiv(total, 256)), dim3(256), 0, s, Ut,
                        Prod, rdeg, ld, total, Xt);
     return hipGetLastError();
 }

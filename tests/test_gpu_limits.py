@@ -289,3 +289,31 @@ def test_top_nodes_of_nan_scores(cdl, m, K):
     F, top = cdl.anomaly_scores(*one_column(cdl, z), top_k=K)
     assert np.isnan(host(F)).all()
     np.testing.assert_array_equal(host(top), np.arange(K))
+
+
+# Right-hand sides of 2^20 columns: 4096 groups of four 64-column blocks for every
+# row are 2^32 work-items and more from 1024 rows on.  The first and the last
+# block's columns against the definition.
+def test_right_hand_sides_past_a_launch_of_32_bits(cdl):
+    n, k = 1040, 1 << 20
+    print("right-hand sides n=%d k=%d" % (n, k), flush=True)
+    B = np.triu(np.random.default_rng(n).uniform(0.1, 1.0, (n, n)), 1)
+    W = np.zeros((cdl.ld(n), cdl.ld(n)))
+    W[:n, :n] = B + B.T
+    Y = cdl.rhs(cdl.Graph(W=dev(W), deg=dev(np.ones(n)), stats=dev(np.ones(4)), n=n), k, SEED)
+
+    def mix(z):
+        z = (z ^ (z >> np.uint64(30))) * np.uint64(0xbf58476d1ce4e5b9)
+        z = (z ^ (z >> np.uint64(27))) * np.uint64(0x94d049bb133111eb)
+        return z ^ (z >> np.uint64(31))
+
+    i, j = (np.triu(v, 1).astype(np.uint64) for v in np.indices((n, n)))
+    root = np.sqrt(B)
+    for beta in (0, k // 64 - 1):
+        with np.errstate(over="ignore"):
+            word = mix(mix(np.uint64(SEED)) ^ (np.uint64(beta << 40) | i << np.uint64(20) | j))
+        for r in (0, 63):
+            q = np.where((word >> np.uint64(r)) & np.uint64(1), -1.0, 1.0) * root   # (i < j: head i, tail j)
+            want = (q.sum(1) - q.sum(0)) / np.sqrt(k)
+            got = host(Y[:, beta * 64 + r].contiguous())
+            assert np.abs(got - want).max() <= n * 2.0 ** -52 * np.abs(want).max()
