@@ -54,8 +54,7 @@ enum GraphTable {
     kGtRows,      // padded rows, four per workgroup: ld / 4
     kGtOne,       // one workgroup per snapshot
     kGtGram,      // upper-triangle tiles of the group's shape
-    kGtSample,    // 64 per snapshot whose selection starts with a sampled bracket (ranks)
-    kGtKeys,      // 64 per such snapshot (its sample's keys from the series)
+    kGtSample,    // 64 per snapshot whose selection starts with a sampled bracket (keys, ranks)
     kGtPass,      // workgroups of a selection's pass over the snapshot
     kGtSym,       // upper 64 x 64 tiles
     kGtNodes64,   // ceil(n / 64)

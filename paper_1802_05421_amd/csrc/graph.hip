@@ -4,15 +4,16 @@
 //
 //   pad_series   copy X into a zero-padded FP64 panel, row norms ||x_i||^2
 //   gram_dist    D2_ij = ||x_i||^2 + ||x_j||^2 - 2 x_i.x_j on FP64 MFMA,
-//                256 x 128 tiles covering the upper triangle (the strictly
-//                lower tiles are never computed or read), stored from the
+//                128 x 128 or 64 x 64 tiles covering the upper triangle
+//                (nothing reads what lies below it), stored from the
 //                accumulators
 //   select       exact lower median of D2 over i < j: a sampled bracket
 //                around the median rank, the keys inside it gathered into a
 //                buffer and ranked by radix passes over their IEEE-754 bit
 //                patterns (order-preserving for D2 >= 0); the same radix
-//                passes over the whole upper triangle when the bracket
-//                misses the rank or overflows the buffer
+//                passes over the upper triangle's keys inside the bracket when
+//                the buffer does not hold them, over all of it when the
+//                bracket misses the rank
 //   exp_sym      per upper 64 x 64 tile: W = exp(-D2 / sigma^2) in place,
 //                W_ii = 0, written with its mirror; row and column sums
 //                into one partial per (tile column, node)
@@ -21,8 +22,9 @@
 //
 // Streamed snapshots (no n x n matrix stored) use the same tiles on row
 // panels: gram_dist over the panel's upper tiles (median sweeps) or all of
-// its tiles, optionally with the weights formed in the epilogue; select by
-// radix digits from the top bit, one sweep over the upper panels per digit;
+// its tiles, optionally with the weights formed in the epilogue; select by a
+// sampled bracket gathered in one sweep over the upper panels, or by one sweep per
+// radix digit;
 // exp_rows for the weights, degrees and Frobenius rows of a panel.
 #include "batch.h"
 #include "common.h"
@@ -601,8 +603,9 @@ __device__ inline void sel_pair(unsigned long long u, int64_t n, int64_t &a, int
 // Keys of the sample pairs from the padded series, before the Gram: one wave
 // per pair, D2 = sq_a + sq_b - 2 x_a.x_b with the dot product summed over the
 // lanes (another order than the Gram's: an estimate of the quantile, which is
-// all the bracket needs; the counts against it are exact).  Four pairs a wave:
-// each costs a round trip to memory, so they are spread over the whole chip.
+// all the bracket needs; the counts against it are exact).  Four pairs a wave
+// (sixteen where the snapshots of a group fill the chip): each costs a round trip
+// to memory, so they are spread over the whole chip.
 __device__ __forceinline__ void select_sample_keys_body(const double *Xp, int64_t Tp,
                                                         const double *sqn, int64_t n, int samples,
                                                         unsigned long long *keys, int wave,
@@ -1658,7 +1661,6 @@ int graph_table_count(int tb, int64_t n, int64_t ld, bool bracket, int gram_shap
     case kGtOne: return 1;
     case kGtGram: return (int)gram_wgs(gram_shape, kGramUpper, ld, 0, ld);
     case kGtSample: return bracket ? kSelSample / 64 : 0;
-    case kGtKeys: return bracket ? kSelSample / 64 : 0;
     case kGtPass: return select_grid(n, bracket);
     case kGtSym: return sym_tiles64(ld);
     case kGtNodes64: return (int)cdiv(n, 64);
@@ -1784,8 +1786,8 @@ hipError_t launch_graph_grouped(const GraphSnap *snaps, const int *tables, const
     hipLaunchKernelGGL(k_pad_grouped, dim3(totals[kGtRows]), dim3(256), 0, s, snaps, tb(kGtRows), P);
     // the brackets from samples of the series; the Gram counts and gathers them
     if (select && totals[kGtSample] > 0) {
-        hipLaunchKernelGGL(k_select_keys_grouped, dim3(totals[kGtKeys]), dim3(256), 0, s, snaps,
-                           tb(kGtKeys), P);
+        hipLaunchKernelGGL(k_select_keys_grouped, dim3(totals[kGtSample]), dim3(256), 0, s, snaps,
+                           tb(kGtSample), P);
         hipLaunchKernelGGL(k_select_rank_grouped, dim3(totals[kGtSample]), dim3(1024), 0, s, snaps,
                            tb(kGtSample), P);
     }
