@@ -980,11 +980,6 @@ static double host_sum(const double *v, int count) {
 }
 static double host_sum(const std::vector<double> &v) { return host_sum(v.data(), (int)v.size()); }
 
-// Up to this many norm partials a level's workgroups write straight into pinned
-// memory (8 bytes each over the bus, behind the kernel's own work); more are
-// gathered by a launch of their own.
-constexpr int kHostNorms = 2112;
-
 cdl_status cdl_build_chain(cdl_ctx *ctx, const double *W, const double *deg, const double *stats,
                            int64_t n, cdl_prec prec, int depth, int depth_max, double chain_eps,
                            int lazy, void *chain, size_t chain_bytes, cdl_chain_info *info) {
@@ -1010,9 +1005,12 @@ cdl_status cdl_build_chain(cdl_ctx *ctx, const double *W, const double *deg, con
 
     { Timed t_(ctx, "chain_prep"); HIPCHK(launch_chain_prep(deg, stats, n, ld, info->lazy, c.dmn, c.dm, c.u, s)); }
     // The partial norms of level 0 (rounded and exact) and of every further
-    // level, each in its own place of the staging buffer.  A chain of given depth
-    // is built without a look at them (at n = 256 a read after each of its levels
-    // took three times as long as the squarings), then they are checked in order.
+    // level, each in its own place of the staging buffer, where the kernels write
+    // them: 8 bytes a workgroup over the bus, behind its own work (a level 0 of 2080,
+    // 32896 and 131328 tiles 50, 380 and 1485 us; gathered by a launch after it 52,
+    // 392 and 1535).  A chain of given depth is built without a look at them (at n =
+    // 256 a read after each of its levels took three times as long as the squarings),
+    // then they are checked in order.
     const int nst = sym_tiles64(ld), ntl = square_tiles_of(prec, ld);
     const size_t place0 = ((size_t)nst * sizeof(double) + 255) / 256 * 256;
     const size_t place = ((size_t)ntl * sizeof(double) + 255) / 256 * 256;
@@ -1020,34 +1018,13 @@ cdl_status cdl_build_chain(cdl_ctx *ctx, const double *W, const double *deg, con
     char *stage_dev = nullptr;
     HIPCHK(stage_reserve(ctx, s, 2 * place0 + (size_t)ahead * place, &stage_dev));
     const char *stage = (const char *)ctx->stage;
-    // copies partials that the device kept to their place
-    auto gather = [&](double *p0, int n0, size_t off0, double *p1, size_t off1) {
-        cdl::ReadOut out{};
-        out.count = p1 ? 2 : 1;
-        out.src[0] = (const uint32_t *)p0;
-        out.dst[0] = (uint32_t *)(stage_dev + off0);
-        out.src[1] = (const uint32_t *)p1;
-        out.dst[1] = (uint32_t *)(stage_dev + off1);
-        out.words[0] = out.words[1] = (size_t)n0 * 2;
-        return cdl::launch_read_out(out, s);
-    };
-    {
-        const bool host = nst <= kHostNorms;
-        { Timed t_(ctx, "normalize"); HIPCHK(launch_normalize(prec, W, ld, n, c.dmn, c.u, info->lazy, c.levels,
-                                       host ? (double *)stage_dev : c.fro,
-                                       host ? (double *)(stage_dev + place0) : c.fro64, s)); }
-        if (!host) HIPCHK(gather(c.fro, nst, 0, c.fro64, place0));
-    }
+    { Timed t_(ctx, "normalize"); HIPCHK(launch_normalize(prec, W, ld, n, c.dmn, c.u, info->lazy, c.levels, (double *)stage_dev,
+                                   (double *)(stage_dev + place0), s)); }
     // level l + 1 from level l, its norms into place `q`
     auto next_level = [&](int l, int q) -> cdl_status {
-        const size_t off = 2 * place0 + (size_t)q * place;
-        const bool host = ntl <= kHostNorms;
-        const cdl_status sq = square_step(ctx, prec, c.levels + c.level_bytes * l, c.levels + c.level_bytes * l,
-                                          c.levels + c.level_bytes * (l + 1), ld, n, c,
-                                          host ? (double *)(stage_dev + off) : c.fro, true);
-        if (sq != CDL_OK) return sq;
-        if (!host) HIPCHK(gather(c.fro, ntl, off, nullptr, 0));
-        return CDL_OK;
+        return square_step(ctx, prec, c.levels + c.level_bytes * l, c.levels + c.level_bytes * l,
+                           c.levels + c.level_bytes * (l + 1), ld, n, c,
+                           (double *)(stage_dev + 2 * place0 + (size_t)q * place), true);
     };
     if (depth > 0)
         for (int l = 0; l + 1 < depth; ++l) {

@@ -675,6 +675,10 @@ int apply_gemm_tiles(int shape, int64_t ld, int64_t k, int64_t kpad, int nsplit)
 // (4096, 128) over shapes and 1 to 16 splits, product and reduction: 64 x 64
 // tiles at 2, 4 and 4 splits 19.9, 19.1 and 43.3 us, 128 x 128 at the best of its
 // splits 26.7, 26.5 and 46.7, each at the splits of 256-wide tiles 26, 26 and 48.
+// Elsewhere the count it takes against half and twice it, a whole application: (300,
+// 64) 12.7, 13.7, 11.7 us; (700, 512) 18.1, 21.6, 19.7; (1500, 160) 19.0, 22.4, 20.9;
+// (3000, 200) 47.2, 58.6, 50.7; (5000, 300) 148.9, 165.8, 157.9; (6000, 64) 51.6, 61.0,
+// 56.3; (8192, 256) 259.5, 264.0, 262.3.
 static double apply_f32_time(int q, int P, const int64_t *n, const int64_t *ld, const int *nsplit,
                              int64_t k, int64_t kpad) {
     constexpr double eff[9] = {0, 0, 0, 1.0, 0.85, 0.85, 0.88, 0.93, 0.95};
