@@ -171,9 +171,11 @@ __device__ inline void stage_and_store_rows(Core &g, O *sC, F f, O *C, int64_t l
 // Pipeline (two LDS stages): the fragments of k-step q + 1 are read while
 // the MFMAs of k-step q run (sched_group_barrier interleaves one LDS read
 // with the MFMAs that fit beside it); before the last k-step of a stage
-// every wave waits for the next stage's loads and meets the others at a
-// barrier, then reads the next stage's first fragments beside the last
-// k-step's MFMAs and issues the loads of the stage after next into the buffer
+// every wave waits for the next stage's loads and for its own last reads (without
+// the latter another wave's loads could overtake them; it costs a third of a
+// percent of a squaring at n = 8192) and meets the others at a barrier, then reads
+// the next stage's first fragments beside the last k-step's MFMAs and issues the
+// loads of the stage after next into the buffer
 // just released.  The loop body is uniform; the last stage is peeled.
 
 typedef __attribute__((address_space(3))) void lds_void;
@@ -333,8 +335,10 @@ struct DmaCore {
                 mmas(f[q & 1]);
                 interleave();
             }
-            wait_vmcnt<0>();      // stage kt + 1, issued one stage ago, has landed
-            lds_barrier();        // ... for every wave, and nobody reads stage kt any more
+            // stage kt + 1, issued one stage ago, has landed and this wave's last
+            // reads of stage kt have returned; then the same for every wave
+            wait_vmcnt_lds<0>();
+            lds_barrier();
             load_frags(smem + ((kt + 1) & 1) * STAGE, 0, f[0]);
             mmas(f[1]);
             interleave();
@@ -348,6 +352,7 @@ struct DmaCore {
             interleave();
         }
         mmas(f[1]);
+        wait_vmcnt_lds<0>();
         lds_barrier();
     }
 
