@@ -317,3 +317,16 @@ def test_right_hand_sides_past_a_launch_of_32_bits(cdl):
             want = (q.sum(1) - q.sum(0)) / np.sqrt(k)
             got = host(Y[:, beta * 64 + r].contiguous())
             assert np.abs(got - want).max() <= n * 2.0 ** -52 * np.abs(want).max()
+
+
+# The same crowd in grouped launches, beside a snapshot of spread distances.
+def test_median_of_crowded_distances_in_a_group(cdl):
+    rng = np.random.default_rng(9)
+    C = 64
+    Q = np.linalg.qr(rng.standard_normal((C, C)))[0]
+    sizes = [900, 150, 2000, 700]
+    Xs, gids = mixed_snapshots(sizes, C, 9)
+    for t in (0, 1, 2):
+        Xs[t] = dev(Q[rng.integers(0, C, sizes[t])])
+    print("crowded group", sizes, flush=True)
+    batched_equals_per_snapshot(cdl, Xs, gids, prec="fp32")
