@@ -205,8 +205,9 @@ cdl_status cdl_ctx_set_solve_depth(cdl_ctx *ctx, int depth);
  * brackets the target rank, one pass over the matrix (streamed: one sweep
  * over the recomputed upper panels) counts the keys below the bracket and
  * collects those inside, and the radix passes run over the collected keys
- * (over the matrix, or one sweep per 12-bit digit, when the rank falls
- * outside the bracket).  1: radix passes over the matrix (digit sweeps) only.
+ * (over the matrix's keys inside the bracket when there are more than the
+ * workspace holds, over all of them when the rank falls outside; streamed: one
+ * sweep per 12-bit digit).  1: radix passes over the matrix (digit sweeps) only.
  * Both are exact and give the same sigma.  CDL_E_ARG for other values. */
 cdl_status cdl_ctx_set_select(cdl_ctx *ctx, int mode);
 

@@ -82,9 +82,11 @@ hipError_t launch_select_pick(SelectState *st, double *stats, hipStream_t s);
 // Streamed bracket: a sample of distances computed from the series brackets
 // the median rank; one sweep of launch_select_bracket_panel over the upper
 // panels counts keys below the bracket and gathers those inside into buf (at
-// most cap = select_stream_keys(n)); launch_select_check moves the radix to
-// the buffer (st->src = 1) when the rank lies inside and nothing overflowed;
-// then launch_select_buffer_pass (one radix pass and pick) until st->mode = 2.
+// most cap = select_stream_keys(n)); launch_select_check moves the radix into
+// the bracket when the rank lies inside: to the buffer (st->src = 1), then
+// launch_select_buffer_pass (one radix pass and pick) until st->mode = 2, or,
+// where the buffer overflowed, to the panels' keys inside (st->src = 2), then
+// panels and picks as without a bracket.
 int64_t select_stream_keys(int64_t n);
 // (the sample uses buf as scratch and resets st: launch_select_start_top
 // comes after it)
@@ -109,8 +111,8 @@ hipError_t launch_exp_rows(double *Wp, int64_t ld, int64_t n, int64_t row0, int6
 hipError_t launch_select_presample(const double *Xp, int64_t Tp, const double *sqn, int64_t n,
                                    SelectState *st, unsigned long long *buf, hipStream_t s);
 // The exact lower median after the Gram: gathered = the Gram gathered the
-// bracket into buf (radix passes over it when it holds the target rank),
-// else radix passes over the matrix only.
+// bracket into buf (radix passes over it, or over the matrix's keys inside the
+// bracket, when the target rank lies there), else radix passes over the matrix only.
 hipError_t launch_select_median(const double *D2, int64_t ld, int64_t n,
                                 SelectState *st, unsigned long long *buf, bool gathered,
                                 double *stats, hipStream_t s);
