@@ -245,7 +245,9 @@ cdl_status cdl_timing_reset(cdl_ctx *ctx);
  *               one choice;
  *   "apply"     the chain application (cdl_solve_embedding*), BF16/FP16/FP32
  *               levels: the split-K count, the default (0), half (1) or
- *               twice (2) it; FP64 levels: one choice;
+ *               twice (2) it (FP32 levels: of the default at the call's own k,
+ *               while an entry serves every k of its padded k); FP64 levels:
+ *               one choice;
  *   "residual"  the FP64 residual product W X of the solves: split-K count,
  *               choices as for "apply".
  * A table per process keeps, per GPU architecture name, family, element
