@@ -330,3 +330,37 @@ def test_median_of_crowded_distances_in_a_group(cdl):
         Xs[t] = dev(Q[rng.integers(0, C, sizes[t])])
     print("crowded group", sizes, flush=True)
     batched_equals_per_snapshot(cdl, Xs, gids, prec="fp32")
+
+
+# Two scales at once: most nodes are silent (distance 0 between them), the others
+# repeat patterns of norm 1, so that the median's crowd lies at 1 but for rounding and
+# the bracket may reach down to 0: half the pairs are silent.  Nested: some patterns
+# have norms that differ from 1 at the scale of every 12 bits, so that no pass finds
+# the crowd alone and four digits leave it unresolved.
+@pytest.mark.parametrize("n", [400, 900, 2500, 4096])
+@pytest.mark.parametrize("nested", [False, True])
+def test_median_of_a_crowd_beside_zeros(cdl, n, nested):
+    print("silent nodes n=%d nested=%d" % (n, nested), flush=True)
+    rng = np.random.default_rng(n)
+    C = 200
+    Q = np.linalg.qr(rng.standard_normal((C, C)))[0]
+    X = Q[rng.integers(0, C, n)]
+    if nested:
+        X *= np.sqrt(1.0 + rng.choice([0.0, 2.0 ** -13, 2.0 ** -25, 2.0 ** -37], (n, 1), p=[0.85, 0.05, 0.05, 0.05]))
+    live = rng.permutation(n) < int(0.295 * n)
+    X[~live] = 0.0
+    sig = []
+    for mode in (0, 1):
+        cdl.set_select(mode)
+        try:
+            sig.append(cdl.build_graph(dev(X)).host_stats()["sigma"])
+        finally:
+            cdl.set_select(0)
+    assert sig[0] == sig[1]
+    st, _, _ = cdl.stream_embedding(dev(X), 2, SEED, tol=1e-6, max_iter=64, panel_rows=512)
+    assert st.host_stats()["sigma"] == sig[0]
+    zeros = (n - live.sum()) * (n - live.sum() - 1) // 2
+    if (n * (n - 1) // 2 - 1) // 2 >= zeros:
+        assert sig[0] ** 2 == pytest.approx(1.0, rel=1e-13)
+    else:
+        assert sig[0] == 0.0
